@@ -122,12 +122,22 @@ WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
   // room for the list of half-size tiles too (a call whose chunks are all short chooses them)
   const int tile_tokens = std::max(1, kAppendTileRows / 2 / group);
   w.workers = (int32_t)std::min<int64_t>((int64_t)total_q / tile_tokens + d.batch + 1, INT32_MAX);
+  // Tiles may be cut into pieces, within limits on the whole launch (kSplitPieces workgroups, kSplitSlots of them with
+  // partials); a table whose contexts are all shorter than two pieces has nothing to cut.
+  if (d.q_dtype != ROLLATTN_F32 && d.num_kv_heads <= kSplitSlots / 2 &&
+      d.max_pages_per_seq > (2 * kMinPieceBlocks - 1) * (kAppendBlockTokens / kPageSize)) {
+    w.max_pieces = kSplitPieces / d.num_kv_heads;
+    w.max_slots = kSplitSlots / d.num_kv_heads;
+  }
+  w.list_cap = std::max(w.workers, w.max_pieces);
+  const size_t parts = (size_t)w.max_slots * d.num_kv_heads * (kAppendTileRows / 32);   // 32 rows each
   size_t off = 0;
   w.header = off;      off += align256(sizeof(int32_t) * kPlanWords);
-  w.wstart = off;      off += align256(sizeof(int32_t) * kTileRecWords * (size_t)w.workers);
+  w.wstart = off;      off += align256(sizeof(int32_t) * kTileRecWords * (size_t)w.list_cap);
   w.prefix = off;
-  w.partial_ml = off;
-  w.partial_o = off;
+  w.merge_rec = off;   off += align256(sizeof(int32_t) * kTileRecWords * (size_t)(w.max_slots / 2));
+  w.partial_ml = off;  off += align256(sizeof(float) * 2 * 32 * parts);
+  w.partial_o = off;   off += align256(sizeof(float) * 32 * d.head_dim * parts);
   w.total = off;
   return w;
 }
@@ -203,16 +213,20 @@ int rollattn_debug_read_append_plan(const rollattn_desc* desc, const void* works
   if (e != hipSuccess) return fail_hip(e);
   const char* base = (const char*)workspace;
   int32_t header[kPlanWords];
-  std::vector<int32_t> rec((size_t)w.workers * kTileRecWords);
+  std::vector<int32_t> rec((size_t)w.list_cap * kTileRecWords);
   e = hipMemcpy(header, base + w.header, sizeof(header), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemcpy(rec.data(), base + w.wstart, sizeof(int32_t) * rec.size(), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail_hip(e);
-  const int32_t n = std::max(0, std::min(header[kPlanTiles], w.workers));
-  *n_tiles_out = n;
-  for (int32_t i = 0; i < n; ++i) {
-    tiles_out[2 * i] = rec[(size_t)i * kTileRecWords];
-    tiles_out[2 * i + 1] = rec[(size_t)i * kTileRecWords + 1];
+  const int32_t n = std::max(0, std::min(header[kPlanTiles], w.list_cap));
+  int32_t tiles = 0;
+  for (int32_t i = 0; i < n && tiles < w.workers; ++i) {
+    const int32_t* r = rec.data() + (size_t)i * kTileRecWords;
+    if (r[5] != 0) continue;                     // a later piece of the tile before it
+    tiles_out[2 * tiles] = r[0];
+    tiles_out[2 * tiles + 1] = r[1];
+    ++tiles;
   }
+  *n_tiles_out = tiles;
   return ROLLATTN_OK;
 }
 
@@ -389,9 +403,18 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
   // half tiles, whose blocks the two waves of a SIMD share
   const bool half_tiles = desc->q_dtype != ROLLATTN_F32 && (int64_t)max_q_len * a.group <= kAppendTileRows / 2;
   if (half_tiles) a.tile_tokens = std::max(1, kAppendTileRows / 2 / a.group);
-  // tiles this call can have at most (<= the capacity of the workspace, which is laid out for half tiles)
-  const int32_t tile_cap = (int32_t)std::min<int64_t>((int64_t)total_q / a.tile_tokens + desc->batch + 1, w.workers);
+  // tiles this call can have at most (<= the capacity of the workspace, which is laid out for half tiles), or pieces
+  const int32_t max_tiles = (int32_t)std::min<int64_t>((int64_t)total_q / a.tile_tokens + desc->batch + 1, w.workers);
+  // ... and at least (every group of attn_decode_shared is one; in a mixed step up to B rows are not chunk rows): a list
+  // that is too long to be cut, or as good as even already, needs neither the decision nor the merge launch
+  const int64_t min_tiles = noncausal ? desc->batch : ((int64_t)total_q - (skip_unit_chunks ? desc->batch : 0)) / a.tile_tokens;
+  const bool may_cut = min_tiles <= w.max_pieces && !(noncausal && min_tiles * a.hkv >= kNumCUs);
+  const int32_t max_pieces = may_cut ? w.max_pieces : 0;
+  const int32_t tile_cap = std::max(max_tiles, max_pieces);
   a.tile_cap = tile_cap;
+  a.merge_rec = (const int32_t*)(base + w.merge_rec);
+  a.partial_ml = (float*)(base + w.partial_ml);
+  a.partial_o = (float*)(base + w.partial_o);
   a.total_q = total_q;
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
@@ -408,8 +431,13 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
     if (e != hipSuccess) return fail_hip(e);
     return ROLLATTN_OK;
   }
-  e = launch_plan_append(q_lens, q_offsets, ctx_lens, desc->batch, a.tile_tokens, tile_cap, skip_unit_chunks, a.header,
-                         (int32_t*)(base + w.wstart), s);
+  AppendPlanArgs pa{};
+  pa.q_lens = q_lens; pa.q_offsets = q_offsets; pa.ctx_lens = ctx_lens;
+  pa.batch = desc->batch; pa.hkv = a.hkv; pa.tile_tokens = a.tile_tokens;
+  pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_slots = w.max_slots;
+  pa.skip_unit_chunks = skip_unit_chunks; pa.noncausal = noncausal;
+  pa.header = a.header; pa.tile_rec = (int32_t*)(base + w.wstart); pa.merge_rec = (int32_t*)(base + w.merge_rec);
+  e = launch_plan_append(pa, s);
   if (e != hipSuccess) return fail_hip(e);
   {
     ProfileScope prof(s);
@@ -427,6 +455,10 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
     prof.stop();
   }
   if (e != hipSuccess) return fail_hip(e);
+  if (max_pieces) {
+    e = launch_append_merge(a, desc->head_dim, std::min(max_tiles, w.max_slots / 2), s);
+    if (e != hipSuccess) return fail_hip(e);
+  }
   return ROLLATTN_OK;
 }
 

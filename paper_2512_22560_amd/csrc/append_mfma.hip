@@ -64,7 +64,7 @@ constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kRowsPerWave = 32;
 static_assert(kWaves * kRowsPerWave == kAppendTileRows, "tile rows");
-constexpr int kBlockTokens = 64;                   // KV tokens staged per step
+constexpr int kBlockTokens = kAppendBlockTokens;   // KV tokens staged per step
 constexpr float kSumLimit = 16384.f;               // a lane's 32 probabilities of a block may add up to this much before the row's reference moves
 
 // Row t of an S^T tile holds this token of its 16-token group: the middle two quads are
@@ -91,6 +91,30 @@ __device__ __forceinline__ void fp8x16_to_bf16(const uintx4 raw, uintx4& lo, uin
   }
   lo = uintx4{o[0], o[1], o[2], o[3]};
   hi = uintx4{o[4], o[5], o[6], o[7]};
+}
+
+// Normalises and stores one 32-wide accumulator tile: lane (row n32, half h2) owns dims (i/4)*8 + h2*4 + i%4 of it, four
+// at a time (o(i4, e): dim e of group i4).  The two lanes of a row first trade every other group of four, so that each
+// holds runs of eight dims and stores 16 bytes at a time: half as many store instructions, each of which touches 32 rows.
+// dst: the tile's dims in the row's output, + 8 for the upper lane of the row.
+template <class O>
+__device__ __forceinline__ void store_row_dims(__bf16* dst, bool row_ok, float inv, O&& o) {
+  uintx2 g[4];
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) {
+    bf16x4 pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o(i4, e) * inv);
+    g[i4] = __builtin_bit_cast(uintx2, pk);
+  }
+#pragma unroll
+  for (int pr = 0; pr < 2; ++pr) {
+    // h2 = 0 keeps its group 2 pr (dims 8 pr .. + 3 of the 16) and gets the other lane's; h2 = 1 gets this lane's group
+    // 2 pr + 1 and keeps its own: lower lane dims 16 pr + 0 .. 7, upper lane dims 16 pr + 8 .. 15
+    const uintx2 w0 = __builtin_amdgcn_permlane32_swap(g[2 * pr][0], g[2 * pr + 1][0], false, false);
+    const uintx2 w1 = __builtin_amdgcn_permlane32_swap(g[2 * pr][1], g[2 * pr + 1][1], false, false);
+    if (row_ok) *(uintx4*)(dst + pr * 16) = uintx4{w0[0], w1[0], w0[1], w1[1]};
+  }
 }
 
 template <class F, int... I>
@@ -150,21 +174,28 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // heads x, x + 8, ...  With 1, 2 or 4 KV heads a head's tiles would be dealt to 8, 4 or 2 XCDs and each of
   // them would fetch the whole stream; there the 8 / Hkv XCDs that serve a head take turns by runs of
   // kAppendXcdRun consecutive tiles of the list (the list keeps a trajectory's tiles together).
-  int tile, g;
-  if (hkv < kXcds && kXcds % hkv == 0) {
-    const int x = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int parts = kXcds / hkv;
-    g = x % hkv;
-    tile = (slot / kAppendXcdRun) * (parts * kAppendXcdRun) + (x / hkv) * kAppendXcdRun + slot % kAppendXcdRun;
-  } else {
-    tile = blockIdx.x / hkv;
-    g = blockIdx.x - tile * hkv;
-  }
+  auto tile_of = [](int block, int hkv, int& g) __attribute__((always_inline)) -> int {
+    if (hkv < kXcds && kXcds % hkv == 0) {
+      const int x = block % kXcds, slot = block / kXcds;
+      const int parts = kXcds / hkv;
+      g = x % hkv;
+      return (slot / kAppendXcdRun) * (parts * kAppendXcdRun) + (x / hkv) * kAppendXcdRun + slot % kAppendXcdRun;
+    }
+    const int tile = block / hkv;
+    g = block - tile * hkv;
+    return tile;
+  };
+  int g;
+  const int tile = tile_of(blockIdx.x, hkv, g);
   // The tile's record does not wait for the tile count (the index is clamped to the list's capacity): both loads
   // leave together, and everything else the workgroup needs to start hangs off the record alone.
   typedef const __attribute__((address_space(4))) int32_t* const_rec_p;
   const const_rec_p rec = (const_rec_p)(a.tile_rec + (size_t)min(tile, a.tile_cap - 1) * kTileRecWords);
-  const int b = rec[0], q0 = rec[1], n_b = rec[2], ctx = rec[3], q_off = rec[4];
+  // A record is a whole tile, or a piece of one: blocks [blk0, blk0 + n_blocks) of the context.  The piece sees the
+  // context as if it started there (table, length and positions shifted), so nothing below differs; rows whose last
+  // token lies before it have negative positions and see nothing.
+  const int b = rec[0], q0 = rec[1], n_b = rec[2], q_off = rec[4], blk0 = rec[5], n_blocks = rec[6];
+  const int ctx = rec[3] - blk0 * kBlockTokens;
   if (tile >= n_tiles) return;
   __shared__ long clock_s[2];
   if (a.clock_sums && threadIdx.x == 0) {
@@ -178,13 +209,11 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // all of [0, L_b), the rows' own tokens lie outside this range.
   const bool causal = a.noncausal == 0;
   const int pos0 = causal ? ctx - n_b + q0 : ctx - 1;    // position of the tile's first token
-  const int kv_end = causal ? pos0 + tokens_here : ctx;  // tokens [0, kv_end) are visible to some row
-  const int n_blocks = (kv_end + kBlockTokens - 1) / kBlockTokens;
   // Page ids and page scales are inputs nobody writes during the call: reading them through the
   // constant address space lets every such load (all uniform) take the scalar path.
   typedef const __attribute__((address_space(4))) int32_t* const_i32_p;
   typedef const __attribute__((address_space(4))) float* const_f32_p;
-  const const_i32_p table = (const_i32_p)(a.page_table + (size_t)b * a.max_pages);
+  const const_i32_p table = (const_i32_p)(a.page_table + (size_t)b * a.max_pages + blk0 * (kBlockTokens / kPageSize));
   const const_f32_p k_scale_c = (const_f32_p)a.k_scale;
   const const_f32_p v_scale_c = (const_f32_p)a.v_scale;
   const size_t tile_stride = (size_t)kPageSize * kSrcRowBytes;
@@ -834,40 +863,133 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
 #undef BARRIER_RAW
 #undef DMA_WAIT
 
-  // ---- normalise and store: lane (row n32, half h2) owns dims dt*32 + (i/4)*8 + h2*4 + i%4, four dims at a
-  // time.  The two lanes of a row first trade every other group of four, so that each holds runs of eight dims
-  // and stores 16 bytes at a time: half as many store instructions, each of which touches 32 rows.
+  // ---- normalise and store.  Where the rows go is worked out again here, from the thread and workgroup numbers, the
+  // kernel's arguments and the tile's record, all read anew: what only the end of a tile needs occupies no register
+  // during the loop (FP8, D = 128: 256 vector registers of 256 otherwise, and scalar ones that spill).
+  typedef const __attribute__((address_space(4))) AppendArgs* const_args_p;
+  const_args_p args_e = (const_args_p)__builtin_amdgcn_kernarg_segment_ptr();
+  int block_e = blockIdx.x, tid_e = threadIdx.x;
+  asm volatile("" : "+s"(args_e), "+s"(block_e), "+v"(tid_e));
+  const int hkv_e = args_e->hkv, group_e = args_e->group;
+  int g_e;
+  const int tile_e = tile_of(block_e, hkv_e, g_e);
+  const const_rec_p rec_e = (const_rec_p)(args_e->tile_rec + (size_t)tile_e * kTileRecWords);
+  const int q0_e = rec_e[1], n_e = rec_e[2], qoff_e = rec_e[4], slot = rec_e[7];
+  const int lane_e = tid_e & 63, wave_e = __builtin_amdgcn_readfirstlane(tid_e >> 6), row_wave_e = HALF ? (wave_e & 3) : wave_e;
+  const int rows_e = min(args_e->tile_tokens, n_e - q0_e) * group_e;
+  const int row_e = row_wave_e * kRowsPerWave + (lane_e & 31);
+  const bool upper = lane_e >= 32;
+  const bool ok = row_e < rows_e;
   l_run = xor32_add(l_run);
-  const float inv = 1.f / l_run;
-  // log2 of the row's softmax denominator, for callers that merge this result with another range's
-  if (row_ok && a.lse && h2 == 0) a.lse[(size_t)(q_off + q0 + tok_in_tile) * a.hq + head] = m_run + __builtin_amdgcn_logf(l_run);
-  __bf16* orow = (__bf16*)a.out + ((size_t)(q_off + q0 + tok_in_tile) * a.hq + head) * D;
+  if (slot >= 0) {
+    // a piece of a tile: accumulators as they lie, 16 bytes per lane and store, reference and sum of each row
+    if (row_wave_e * kRowsPerWave < rows_e) {
+      const size_t part = ((size_t)slot * hkv_e + g_e) * kWaves + row_wave_e;
+      float* po = args_e->partial_o + part * (kRowsPerWave * D) + lane_e * 4;
 #pragma unroll
-  for (int dt = 0; dt < kDT; ++dt) {
-    uintx2 g[4];
+      for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      bf16x4 pk;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(acc[dt][i4 * 4 + e] * inv);
-      g[i4] = __builtin_bit_cast(uintx2, pk);
+        for (int i4 = 0; i4 < 4; ++i4)
+          *(floatx4*)(po + (dt * 4 + i4) * 256) = floatx4{acc[dt][i4 * 4], acc[dt][i4 * 4 + 1], acc[dt][i4 * 4 + 2], acc[dt][i4 * 4 + 3]};
+      if (!upper) *(floatx2*)(args_e->partial_ml + (part * kRowsPerWave + lane_e) * 2) = floatx2{m_run, l_run};
     }
+  } else {
+    const int tok_e = row_e / group_e;
+    const size_t orow = (size_t)(qoff_e + q0_e + tok_e) * args_e->hq + g_e * group_e + (row_e - tok_e * group_e);
+    const float inv = 1.f / l_run;
+    // log2 of the row's softmax denominator, for callers that merge this result with another range's
+    if (ok && args_e->lse && !upper) args_e->lse[orow] = m_run + __builtin_amdgcn_logf(l_run);
+    __bf16* dst = (__bf16*)args_e->out + orow * D + (upper ? 8 : 0);
 #pragma unroll
-    for (int pr = 0; pr < 2; ++pr) {
-      // h2 = 0 keeps its group 2 pr (dims 8 pr .. + 3 of the 16) and gets the other lane's; h2 = 1 gets this lane's group
-      // 2 pr + 1 and keeps its own: lower lane dims 16 pr + 0 .. 7, upper lane dims 16 pr + 8 .. 15
-      const uintx2 w0 = __builtin_amdgcn_permlane32_swap(g[2 * pr][0], g[2 * pr + 1][0], false, false);
-      const uintx2 w1 = __builtin_amdgcn_permlane32_swap(g[2 * pr][1], g[2 * pr + 1][1], false, false);
-      if (row_ok) *(uintx4*)(orow + dt * 32 + pr * 16 + h2 * 8) = uintx4{w0[0], w1[0], w0[1], w1[1]};
-    }
+    for (int dt = 0; dt < kDT; ++dt)
+      store_row_dims(dst + dt * 32, ok, inv, [&](int i4, int e) __attribute__((always_inline)) { return acc[dt][i4 * 4 + e]; });
   }
-  if (a.clock_sums && threadIdx.x == 0) {
-    atomicAdd(a.clock_sums, (unsigned long long)(__builtin_amdgcn_s_memtime() - clock_s[0]));
-    atomicAdd(a.clock_sums + 1, (unsigned long long)(__builtin_amdgcn_s_memrealtime() - clock_s[1]));
+  if (args_e->clock_sums && tid_e == 0) {
+    atomicAdd(args_e->clock_sums, (unsigned long long)(__builtin_amdgcn_s_memtime() - clock_s[0]));
+    atomicAdd(args_e->clock_sums + 1, (unsigned long long)(__builtin_amdgcn_s_memrealtime() - clock_s[1]));
   }
 }
 
+// Merge of the pieces of a tile: one wave per (cut tile, KV head, 32 rows, 32 dims), lanes as in the append kernel's
+// accumulators.  M = max_s m_s; out = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s.  A piece that a row did not see has
+// m = -inf and weight zero; some piece has seen the row (its own token is in the last one it sees).
+// Bound by the latency of the partials' loads (a few hundred kilobytes per tile out of L2 and the memory-side cache):
+// four waves of different dims per row group keep each wave's chain to one 4 KB load per piece, and four pieces are
+// under way at a time.
+template <int D>
+__global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
+  constexpr int kDT = D / 32;
+  const int lane = threadIdx.x & 63;
+  const int n32 = lane & 31, h2 = lane >> 5;
+  const int wave = threadIdx.x >> 6;
+  const int g = blockIdx.x % a.hkv, sub = blockIdx.x / a.hkv;    // head fastest, as in the append kernel: with 8 heads the XCD that wrote the partials reads them
+  const int unit = sub * (256 / 64) + wave;
+  const int dt = unit % kDT, row_wave = (unit / kDT) % kWaves, m = unit / (kDT * kWaves);
+  const int n_merges = a.header[kPlanMerges];
+  const int32_t* rec = a.merge_rec + (size_t)m * kTileRecWords;     // (room for every m of the grid: leaves together with the count)
+  const int q0 = rec[0], n_b = rec[1], q_off = rec[2], slot0 = rec[3], pieces = rec[4];
+  if (m >= n_merges) return;
+  const int rows_here = min(a.tile_tokens, n_b - q0) * a.group;
+  if (row_wave * kRowsPerWave >= rows_here) return;
+  const size_t stride = (size_t)a.hkv * kWaves;            // parts from one piece to the next
+  const size_t part0 = (size_t)slot0 * stride + (size_t)g * kWaves + row_wave;
+  const floatx2* ml = (const floatx2*)a.partial_ml + part0 * kRowsPerWave + n32;
+  const float* po = a.partial_o + part0 * (kRowsPerWave * D) + (dt * 4 * 64 + lane) * 4;
+  floatx4 o[4];
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) o[i4] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float ref = -INFINITY, l = 0.f;
+  constexpr int kBatch = 4;                                // pieces under way at a time (past the last one: the last one again, weight zero)
+  for (int s0 = 0; s0 < pieces; s0 += kBatch) {
+    floatx2 x[kBatch];
+    floatx4 y[kBatch][4];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const size_t s = min(s0 + i, pieces - 1) * stride;
+      x[i] = ml[s * kRowsPerWave];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) y[i][i4] = *(const floatx4*)(po + s * (kRowsPerWave * D) + i4 * 256);
+    }
+    float top = ref;
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      if (s0 + i >= pieces) x[i][0] = -INFINITY;
+      top = fmaxf(top, x[i][0]);
+    }
+    const float base = (top == -INFINITY) ? 0.f : top;
+    const float keep = __builtin_amdgcn_exp2f(ref - base);
+    ref = top;
+    l *= keep;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) o[i4] *= keep;
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const float f = __builtin_amdgcn_exp2f(x[i][0] - base);
+      l += f * x[i][1];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) o[i4] += f * y[i][i4];
+    }
+  }
+  const int row = row_wave * kRowsPerWave + n32;
+  const bool row_ok = row < rows_here;
+  const int tok = row / a.group;
+  const size_t orow = (size_t)(q_off + q0 + tok) * a.hq + g * a.group + (row - tok * a.group);
+  if (row_ok && a.lse && dt == 0 && h2 == 0) a.lse[orow] = ref + __builtin_amdgcn_logf(l);
+  const float inv = 1.f / l;
+  store_row_dims((__bf16*)a.out + orow * D + dt * 32 + h2 * 8, row_ok, inv, [&](int i4, int e) { return o[i4][e]; });
+}
+
 }  // namespace
+
+hipError_t launch_append_merge(const AppendArgs& a, int head_dim, int max_merges, hipStream_t s) {
+  const dim3 grid((unsigned)((max_merges * kWaves * (head_dim / 32) + 3) / 4 * a.hkv));
+  if (head_dim == 128) {
+    hipLaunchKernelGGL((append_merge_kernel<128>), grid, dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((append_merge_kernel<64>), grid, dim3(256), 0, s, a);
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s) {
   if (head_dim == 128 && !fp8 && !half_tiles) {

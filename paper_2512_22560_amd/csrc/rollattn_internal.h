@@ -18,22 +18,29 @@ constexpr int kF32DecodeWgs = 4 * kNumCUs;    // one workgroup-worker each
 constexpr int kF32HeadTile = 4;         // query heads per float32 decode row
 constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pairs) per append workgroup
 constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
+constexpr int kAppendBlockTokens = 64;  // KV tokens staged per step of the append kernel
 constexpr int kTileRecWords = 8;       // append: int32 per tile record (32 bytes: one scalar load)
+constexpr int kSplitPieces = 1024;      // append: a list whose tiles are cut into pieces has at most this many workgroups
+constexpr int kSplitSlots = 512;        // append: ... and this many of them leave partials (2 MB of workspace each 16 slots at D = 128)
+constexpr int kMinPieceBlocks = 8;      // append: shorter pieces cost more in their start and end than they save
 constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list that one XCD takes in a row (one per CU)
 
 // Header words of the plan, at the start of the workspace.
-enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanWords = 64 };
+enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5, kPlanWords = 64 };
 
 // Byte offsets of the workspace regions (all multiples of 256).
 struct WorkspaceLayout {
   int32_t workers;        // decode: number of workers W; append: capacity in query tiles
+  int32_t list_cap;       // append: capacity of the work list, in tiles or pieces of tiles
+  int32_t max_pieces, max_slots;   // append: limits of a list whose tiles are cut (0: this call cuts none)
   int32_t head_tile;      // decode: query heads per row (16 or 4)
   int32_t rows_per_b;     // decode: rows per trajectory = Hkv * ceil(G / head_tile)
   size_t header;          // int32[kPlanWords]
   size_t prefix;          // decode: int32[B + 1] exclusive scan of per-trajectory block counts
   size_t wstart;          // decode: int32[W][4] first (b, row, block) of every worker; append: int32[cap][8] tile records
-  size_t partial_ml;      // float[2 W][head_tile][2]   (max in log2 units, sum)
-  size_t partial_o;       // float[2 W][head_tile][D]   un-normalised
+  size_t merge_rec;       // append: int32[max_slots / 2][8], one record per tile that was cut into pieces
+  size_t partial_ml;      // float[2 W][head_tile][2]   (max in log2 units, sum); append: float[slots][Hkv][8][32][2]
+  size_t partial_o;       // float[2 W][head_tile][D]   un-normalised; append: float[slots][Hkv][8][D / 8][64][4], as the accumulators lie
   size_t total;
 };
 
@@ -76,8 +83,13 @@ struct AppendArgs {
   const float* k_scale;
   const float* v_scale;
   int32_t* header;
-  const int32_t* tile_rec;   // [tile_cap][kTileRecWords]: (b, first row of the tile in its chunk, n_b, L_b, q_offsets[b], 0, 0, 0)
+  // [tile_cap][kTileRecWords]: (b, first row of the tile in its chunk, n_b, L_b, q_offsets[b], first block, number of
+  // blocks, slot); slot: -1 for a whole tile, else where this piece of one leaves its partial result
+  const int32_t* tile_rec;
   int32_t tile_cap;
+  const int32_t* merge_rec;  // (first row of the tile, n_b, q_offsets[b], first slot, pieces, 0, 0, 0) of every tile that was cut
+  float* partial_ml;
+  float* partial_o;
   int32_t batch, hq, hkv, group, max_pages, tile_tokens, total_q;
   float scale_log2;
   float* lse;           // optional [total_q][Hq], as in DecodeArgs
@@ -87,19 +99,34 @@ struct AppendArgs {
   unsigned long long* clock_sums;
 };
 
+// Inputs and outputs of the append work list.
+struct AppendPlanArgs {
+  const int32_t* q_lens;
+  const int32_t* q_offsets;
+  const int32_t* ctx_lens;
+  int32_t batch, hkv, tile_tokens;
+  int32_t cap;                     // room in the list
+  int32_t max_pieces, max_slots;   // cut tiles into pieces only within these (0: never)
+  bool skip_unit_chunks;           // mixed step: chunks of one token are decode rows
+  bool noncausal;
+  int32_t* header;
+  int32_t* tile_rec;
+  int32_t* merge_rec;
+};
+
 // Launchers (defined in the .hip files).  Each returns the hipError_t of its launch.
 // workers: how many the partition is cut for; slots >= workers: records written (those past `workers` say "no blocks")
 hipError_t launch_plan_decode(const int32_t* ctx_lens, const int32_t* q_lens, int32_t batch, int32_t rows_per_b,
                               int32_t workers, int32_t slots, int32_t* header, int32_t* prefix, int32_t* wstart, hipStream_t s);
-hipError_t launch_plan_append(const int32_t* q_lens, const int32_t* q_offsets, const int32_t* ctx_lens, int32_t batch,
-                              int32_t tile_tokens, int32_t cap, bool skip_unit_chunks, int32_t* header, int32_t* tile_rec,
-                              hipStream_t s);
+hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, int grid, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int grid, hipStream_t s);
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s);
 // half_tiles: every tile has at most kAppendTileRows / 2 rows (a.tile_tokens is set accordingly) and the
 // two waves of a SIMD split each block of a tile between them instead of owning different rows
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s);
+// folds the pieces of the tiles that were cut (max_merges: at most this many tiles)
+hipError_t launch_append_merge(const AppendArgs& a, int head_dim, int max_merges, hipStream_t s);
 hipError_t launch_append_f32(const AppendArgs& a, int head_dim, int grid, hipStream_t s);
 hipError_t launch_kv_write(const void* k_new, const void* v_new, const int32_t* q_lens, const int32_t* q_offsets,
                            void* k_pages, void* v_pages, const int32_t* page_table, const int32_t* ctx_lens,

@@ -1,0 +1,61 @@
+"""Append calls with few tiles: their tiles are cut into pieces of the context whose partial results a merge folds."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as O
+from paper_2512_22560_amd import binding as B
+from paper_2512_22560_amd import workloads as W
+from tests.gpu_common import check, oracle_append
+from tests.helpers import oracle_args
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _append(b):
+    w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    ws = B.alloc_workspace(desc, b.total_q, DEV)
+    out, lse = B.attn_append_lse(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale,
+                                 max_q_len=int(b.q_lens_host.max()), k_scale=b.k_scale, v_scale=b.v_scale, workspace=ws)
+    pieces, merges = ws.view(torch.int32)[4:6].tolist()
+    return out, lse, pieces, merges, B.read_append_plan(desc, ws, b.total_q)
+
+
+# (name, batch, Hq, Hkv, D, prefix, new tokens, cut): contexts too short to be cut, on and just past a block edge; one tile and several; half tiles; chunks longer than a piece, whose first
+# rows do not see its later pieces; groups that leave a tile ragged; one KV head and more than eight
+CASES = [
+    ("below", 1, 8, 8, 128, (900, 900), (40, 40), False), ("block_edge", 1, 8, 8, 128, (1495, 1495), (41, 41), True),
+    ("past_edge", 1, 8, 8, 128, (1496, 1496), (41, 41), True), ("long", 2, 32, 8, 128, (6000, 9000), (3, 3), True),
+    ("half", 5, 64, 4, 128, (100, 9000), (1, 8), True), ("causal", 1, 16, 4, 128, (0, 0), (3001, 3001), True),
+    ("g3_d64", 3, 6, 2, 64, (2000, 5000), (100, 300), True), ("one_head", 2, 40, 1, 128, (3000, 8000), (5, 70), True),
+    ("sixteen", 2, 16, 16, 64, (2500, 2600), (257, 300), True), ("skewed", 30, 16, 4, 128, (10, 14000), (1, 200), True),
+]
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("name,batch,hq,hkv,d,prefix,new,cut", CASES, ids=[c[0] for c in CASES])
+def test_pieces_and_merge_against_the_oracle(name, batch, hq, hkv, d, prefix, new, cut, kvd):
+    b = W.build(W.Workload(name, batch, hq, hkv, d, "bf16", kvd, ("loguniform" if name == "skewed" else "uniform", *prefix),
+                           qlen=("uniform", *new), ctx_is_prefix=True, seed=W.BASE_SEED + 91), DEV)
+    out, lse, pieces, merges, tiles = _append(b)
+    assert (merges > 0) == cut and (pieces > len(tiles)) == cut
+    half = int(b.q_lens_host.max()) * (hq // hkv) <= 128
+    assert np.array_equal(tiles, O.append_tile_plan(b.q_lens_host, b.ctx_lens_host, max(1, (128 if half else 256) // (hq // hkv)))[:, :2])
+    check(out, oracle_append(b), "bf16", name)
+    if b.total_q * hq <= 5000:                        # (the oracle's denominators go row by row)
+        ref = O.attn_lse(W.raw_numpy(b.q), b.q_lens_host, **{k: v for k, v in oracle_args(b).items() if k not in ("v_pages", "v_scale")})
+        # log2 of the denominators: as tests/test_gpu_lse_merge.py states for append over bf16 pools (the scaled query is rounded)
+        assert np.abs(lse.double().cpu().numpy() - ref).max() <= 1e-2
+    again = _append(b)
+    assert torch.equal(out, again[0]) and torch.equal(lse, again[1])
+
+
+def test_shared_prompts_of_few_groups_are_cut_too():
+    shared = np.array([4000, 0])                      # one long prompt, one group that shares nothing
+    b = W.build(W.Workload("sp", 16, 32, 8, 128, "bf16", "bf16", ("uniform", 4100, 4400), seed=W.BASE_SEED + 92), DEV)
+    b = W.alias_shared_prefix(b, 8, shared)
+    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8,
+                               shared_lens=torch.from_numpy(shared.astype(np.int32)).to(DEV), sm_scale=b.workload.sm_scale)
+    check(out, O.attn_decode(W.raw_numpy(b.q), **oracle_args(b)), "bf16", "shared")
