@@ -1,0 +1,37 @@
+"""The merge of split rows at every count of pieces where it changes its way of folding them."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as O
+from paper_2512_22560_amd import binding as B
+from paper_2512_22560_amd import workloads as W
+from tests.gpu_common import check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+PIECES = [0, 1, 2, 3, 4, 5, 6, 8, 9, 15, 16, 17, 18, 64, 65, 131]
+
+
+# group 5 and 3: the last chunk of a row is not full; 20: a second head tile; 16 over 8 KV heads: a workgroup takes several chunks
+@pytest.mark.parametrize("qd,hkv,group,d,copies", [("f32", 1, 5, 64, 1), ("f32", 1, 4, 128, 1), ("bf16", 2, 5, 128, 1), ("bf16", 1, 20, 64, 1),
+                                                   ("bf16", 1, 3, 64, 1), ("bf16", 8, 16, 128, 3)])
+def test_rows_of_every_number_of_pieces(qd, hkv, group, d, copies):
+    # with fewer blocks than workers every block of 32 tokens is a piece (with three copies over eight heads: every few)
+    lens = np.array([max(0, 32 * p - (p % 3)) for p in PIECES] * copies)
+    b = W.build(W.Workload("pieces", len(lens), hkv * group, hkv, d, qd, qd, ("const", 1), seed=W.BASE_SEED + 95), DEV)
+    w, dt = b.workload, torch.float32 if qd == "f32" else torch.bfloat16
+    gen = torch.Generator(device=DEV).manual_seed(96)
+    pages = (lens + 15) // 16
+    table = np.full((len(lens), int(pages.max())), -1, dtype=np.int32)
+    ids = np.random.default_rng(97).permutation(int(pages.sum())).astype(np.int32)
+    for i, end in enumerate(np.cumsum(pages)):
+        table[i, :pages[i]] = ids[end - pages[i]:end]
+    k, v = (torch.randn((int(pages.sum()), hkv, 16, d), generator=gen, device=DEV).to(dt) for _ in range(2))
+    pt, cl = torch.from_numpy(table).to(DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    out, lse = B.attn_decode_lse(b.q, k, v, pt, cl, sm_scale=w.sm_scale)
+    args = dict(k_pages=W.raw_numpy(k), v_pages=W.raw_numpy(v), page_table=table, ctx_lens=lens, sm_scale=w.sm_scale, q_dtype=qd, kv_dtype=qd)
+    check(out, O.attn_decode(W.raw_numpy(b.q), **args), qd, "pieces")
+    assert torch.isneginf(lse[cl == 0]).all() and torch.isfinite(lse[cl > 0]).all() and not out[cl == 0].any()
+    again, lse2 = B.attn_decode_lse(b.q, k, v, pt, cl, sm_scale=w.sm_scale)
+    assert torch.equal(out, again) and torch.equal(lse, lse2)
