@@ -257,12 +257,18 @@ static int append_limits(const rollattn_desc& d) {
   return ROLLATTN_OK;
 }
 
-// attn_decode proper; lse (optional, device [B][Hq]) receives log2 of every row's softmax denominator.
-// q_lens / q_offsets (both or neither): the mixed step, see DecodeArgs.
-static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
-                       const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
-                       size_t workspace_bytes, void* hip_stream, float* lse, const int32_t* q_lens = nullptr,
-                       const int32_t* q_offsets = nullptr) {
+// A decode call whose arguments have been checked: its plan's inputs and its kernels' arguments.
+struct DecodeCall {
+  DecodePlanArgs plan;
+  DecodeArgs args;
+};
+
+// Argument checks of attn_decode and the arguments of its launches; lse (optional, device [B][Hq]) receives log2 of every
+// row's softmax denominator.  q_lens / q_offsets (both or neither): the mixed step, see DecodeArgs.  call stays untouched,
+// with an empty batch, where there is nothing to launch.
+static int decode_prepare(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
+                          const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
+                          size_t workspace_bytes, float* lse, const int32_t* q_lens, const int32_t* q_offsets, DecodeCall* call) {
   int rc = check_desc(desc);
   if (rc) return rc;
   if (desc->batch == 0) return ROLLATTN_OK;
@@ -275,9 +281,8 @@ static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_p
   rc = decode_limits(*desc);
   if (rc) return rc;
 
-  hipStream_t s = (hipStream_t)hip_stream;
   char* base = (char*)workspace;
-  DecodeArgs a{};
+  DecodeArgs& a = call->args;
   a.q = q; a.k_pages = k_pages; a.v_pages = v_pages; a.page_table = page_table; a.ctx_lens = ctx_lens;
   a.out = out; a.k_scale = desc->k_scale; a.v_scale = desc->v_scale;
   a.header = (const int32_t*)(base + w.header);
@@ -292,12 +297,18 @@ static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_p
   a.lse = lse;
   a.q_lens = q_lens;
   a.q_offsets = q_offsets;
-
+  DecodePlanArgs& d = call->plan;
+  d.ctx_lens = ctx_lens; d.q_lens = q_lens; d.batch = desc->batch; d.rows_per_b = w.rows_per_b;
   // (the launch has w.workers workers whatever the partition is cut for: the others get a record without blocks)
-  hipError_t e = launch_plan_decode(ctx_lens, q_lens, desc->batch, w.rows_per_b, plan_workers(w), w.workers,
-                                    (int32_t*)(base + w.header), (int32_t*)(base + w.prefix), (int32_t*)(base + w.wstart), s);
-  if (e != hipSuccess) return fail_hip(e);
+  d.workers = plan_workers(w); d.slots = w.workers;
+  d.header = (int32_t*)(base + w.header); d.prefix = (int32_t*)(base + w.prefix); d.wstart = (int32_t*)(base + w.wstart);
+  return ROLLATTN_OK;
+}
+
+// The launches behind the plan.  shared: the other half of attn_decode_shared, folded in by the merge.
+static int decode_launch(const rollattn_desc* desc, const DecodeArgs& a, hipStream_t s, const SharedHalf* shared = nullptr) {
   const bool f32 = desc->q_dtype == ROLLATTN_F32;
+  hipError_t e;
   {
     ProfileScope prof(s);
     if (f32) {
@@ -308,9 +319,21 @@ static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_p
     prof.stop();
   }
   if (e != hipSuccess) return fail_hip(e);
-  e = launch_combine(a, desc->head_dim, !f32, s);
+  e = shared ? launch_combine_shared(a, *shared, desc->head_dim, s) : launch_combine(a, desc->head_dim, !f32, s);
   if (e != hipSuccess) return fail_hip(e);
   return ROLLATTN_OK;
+}
+
+static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
+                       const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
+                       size_t workspace_bytes, void* hip_stream, float* lse) {
+  DecodeCall call{};
+  const int rc = decode_prepare(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, workspace_bytes, lse, nullptr,
+                                nullptr, &call);
+  if (rc || call.args.batch == 0) return rc;
+  const hipError_t e = launch_plan_decode(call.plan, (hipStream_t)hip_stream);
+  if (e != hipSuccess) return fail_hip(e);
+  return decode_launch(desc, call.args, (hipStream_t)hip_stream);
 }
 
 int attn_decode(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
@@ -369,19 +392,27 @@ int attn_decode_static(const rollattn_desc* desc, const void* q, const void* k_p
 // attn_append proper.  table_stride: int32 entries between the page-table rows of consecutive
 // trajectories; noncausal: every row sees all of [0, L_b) (then n_b <= L_b is not required);
 // lse as in decode_impl, [total_q][Hq].  table_stride and noncausal are for the bf16 kernels only.
-static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int32_t* q_lens, const int32_t* q_offsets,
-                       int32_t total_q, int32_t max_q_len, const void* k_pages, const void* v_pages,
-                       const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
-                       size_t workspace_bytes, void* hip_stream, int32_t table_stride, bool noncausal, float* lse,
-                       bool skip_unit_chunks = false) {
+struct AppendCall {
+  AppendPlanArgs plan;
+  AppendArgs args;
+  bool half_tiles;
+  int32_t tile_cap, max_merges;    // room in the list; tiles that may have been cut (0: no merge)
+};
+
+static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const int32_t* q_lens, const int32_t* q_offsets,
+                          int32_t total_q, int32_t max_q_len, const void* k_pages, const void* v_pages,
+                          const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
+                          size_t workspace_bytes, int32_t table_stride, bool noncausal, float* lse, bool skip_unit_chunks,
+                          AppendCall* call) {
   int rc = check_desc(desc);
   if (rc) return rc;
   if (total_q < 0 || max_q_len < 0) return ROLLATTN_EINVAL;
   rc = append_limits(*desc);
   if (rc) return rc;
   if (desc->batch == 0 || total_q == 0) return ROLLATTN_OK;
-  if (!q_chunk || !q_lens || !q_offsets || !k_pages || !v_pages || !page_table || !ctx_lens || !out || !workspace)
-    return ROLLATTN_EINVAL;
+  // (the lengths of a non-causal call's chunks are the plan's own)
+  if (!q_chunk || !k_pages || !v_pages || !page_table || !out || !workspace) return ROLLATTN_EINVAL;
+  if (!noncausal && (!q_lens || !q_offsets || !ctx_lens)) return ROLLATTN_EINVAL;
   if (!aligned16(q_chunk) || !aligned16(q_lens) || !aligned16(q_offsets) || !aligned16(k_pages) ||
       !aligned16(v_pages) || !aligned16(page_table) || !aligned16(ctx_lens) || !aligned16(out) ||
       !aligned16(workspace))
@@ -389,9 +420,8 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
   const WorkspaceLayout w = append_layout(*desc, total_q);
   if (workspace_bytes < w.total) return ROLLATTN_EWORKSPACE;
 
-  hipStream_t s = (hipStream_t)hip_stream;
   char* base = (char*)workspace;
-  AppendArgs a{};
+  AppendArgs& a = call->args;
   a.q = q_chunk; a.k_pages = k_pages; a.v_pages = v_pages; a.page_table = page_table; a.ctx_lens = ctx_lens;
   a.q_lens = q_lens; a.q_offsets = q_offsets; a.out = out; a.k_scale = desc->k_scale; a.v_scale = desc->v_scale;
   a.header = (int32_t*)(base + w.header);
@@ -401,7 +431,7 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
   a.tile_tokens = std::max(1, kAppendTileRows / a.group);
   // No chunk longer than half a tile (a few new tokens per trajectory; the members of a group in attn_decode_shared):
   // half tiles, whose blocks the two waves of a SIMD share
-  const bool half_tiles = desc->q_dtype != ROLLATTN_F32 && (int64_t)max_q_len * a.group <= kAppendTileRows / 2;
+  const bool half_tiles = call->half_tiles = desc->q_dtype != ROLLATTN_F32 && (int64_t)max_q_len * a.group <= kAppendTileRows / 2;
   if (half_tiles) a.tile_tokens = std::max(1, kAppendTileRows / 2 / a.group);
   // tiles this call can have at most (<= the capacity of the workspace, which is laid out for half tiles), or pieces
   const int32_t max_tiles = (int32_t)std::min<int64_t>((int64_t)total_q / a.tile_tokens + desc->batch + 1, w.workers);
@@ -419,47 +449,69 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
   a.noncausal = noncausal ? 1 : 0;
-  a.clock_sums = nullptr;
 
+  AppendPlanArgs& pa = call->plan;
+  pa.q_lens = q_lens; pa.q_offsets = q_offsets; pa.ctx_lens = ctx_lens;
+  pa.batch = desc->batch; pa.hkv = a.hkv; pa.tile_tokens = a.tile_tokens;
+  pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_slots = w.max_slots;
+  pa.skip_unit_chunks = skip_unit_chunks; pa.noncausal = noncausal;
+  pa.header = a.header; pa.tile_rec = (int32_t*)(base + w.wstart); pa.merge_rec = (int32_t*)(base + w.merge_rec);
+  call->tile_cap = tile_cap;
+  call->max_merges = max_pieces ? std::min(max_tiles, w.max_slots / 2) : 0;
+  return ROLLATTN_OK;
+}
+
+// The launches behind the plan (float32 has no plan: rows are enumerated directly).
+static int append_launch(const rollattn_desc* desc, AppendCall& call, hipStream_t s) {
+  AppendArgs& a = call.args;
   hipError_t e;
   if (desc->q_dtype == ROLLATTN_F32) {
     const int tiles = (a.group + 3) / 4;
-    const int grid = (int)std::min<int64_t>((int64_t)total_q * a.hkv * tiles, 1 << 20);
+    const int grid = (int)std::min<int64_t>((int64_t)a.total_q * a.hkv * tiles, 1 << 20);
     ProfileScope prof(s);
     e = launch_append_f32(a, desc->head_dim, grid, s);
     prof.stop();
     if (e != hipSuccess) return fail_hip(e);
     return ROLLATTN_OK;
   }
-  AppendPlanArgs pa{};
-  pa.q_lens = q_lens; pa.q_offsets = q_offsets; pa.ctx_lens = ctx_lens;
-  pa.batch = desc->batch; pa.hkv = a.hkv; pa.tile_tokens = a.tile_tokens;
-  pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_slots = w.max_slots;
-  pa.skip_unit_chunks = skip_unit_chunks; pa.noncausal = noncausal;
-  pa.header = a.header; pa.tile_rec = (int32_t*)(base + w.wstart); pa.merge_rec = (int32_t*)(base + w.merge_rec);
-  e = launch_plan_append(pa, s);
-  if (e != hipSuccess) return fail_hip(e);
   {
     ProfileScope prof(s);
     // one workgroup per (tile, KV head); with fewer than 8 heads the kernel deals runs of tiles to the XCDs
     // of a head, which needs up to one run of slack per XCD (see the kernel's index mapping)
-    int64_t grid64 = (int64_t)tile_cap * a.hkv;
+    int64_t grid64 = (int64_t)call.tile_cap * a.hkv;
     if (a.hkv < kXcds && kXcds % a.hkv == 0) {
       const int64_t parts = kXcds / a.hkv;
-      grid64 = kXcds * (((int64_t)tile_cap + parts - 1) / parts + kAppendXcdRun);
+      grid64 = kXcds * (((int64_t)call.tile_cap + parts - 1) / parts + kAppendXcdRun);
     }
     const int grid = (int)std::min<int64_t>(grid64, INT32_MAX);
     int dev = -1;
     if (prof.on && hipGetDevice(&dev) == hipSuccess && dev == g_clock_dev) a.clock_sums = g_clock_sums;
-    e = launch_append_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3, half_tiles, grid, s);
+    e = launch_append_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3, call.half_tiles, grid, s);
     prof.stop();
   }
   if (e != hipSuccess) return fail_hip(e);
-  if (max_pieces) {
-    e = launch_append_merge(a, desc->head_dim, std::min(max_tiles, w.max_slots / 2), s);
+  if (call.max_merges) {
+    e = launch_append_merge(a, desc->head_dim, call.max_merges, s);
     if (e != hipSuccess) return fail_hip(e);
   }
   return ROLLATTN_OK;
+}
+
+static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int32_t* q_lens, const int32_t* q_offsets,
+                       int32_t total_q, int32_t max_q_len, const void* k_pages, const void* v_pages,
+                       const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
+                       size_t workspace_bytes, void* hip_stream, float* lse) {
+  if (!desc) return ROLLATTN_EINVAL;
+  AppendCall call{};
+  const int rc = append_prepare(desc, q_chunk, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
+                                workspace, workspace_bytes, desc->max_pages_per_seq, false, lse, false, &call);
+  if (rc || call.args.batch == 0) return rc;
+  hipStream_t s = (hipStream_t)hip_stream;
+  if (desc->q_dtype != ROLLATTN_F32) {
+    const hipError_t e = launch_plan_append(call.plan, s);
+    if (e != hipSuccess) return fail_hip(e);
+  }
+  return append_launch(desc, call, s);
 }
 
 int attn_append(const rollattn_desc* desc, const void* q_chunk, const int32_t* q_lens, const int32_t* q_offsets,
@@ -468,7 +520,7 @@ int attn_append(const rollattn_desc* desc, const void* q_chunk, const int32_t* q
                 size_t workspace_bytes, void* hip_stream) {
   if (!desc) return ROLLATTN_EINVAL;
   return append_impl(desc, q_chunk, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                     workspace, workspace_bytes, hip_stream, desc->max_pages_per_seq, false, nullptr);
+                     workspace, workspace_bytes, hip_stream, nullptr);
 }
 
 int attn_decode_lse(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
@@ -487,7 +539,7 @@ int attn_append_lse(const rollattn_desc* desc, const void* q_chunk, const int32_
   if (desc->batch > 0 && total_q > 0 && !lse) return ROLLATTN_EINVAL;
   if (lse && !aligned16(lse)) return ROLLATTN_EALIGN;
   return append_impl(desc, q_chunk, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                     workspace, workspace_bytes, hip_stream, desc->max_pages_per_seq, false, lse);
+                     workspace, workspace_bytes, hip_stream, lse);
 }
 
 int attn_merge(const rollattn_desc* desc, int64_t rows, const void* o1, const float* lse1, const void* o2,
@@ -530,7 +582,7 @@ int attn_step(const rollattn_desc* desc, const void* q, const int32_t* q_lens, c
   if (desc->q_dtype == ROLLATTN_F32) {
     // the float32 path has one kernel for chunks of any length, one token included
     return append_impl(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                       workspace, workspace_bytes, hip_stream, desc->max_pages_per_seq, false, nullptr);
+                       workspace, workspace_bytes, hip_stream, nullptr);
   }
   if (!q || !q_lens || !q_offsets || !k_pages || !v_pages || !page_table || !ctx_lens || !out) return ROLLATTN_EINVAL;
   if (!aligned16(q) || !aligned16(q_lens) || !aligned16(q_offsets) || !aligned16(k_pages) || !aligned16(v_pages) ||
@@ -540,21 +592,29 @@ int attn_step(const rollattn_desc* desc, const void* q, const int32_t* q_lens, c
   if (!rc) rc = decode_limits(*desc);
   if (rc) return rc;
   const size_t dec_bytes = align256(decode_layout(*desc).total);
-  // the long tiles of the chunks first, then the decode rows and their merge; all on one stream, disjoint output rows
-  rc = append_impl(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                   (char*)workspace + dec_bytes, workspace_bytes - dec_bytes, hip_stream, desc->max_pages_per_seq, false,
-                   nullptr, /*skip_unit_chunks=*/true);
+  AppendCall app{};
+  DecodeCall dec{};
+  rc = append_prepare(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
+                      (char*)workspace + dec_bytes, workspace_bytes - dec_bytes, desc->max_pages_per_seq, false, nullptr,
+                      /*skip_unit_chunks=*/true, &app);
+  if (!rc) rc = decode_prepare(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, dec_bytes, nullptr, q_lens, q_offsets, &dec);
   if (rc) return rc;
-  return decode_impl(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, dec_bytes, hip_stream, nullptr, q_lens,
-                     q_offsets);
+  // both plans in one launch, then the long tiles of the chunks first, then the decode rows and their merge; all on one
+  // stream, disjoint output rows
+  hipStream_t s = (hipStream_t)hip_stream;
+  const hipError_t e = launch_plan_step(app.plan, dec.plan, s);
+  if (e != hipSuccess) return fail_hip(e);
+  rc = append_launch(desc, app, s);
+  if (rc) return rc;
+  return decode_launch(desc, dec.args, s);
 }
 
 namespace {
-// Workspace of attn_decode_shared: the two inner workspaces, the two halves' rows and denominators,
-// the group "chunk" description and the shifted private tables.
+// Workspace of attn_decode_shared: the two inner workspaces, the two halves' rows and denominators, and where every
+// trajectory's private part starts.
 struct SharedLayout {
   rollattn_desc grp;      // descriptor of the shared half: one "trajectory" per group
-  size_t dec_ws, app_ws, o1, o2, d1, d2, grp_ctx, grp_qlens, grp_qoff, sfx_ctx, sfx_table, total;
+  size_t dec_ws, app_ws, o1, o2, d1, d2, own_ctx, own_page, total;
   size_t dec_bytes, app_bytes;
 };
 SharedLayout shared_layout(const rollattn_desc& d, int32_t group_size) {
@@ -562,7 +622,6 @@ SharedLayout shared_layout(const rollattn_desc& d, int32_t group_size) {
   L.grp = d;
   L.grp.batch = d.batch / group_size;
   const size_t rows = (size_t)d.batch * d.num_q_heads;
-  const size_t groups = (size_t)L.grp.batch;
   L.dec_bytes = decode_layout(d).total;
   L.app_bytes = append_layout(L.grp, d.batch).total;
   size_t off = 0;
@@ -572,11 +631,8 @@ SharedLayout shared_layout(const rollattn_desc& d, int32_t group_size) {
   L.o2 = off;        off += align256(rows * d.head_dim * 2);
   L.d1 = off;        off += align256(rows * sizeof(float));
   L.d2 = off;        off += align256(rows * sizeof(float));
-  L.grp_ctx = off;   off += align256(groups * sizeof(int32_t));
-  L.grp_qlens = off; off += align256(groups * sizeof(int32_t));
-  L.grp_qoff = off;  off += align256((groups + 1) * sizeof(int32_t));
-  L.sfx_ctx = off;   off += align256((size_t)d.batch * sizeof(int32_t));
-  L.sfx_table = off; off += align256((size_t)d.batch * d.max_pages_per_seq * sizeof(int32_t));
+  L.own_ctx = off;   off += align256((size_t)d.batch * sizeof(int32_t));
+  L.own_page = off;  off += align256((size_t)d.batch * sizeof(int32_t));
   L.total = off;
   return L;
 }
@@ -612,27 +668,27 @@ int attn_decode_shared(const rollattn_desc* desc, const void* q, const void* k_p
   if (rc) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
   char* base = (char*)workspace;
-  int32_t* grp_ctx = (int32_t*)(base + L.grp_ctx);
-  int32_t* grp_qlens = (int32_t*)(base + L.grp_qlens);
-  int32_t* grp_qoff = (int32_t*)(base + L.grp_qoff);
-  int32_t* sfx_ctx = (int32_t*)(base + L.sfx_ctx);
-  int32_t* sfx_table = (int32_t*)(base + L.sfx_table);
-  hipError_t e = launch_shared_prep(ctx_lens, shared_lens, page_table, desc->batch, group_size, desc->max_pages_per_seq,
-                                    grp_ctx, grp_qlens, grp_qoff, sfx_ctx, sfx_table, s);
-  if (e != hipSuccess) return fail_hip(e);
-  // shared half: the members' query rows of a group as one chunk over the group's first S tokens
-  rc = append_impl(&L.grp, q, grp_qlens, grp_qoff, desc->batch, group_size, k_pages, v_pages, page_table, grp_ctx,
-                   base + L.o1, base + L.app_ws, L.app_bytes, hip_stream, group_size * desc->max_pages_per_seq, true,
-                   (float*)(base + L.d1));
+  SharedPlanArgs sh{};
+  sh.ctx_lens = ctx_lens; sh.shared_lens = shared_lens; sh.batch = desc->batch; sh.group_size = group_size;
+  sh.own_ctx = (int32_t*)(base + L.own_ctx);
+  sh.own_page = (int32_t*)(base + L.own_page);
+  // shared half: the members' query rows of a group as one chunk over the group's first S tokens, behind its first
+  // member's table; private half: every trajectory from token S on
+  AppendCall app{};
+  DecodeCall dec{};
+  rc = append_prepare(&L.grp, q, nullptr, nullptr, desc->batch, group_size, k_pages, v_pages, page_table, nullptr,
+                      base + L.o1, base + L.app_ws, L.app_bytes, group_size * desc->max_pages_per_seq, true,
+                      (float*)(base + L.d1), false, &app);
+  if (!rc) rc = decode_prepare(desc, q, k_pages, v_pages, page_table, sh.own_ctx, base + L.o2, base + L.dec_ws, L.dec_bytes,
+                               (float*)(base + L.d2), nullptr, nullptr, &dec);
   if (rc) return rc;
-  // private half: every trajectory from token S on
-  rc = decode_impl(desc, q, k_pages, v_pages, sfx_table, sfx_ctx, base + L.o2, base + L.dec_ws, L.dec_bytes, hip_stream,
-                   (float*)(base + L.d2));
-  if (rc) return rc;
-  e = launch_merge_states(base + L.o1, (const float*)(base + L.d1), base + L.o2, (const float*)(base + L.d2), out, nullptr,
-                          (long)desc->batch * desc->num_q_heads, desc->head_dim, /*f32=*/false, s);
+  dec.args.first_page = sh.own_page;
+  const hipError_t e = launch_plan_shared(sh, app.plan, dec.plan, s);
   if (e != hipSuccess) return fail_hip(e);
-  return ROLLATTN_OK;
+  rc = append_launch(&L.grp, app, s);
+  if (rc) return rc;
+  const SharedHalf shared{base + L.o1, (const float*)(base + L.d1), out};
+  return decode_launch(desc, dec.args, s, &shared);
 }
 
 int kv_write(const rollattn_desc* desc, const void* k_new, const void* v_new, const int32_t* q_lens,

@@ -35,9 +35,14 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ floatx4 widen(const bf16x4 x) { return floatx4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]}; }
+
 // One workgroup per (row, run of chunks_per_wg chunks of it).
-template <int D, bool OUT_BF16>
-__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, int wgs_per_row, int chunks_per_wg) {
+// SHARED (attn_decode_shared): another result over the first part of every context is folded in as one more piece, with
+// the weight 2^d of its denominator, and every row is written: one that a single worker finished is read back as a piece.
+// The merge of the two halves as a launch of its own cost 8 us of a 268 us step and rounded split rows to bf16 in between.
+template <int D, bool OUT_BF16, bool SHARED>
+__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, const SharedHalf other, int wgs_per_row, int chunks_per_wg) {
   __shared__ __attribute__((aligned(16))) float sum_s[kWaves][64][4];
   __shared__ float ml_s[kWaves][64][2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -55,7 +60,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, i
   const long r0 = (long)a.rows_per_b * first + (long)r * n;
   const int wf = n ? (int)(r0 / per) : 0;
   const int wl = n ? (int)((r0 + n - 1) / per) : 0;
-  if (n && wf == wl) return;                                // one worker had the whole row
+  if (!SHARED && n && wf == wl) return;                     // one worker had the whole row
   const int pieces = n ? wl - wf + 1 : 0;
   const int first_slot = ((long)wf * per < r0) ? 1 : 0;
   const size_t orow0 = (size_t)(a.q_offsets ? a.q_offsets[b] : b) * a.hq + (size_t)g * a.group + h0;   // where the row's first head goes
@@ -99,7 +104,21 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, i
         o += f * y[i];
       }
     };
-    if (pieces == 0) {}                                     // nothing to fold: a zero row
+    const size_t dst = orow0 * D + at;
+    floatx4 o1 = {0.f, 0.f, 0.f, 0.f};
+    float d1 = -INFINITY;
+    if constexpr (SHARED) {
+      if (ok) {
+        o1 = widen(*(const bf16x4*)((const __bf16*)other.out + dst));
+        d1 = other.lse[orow0 + head];
+        if (pieces == 1) {
+          o = widen(*(const bf16x4*)((const __bf16*)a.out + dst));
+          m = a.lse[orow0 + head];
+          l = 1.f;
+        }
+      }
+    }
+    if (pieces < 2) {}                                      // nothing to fold (none: a zero row)
     else if (pieces == 2) fold(0, std::integral_constant<int, 2>{});
     else if (pieces == 3) fold(0, std::integral_constant<int, 3>{});
     else if (pieces <= 5) fold(0, std::integral_constant<int, 5>{});
@@ -126,9 +145,19 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, i
       if (wave != 0) continue;
     }
     if (!ok) continue;
+    if constexpr (SHARED) {
+      const float top = fmaxf(m, d1), base = (top == -INFINITY) ? 0.f : top;
+      const float w1 = __builtin_amdgcn_exp2f(d1 - base), w2 = __builtin_amdgcn_exp2f(m - base);   // 2^-inf = 0
+      const float tot = w1 + w2 * l, inv = tot > 0.f ? 1.f / tot : tot;
+      o = (w1 * o1 + w2 * o) * inv;
+      bf16x4 pk;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)o[e];
+      *(bf16x4*)((__bf16*)other.result + dst) = pk;
+      continue;
+    }
     const float inv = n ? 1.f / l : 0.f;
     if (a.lse && at % D == 0) a.lse[orow0 + head] = n ? m + __builtin_amdgcn_logf(l) : -INFINITY;
-    const size_t dst = orow0 * D + at;
     if constexpr (OUT_BF16) {
       bf16x4 pk;
 #pragma unroll
@@ -198,23 +227,45 @@ hipError_t launch_check_inputs(const int32_t* page_table, const int32_t* ctx_len
   return hipGetLastError();
 }
 
-hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s) {
+namespace {
+struct CombineGrid {
+  dim3 grid;
+  int wgs_per_row, chunks_per_wg;
+};
+CombineGrid combine_grid(const DecodeArgs& a, int head_dim) {
   const int chunks = (std::min(a.head_tile, a.group) * head_dim + kChunkFloats - 1) / kChunkFloats;
   const long rows = (long)a.batch * a.rows_per_b;
   // A workgroup per chunk while those are few enough to be resident at once, so that the waves of a row of many pieces
   // have one chunk to share; with more rows (of few pieces each) a chunk per wave.
   const int chunks_per_wg = rows * chunks <= kCombineResident ? 1 : std::min(chunks, kWaves);
   const int wgs_per_row = (chunks + chunks_per_wg - 1) / chunks_per_wg;
-  const dim3 grid((unsigned)(rows * wgs_per_row));
-  if (rows == 0) return hipSuccess;
+  return {dim3((unsigned)(rows * wgs_per_row)), wgs_per_row, chunks_per_wg};
+}
+}  // namespace
+
+hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s) {
+  const CombineGrid c = combine_grid(a, head_dim);
+  const SharedHalf none{};
   if (head_dim == 128 && out_bf16) {
-    hipLaunchKernelGGL((combine_kernel<128, true>), grid, dim3(kThreads), 0, s, a, wgs_per_row, chunks_per_wg);
+    hipLaunchKernelGGL((combine_kernel<128, true, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
   } else if (head_dim == 128) {
-    hipLaunchKernelGGL((combine_kernel<128, false>), grid, dim3(kThreads), 0, s, a, wgs_per_row, chunks_per_wg);
+    hipLaunchKernelGGL((combine_kernel<128, false, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
   } else if (head_dim == 64 && out_bf16) {
-    hipLaunchKernelGGL((combine_kernel<64, true>), grid, dim3(kThreads), 0, s, a, wgs_per_row, chunks_per_wg);
+    hipLaunchKernelGGL((combine_kernel<64, true, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
   } else if (head_dim == 64) {
-    hipLaunchKernelGGL((combine_kernel<64, false>), grid, dim3(kThreads), 0, s, a, wgs_per_row, chunks_per_wg);
+    hipLaunchKernelGGL((combine_kernel<64, false, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_combine_shared(const DecodeArgs& a, const SharedHalf& shared, int head_dim, hipStream_t s) {
+  const CombineGrid c = combine_grid(a, head_dim);
+  if (head_dim == 128) {
+    hipLaunchKernelGGL((combine_kernel<128, true, true>), c.grid, dim3(kThreads), 0, s, a, shared, c.wgs_per_row, c.chunks_per_wg);
+  } else if (head_dim == 64) {
+    hipLaunchKernelGGL((combine_kernel<64, true, true>), c.grid, dim3(kThreads), 0, s, a, shared, c.wgs_per_row, c.chunks_per_wg);
   } else {
     return hipErrorInvalidValue;
   }

@@ -136,7 +136,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
   float ksc[G_::kStages], vsc[G_::kStages];   // FP8: page scales of this lane's 8 tokens
   auto load_window = [&](int k) {
     const int pg = k * 64 + lane;
-    return (pg < ((pc.len + kPageSize - 1) >> 4)) ? a.page_table[(size_t)pc.b * a.max_pages + pg] : 0;
+    const int* row = a.page_table + (size_t)pc.b * a.max_pages + (a.first_page ? a.first_page[pc.b] : 0);
+    return (pg < ((pc.len + kPageSize - 1) >> 4)) ? row[pg] : 0;
   };
   auto issue = [&](int stage) {
     const int k = pc.blk >> 5;

@@ -63,19 +63,22 @@ __device__ int block_exclusive_scan(int v, int4* wave_tot /*[kPlanThreads / 256]
 // workers in equal contiguous runs of per = ceil(T / W) blocks.  Written out: the exclusive
 // scan of n_b, the run length, T, and for every worker one 16-byte record with all it needs to
 // start: (b, r << 20 | block, L_b, blocks in its run), or b = -1 for a worker without blocks.
-// With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
-__global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(
-    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ q_lens, int32_t batch, int32_t rows_per_b,
-    int32_t workers, int32_t slots, int32_t* __restrict__ header, int32_t* __restrict__ prefix, int32_t* __restrict__ wstart) {
+// len_of(b): tokens of trajectory b that take part.
+template <class L>
+__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, L&& len_of) {
   __shared__ int4 wave_tot[kPlanThreads / 256];
   __shared__ int prefix_s[kLdsPrefix + 1];
   const int tid = threadIdx.x;
+  const int32_t batch = a.batch, rows_per_b = a.rows_per_b, workers = a.workers, slots = a.slots;
+  int32_t* const header = a.header;
+  int32_t* const prefix = a.prefix;
+  int32_t* const wstart = a.wstart;
   const bool in_lds = batch <= kLdsPrefix;
   __shared__ int len_s[kLdsPrefix];
   int running = 0;
   for (int b0 = 0; b0 < batch; b0 += kPlanThreads) {
     const int b = b0 + tid;
-    const int len = (b < batch && (!q_lens || q_lens[b] == 1)) ? ctx_lens[b] : 0;
+    const int len = b < batch ? len_of(b) : 0;
     const int count = (len + kBlockTokens - 1) / kBlockTokens;
     int tile_total;
     const int first = running + block_exclusive_scan(count, wave_tot, &tile_total);
@@ -117,11 +120,18 @@ __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(
       const int n = pf[lo + 1] - pf[lo];
       const int rem = (int)(x - (long)rows_per_b * pf[lo]);
       const int mine = (int)min((long)per, (long)total - x);
-      st = make_int4(lo, ((rem / n) << 20) | (rem % n), in_lds ? len_s[lo] : ctx_lens[lo], mine);   // lo has blocks, so it takes part
+      st = make_int4(lo, ((rem / n) << 20) | (rem % n), in_lds ? len_s[lo] : len_of(lo), mine);
     }
     *(int4*)(wstart + 4 * w) = st;
   }
 }
+
+// With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
+__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a) {
+  plan_decode(a, [&](int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; });
+}
+
+__global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodePlanArgs a) { plan_decode(a); }
 
 // Append work list: each chunk cut into tiles of tile_tokens query tokens.  A tile's cost grows
 // with its trajectory's context, and workgroups are dispatched in list order, so (for batches that
@@ -154,7 +164,16 @@ __device__ __forceinline__ float split_price(float p, float blocks, float pieces
   return fmaxf(p + kPieceCost, load + u * (p + kPieceCost) * (ceilf(w) - w));
 }
 
-__global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendPlanArgs a) {
+// What the append plan asks about a chunk: its context, its rows, where they start in the packed query.
+struct ChunkLens {
+  const int32_t *ctx_lens, *q_lens, *q_offsets;
+  __device__ __forceinline__ int ctx(int b) const { return ctx_lens[b]; }
+  __device__ __forceinline__ int rows(int b) const { return q_lens[b]; }
+  __device__ __forceinline__ int offset(int b) const { return q_offsets[b]; }
+};
+
+template <class C>
+__device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& chunk) {
   __shared__ int4 wave_tot[kPlanThreads / 256];
   __shared__ int len_s[kRankBatch];
   __shared__ int order_s[kRankBatch];
@@ -162,7 +181,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendP
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
   if (ranked) {
-    for (int b = tid; b < batch; b += kPlanThreads) len_s[b] = a.ctx_lens[b];
+    for (int b = tid; b < batch; b += kPlanThreads) len_s[b] = chunk.ctx(b);
     __syncthreads();
     for (int b = tid; b < batch; b += kPlanThreads) {
       const int mine = len_s[b];
@@ -186,7 +205,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendP
     int b = 0, count = 0, q_len = 0;
     if (p < batch) {
       b = ranked ? order_s[p] : p;
-      q_len = a.q_lens[b];
+      q_len = chunk.rows(b);
       count = (q_len + tile_tokens - 1) / tile_tokens;
       if (a.skip_unit_chunks && q_len == 1) count = 0;   // mixed step: the decode kernel takes these
     }
@@ -196,8 +215,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendP
     count_s[tid] = count;
     b_s[tid] = b;
     qlen_s[tid] = q_len;
-    ctx_s[tid] = p < batch ? a.ctx_lens[b] : 0;
-    qoff_s[tid] = p < batch ? a.q_offsets[b] : 0;
+    ctx_s[tid] = p < batch ? chunk.ctx(b) : 0;
+    qoff_s[tid] = p < batch ? chunk.offset(b) : 0;
     __syncthreads();
     // One 32-byte record per tile with everything the tile's workgroup needs to start, so that it gets there with
     // one dependent load instead of a chain of them: (b, first row, n_b, L_b, q_offsets[b], first block, blocks, slot).
@@ -313,17 +332,83 @@ __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendP
   }
 }
 
+__global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendPlanArgs a) {
+  plan_append(a, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
+}
+
+// Both plans of a mixed step side by side.
+__global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPlanArgs a, const DecodePlanArgs d) {
+  if (blockIdx.x == 0) plan_append(a, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
+  else plan_decode(d);
+}
+
+// Decode of groups that share a prompt: per group the shared length actually used, S = floor32(min(shared_lens[group],
+// min over the group of L_b - 1)), so that every trajectory keeps at least its current token for itself and the private
+// part starts on a block boundary.  One workgroup plans the shared half (a chunk per group, its members' query rows, over
+// the group's first S tokens), the other one the private half (every trajectory from token S on), whose lengths and
+// first table entries it writes out for the decode kernel.  Each works S out for itself: a launch that did, and
+// copied the table shifted by S, took 5 us, and the plans one after the other 12 where this launch takes 8 (64 groups of 8).
+constexpr int kSharedGroups = 2048;   // up to this many groups their lengths are settled in LDS
+
+__global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedPlanArgs sh, const AppendPlanArgs a, const DecodePlanArgs d) {
+  __shared__ int used_s[kSharedGroups];
+  const int groups = sh.batch / sh.group_size;
+  const bool in_lds = groups <= kSharedGroups;
+  if (in_lds) {
+    for (int g = threadIdx.x; g < groups; g += kPlanThreads) used_s[g] = max(0, sh.shared_lens[g]);
+    __syncthreads();
+    for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) atomicMin(&used_s[b / sh.group_size], max(0, sh.ctx_lens[b] - 1));
+    __syncthreads();
+  }
+  auto used = [&](int g) -> int {
+    int s;
+    if (in_lds) {
+      s = used_s[g];
+    } else {
+      s = sh.shared_lens[g];
+      for (int m = 0; m < sh.group_size; ++m) s = min(s, sh.ctx_lens[(size_t)g * sh.group_size + m] - 1);
+      s = max(s, 0);
+    }
+    return s & ~(kBlockTokens - 1);
+  };
+  if (blockIdx.x == 0) {
+    struct Groups {
+      decltype(used)& len;
+      int size;
+      __device__ __forceinline__ int ctx(int g) const { return len(g); }
+      __device__ __forceinline__ int rows(int) const { return size; }
+      __device__ __forceinline__ int offset(int g) const { return g * size; }
+    };
+    plan_append(a, Groups{used, sh.group_size});
+  } else {
+    for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) {
+      const int s = used(b / sh.group_size);
+      sh.own_ctx[b] = sh.ctx_lens[b] - s;
+      sh.own_page[b] = s / kPageSize;
+    }
+    plan_decode(d, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
+  }
+}
+
 }  // namespace
 
-hipError_t launch_plan_decode(const int32_t* ctx_lens, const int32_t* q_lens, int32_t batch, int32_t rows_per_b,
-                              int32_t workers, int32_t slots, int32_t* header, int32_t* prefix, int32_t* wstart, hipStream_t s) {
-  hipLaunchKernelGGL(plan_decode_kernel, dim3(1), dim3(kPlanThreads), 0, s, ctx_lens, q_lens, batch, rows_per_b, workers,
-                     slots, header, prefix, wstart);
+hipError_t launch_plan_decode(const DecodePlanArgs& d, hipStream_t s) {
+  hipLaunchKernelGGL(plan_decode_kernel, dim3(1), dim3(kPlanThreads), 0, s, d);
   return hipGetLastError();
 }
 
 hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(plan_append_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
+  hipLaunchKernelGGL(plan_step_kernel, dim3(2), dim3(kPlanThreads), 0, s, a, d);
+  return hipGetLastError();
+}
+
+hipError_t launch_plan_shared(const SharedPlanArgs& sh, const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
+  hipLaunchKernelGGL(plan_shared_kernel, dim3(2), dim3(kPlanThreads), 0, s, sh, a, d);
   return hipGetLastError();
 }
 

@@ -69,6 +69,15 @@ struct DecodeArgs {
   // as empty here; the query and output row of trajectory b is q_offsets[b] instead of b.
   const int32_t* q_lens;
   const int32_t* q_offsets;
+  // Private half of attn_decode_shared (null otherwise): the context of trajectory b starts at this entry of its table row.
+  const int32_t* first_page;
+};
+
+// The shared half's result, which the merge of the private half's rows folds in (attn_decode_shared; all null otherwise).
+struct SharedHalf {
+  const void* out;      // bf16 [B][Hq][D], normalised
+  const float* lse;     // [B][Hq]
+  void* result;         // where the whole rows go
 };
 
 struct AppendArgs {
@@ -99,6 +108,26 @@ struct AppendArgs {
   unsigned long long* clock_sums;
 };
 
+// Inputs and outputs of the decode partition.
+struct DecodePlanArgs {
+  const int32_t* ctx_lens;
+  const int32_t* q_lens;           // mixed step, else null
+  int32_t batch, rows_per_b;
+  int32_t workers, slots;          // how many the partition is cut for; records written (those past `workers` say "no blocks")
+  int32_t* header;
+  int32_t* prefix;
+  int32_t* wstart;
+};
+
+// Inputs and outputs of the shared lengths of attn_decode_shared.
+struct SharedPlanArgs {
+  const int32_t* ctx_lens;
+  const int32_t* shared_lens;
+  int32_t batch, group_size;
+  int32_t* own_ctx;                // [B] tokens past the shared ones
+  int32_t* own_page;               // [B] table entry they start at
+};
+
 // Inputs and outputs of the append work list.
 struct AppendPlanArgs {
   const int32_t* q_lens;
@@ -115,13 +144,16 @@ struct AppendPlanArgs {
 };
 
 // Launchers (defined in the .hip files).  Each returns the hipError_t of its launch.
-// workers: how many the partition is cut for; slots >= workers: records written (those past `workers` say "no blocks")
-hipError_t launch_plan_decode(const int32_t* ctx_lens, const int32_t* q_lens, int32_t batch, int32_t rows_per_b,
-                              int32_t workers, int32_t slots, int32_t* header, int32_t* prefix, int32_t* wstart, hipStream_t s);
+hipError_t launch_plan_decode(const DecodePlanArgs& d, hipStream_t s);
 hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s);
+// two plans at once; launch_plan_shared reads the lengths of both from `sh` (those in a and d are not used)
+hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s);
+hipError_t launch_plan_shared(const SharedPlanArgs& sh, const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, int grid, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int grid, hipStream_t s);
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s);
+// the same for bf16 rows of which `shared` holds another part of the context: every row is written, to shared.result
+hipError_t launch_combine_shared(const DecodeArgs& a, const SharedHalf& shared, int head_dim, hipStream_t s);
 // half_tiles: every tile has at most kAppendTileRows / 2 rows (a.tile_tokens is set accordingly) and the
 // two waves of a SIMD split each block of a tile between them instead of owning different rows
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s);
@@ -132,9 +164,6 @@ hipError_t launch_kv_write(const void* k_new, const void* v_new, const int32_t* 
                            void* k_pages, void* v_pages, const int32_t* page_table, const int32_t* ctx_lens,
                            float* k_scale, float* v_scale, int32_t batch, int32_t hkv, int32_t max_pages,
                            int32_t max_q_len, int head_dim, int src_bytes, bool fp8, hipStream_t s);
-hipError_t launch_shared_prep(const int32_t* ctx_lens, const int32_t* shared_lens, const int32_t* page_table, int32_t batch,
-                              int32_t group_size, int32_t max_pages, int32_t* grp_ctx, int32_t* grp_qlens, int32_t* grp_qoff,
-                              int32_t* sfx_ctx, int32_t* sfx_table, hipStream_t s);
 hipError_t launch_merge_states(const void* o1, const float* d1, const void* o2, const float* d2, void* out, float* d_out,
                                long rows, int head_dim, bool f32, hipStream_t s);
 hipError_t launch_check_inputs(const int32_t* page_table, const int32_t* ctx_lens, const int32_t* q_lens,

@@ -6,7 +6,7 @@ import torch
 from oracle import attention as O
 from paper_2512_22560_amd import binding as B
 from paper_2512_22560_amd import workloads as W
-from tests.gpu_common import check
+from tests.gpu_common import check, oracle_decode
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -35,3 +35,16 @@ def test_rows_of_every_number_of_pieces(qd, hkv, group, d, copies):
     assert torch.isneginf(lse[cl == 0]).all() and torch.isfinite(lse[cl > 0]).all() and not out[cl == 0].any()
     again, lse2 = B.attn_decode_lse(b.q, k, v, pt, cl, sm_scale=w.sm_scale)
     assert torch.equal(out, again) and torch.equal(lse, lse2)
+
+
+# more groups than the plan keeps in LDS; odd groups with a long private part (many pieces per row), one without shared
+# tokens and one whose member is shorter than the prompt; one long prompt and private parts of one token (one piece per row)
+@pytest.mark.parametrize("group_size,groups,ctx,shared", [(1, 2049, (1, 70), 32), (3, 3, (3000, 9000), 2500), (3, 4, (64, 700), 640), (8, 2, (1025, 1025), 1024)])
+def test_shared_half_folds_into_rows_of_every_kind(group_size, groups, ctx, shared):
+    b = W.build(W.Workload("fold", group_size * groups, 16, 4, 128, "bf16", "bf16", ("uniform", *ctx), seed=W.BASE_SEED + 98), DEV)
+    used = np.full(groups, shared)
+    used[-1] = 0 if groups == 3 else shared
+    b = W.alias_shared_prefix(b, group_size, np.minimum(used, b.ctx_lens_host.reshape(groups, group_size).min(1)))
+    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=group_size,
+                               shared_lens=torch.from_numpy(used.astype(np.int32)).to(DEV), sm_scale=b.workload.sm_scale)
+    check(out, oracle_decode(b), "bf16", "shared")
