@@ -331,9 +331,28 @@ static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_p
   const int rc = decode_prepare(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, workspace_bytes, lse, nullptr,
                                 nullptr, &call);
   if (rc || call.args.batch == 0) return rc;
-  const hipError_t e = launch_plan_decode(call.plan, (hipStream_t)hip_stream);
-  if (e != hipSuccess) return fail_hip(e);
-  return decode_launch(desc, call.args, (hipStream_t)hip_stream);
+  hipStream_t s = (hipStream_t)hip_stream;
+  const bool f32 = desc->q_dtype == ROLLATTN_F32;
+  // A launch of its own for the plan costs its 3 to 5 us and the gap behind it.  Small batches do without.  Over MFMA every
+  // wave finds its own start, a lane per trajectory (64 contexts of 512 .. 8k, 32/8/128, bf16: 159.6 -> 155.0 us; with more
+  // trajectories the step is long enough not to notice).  Short float32 contexts are not cut at all while their rows fit the
+  // chip at once (8/2/64, one launch against three: 4 contexts of 256 tokens 4.2 against 10.5 us, 64 of 512 tokens 11.3
+  // against 16.3; but 256 of 16 tokens 13.2 against 10.5).
+  const bool alone = f32 ? desc->max_pages_per_seq <= kDirectPages && (int64_t)desc->batch * call.args.rows_per_b <= kNumCUs
+                         : desc->batch <= kWavePlanBatch;
+  if (alone) {
+    call.args.plan = call.plan;
+  } else {
+    const hipError_t e = launch_plan_decode(call.plan, s);
+    if (e != hipSuccess) return fail_hip(e);
+  }
+  if (f32 && call.args.plan.batch) {
+    ProfileScope prof(s);
+    const hipError_t e = launch_decode_f32_direct(call.args, desc->head_dim, s);
+    prof.stop();
+    return e == hipSuccess ? ROLLATTN_OK : fail_hip(e);
+  }
+  return decode_launch(desc, call.args, s);
 }
 
 int attn_decode(const rollattn_desc* desc, const void* q, const void* k_pages, const void* v_pages,

@@ -953,7 +953,11 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
     float top = ref;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      if (s0 + i >= pieces) x[i][0] = -INFINITY;
+      if (s0 + i >= pieces) {                              // (zero times an infinity would not be zero)
+        x[i][0] = -INFINITY;
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) y[i][i4] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
       top = fmaxf(top, x[i][0]);
     }
     const float base = (top == -INFINITY) ? 0.f : top;

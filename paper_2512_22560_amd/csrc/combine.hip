@@ -90,7 +90,10 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, c
       float top = m;
 #pragma unroll
       for (int i = 0; i < kN; ++i) {
-        if (s0 + i * step >= pieces) x[i][0] = -INFINITY;
+        if (s0 + i * step >= pieces) {                      // (zero times an infinity would not be zero)
+          x[i] = floatx2{-INFINITY, 0.f};
+          y[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
         top = fmaxf(top, x[i][0]);
       }
       const float keep = __builtin_amdgcn_exp2f(m - top);   // (a partial has seen at least one token: its maximum is finite)

@@ -14,7 +14,7 @@
 // The transposed products keep "head" on the lane axis in both results, so the online
 // softmax state (running max, running sum, rescale factor) is one scalar per lane and P
 // feeds the second product straight from the first one's accumulator registers.
-#include "rollattn_internal.h"
+#include "plan_device.h"
 
 namespace rollattn {
 
@@ -100,7 +100,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
   unsigned char* const v_lds = lds[wave] + G_::kTileBytes;
 
   const int worker = blockIdx.x * kWaves + wave;
-  const int4 start = *(const int4*)(a.wstart + 4 * worker);   // (b, r << 20 | block, L_b, run length)
+  // (b, r << 20 | block, L_b, run length)
+  const int4 start = a.plan.batch ? plan_decode_in_wave(a.plan, worker) : *(const int4*)(a.wstart + 4 * worker);
   if (start.x < 0) return;
   const int n_mine = __builtin_amdgcn_readfirstlane(start.w);
   const int group = a.group, hkv = a.hkv, rows_per_b = a.rows_per_b;

@@ -1,26 +1,11 @@
 // Device-side planning: turns ctx_lens / q_lens into compact work lists without a host
 // round trip, so a call never synchronises.  The partition depends on the lengths only,
 // never on physical page ids.
-#include "rollattn_internal.h"
+#include "plan_device.h"
 
 namespace rollattn {
 
 namespace {
-
-constexpr int kPlanThreads = 1024;
-
-constexpr int kLdsPrefix = 8192;   // batches up to this size keep the scan in LDS for the searches
-
-// Inclusive scan over the wave in six cross-lane steps of the vector ALU (rows of 16, then their last lanes broadcast).
-__device__ __forceinline__ int wave_inclusive_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return x;
-}
 
 __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), 63); }
 
@@ -35,95 +20,6 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) {
   step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
   step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
   return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
-
-// Exclusive scan of one int per thread across the workgroup; returns this thread's prefix
-// and leaves the workgroup total in *total.  A plan kernel is one workgroup that every CU waits for, so its barriers
-// and LDS round trips count: two barriers, four reads.
-__device__ int block_exclusive_scan(int v, int4* wave_tot /*[kPlanThreads / 256]*/, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int incl = wave_inclusive_scan(v);
-  if (lane == 63) ((int*)wave_tot)[wave] = incl;
-  __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kPlanThreads / 256; ++i) {
-    const int4 t = wave_tot[i];
-    base += (4 * i < wave ? t.x : 0) + (4 * i + 1 < wave ? t.y : 0) + (4 * i + 2 < wave ? t.z : 0) + (4 * i + 3 < wave ? t.w : 0);
-    tot += t.x + t.y + t.z + t.w;
-  }
-  *total = tot;
-  __syncthreads();
-  return base + incl - v;
-}
-
-// Decode partition.  Every trajectory is cut into blocks of kBlockTokens tokens; the rows
-// (trajectory b, row r in [0, rows_per_b)) are laid end to end, b outermost, each with
-// n_b = ceil(L_b / kBlockTokens) blocks; the resulting sequence of T blocks is dealt to the W
-// workers in equal contiguous runs of per = ceil(T / W) blocks.  Written out: the exclusive
-// scan of n_b, the run length, T, and for every worker one 16-byte record with all it needs to
-// start: (b, r << 20 | block, L_b, blocks in its run), or b = -1 for a worker without blocks.
-// len_of(b): tokens of trajectory b that take part.
-template <class L>
-__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, L&& len_of) {
-  __shared__ int4 wave_tot[kPlanThreads / 256];
-  __shared__ int prefix_s[kLdsPrefix + 1];
-  const int tid = threadIdx.x;
-  const int32_t batch = a.batch, rows_per_b = a.rows_per_b, workers = a.workers, slots = a.slots;
-  int32_t* const header = a.header;
-  int32_t* const prefix = a.prefix;
-  int32_t* const wstart = a.wstart;
-  const bool in_lds = batch <= kLdsPrefix;
-  __shared__ int len_s[kLdsPrefix];
-  int running = 0;
-  for (int b0 = 0; b0 < batch; b0 += kPlanThreads) {
-    const int b = b0 + tid;
-    const int len = b < batch ? len_of(b) : 0;
-    const int count = (len + kBlockTokens - 1) / kBlockTokens;
-    int tile_total;
-    const int first = running + block_exclusive_scan(count, wave_tot, &tile_total);
-    if (b < batch) {
-      prefix[b] = first;
-      if (in_lds) {
-        prefix_s[b] = first;
-        len_s[b] = len;
-      }
-    }
-    running += tile_total;
-  }
-  if (tid == 0) {
-    prefix[batch] = running;
-    if (in_lds) prefix_s[batch] = running;
-  }
-  const int total = running * rows_per_b;
-  const int per = max(1, (total + workers - 1) / workers);
-  if (tid == 0) {
-    header[kPlanPer] = per;
-    header[kPlanTotal] = total;
-    header[kPlanWorkers] = workers;
-    header[kPlanRowsPerB] = rows_per_b;
-  }
-  __threadfence_block();
-  __syncthreads();   // prefix[] written above is read below by other threads of this workgroup
-  for (int w = tid; w < slots; w += kPlanThreads) {
-    const long x = (long)w * per;
-    int4 st = make_int4(-1, 0, 0, 0);
-    if (w < workers && x < total) {
-      // largest b with rows_per_b * prefix[b] <= x (rows without blocks can never be the answer
-      // because the next row then starts at the same position)
-      const int* pf = in_lds ? prefix_s : prefix;
-      int lo = 0, hi = batch;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((long)rows_per_b * pf[mid] <= x) lo = mid; else hi = mid;
-      }
-      const int n = pf[lo + 1] - pf[lo];
-      const int rem = (int)(x - (long)rows_per_b * pf[lo]);
-      const int mine = (int)min((long)per, (long)total - x);
-      st = make_int4(lo, ((rem / n) << 20) | (rem % n), in_lds ? len_s[lo] : len_of(lo), mine);
-    }
-    *(int4*)(wstart + 4 * w) = st;
-  }
 }
 
 // With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.

@@ -16,6 +16,8 @@ constexpr int kMfmaDecodeWgs = 2 * kNumCUs;   // 4 wave-workers each
 constexpr int kMfmaHeadTile = 16;       // query heads per MFMA decode row
 constexpr int kF32DecodeWgs = 4 * kNumCUs;    // one workgroup-worker each
 constexpr int kF32HeadTile = 4;         // query heads per float32 decode row
+constexpr int kWavePlanBatch = 64;      // batches up to this size are planned by every decode wave for itself
+constexpr int kDirectPages = 32;        // float32 contexts of at most this many pages are not cut
 constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pairs) per append workgroup
 constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
 constexpr int kAppendBlockTokens = 64;  // KV tokens staged per step of the append kernel
@@ -47,6 +49,17 @@ struct WorkspaceLayout {
 WorkspaceLayout decode_layout(const rollattn_desc& d);
 WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q);
 
+// Inputs and outputs of the decode partition.
+struct DecodePlanArgs {
+  const int32_t* ctx_lens;
+  const int32_t* q_lens;           // mixed step, else null
+  int32_t batch, rows_per_b;
+  int32_t workers, slots;          // how many the partition is cut for; records written (those past `workers` say "no blocks")
+  int32_t* header;
+  int32_t* prefix;
+  int32_t* wstart;
+};
+
 // Kernel arguments (passed by value).
 struct DecodeArgs {
   const void* q;
@@ -71,6 +84,8 @@ struct DecodeArgs {
   const int32_t* q_offsets;
   // Private half of attn_decode_shared (null otherwise): the context of trajectory b starts at this entry of its table row.
   const int32_t* first_page;
+  // Set (batch > 0) where no plan was launched: the decode kernel plans for itself.
+  DecodePlanArgs plan;
 };
 
 // The shared half's result, which the merge of the private half's rows folds in (attn_decode_shared; all null otherwise).
@@ -108,17 +123,6 @@ struct AppendArgs {
   unsigned long long* clock_sums;
 };
 
-// Inputs and outputs of the decode partition.
-struct DecodePlanArgs {
-  const int32_t* ctx_lens;
-  const int32_t* q_lens;           // mixed step, else null
-  int32_t batch, rows_per_b;
-  int32_t workers, slots;          // how many the partition is cut for; records written (those past `workers` say "no blocks")
-  int32_t* header;
-  int32_t* prefix;
-  int32_t* wstart;
-};
-
 // Inputs and outputs of the shared lengths of attn_decode_shared.
 struct SharedPlanArgs {
   const int32_t* ctx_lens;
@@ -150,6 +154,8 @@ hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s);
 hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s);
 hipError_t launch_plan_shared(const SharedPlanArgs& sh, const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, int grid, hipStream_t s);
+// float32, one launch for plan, attention and output: a workgroup per row, for tables of at most kDirectPages pages and no more rows than CUs
+hipError_t launch_decode_f32_direct(const DecodeArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int grid, hipStream_t s);
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s);
 // the same for bf16 rows of which `shared` holds another part of the context: every row is written, to shared.result

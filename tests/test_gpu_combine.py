@@ -7,6 +7,7 @@ from oracle import attention as O
 from paper_2512_22560_amd import binding as B
 from paper_2512_22560_amd import workloads as W
 from tests.gpu_common import check, oracle_decode
+from tests.helpers import oracle_args
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -48,3 +49,34 @@ def test_shared_half_folds_into_rows_of_every_kind(group_size, groups, ctx, shar
     out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=group_size,
                                shared_lens=torch.from_numpy(used.astype(np.int32)).to(DEV), sm_scale=b.workload.sm_scale)
     check(out, oracle_decode(b), "bf16", "shared")
+
+
+# one row, a last token that is alone in its step, more rows than lanes in a wave, the longest table that is not cut and the shortest that is
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx", [(1, 4, 1, 64, (1, 1)), (4, 8, 2, 64, (32, 256)), (5, 5, 1, 128, (63, 130)), (70, 12, 2, 64, (0, 200)), (64, 8, 1, 128, (0, 512)),
+                                                (3, 8, 2, 64, (500, 512)), (3, 8, 2, 128, (257, 512)), (3, 8, 2, 64, (513, 520))])
+def test_short_float32_contexts(batch, hq, hkv, d, ctx):
+    b = W.build(W.Workload("short", batch, hq, hkv, d, "f32", "f32", ("uniform", *ctx), seed=W.BASE_SEED + 99), DEV)
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=b.workload.sm_scale)
+    ws = B.alloc_workspace(desc, batch, DEV)
+    out, lse = B.attn_decode_lse(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=b.workload.sm_scale, workspace=ws)
+    check(out, oracle_decode(b), "f32", "short")
+    assert torch.equal(torch.isneginf(lse), (b.ctx_lens == 0)[:, None].expand_as(lse))
+    per, total, starts = B.read_plan(desc, ws)
+    o_per, o_total, o_starts, _ = O.split_plan(b.ctx_lens_host, hkv * -(-hq // hkv // 4), B.plan_workers(desc))
+    assert (per, total) == (o_per, o_total) and np.array_equal(starts, o_starts)
+
+
+# up to 64 trajectories every wave plans for itself; empty ones in front, between and behind
+@pytest.mark.parametrize("batch,lens", [(1, [1]), (1, [40000]), (3, [0, 33, 0]), (2, [0, 0]), (64, None), (65, None)])
+def test_small_batches_are_planned_by_the_decode_waves(batch, lens):
+    lens = np.array(lens if lens else np.random.default_rng(batch).integers(0, 900, batch) * np.random.default_rng(9).integers(0, 2, batch))
+    b = W.build(W.Workload("waves", batch, 20, 2, 128, "bf16", "fp8_e4m3", ("const", max(1, int(lens.max()))), seed=W.BASE_SEED + 100), DEV)
+    cl = torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=b.workload.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    ws = B.alloc_workspace(desc, batch, DEV)
+    out = B.attn_decode(b.q, b.k_pages, b.v_pages, b.page_table, cl, sm_scale=b.workload.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale, workspace=ws)
+    args = dict(oracle_args(b), ctx_lens=lens)
+    check(out, O.attn_decode(W.raw_numpy(b.q), **args), "bf16", "waves")
+    per, total, starts = B.read_plan(desc, ws)
+    o_per, o_total, o_starts, _ = O.split_plan(lens, 2, B.plan_workers(desc))
+    assert (per, total) == (o_per, o_total) and np.array_equal(starts, o_starts)
