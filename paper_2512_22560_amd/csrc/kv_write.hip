@@ -46,15 +46,21 @@ __device__ __forceinline__ void bf16x8_to_float(const uintx4 raw, float* x) {
   }
 }
 
+// Largest of one non-negative float per thread (as integers they order the same), one barrier: lds is used once.
 __device__ __forceinline__ float block_max(float v, float* lds) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+  int x = __float_as_int(v);
+  auto step = [&](int other) { x = max(x, other); };
+  step(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
+  step(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
+  step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
+  if ((threadIdx.x & 63) == 63) lds[threadIdx.x >> 6] = __int_as_float(x);
   __syncthreads();
   float r = lds[0];
 #pragma unroll
   for (int w = 1; w < kThreads / 64; ++w) r = fmaxf(r, lds[w]);
-  __syncthreads();
   return r;
 }
 
@@ -72,77 +78,95 @@ struct KvWriteArgs {
   int32_t hkv, max_pages;
 };
 
+// Bound by the latency of each workgroup's chain (lengths -> page id and rows -> maximum -> codes), so nothing on it waits
+// that need not: the lengths and the offset leave together, the rows' addresses hang off these alone and the page id is on
+// its way meanwhile, all of a thread's rows leave before the first is looked at, heads and slots are stepped, not divided.
+// As the compiler ordered the plain statements that was five dependent scalar loads and a row at a time: 24.0 us against
+// 22.4 for the chunks of 128 trajectories (32 .. 512 tokens, 4 heads of 128, FP8: 110 MB), 20.1 if the divisions were free.
 // SRC_BYTES: 4 (float32) or 2 (bf16); FP8: pool holds E4M3 codes, else the source type
 template <int D, int SRC_BYTES, bool FP8>
 __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a) {
   __shared__ float red[kThreads / 64];
   const int b = blockIdx.y;
-  const int n = a.q_lens[b];
-  const int len = a.ctx_lens[b];
+  int n = a.q_lens[b], len = a.ctx_lens[b], q_off = a.q_offsets[b], hkv = a.hkv, max_pages = a.max_pages;
+  asm volatile("" : "+s"(n), "+s"(len), "+s"(q_off), "+s"(hkv), "+s"(max_pages));   // arrived: one wait for all of them
   const int first = len - n;
   const int page_i = first / kPageSize + blockIdx.x;
   if (n <= 0 || page_i * kPageSize >= len) return;
   const int lo = max(first, page_i * kPageSize), hi = min(len, (page_i + 1) * kPageSize);
   const int s0 = lo - page_i * kPageSize, slots = hi - lo;
-  const int64_t phys = a.page_table[(size_t)b * a.max_pages + page_i];
-  const int hkv = a.hkv;
+  // (the constant address space: nobody writes the table during the call, and a scalar load stays out of the rows' way)
+  const int32_t page_id = ((const __attribute__((address_space(4))) int32_t*)a.page_table)[(size_t)b * max_pages + page_i];
   constexpr int kElems = 16 / SRC_BYTES;                 // source elements per 16-byte chunk
   constexpr int kChunksPerRow = D / kElems;
   const int chunks = slots * hkv * kChunksPerRow;        // per pool
-  const size_t src_row0 = (size_t)(a.q_offsets[b] + lo - first);
+  const size_t src_row0 = (size_t)(q_off + lo - first);
+  // Chunks come in source order (slot, head, chunk of the row); a thread takes every kThreads-th of them.
+  constexpr int kRowStep = kThreads / kChunksPerRow;
+  const int slot_step = kRowStep / hkv, head_step = kRowStep - slot_step * hkv;
+  const int col = threadIdx.x % kChunksPerRow;
+  int slot = (int)threadIdx.x / kChunksPerRow / hkv, h = (int)threadIdx.x / kChunksPerRow - slot * hkv;
+  auto advance = [&]() {
+    slot += slot_step;
+    h += head_step;
+    if (h >= hkv) {
+      h -= hkv;
+      ++slot;
+    }
+  };
 
   {
     const int pool = blockIdx.z;                          // 0: K, 1: V -- the two pools have nothing in common
     const unsigned char* src = (const unsigned char*)(pool ? a.v_new : a.k_new) + src_row0 * hkv * D * SRC_BYTES;
     unsigned char* pages = (unsigned char*)(pool ? a.v_pages : a.k_pages);
     if constexpr (!FP8) {
-      unsigned char* tile = pages + (size_t)phys * hkv * kPageSize * D * SRC_BYTES;
       // four loads in flight per lane before the first store: the copy is all latency otherwise
       constexpr int kBatch = 4;
       for (int c0 = threadIdx.x; c0 < chunks; c0 += kBatch * kThreads) {
         uintx4 v[kBatch];
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int c = c0 + i * kThreads;
-          if (c < chunks) v[i] = *(const uintx4*)(src + (size_t)c * 16);
-        }
+        for (int i = 0; i < kBatch; ++i) v[i] = *(const uintx4*)(src + (size_t)min(c0 + i * kThreads, chunks - 1) * 16);
+        unsigned char* tile = pages + (size_t)(int64_t)page_id * hkv * kPageSize * D * SRC_BYTES;
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
-          const int c = c0 + i * kThreads;
-          if (c < chunks) {
-            const int col = c % kChunksPerRow, rh = c / kChunksPerRow;   // source order: slot, head, chunk
-            const int h = rh % hkv, slot = rh / hkv;
-            *(uintx4*)(tile + ((size_t)(h * kPageSize + s0 + slot) * D) * SRC_BYTES + col * 16) = v[i];
-          }
+          if (c0 + i * kThreads < chunks) *(uintx4*)(tile + ((size_t)(h * kPageSize + s0 + slot) * D) * SRC_BYTES + col * 16) = v[i];
+          advance();
         }
       }
     } else {
       static_assert(!FP8 || SRC_BYTES == 2, "FP8 pools are written from bf16 rows");
-      float* scale = pool ? a.v_scale : a.k_scale;
-      unsigned char* tile = pages + (size_t)phys * hkv * kPageSize * D;
       // The rows are needed twice, for the maximum and for the codes: a page's worth (up to kKeep
       // chunks per thread, which covers 8 KV heads at D = 128) stays in registers in between.
       constexpr int kKeep = 8;
       const bool keep = chunks <= kKeep * kThreads;
       uintx4 held[kKeep];
       float amax = 0.f;
+      auto see = [&](const uintx4 raw) {
+        float x[8];
+        bf16x8_to_float(raw, x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
+      };
+      if (keep) {
+        // (past the last chunk the last one again: the maximum does not mind)
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i)
+          if (i * kThreads < chunks) held[i] = *(const uintx4*)(src + (size_t)min((int)threadIdx.x + i * kThreads, chunks - 1) * 16);
+      }
+      float* scale = (pool ? a.v_scale : a.k_scale) + page_id;
+      unsigned char* tile = pages + (size_t)(int64_t)page_id * hkv * kPageSize * D;
+      float s_old = 0.f;
+      if (s0) {
+        int bits = __builtin_amdgcn_readfirstlane(__float_as_int(*scale));
+        asm volatile("" : "+s"(bits));                    // here, before the barrier that the new scale is written behind
+        s_old = __int_as_float(bits);
+      }
       if (keep) {
 #pragma unroll
-        for (int i = 0; i < kKeep; ++i) {
-          const int c = threadIdx.x + i * kThreads;
-          held[i] = c < chunks ? *(const uintx4*)(src + (size_t)c * 16) : uintx4{0, 0, 0, 0};
-          float x[8];
-          bf16x8_to_float(held[i], x);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
-        }
+        for (int i = 0; i < kKeep; ++i)
+          if (i * kThreads < chunks) see(held[i]);
       } else {
-        for (int c = threadIdx.x; c < chunks; c += kThreads) {
-          float x[8];
-          bf16x8_to_float(*(const uintx4*)(src + (size_t)c * 16), x);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(x[i]));
-        }
+        for (int c = threadIdx.x; c < chunks; c += kThreads) see(*(const uintx4*)(src + (size_t)c * 16));
       }
       amax = block_max(amax, red);
       const float need = amax / kE4m3Max;
@@ -150,16 +174,15 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
       if (s0 == 0) {
         s_new = amax > 0.f ? need : 1.f;
       } else {
-        const float s_old = scale[phys];
         s_new = s_old;
         if (need > s_old) {
           s_new = need;
           // the codes already in slots [0, s0): code <- enc(dec(code) * s_old / s_new), eight at a time
           const int old_chunks = hkv * s0 * (D / 8);
           for (int c = threadIdx.x; c < old_chunks; c += kThreads) {
-            const int col = c % (D / 8), rh = c / (D / 8);
-            const int slot = rh % s0, h = rh / s0;
-            uintx2* p = (uintx2*)(tile + (size_t)(h * kPageSize + slot) * D + col * 8);
+            const int ocol = c % (D / 8), rh = c / (D / 8);
+            const int oslot = rh % s0, oh = rh / s0;
+            uintx2* p = (uintx2*)(tile + (size_t)(oh * kPageSize + oslot) * D + ocol * 8);
             const uintx2 w = *p;
             float x[8];
 #pragma unroll
@@ -184,9 +207,7 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
       const bool fast_div = s_new >= 0x1p-100f && s_new <= 0x1p+100f;
       const float r0 = __builtin_amdgcn_rcpf(s_new);
       const float r1 = __builtin_fmaf(__builtin_fmaf(-s_new, r0, 1.f), r0, r0);
-      auto emit = [&](int c, const uintx4 raw) {
-        const int col = c % kChunksPerRow, rh = c / kChunksPerRow;
-        const int h = rh % hkv, slot = rh / hkv;
+      auto emit = [&](const uintx4 raw) {
         float x[8];
         bf16x8_to_float(raw, x);
         if (fast_div) {
@@ -205,14 +226,16 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
       if (keep) {
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) {
-          const int c = threadIdx.x + i * kThreads;
-          if (c < chunks) emit(c, held[i]);
+          if ((int)threadIdx.x + i * kThreads < chunks) emit(held[i]);
+          advance();
         }
       } else {
-        for (int c = threadIdx.x; c < chunks; c += kThreads) emit(c, *(const uintx4*)(src + (size_t)c * 16));
+        for (int c = threadIdx.x; c < chunks; c += kThreads) {
+          emit(*(const uintx4*)(src + (size_t)c * 16));
+          advance();
+        }
       }
-      __syncthreads();                                   // every read of the old scale is done
-      if (threadIdx.x == 0) scale[phys] = s_new;
+      if (threadIdx.x == 0) *scale = s_new;                // (every wave had the old one before the barrier of block_max)
     }
   }
 }
