@@ -939,12 +939,13 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
 #pragma unroll
   for (int i4 = 0; i4 < 4; ++i4) o[i4] = floatx4{0.f, 0.f, 0.f, 0.f};
   float ref = -INFINITY, l = 0.f;
-  constexpr int kBatch = 4;                                // pieces under way at a time (past the last one: the last one again, weight zero)
-  for (int s0 = 0; s0 < pieces; s0 += kBatch) {
-    floatx2 x[kBatch];
-    floatx4 y[kBatch][4];
+  // folds kN pieces from s0 on (past the last one: the last one again, with weight zero)
+  auto fold = [&](int s0, auto n_c) __attribute__((always_inline)) {
+    constexpr int kN = decltype(n_c)::value;
+    floatx2 x[kN];
+    floatx4 y[kN][4];
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
+    for (int i = 0; i < kN; ++i) {
       const size_t s = min(s0 + i, pieces - 1) * stride;
       x[i] = ml[s * kRowsPerWave];
 #pragma unroll
@@ -952,7 +953,7 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
     }
     float top = ref;
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
+    for (int i = 0; i < kN; ++i) {
       if (s0 + i >= pieces) {                              // (zero times an infinity would not be zero)
         x[i][0] = -INFINITY;
 #pragma unroll
@@ -967,13 +968,18 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) o[i4] *= keep;
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
+    for (int i = 0; i < kN; ++i) {
       const float f = __builtin_amdgcn_exp2f(x[i][0] - base);
       l += f * x[i][1];
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) o[i4] += f * y[i][i4];
     }
-  }
+  };
+  // four pieces under way at a time; loading one twice is as slow as loading another, so the usual two and three have
+  // folds of their own
+  if (pieces == 2) fold(0, std::integral_constant<int, 2>{});
+  else if (pieces == 3) fold(0, std::integral_constant<int, 3>{});
+  else for (int s0 = 0; s0 < pieces; s0 += 4) fold(s0, std::integral_constant<int, 4>{});
   const int row = row_wave * kRowsPerWave + n32;
   const bool row_ok = row < rows_here;
   const int tok = row / a.group;

@@ -169,7 +169,8 @@ __global__ __launch_bounds__(kDirectThreads) void decode_f32_direct_kernel(const
   __shared__ __attribute__((aligned(16))) float o_out[HT][D];
   __shared__ float ml_out[HT][2];
   if (blockIdx.x == gridDim.x - 1) {
-    plan_decode(a.plan, [&](int b) { return a.ctx_lens[b]; });
+    __shared__ DecodePlanLds plan_lds;
+    plan_decode(a.plan, plan_lds, [&](int b) { return a.ctx_lens[b]; });
     return;
   }
   const int n_ht = (a.group + HT - 1) / HT, rows = a.hkv * n_ht;

@@ -23,11 +23,14 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) {
 }
 
 // With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
-__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a) {
-  plan_decode(a, [&](int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; });
+__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds) {
+  plan_decode(a, lds, [&](int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; });
 }
 
-__global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodePlanArgs a) { plan_decode(a); }
+__global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodePlanArgs a) {
+  __shared__ DecodePlanLds lds;
+  plan_decode(a, lds);
+}
 
 // Append work list: each chunk cut into tiles of tile_tokens query tokens.  A tile's cost grows
 // with its trajectory's context, and workgroups are dispatched in list order, so (for batches that
@@ -68,40 +71,53 @@ struct ChunkLens {
   __device__ __forceinline__ int offset(int b) const { return q_offsets[b]; }
 };
 
+struct AppendPlanLds {
+  int4 wave_tot[kPlanThreads / 256];
+  int4 tile_s[kSplitTiles];            // the first kSplitTiles tiles of the list, for the decision about pieces: record ...
+  int len_s[kRankBatch], order_s[kRankBatch];
+  int2 chunk_s[kRankBatch];            // rows and offset of a chunk
+  int first_s[kPlanThreads], count_s[kPlanThreads], b_s[kPlanThreads], qlen_s[kPlanThreads], ctx_s[kPlanThreads], qoff_s[kPlanThreads];
+  int tile_qoff_s[kSplitTiles], blocks_s[kSplitTiles];   // ... and number of blocks
+  int pieces_s[64];
+};
+
 template <class C>
-__device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& chunk) {
-  __shared__ int4 wave_tot[kPlanThreads / 256];
-  __shared__ int len_s[kRankBatch];
-  __shared__ int order_s[kRankBatch];
+__device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanLds& lds, const C& chunk) {
+  auto& [wave_tot, tile_s, len_s, order_s, chunk_s, first_s, count_s, b_s, qlen_s, ctx_s, qoff_s, tile_qoff_s, blocks_s, pieces_s] = lds;
   const int tid = threadIdx.x;
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
   if (ranked) {
-    for (int b = tid; b < batch; b += kPlanThreads) len_s[b] = chunk.ctx(b);
+    // everything the plan reads, in one round trip to memory
+    const int padded = (batch + 3) & ~3;
+    for (int b = tid; b < padded; b += kPlanThreads) {
+      len_s[b] = b < batch ? chunk.ctx(b) : INT32_MIN;   // (the padding ranks behind everything)
+      if (b < batch) chunk_s[b] = make_int2(chunk.rows(b), chunk.offset(b));
+    }
     __syncthreads();
     for (int b = tid; b < batch; b += kPlanThreads) {
       const int mine = len_s[b];
       int rank = 0;
-      for (int o = 0; o < batch; ++o) {
-        const int other = len_s[o];
-        rank += (other > mine || (other == mine && o < b)) ? 1 : 0;
+      for (int o = 0; o < padded; o += 4) {
+        const int4 other = *(const int4*)(len_s + o);
+        rank += (other.x > mine || (other.x == mine && o < b)) ? 1 : 0;
+        rank += (other.y > mine || (other.y == mine && o + 1 < b)) ? 1 : 0;
+        rank += (other.z > mine || (other.z == mine && o + 2 < b)) ? 1 : 0;
+        rank += (other.w > mine || (other.w == mine && o + 3 < b)) ? 1 : 0;
       }
       order_s[rank] = b;
     }
     __syncthreads();
   }
-  __shared__ int first_s[kPlanThreads], count_s[kPlanThreads], b_s[kPlanThreads], qlen_s[kPlanThreads], ctx_s[kPlanThreads],
-      qoff_s[kPlanThreads];
-  // the first kSplitTiles tiles of the list, for the decision about pieces: record and number of blocks
-  __shared__ int4 tile_s[kSplitTiles];
-  __shared__ int tile_qoff_s[kSplitTiles], blocks_s[kSplitTiles];
   int running = 0;
   for (int p0 = 0; p0 < batch; p0 += kPlanThreads) {
     const int p = p0 + tid;
-    int b = 0, count = 0, q_len = 0;
+    int b = 0, count = 0, q_len = 0, q_off = 0, ctx = 0;
     if (p < batch) {
       b = ranked ? order_s[p] : p;
-      q_len = chunk.rows(b);
+      q_len = ranked ? chunk_s[b].x : chunk.rows(b);
+      q_off = ranked ? chunk_s[b].y : chunk.offset(b);
+      ctx = ranked ? len_s[b] : chunk.ctx(b);
       count = (q_len + tile_tokens - 1) / tile_tokens;
       if (a.skip_unit_chunks && q_len == 1) count = 0;   // mixed step: the decode kernel takes these
     }
@@ -111,8 +127,8 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& ch
     count_s[tid] = count;
     b_s[tid] = b;
     qlen_s[tid] = q_len;
-    ctx_s[tid] = p < batch ? chunk.ctx(b) : 0;
-    qoff_s[tid] = p < batch ? chunk.offset(b) : 0;
+    ctx_s[tid] = ctx;
+    qoff_s[tid] = q_off;
     __syncthreads();
     // One 32-byte record per tile with everything the tile's workgroup needs to start, so that it gets there with
     // one dependent load instead of a chain of them: (b, first row, n_b, L_b, q_offsets[b], first block, blocks, slot).
@@ -121,7 +137,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& ch
     // the next one starts, and are never the last such).
     const int end = min(running + tile_total, a.cap);
     for (int t = running + tid; t < end; t += kPlanThreads) {
-      int lo = 0, hi = kPlanThreads;
+      int lo = 0, hi = min(kPlanThreads, batch - p0);
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (first_s[mid] <= t) lo = mid; else hi = mid;
@@ -150,7 +166,6 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& ch
   if (a.max_pieces == 0 || tiles == 0 || tiles > min(kSplitTiles, a.max_pieces)) return;
 
   // ---- pieces: 64 limits P tried side by side, four per wave.  Two barriers to here: every wave totals the whole list.
-  __shared__ int pieces_s[64];
   const int lane = tid & 63, wave = tid >> 6;
   int blocks_total = 0;
   unsigned longest_seen = 0;
@@ -229,13 +244,22 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, const C& ch
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendPlanArgs a) {
-  plan_append(a, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
+  __shared__ AppendPlanLds lds;
+  plan_append(a, lds, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
 }
 
-// Both plans of a mixed step side by side.
+// Two plans side by side, a workgroup each.
+union PlanLds {
+  AppendPlanLds append;
+  DecodePlanLds decode;
+  __device__ PlanLds() {}
+};
+
+// Both plans of a mixed step.
 __global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPlanArgs a, const DecodePlanArgs d) {
-  if (blockIdx.x == 0) plan_append(a, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
-  else plan_decode(d);
+  __shared__ PlanLds lds;
+  if (blockIdx.x == 0) plan_append(a, lds.append, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
+  else plan_decode(d, lds.decode);
 }
 
 // Decode of groups that share a prompt: per group the shared length actually used, S = floor32(min(shared_lens[group],
@@ -244,9 +268,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPla
 // the group's first S tokens), the other one the private half (every trajectory from token S on), whose lengths and
 // first table entries it writes out for the decode kernel.  Each works S out for itself: a launch that did, and
 // copied the table shifted by S, took 5 us, and the plans one after the other 12 where this launch takes 8 (64 groups of 8).
-constexpr int kSharedGroups = 2048;   // up to this many groups their lengths are settled in LDS
+constexpr int kSharedGroups = 4096;   // up to this many groups their lengths are settled in LDS
 
 __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedPlanArgs sh, const AppendPlanArgs a, const DecodePlanArgs d) {
+  __shared__ PlanLds lds;
   __shared__ int used_s[kSharedGroups];
   const int groups = sh.batch / sh.group_size;
   const bool in_lds = groups <= kSharedGroups;
@@ -275,14 +300,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
       __device__ __forceinline__ int rows(int) const { return size; }
       __device__ __forceinline__ int offset(int g) const { return g * size; }
     };
-    plan_append(a, Groups{used, sh.group_size});
+    plan_append(a, lds.append, Groups{used, sh.group_size});
   } else {
     for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) {
       const int s = used(b / sh.group_size);
       sh.own_ctx[b] = sh.ctx_lens[b] - s;
       sh.own_page[b] = s / kPageSize;
     }
-    plan_decode(d, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
+    plan_decode(d, lds.decode, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
   }
 }
 

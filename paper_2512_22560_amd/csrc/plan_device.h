@@ -48,17 +48,21 @@ __device__ int block_exclusive_scan(int v, int4* wave_tot /*[kPlanThreads / 256]
 // scan of n_b, the run length, T, and for every worker one 16-byte record with all it needs to
 // start: (b, r << 20 | block, L_b, blocks in its run), or b = -1 for a worker without blocks.
 // len_of(b): tokens of trajectory b that take part.
+struct DecodePlanLds {
+  int4 wave_tot[kPlanThreads / 256];
+  int prefix_s[kLdsPrefix + 1], len_s[kLdsPrefix];
+};
 template <class L>
-__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, L&& len_of) {
-  __shared__ int4 wave_tot[kPlanThreads / 256];
-  __shared__ int prefix_s[kLdsPrefix + 1];
+__device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds, L&& len_of) {
+  int4* const wave_tot = lds.wave_tot;
+  int* const prefix_s = lds.prefix_s;
+  int* const len_s = lds.len_s;
   const int tid = threadIdx.x;
   const int32_t batch = a.batch, rows_per_b = a.rows_per_b, workers = a.workers, slots = a.slots;
   int32_t* const header = a.header;
   int32_t* const prefix = a.prefix;
   int32_t* const wstart = a.wstart;
   const bool in_lds = batch <= kLdsPrefix;
-  __shared__ int len_s[kLdsPrefix];
   int running = 0;
   for (int b0 = 0; b0 < batch; b0 += kPlanThreads) {
     const int b = b0 + tid;

@@ -40,7 +40,7 @@ def test_rows_of_every_number_of_pieces(qd, hkv, group, d, copies):
 
 # more groups than the plan keeps in LDS; odd groups with a long private part (many pieces per row), one without shared
 # tokens and one whose member is shorter than the prompt; one long prompt and private parts of one token (one piece per row)
-@pytest.mark.parametrize("group_size,groups,ctx,shared", [(1, 2049, (1, 70), 32), (3, 3, (3000, 9000), 2500), (3, 4, (64, 700), 640), (8, 2, (1025, 1025), 1024)])
+@pytest.mark.parametrize("group_size,groups,ctx,shared", [(1, 4097, (1, 70), 32), (3, 3, (3000, 9000), 2500), (3, 4, (64, 700), 640), (8, 2, (1025, 1025), 1024)])
 def test_shared_half_folds_into_rows_of_every_kind(group_size, groups, ctx, shared):
     b = W.build(W.Workload("fold", group_size * groups, 16, 4, 128, "bf16", "bf16", ("uniform", *ctx), seed=W.BASE_SEED + 98), DEV)
     used = np.full(groups, shared)
