@@ -125,36 +125,35 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# What follows runs on the host in front of every launch, and the smallest calls are no longer than it (a decode step of
+# four short float32 contexts: 4 us on the GPU), so it stays short: addresses as plain integers, the descriptor's fields by
+# position, the current stream's handle without a stream object.
+_DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16, torch.uint8: FP8_E4M3, torch.float8_e4m3fn: FP8_E4M3}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype in (torch.uint8, torch.float8_e4m3fn):
-        return FP8_E4M3
-    raise TypeError(f"unsupported element type {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported element type {t.dtype}")
+    return code
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def make_desc(q, k_pages, page_table, *, sm_scale, k_scale=None, v_scale=None, batch=None) -> Desc:
     num_pages, hkv, page_size, d = k_pages.shape
-    return Desc(
-        batch=int(page_table.shape[0] if batch is None else batch), num_q_heads=int(q.shape[1]),
-        num_kv_heads=int(hkv), head_dim=int(d), page_size=int(page_size),
-        max_pages_per_seq=int(page_table.shape[1]), num_pages=int(num_pages), q_dtype=_dtype_code(q),
-        kv_dtype=_dtype_code(k_pages), sm_scale=float(sm_scale),
-        k_scale=None if k_scale is None else k_scale.data_ptr(),
-        v_scale=None if v_scale is None else v_scale.data_ptr(),
-    )
+    table = page_table.shape
+    # in the order of Desc._fields_
+    return Desc(table[0] if batch is None else int(batch), q.shape[1], hkv, d, page_size, table[1], num_pages, _dtype_code(q),
+                _dtype_code(k_pages), float(sm_scale), _ptr(k_scale), _ptr(v_scale))
 
 
 def workspace_bytes(desc: Desc, total_q: int) -> int:
