@@ -39,8 +39,8 @@
 //     product; the row sum divides each page's share by vs again (four multiplies per block).
 //
 // Half tiles.  A call whose chunks all fit into 128 rows gets tiles of 128 rows: waves w and w + 4 then own the
-// same 32 rows and split every block, 32 tokens each, and their two running states are merged when the
-// tile ends (see the template parameter HALF below).
+// same 32 rows and split every step, and their two running states are merged when the tile ends.  Over FP8 pools a
+// step is two blocks there, 64 tokens to each wave (see the template parameter HALF below).
 #include <type_traits>
 #include <utility>
 
@@ -128,19 +128,25 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // HALF: for tiles of at most 128 rows.  With the plain layout such a tile keeps only the leading four waves busy
 // and the two pipelines of a SIMD take turns.  Here waves w and w + 4 both own rows 32 (w % 4) .. and split every
-// block between them: the leading wave takes its first 32 tokens, the trailing wave the other 32, each with a
+// step between them: the leading wave takes its first half, the trailing wave the other one, each with a
 // running reference, sum and accumulator of its own, merged through LDS when the tile ends.
+// What a phase costs besides its scores (tile loads, page ids and scales, their waits, the barrier) does not shrink with
+// them.  FP8 pools: two tiles of 128 tokens per pool fit the LDS, so a step is 128 tokens and each wave's share a whole
+// block (decode of 64 groups of 8 with prompts of 8192 tokens, 64/4/128: 253 -> 242 us in all, with steps of one block and
+// of two).  bf16 pools: a ring of four tiles is all the LDS there is, a step stays one block, 32 tokens to each wave.
 template <int D, bool FP8, bool HALF>
 __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs a) {
+  // KV tokens staged per step of the loop
+  constexpr int kStepTokens = HALF && FP8 ? 2 * kBlockTokens : kBlockTokens;
   constexpr int kRowBytes = D * 2;                 // bf16 rows in LDS
   constexpr int kChunks = kRowBytes / 16;          // 16-byte chunks per LDS row
-  constexpr int kTileBytes = kBlockTokens * kRowBytes;
+  constexpr int kTileBytes = kStepTokens * kRowBytes;
   constexpr int kSrcRowBytes = D * (FP8 ? 1 : 2);  // row bytes in HBM
   constexpr int kSrcChunks = kSrcRowBytes / 16;
-  constexpr int kLoads = (kBlockTokens * kSrcChunks + kThreads - 1) / kThreads;   // per pool, per thread
+  constexpr int kLoads = (kStepTokens * kSrcChunks + kThreads - 1) / kThreads;   // per pool, per thread
   constexpr int kKK = D / 16;                      // 16-deep steps of the QK product
   constexpr int kDT = D / 32;                      // 32-wide output tiles along D
-  static_assert((kBlockTokens * kSrcChunks) % kThreads == 0 || kBlockTokens * kSrcChunks < kThreads, "staging shape");
+  static_assert((kStepTokens * kSrcChunks) % kThreads == 0 || kStepTokens * kSrcChunks < kThreads, "staging shape");
 
   // bf16 pools go from HBM straight into LDS (no register stop): a ring of four tiles per pool gives
   // every load a whole block period to land.  FP8 pools pass through registers to be widened: their
@@ -149,13 +155,12 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[kRing][kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[kRing][kTileBytes];
   // HALF: where the trailing waves leave their result for the leading ones: per wave pair the accumulators
-  // [D / 32][4][64 lanes] as 16-byte quads, and reference and sum.  The accumulators of the four pairs are as large
-  // as four bf16 tiles: over bf16 pools they go into the K ring, which nobody reads or loads into any more by
-  // then (every wave has waited for its last loads, and the last read of a K tile lies before the trailing
-  // waves' last barrier); the two FP8 tiles of the K ring are too small, there the accumulators get LDS of their own.
+  // [D / 32][4][64 lanes] as 16-byte quads, and reference and sum.  The accumulators of the four pairs go into the K ring,
+  // which nobody reads, loads into or widens into any more by then (bf16: every wave has waited for its last loads; FP8: the
+  // last tile is widened in a wave's last matrix phase but one; the last read of a K tile lies before the trailing waves'
+  // last barrier).
   constexpr int kMergeAcc = (D / 32) * 16 * 64;      // floats per wave pair
-  static_assert(!HALF || FP8 || (size_t)kRing * kTileBytes >= (size_t)(kWaves / 2) * kMergeAcc * sizeof(float), "K ring holds the accumulators");
-  __shared__ __attribute__((aligned(16))) float merge_acc_s[HALF && FP8 ? kWaves / 2 : 1][HALF && FP8 ? kMergeAcc : 4];
+  static_assert(!HALF || (size_t)kRing * kTileBytes >= (size_t)(kWaves / 2) * kMergeAcc * sizeof(float), "K ring holds the accumulators");
   __shared__ float merge_ml_s[HALF ? kWaves / 2 : 1][HALF ? 128 : 1];
 
   const int tid = threadIdx.x;
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // A record is a whole tile, or a piece of one: blocks [blk0, blk0 + n_blocks) of the context.  The piece sees the
   // context as if it started there (table, length and positions shifted), so nothing below differs; rows whose last
   // token lies before it have negative positions and see nothing.
-  const int b = rec[0], q0 = rec[1], n_b = rec[2], q_off = rec[4], blk0 = rec[5], n_blocks = rec[6];
+  const int b = rec[0], q0 = rec[1], n_b = rec[2], q_off = rec[4], blk0 = rec[5], n_blocks = kStepTokens == kBlockTokens ? rec[6] : (rec[6] + 1) / 2;   // (the latter in steps of the loop)
   const int ctx = rec[3] - blk0 * kBlockTokens;
   if (tile >= n_tiles) return;
   __shared__ long clock_s[2];
@@ -221,15 +226,20 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // ---- this lane's query row
   const int grp = wave >> 2;   // 0: leading half of the workgroup, 1: the half that runs one phase behind (waves w and w + 4 share a SIMD)
   const int row_wave = HALF ? (wave & 3) : wave;         // which 32 rows of the tile this wave owns
-  const int sub0 = HALF ? grp : 0;                       // HALF: which 32 tokens of every block
+  const int tok_wave = HALF ? grp * (kStepTokens / 2) : 0;   // HALF: where this wave's half of every step starts
   const int row = row_wave * kRowsPerWave + n32;
   const bool row_ok = row < rows_here;
   const int tok_in_tile = row / group;
   const int head = g * group + (row - tok_in_tile * group);
-  const int my_pos = row_ok ? (causal ? pos0 + tok_in_tile : pos0) : -1;   // last visible token of this row
+  int my_pos = row_ok ? (causal ? pos0 + tok_in_tile : pos0) : -1;   // last visible token of this row
   // blocks that end at or before this position are fully visible to every row of the wave
   const bool wave_active = row_wave * kRowsPerWave < rows_here;
-  const int wave_min_pos = wave_active ? (causal ? pos0 + (row_wave * kRowsPerWave) / group : pos0) : -1;
+  int wave_min_pos = wave_active ? (causal ? pos0 + (row_wave * kRowsPerWave) / group : pos0) : -1;
+  if constexpr (kStepTokens != kBlockTokens) {
+    // a piece of an odd number of blocks ends inside its last step: what follows is another piece's
+    my_pos = min(my_pos, rec[6] * kBlockTokens - 1);
+    wave_min_pos = min(wave_min_pos, rec[6] * kBlockTokens - 1);
+  }
 
   if (n_blocks <= 0) {                                   // nothing to attend to (non-causal mode with L_b = 0): zero rows
     if (row_ok) {
@@ -273,8 +283,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   const int live_pages = (ctx + kPageSize - 1) / kPageSize;
   const int last_blk = n_blocks - 1;
   const int last_slot = (ctx - 1) % kPageSize;
-  constexpr int kPagesPerBlock = kBlockTokens / kPageSize;
-  constexpr bool kAllThreadsLoad = kBlockTokens * kSrcChunks >= kThreads;
+  constexpr int kPagesPerBlock = kStepTokens / kPageSize;
+  constexpr bool kAllThreadsLoad = kStepTokens * kSrcChunks >= kThreads;
   // Chunk idx = j * kThreads + tid of a block sits in LDS row idx / kChunks at chunk position
   // (idx % kChunks), holding the row's chunk (position ^ key): key = row & 15 for K, (row & 3) << 2
   // for V.  The register path (FP8) applies the swizzle when it writes LDS; the direct path has to
@@ -328,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     constexpr int slot = decltype(slot_c)::value;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kBlockTokens) {
+      if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
         const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, tile_off_of(pk[j]), j), va = tile_addr(a.v_pages, 1, u, tile_off_of(pv[j]), j);
         kreg[slot][j] = *(const uintx4*)(ka.base + ka.off);
         vreg[slot][j] = *(const uintx4*)(va.base + va.off);
@@ -354,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   };
 #define DMA_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n))
 
-  // FP8: scales of the pages of a block that this wave's tokens lie in (all four; HALF: two), by scalar loads,
+  // FP8: scales of the pages of a block that this wave's tokens lie in (four, or two of them), by scalar loads,
   // folded with the softmax scale; the page ids behind them are fetched one vector phase before the scales,
   // the scales one vector phase before use
   constexpr int kPg = HALF ? kPagesPerBlock / 2 : kPagesPerBlock;
@@ -363,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   auto fetch_spids = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll
     for (int p = 0; p < kPg; ++p)
-      spid[p] = FP8 ? table[min(min(blk, last_blk) * kPagesPerBlock + sub0 * kPg + p, live_pages - 1)] : 0;
+      spid[p] = FP8 ? table[min(min(blk, last_blk) * kPagesPerBlock + (HALF ? grp * kPg : 0) + p, live_pages - 1)] : 0;
   };
   auto load_scales = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -397,13 +407,13 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
                  (((dt * 4 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ ((tv & 3) << 2)) & (kChunks - 1)) * 16 + (j & 1) * 8;
   }
 
-  constexpr int kSubs = HALF ? 1 : kBlockTokens / 32;   // 32-token sub-blocks of a block that this wave works on
+  constexpr int kSubs = kStepTokens / (HALF ? 64 : 32);   // 32-token sub-blocks of a step that this wave works on
   constexpr int kPvSteps = 8 * kSubs, kSteps = 16 * kSubs;
-  const int sub_bytes = sub0 * 32 * kRowBytes;           // HALF: where this wave's tokens start in a K or V tile
+  const int sub_bytes = tok_wave * kRowBytes;           // HALF: where this wave's tokens start in a K or V tile
   floatx16 s[kSubs];        // scores of the block between its two phases
   bf16x8 pop[kSubs][2];     // its probabilities, as B operands of the second product
 
-  // ---- matrix phase: up to kSteps (32; HALF: 16) MFMA steps, O^T += V^T P^T for the previous block (the
+  // ---- matrix phase: up to kSteps (32; HALF over bf16 pools: 16) MFMA steps, O^T += V^T P^T for the previous block (the
   // first kPvSteps, V buffer at vbo) and S^T = K Q^T for this one (the others, K buffer at kbo).  Every step
   // needs one 32x16 operand from LDS; the reads run kAhead steps in front of the MFMAs that consume them,
   // because during this phase no second wave hides the LDS latency.  The phase has 32 schedule positions
@@ -514,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
         for (int p = 0; p < kPg; ++p) sc[p] = 1.f;
       }
     }
-    const int tok0 = blk * kBlockTokens + sub0 * 32;     // first token of this wave's share of the block
+    const int tok0 = blk * kStepTokens + tok_wave;     // first token of this wave's share of the block
     if (tok0 + kSubs * 32 - 1 > wave_min_pos) {        // causal edge or ragged end inside this block
 #pragma unroll
       for (int sub = 0; sub < kSubs; ++sub)
@@ -546,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
           if ((i & 7) == 0) psum[pg] = p[sub][i];
           else psum[pg] += p[sub][i];
         }
-      if constexpr (HALF) return FP8 ? psum[0] * ivs[0] + psum[1] * ivs[1] : psum[0] + psum[1];
+      if constexpr (kPg == 2) return psum[0] + psum[1];
       else if constexpr (FP8) return (psum[0] * ivs[0] + psum[1] * ivs[1]) + (psum[2] * ivs[2] + psum[3] * ivs[3]);
       else return (psum[0] + psum[1]) + (psum[2] + psum[3]);
     };
@@ -566,7 +576,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
         pm[q] = fmaxf(x, s[sub][o + 7]);
       }
       float mloc;
-      if constexpr (HALF) mloc = FP8 ? fmaxf(pm[0] * sc[0], pm[1] * sc[1]) : fmaxf(pm[0], pm[1]) + m_old;
+      if constexpr (kPg == 2) mloc = fmaxf(pm[0], pm[1]) + m_old;
       else if constexpr (FP8) mloc = fmaxf(fmaxf(pm[0] * sc[0], pm[1] * sc[1]), fmaxf(pm[2] * sc[2], pm[3] * sc[3]));
       else mloc = fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) + m_old;
       const float m_new = fmaxf(m_run, xor32_max(mloc));           // the same in both lanes of a row
@@ -648,7 +658,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
       uintx4 k0[kLoads];
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
-        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kBlockTokens) {
+        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
           const TileAddr ka = tile_addr(a.k_pages, 0, 0, tile_off_of(h0[j]), j);
           k0[j] = *(const uintx4*)(ka.base + ka.off);
         }
@@ -656,7 +666,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
       issue(1, h2, h1, odd);
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
-        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kBlockTokens) put(k_lds[0], woff[j][0], k0[j]);
+        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) put(k_lds[0], woff[j][0], k0[j]);
     } else {
       const int* hh[4] = {h0, h1, h2, h3};
 #pragma unroll
@@ -701,7 +711,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
         // (units past the tile's last block are not loaded: what the registers then hold is widened into tiles nobody reads)
-        if (u <= last_blk && (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kBlockTokens)) {
+        if (u <= last_blk && (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens)) {
           const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, toff[0][j], j), va = tile_addr(a.v_pages, 1, u, toff[1][j], j);
           kreg[slot][j] = *(const uintx4*)(ka.base + ka.off);
           vreg[slot][j] = *(const uintx4*)(va.base + va.off);
@@ -725,7 +735,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
       constexpr int slot = decltype(slot_c)::value, pos = decltype(pos_c)::value;
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
-        const bool mine = kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kBlockTokens;
+        const bool mine = kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens;
         if (pos == 2 + 12 * j / kLoads && mine) put(k_lds[0] + ko[1], woff[j][0], kreg[slot][j]);
         if (pos == 6 + 12 * j / kLoads && mine) put(v_lds[0] + ko[0], woff[j][1], vreg[slot][j]);
       }
@@ -738,18 +748,13 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     if constexpr (FP8) {
       // scales of block i + 1: all loads in one statement, so that each keeps a register of its
       // own (the compiler would recycle one register and wait after every load)
-      if constexpr (HALF)
-        asm volatile(
-            "s_load_dword %0, %4, %6\n\ts_load_dword %1, %4, %7\n\ts_load_dword %2, %5, %6\n\ts_load_dword %3, %5, %7"
-            : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(vraw[0]), "=&s"(vraw[1])
-            : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u));
-      else
+      static_assert(kPg == 4, "four pages of a step per wave");
       asm volatile(
           "s_load_dword %0, %8, %10\n\ts_load_dword %1, %8, %11\n\ts_load_dword %2, %8, %12\n\ts_load_dword %3, %8, %13\n\t"
           "s_load_dword %4, %9, %10\n\ts_load_dword %5, %9, %11\n\ts_load_dword %6, %9, %12\n\ts_load_dword %7, %9, %13"
-          : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(kraw[2 % kPg]), "=&s"(kraw[3 % kPg]), "=&s"(vraw[0]), "=&s"(vraw[1]), "=&s"(vraw[2 % kPg]), "=&s"(vraw[3 % kPg])
-          : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u), "s"((unsigned)spid[2 % kPg] * 4u),
-            "s"((unsigned)spid[3 % kPg] * 4u));
+          : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(kraw[2]), "=&s"(kraw[3]), "=&s"(vraw[0]), "=&s"(vraw[1]), "=&s"(vraw[2]), "=&s"(vraw[3])
+          : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u), "s"((unsigned)spid[2] * 4u),
+            "s"((unsigned)spid[3] * 4u));
       fetch_spids(i + 2);
     }
   };
@@ -757,11 +762,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) { pid_new[j] = __builtin_amdgcn_readfirstlane(pid_new[j]); asm volatile("" : "+s"(pid_new[j])); }   // arrived here, not wherever it is used next
     if constexpr (FP8) {
-      if constexpr (HALF)
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(vraw[0]), "+s"(vraw[1]));
-      else
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(kraw[2 % kPg]), "+s"(kraw[3 % kPg]), "+s"(vraw[0]), "+s"(vraw[1]), "+s"(vraw[2 % kPg]), "+s"(vraw[3 % kPg]));
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(kraw[2]), "+s"(kraw[3]), "+s"(vraw[0]), "+s"(vraw[1]), "+s"(vraw[2]), "+s"(vraw[3]));
 #pragma unroll
       for (int p = 0; p < kPg; ++p) {
         spid[p] = __builtin_amdgcn_readfirstlane(spid[p]);
@@ -822,7 +824,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     }
   };
   if (wave_active) run(std::true_type{}); else run(std::false_type{});
-  float* const mine = !HALF ? nullptr : FP8 ? merge_acc_s[FP8 ? (wave & 3) : 0] : (float*)&k_lds[0][0] + (wave & 3) * kMergeAcc;
+  float* const mine = (float*)&k_lds[0][0] + (wave & 3) * kMergeAcc;   // HALF only
   float* const mine_ml = merge_ml_s[HALF ? (wave & 3) : 0];
   if constexpr (HALF) {
     // The trailing wave of a pair hands over its half of the tile: accumulators, reference and (per-lane) sum.

@@ -24,13 +24,14 @@ def _append(b):
 
 
 # (name, batch, Hq, Hkv, D, prefix, new tokens, cut): contexts too short to be cut, on and just past a block edge; one tile and several; half tiles; chunks longer than a piece, whose first
-# rows do not see its later pieces; groups that leave a tile ragged; one KV head and more than eight
+# rows do not see its later pieces; half tiles of one to five blocks; groups that leave a tile ragged; one KV head and more than eight
 CASES = [
     ("below", 1, 8, 8, 128, (900, 900), (40, 40), False), ("block_edge", 1, 8, 8, 128, (1495, 1495), (41, 41), True),
     ("past_edge", 1, 8, 8, 128, (1496, 1496), (41, 41), True), ("long", 2, 32, 8, 128, (6000, 9000), (3, 3), True),
     ("half", 5, 64, 4, 128, (100, 9000), (1, 8), True), ("causal", 1, 16, 4, 128, (0, 0), (3001, 3001), True),
     ("g3_d64", 3, 6, 2, 64, (2000, 5000), (100, 300), True), ("one_head", 2, 40, 1, 128, (3000, 8000), (5, 70), True),
     ("sixteen", 2, 16, 16, 64, (2500, 2600), (257, 300), True), ("skewed", 30, 16, 4, 128, (10, 14000), (1, 200), True),
+    ("steps", 40, 64, 4, 128, (0, 260), (1, 8), False), ("steps_d64", 40, 4, 2, 64, (0, 260), (1, 30), False),
 ]
 
 
