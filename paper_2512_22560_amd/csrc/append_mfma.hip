@@ -419,7 +419,10 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // because during this phase no second wave hides the LDS latency.  The phase has 32 schedule positions
   // spread evenly over its steps; after a step the caller's piece(pos) runs for the positions that belong to
   // it: the FP8 path threads its LDS writes between the MFMAs there.
-  constexpr int kAhead = 4;
+  // (how far ahead, measured with everything else alike.  bf16: 1, 2, 3, 4, 5 steps: 5.33, 4.13, 4.02, 4.05, 4.11 ms on 64 chunks
+  // of 64 .. 1024 tokens behind 2k .. 16k, 32/8/128; 7.20, 5.74, 5.64, 5.66, 5.75 ms without a prefix, 512 .. 8k tokens.
+  // FP8: 3, 4, 5, 6: 12.98, 12.87, 13.07, 13.03 ms on the mixed step of 512 trajectories, 64/4/128)
+  constexpr int kAhead = FP8 ? 4 : 3;
   // bf16 pools: the operands of the first kAhead steps of a phase that starts with the second product are
   // read at the end of the vector phase before it, in front of the barrier (the V tile they come from was
   // complete one phase earlier), so that the phase does not open with an LDS round trip.
