@@ -292,7 +292,7 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   a.partial_o = (float*)(base + w.partial_o);
   a.batch = desc->batch; a.hq = desc->num_q_heads; a.hkv = desc->num_kv_heads;
   a.group = desc->num_q_heads / desc->num_kv_heads; a.max_pages = desc->max_pages_per_seq;
-  a.head_tile = w.head_tile; a.rows_per_b = w.rows_per_b;
+  a.head_tile = w.head_tile; a.rows_per_b = w.rows_per_b; a.num_pages = desc->num_pages;
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
   a.q_lens = q_lens;

@@ -86,23 +86,28 @@ struct Cursor {
   int n, len;      // blocks in the row, context length of the trajectory
 };
 
-template <int D, bool FP8>
-__global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeArgs a) {
-  using G_ = Geo<D, FP8>;
-  // Per wave: one K tile and one V tile.
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * G_::kTileBytes];
+// 16 bytes of a K or V row.  Every byte of the cache is read once per call, by one wave: with the streaming hint it does
+// not displace what is read again (page scales, 32 pages' to a cache line, page table, partials) and the last-level cache
+// does not spend its bandwidth on keeping it.  Worth 8 to 11 % of a launch: 64 contexts of 512 .. 8k (32/8/128, bf16)
+// 154.0 -> 138.1 us with the merge, 256 long-tailed ones (64/8/128) 1440 -> 1323 us, 384 over FP8 pools (64/4/128)
+// 798 -> 713 us (6.3 TB/s, what a streaming read reaches).
+template <bool STREAM>
+__device__ __forceinline__ uint4 load16(const unsigned char* p) {
+  typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+  const uintx4 x = STREAM ? __builtin_nontemporal_load((const uintx4*)p) : *(const uintx4*)p;
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
 
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+template <int D, bool FP8, bool STREAM>
+__device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, unsigned char* const k_lds) {
+  using G_ = Geo<D, FP8>;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (what is worked out from it stays in this instance: shared by both in front of the branch, it would not fit the registers)
+  const int lane = tid & 63;
   const int r16 = lane & 15;   // MFMA row / column index carried by this lane
   const int q4 = lane >> 4;    // which quarter of the contraction this lane feeds
-  unsigned char* const k_lds = lds[wave];
-  unsigned char* const v_lds = lds[wave] + G_::kTileBytes;
+  unsigned char* const v_lds = k_lds + G_::kTileBytes;
 
-  const int worker = blockIdx.x * kWaves + wave;
-  // (b, r << 20 | block, L_b, run length)
-  const int4 start = a.plan.batch ? plan_decode_in_wave(a.plan, worker) : *(const int4*)(a.wstart + 4 * worker);
-  if (start.x < 0) return;
   const int n_mine = __builtin_amdgcn_readfirstlane(start.w);
   const int group = a.group, hkv = a.hkv, rows_per_b = a.rows_per_b;
   const int n_ht = rows_per_b / hkv;
@@ -166,8 +171,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
       for (int j = 0; j < G_::kLoads; ++j) {
         const int row0 = j * G_::kRowsPerLoad;
         const int off = (row0 % kPageSize) * G_::kRowBytes + lane * 16;
-        kreg[stage][j] = *(const uint4*)((row0 < kPageSize ? kt0 : kt1) + off);
-        vreg[stage][j] = *(const uint4*)((row0 < kPageSize ? vt0 : vt1) + off);
+        kreg[stage][j] = load16<STREAM>((row0 < kPageSize ? kt0 : kt1) + off);
+        vreg[stage][j] = load16<STREAM>((row0 < kPageSize ? vt0 : vt1) + off);
       }
     } else {
       // ragged last block of a row: rows at or past L_b are neither read nor left undefined
@@ -178,8 +183,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
         const int row = row0 + lane / G_::kChunks;
         uint4 kv = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
         if (tok0 + row < pc.len) {
-          kv = *(const uint4*)((row0 < kPageSize ? kt0 : kt1) + off);
-          vv = *(const uint4*)((row0 < kPageSize ? vt0 : vt1) + off);
+          kv = load16<STREAM>((row0 < kPageSize ? kt0 : kt1) + off);
+          vv = load16<STREAM>((row0 < kPageSize ? vt0 : vt1) + off);
         }
         kreg[stage][j] = kv;
         vreg[stage][j] = vv;
@@ -374,6 +379,30 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
       }
     }
   }
+}
+
+template <int D, bool FP8>
+__global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeArgs a) {
+  // Per wave: one K tile and one V tile.
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * Geo<D, FP8>::kTileBytes];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int worker = blockIdx.x * kWaves + wave;
+  // (b, r << 20 | block, L_b, run length), and the blocks of all rows
+  int total = 0;
+  int4 start;
+  if (a.plan.batch) {
+    start = plan_decode_in_wave(a.plan, worker, &total);
+  } else {
+    start = *(const int4*)(a.wstart + 4 * worker);
+    total = a.header[kPlanTotal];
+  }
+  if (start.x < 0) return;
+  // Contexts with more pages between them than the pool has share some (grouped rollouts decoded without
+  // attn_decode_shared): then the next reader of a page may find it in a cache, and the hint would cost 13 %
+  // (64 groups of 8 behind 8192 common tokens: 687 against 777 us).  A block is two pages, the last of a row one or two.
+  const bool shared_pages = (long)(total / a.rows_per_b) * 2 - a.batch > a.num_pages;
+  if (shared_pages) decode_worker<D, FP8, false>(a, start, worker, lds[wave]);
+  else decode_worker<D, FP8, true>(a, start, worker, lds[wave]);
 }
 
 }  // namespace

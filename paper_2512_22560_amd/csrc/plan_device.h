@@ -117,14 +117,14 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
 // The same rule for a batch of at most 64 trajectories, worked out by every wave of a decode launch for itself: a lane per
 // trajectory, the search for the worker's start one ballot.  Writes what the plan kernel would have written (the first
 // worker the header and the scan, each worker its record), because the merge and rollattn_debug_read_plan read it.
-// Returns the record (b, r << 20 | block, L_b, blocks in the run), the same in all lanes.
-__device__ __forceinline__ int4 plan_decode_in_wave(const DecodePlanArgs& a, int worker) {
+// Returns the record (b, r << 20 | block, L_b, blocks in the run), the same in all lanes, and the blocks of all rows.
+__device__ __forceinline__ int4 plan_decode_in_wave(const DecodePlanArgs& a, int worker, int* blocks_of_all) {
   const int lane = threadIdx.x & 63;
   const int len = lane < a.batch ? a.ctx_lens[lane] : 0;
   const int count = (len + kBlockTokens - 1) / kBlockTokens;
   const int upto = wave_inclusive_scan(count), first = upto - count;
   const int blocks = __builtin_amdgcn_readlane(upto, 63);
-  const int total = blocks * a.rows_per_b;
+  const int total = *blocks_of_all = blocks * a.rows_per_b;
   const int per = max(1, (total + a.workers - 1) / a.workers);
   const unsigned int x = (unsigned int)worker * (unsigned int)per;
   if (worker == 0) {

@@ -75,6 +75,7 @@ struct DecodeArgs {
   const int32_t* wstart;
   float* partial_ml;
   float* partial_o;
+  int64_t num_pages;
   int32_t batch, hq, hkv, group, max_pages, head_tile, rows_per_b;
   float scale_log2;     // sm_scale * log2(e)
   float* lse;           // optional [B][Hq]: log2 of each row's softmax denominator (reference included)

@@ -80,3 +80,16 @@ def test_small_batches_are_planned_by_the_decode_waves(batch, lens):
     per, total, starts = B.read_plan(desc, ws)
     o_per, o_total, o_starts, _ = O.split_plan(lens, 2, B.plan_workers(desc))
     assert (per, total) == (o_per, o_total) and np.array_equal(starts, o_starts)
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+def test_pages_read_with_and_without_the_streaming_hint(kvd):
+    # four trajectories share pages: with the 100 pages they live on the pool has fewer than their contexts, with 100 more it has not
+    b = W.build(W.Workload("hint", 4, 8, 2, 128, "bf16", kvd, ("const", 768), seed=W.BASE_SEED + 101), DEV)
+    live = [t[:100].clone() for t in (b.k_pages, b.v_pages)]
+    scales = [None if t is None else t[:100].clone() for t in (b.k_scale, b.v_scale)]
+    table = (b.page_table % 100).contiguous()
+    run = lambda k, v, ks, vs: B.attn_decode(b.q, k, v, table, b.ctx_lens, sm_scale=b.workload.sm_scale, k_scale=ks, v_scale=vs)
+    more = lambda t: None if t is None else torch.cat([t, t])
+    out = run(*live, *scales)
+    assert torch.isfinite(out).all() and torch.equal(out, run(*map(more, (*live, *scales))))
