@@ -93,6 +93,12 @@ __device__ __forceinline__ void fp8x16_to_bf16(const uintx4 raw, uintx4& lo, uin
   hi = uintx4{o[4], o[5], o[6], o[7]};
 }
 
+// 16 bytes of a pool; once: nobody reads them again, so they go past the caches' care (see load16 in decode_mfma.hip).
+template <bool ONCE>
+__device__ __forceinline__ uintx4 load16(const unsigned char* p) {
+  return ONCE ? __builtin_nontemporal_load((const uintx4*)p) : *(const uintx4*)p;
+}
+
 // Normalises and stores one 32-wide accumulator tile: lane (row n32, half h2) owns dims (i/4)*8 + h2*4 + i%4 of it, four
 // at a time (o(i4, e): dim e of group i4).  The two lanes of a row first trade every other group of four, so that each
 // holds runs of eight dims and stores 16 bytes at a time: half as many store instructions, each of which touches 32 rows.
@@ -134,7 +140,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 // them.  FP8 pools: two tiles of 128 tokens per pool fit the LDS, so a step is 128 tokens and each wave's share a whole
 // block (decode of 64 groups of 8 with prompts of 8192 tokens, 64/4/128: 253 -> 242 us in all, with steps of one block and
 // of two).  bf16 pools: a ring of four tiles is all the LDS there is, a step stays one block, 32 tokens to each wave.
-template <int D, bool FP8, bool HALF>
+// ONCE: the pools are read with the streaming hint.  For the shared half of attn_decode_shared, where a group is one tile and
+// no other reads its pages (64 groups of 8 behind 8192 tokens, 64/4/128, FP8: 242 -> 236 us in all).  Chunks of a few tokens
+// are one tile each as well, but their prompts may be shared: 256 of 4 tokens in groups behind a common prompt would take
+// 590 instead of 530 us over bf16 pools, against 516 instead of 557 us with prompts of their own.
+template <int D, bool FP8, bool HALF, bool ONCE>
 __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs a) {
   // KV tokens staged per step of the loop
   constexpr int kStepTokens = HALF && FP8 ? 2 * kBlockTokens : kBlockTokens;
@@ -340,8 +350,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     for (int j = 0; j < kLoads; ++j) {
       if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
         const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, tile_off_of(pk[j]), j), va = tile_addr(a.v_pages, 1, u, tile_off_of(pv[j]), j);
-        kreg[slot][j] = *(const uintx4*)(ka.base + ka.off);
-        vreg[slot][j] = *(const uintx4*)(va.base + va.off);
+        kreg[slot][j] = load16<ONCE>(ka.base + ka.off);
+        vreg[slot][j] = load16<ONCE>(va.base + va.off);
       }
     }
   };
@@ -360,7 +370,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // across statements in the code it generates, so it is simply overwritten.
   auto dma = [&](const TileAddr& t, unsigned char* lds_dst) __attribute__((always_inline)) {
     const unsigned int m0 = __builtin_amdgcn_readfirstlane((unsigned int)(uintptr_t)lds_dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(t.off), "s"(t.base) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(m0), "v"(t.off), "s"(t.base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(t.off), "s"(t.base) : "memory");
   };
 #define DMA_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n))
 
@@ -663,7 +674,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
       for (int j = 0; j < kLoads; ++j)
         if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
           const TileAddr ka = tile_addr(a.k_pages, 0, 0, tile_off_of(h0[j]), j);
-          k0[j] = *(const uintx4*)(ka.base + ka.off);
+          k0[j] = load16<ONCE>(ka.base + ka.off);
         }
       issue(0, h1, h0, even);
       issue(1, h2, h1, odd);
@@ -716,8 +727,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
         // (units past the tile's last block are not loaded: what the registers then hold is widened into tiles nobody reads)
         if (u <= last_blk && (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens)) {
           const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, toff[0][j], j), va = tile_addr(a.v_pages, 1, u, toff[1][j], j);
-          kreg[slot][j] = *(const uintx4*)(ka.base + ka.off);
-          vreg[slot][j] = *(const uintx4*)(va.base + va.off);
+          kreg[slot][j] = load16<ONCE>(ka.base + ka.off);
+          vreg[slot][j] = load16<ONCE>(va.base + va.off);
         }
       }
     } else if (u <= last_blk) {
@@ -1007,25 +1018,25 @@ hipError_t launch_append_merge(const AppendArgs& a, int head_dim, int max_merges
 }
 
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s) {
-  if (head_dim == 128 && !fp8 && !half_tiles) {
-    hipLaunchKernelGGL((append_mfma_kernel<128, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 128 && !fp8) {
-    hipLaunchKernelGGL((append_mfma_kernel<128, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 128 && fp8 && !half_tiles) {
-    hipLaunchKernelGGL((append_mfma_kernel<128, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 128 && fp8) {
-    hipLaunchKernelGGL((append_mfma_kernel<128, true, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && !fp8 && !half_tiles) {
-    hipLaunchKernelGGL((append_mfma_kernel<64, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && !fp8) {
-    hipLaunchKernelGGL((append_mfma_kernel<64, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && fp8 && !half_tiles) {
-    hipLaunchKernelGGL((append_mfma_kernel<64, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && fp8) {
-    hipLaunchKernelGGL((append_mfma_kernel<64, true, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+  const bool once = half_tiles && a.noncausal;
+  auto launch = [&](auto d, auto f) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool F = decltype(f)::value;
+    if (once) {
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, true>), dim3(grid), dim3(kThreads), 0, s, a);
+    } else if (half_tiles) {
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
+    } else {
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
+    }
+  };
+  std::integral_constant<int, 128> d128;
+  std::integral_constant<int, 64> d64;
+  if (head_dim == 128 && fp8) launch(d128, std::true_type{});
+  else if (head_dim == 128) launch(d128, std::false_type{});
+  else if (fp8) launch(d64, std::true_type{});
+  else launch(d64, std::false_type{});
   return hipGetLastError();
 }
 
