@@ -397,10 +397,17 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
     total = a.header[kPlanTotal];
   }
   if (start.x < 0) return;
-  // Contexts with more pages between them than the pool has share some (grouped rollouts decoded without
-  // attn_decode_shared): then the next reader of a page may find it in a cache, and the hint would cost 13 %
-  // (64 groups of 8 behind 8192 common tokens: 687 against 777 us).  A block is two pages, the last of a row one or two.
-  const bool shared_pages = (long)(total / a.rows_per_b) * 2 - a.batch > a.num_pages;
+  // Grouped rollouts decoded without attn_decode_shared: the next reader of a page may find it in a cache, and the hint
+  // would cost 13 % (64 groups of 8 behind 8192 common tokens: 687 against 777 us).  Told by a neighbour that starts on the
+  // same page, or by contexts with more pages between them than the pool has (a block is two pages, the last of a row one
+  // or two).  The private half of attn_decode_shared has no page in common with others.
+  bool shared_pages = (long)(total / a.rows_per_b) * 2 - a.batch > a.num_pages;
+  if (!a.first_page) {
+    const int b = __builtin_amdgcn_readfirstlane(start.x);
+    const int32_t* row = a.page_table + (size_t)b * a.max_pages;
+    const int own = row[0], before = b > 0 ? row[-(long)a.max_pages] : -1, after = b + 1 < a.batch ? row[a.max_pages] : -1;
+    shared_pages = shared_pages || own == before || own == after;
+  }
   if (shared_pages) decode_worker<D, FP8, false>(a, start, worker, lds[wave]);
   else decode_worker<D, FP8, true>(a, start, worker, lds[wave]);
 }

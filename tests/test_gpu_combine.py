@@ -92,4 +92,8 @@ def test_pages_read_with_and_without_the_streaming_hint(kvd):
     run = lambda k, v, ks, vs: B.attn_decode(b.q, k, v, table, b.ctx_lens, sm_scale=b.workload.sm_scale, k_scale=ks, v_scale=vs)
     more = lambda t: None if t is None else torch.cat([t, t])
     out = run(*live, *scales)
+    table[1:, 0] = table[0, 0]                     # neighbours that start on the same page: not with the hint either
+    same = run(*live, *scales)
+    assert torch.isfinite(same).all() and torch.equal(same, run(*map(more, (*live, *scales))))
+    table[1:, 0] = b.page_table[1:, 0] % 100
     assert torch.isfinite(out).all() and torch.equal(out, run(*map(more, (*live, *scales))))
