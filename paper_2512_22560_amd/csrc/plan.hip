@@ -47,7 +47,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodeP
 // u = mean piece / P: with equal pieces that is the number of full rounds over the CUs, with unequal ones the later,
 // shorter pieces fill the gaps.  kPieceCost is what a workgroup costs besides its blocks (start, first tiles from HBM,
 // epilogue, hand-over of the CU: 22,000 cycles against 2,500 per block when measured), kMergeCost the merge launch and
-// the float partials' way to memory and back.  The split is taken only where the price drops by a tenth.
+// the float partials' way to memory and back.  Limits whose pieces or partials there is no room for are left out (13 chunks
+// of 64 tokens behind 16k, 32/8/128, bf16: the cheapest would need 91 slots per head).  The split is taken only where the
+// price drops by a tenth.
 // Measured: three observations of 16 .. 512 tokens behind 2k .. 16k (32/8/128, bf16, one of every four CUs idle before)
 // 275 -> 208 us with plan and merge; 33 of 3 .. 96 tokens behind up to 64k (64/4/128, FP8) 1410 -> 652 us.  The decision
 // adds 3 us to the plan of a short list, the merge takes 12 us where tiles were cut and 3 us where none was; lists too
@@ -78,12 +80,12 @@ struct AppendPlanLds {
   int2 chunk_s[kRankBatch];            // rows and offset of a chunk
   int first_s[kPlanThreads], count_s[kPlanThreads], b_s[kPlanThreads], qlen_s[kPlanThreads], ctx_s[kPlanThreads], qoff_s[kPlanThreads];
   int tile_qoff_s[kSplitTiles], blocks_s[kSplitTiles];   // ... and number of blocks
-  int pieces_s[64];
+  int pieces_s[64], slots_s[64];
 };
 
 template <class C>
 __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanLds& lds, const C& chunk) {
-  auto& [wave_tot, tile_s, len_s, order_s, chunk_s, first_s, count_s, b_s, qlen_s, ctx_s, qoff_s, tile_qoff_s, blocks_s, pieces_s] = lds;
+  auto& [wave_tot, tile_s, len_s, order_s, chunk_s, first_s, count_s, b_s, qlen_s, ctx_s, qoff_s, tile_qoff_s, blocks_s, pieces_s, slots_s] = lds;
   const int tid = threadIdx.x;
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
@@ -179,25 +181,39 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const float cus = (float)kNumCUs / (float)a.hkv;      // a list entry is one workgroup per KV head
   const float mean = fmaxf((float)blocks_total / cus, 1.f);
   auto limit_of = [&](int i) { return fmaxf((float)kMinPieceBlocks, ceilf(mean * (0.3f + 0.04f * (float)i))); };
-  float per_limit[4];                                    // (a count off by one where the product rounds: the limits are checked again below)
-  int pieces[4] = {0, 0, 0, 0};
+  float per_limit[4], below[4];
+  int pieces[4] = {0, 0, 0, 0}, slots[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int c = 0; c < 4; ++c) per_limit[c] = __builtin_amdgcn_rcpf(limit_of(wave * 4 + c));
+  for (int c = 0; c < 4; ++c) {
+    const float p = limit_of(wave * 4 + c);
+    per_limit[c] = __builtin_amdgcn_rcpf(p);
+    below[c] = p - 0.5f;
+  }
   for (int t = lane; t < tiles; t += 64) {
     const float n = (float)blocks_s[t];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) pieces[c] += max(1, (int)ceilf(n * per_limit[c]));
+    for (int c = 0; c < 4; ++c) {
+      // n / p rounded up: (n + p - 1/2) / p lies half a block away from every whole number, more than its rounding while it
+      // is below 2^20 / p; a count of that size is past max_pieces whatever its last digit
+      const int k = max(1, (int)((n + below[c]) * per_limit[c]));
+      pieces[c] += k;
+      slots[c] += k > 1 ? k : 0;
+    }
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int n = wave_sum(pieces[c]);
-    if (lane == 0) pieces_s[wave * 4 + c] = n;
+    const int n = wave_sum(pieces[c]), m = wave_sum(slots[c]);
+    if (lane == 0) {
+      pieces_s[wave * 4 + c] = n;
+      slots_s[wave * 4 + c] = m;
+    }
   }
   __syncthreads();
   // prices as integers (a sixteenth of a block), complemented, so that the cheapest is the largest
   const int n_lane = pieces_s[lane];
   const float price_lane = split_price(limit_of(lane), (float)blocks_total, (float)n_lane, cus) + kMergeCost;
-  const unsigned key = (n_lane > tiles && n_lane <= a.max_pieces) ? ~(unsigned)fminf(16.f * price_lane, 6e7f) : 0u;
+  const bool fits = n_lane > tiles && n_lane <= a.max_pieces && slots_s[lane] <= a.max_slots;   // (the cheapest of those there is room for)
+  const unsigned key = fits ? ~(unsigned)fminf(16.f * price_lane, 6e7f) : 0u;
   const unsigned cheapest = wave_max(key);
   const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == cheapest));
   const float best = cheapest ? (float)~cheapest * (1.f / 16.f) : INFINITY;
@@ -207,13 +223,11 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const int mine = tid < tiles ? blocks_s[tid] : 0;
   const int k = tid < tiles ? max(1, (mine + p_max - 1) / p_max) : 0;   // pieces of this thread's tile (one without blocks has zero rows to write)
   const bool cut = k > 1;
-  // pieces and cut tiles in one scan: at most 2 * kSplitTiles of the first (the price counted them, give or take a rounding
-  // per tile), kSplitTiles of the second
+  // pieces and cut tiles in one scan: at most kSplitPieces of the first, kSplitTiles of the second
   int both;
   const int before = block_exclusive_scan(k | (cut ? 1 << 16 : 0), wave_tot, &both);
   const int piece0 = before & 0xffff, merge0 = before >> 16, n_pieces = both & 0xffff, n_merges = both >> 16;
-  const int slot0 = piece0 - (tid - merge0), n_slots = n_pieces - (tiles - n_merges);   // every uncut tile is one piece without a slot
-  if (n_pieces > a.max_pieces || n_slots > a.max_slots) return;
+  const int slot0 = piece0 - (tid - merge0);   // every uncut tile is one piece without a slot
   if (cut) {
     int4* m = (int4*)(a.merge_rec + (size_t)merge0 * kTileRecWords);
     m[0] = make_int4(tile_s[tid].y, tile_s[tid].z, tile_qoff_s[tid], slot0);   // (first row, n_b, q_offsets[b], first slot, pieces)

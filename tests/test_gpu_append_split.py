@@ -31,6 +31,8 @@ CASES = [
     ("half", 5, 64, 4, 128, (100, 9000), (1, 8), True), ("causal", 1, 16, 4, 128, (0, 0), (3001, 3001), True),
     ("g3_d64", 3, 6, 2, 64, (2000, 5000), (100, 300), True), ("one_head", 2, 40, 1, 128, (3000, 8000), (5, 70), True),
     ("sixteen", 2, 16, 16, 64, (2500, 2600), (257, 300), True), ("skewed", 30, 16, 4, 128, (10, 14000), (1, 200), True),
+    # the cheapest cut would need more slots than there are, another one fits
+    ("crowded", 13, 32, 8, 64, (12000, 12000), (64, 64), True),
     ("steps", 40, 64, 4, 128, (0, 260), (1, 8), False), ("steps_d64", 40, 4, 2, 64, (0, 260), (1, 30), False),
 ]
 
