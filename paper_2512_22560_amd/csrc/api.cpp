@@ -122,23 +122,24 @@ WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
   // room for the list of half-size tiles too (a call whose chunks are all short chooses them)
   const int tile_tokens = std::max(1, kAppendTileRows / 2 / group);
   w.workers = (int32_t)std::min<int64_t>((int64_t)total_q / tile_tokens + d.batch + 1, INT32_MAX);
-  // Tiles may be cut into pieces, within limits on the whole launch (kSplitPieces workgroups, kSplitSlots of them with
-  // partials); a table whose contexts are all shorter than two pieces has nothing to cut.
-  if (d.q_dtype != ROLLATTN_F32 && d.num_kv_heads <= kSplitSlots / 2 &&
-      d.max_pages_per_seq > (2 * kMinPieceBlocks - 1) * (kAppendBlockTokens / kPageSize)) {
+  // Tiles may be cut into pieces, within limits on the whole launch
+  if (d.q_dtype != ROLLATTN_F32 && d.num_kv_heads <= kSplitMerges) {
     w.max_pieces = kSplitPieces / d.num_kv_heads;
-    w.max_slots = kSplitSlots / d.num_kv_heads;
+    w.max_merges = kSplitMerges / d.num_kv_heads;
+    w.max_units = kSplitUnits / d.num_kv_heads;
   }
-  w.list_cap = std::max(w.workers, w.max_pieces);
-  const size_t parts = (size_t)w.max_slots * d.num_kv_heads * (kAppendTileRows / 32);   // 32 rows each
+  const size_t rec = sizeof(int32_t) * kTileRecWords, parts = (size_t)w.max_units * d.num_kv_heads;
   size_t off = 0;
   w.header = off;      off += align256(sizeof(int32_t) * kPlanWords);
-  w.wstart = off;      off += align256(sizeof(int32_t) * kTileRecWords * (size_t)w.list_cap);
+  w.wstart = off;
   w.prefix = off;
-  w.merge_rec = off;   off += align256(sizeof(int32_t) * kTileRecWords * (size_t)(w.max_slots / 2));
-  w.partial_ml = off;  off += align256(sizeof(float) * 2 * 32 * parts);
-  w.partial_o = off;   off += align256(sizeof(float) * 32 * d.head_dim * parts);
-  w.total = off;
+  w.total = off + align256(rec * (size_t)w.workers);
+  off += align256(rec * (size_t)w.max_pieces);
+  w.merge_rec = off;   off += align256(rec * (size_t)w.max_merges);
+  w.cut_list = std::max(w.total, off);
+  w.partial_ml = off;  off += align256(sizeof(float) * 2 * kUnitRows * parts);
+  w.partial_o = off;   off += align256(sizeof(float) * kUnitRows * d.head_dim * parts);
+  w.cut_total = std::max(w.total, off);
   return w;
 }
 
@@ -147,6 +148,11 @@ WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
 using namespace rollattn;
 
 static_assert(kPlanBlockTokens == kBlockTokens, "the host twin and the kernels cut rows into the same blocks");
+// The partials of an append call's pieces take the room that the decode partials of the same descriptor take, and its list
+// no more than the start records: a workspace that is large enough for the decode call lets an append call cut its tiles,
+// and attn_step and attn_decode_shared lend the one region to both halves in turn.
+static_assert(kSplitUnits * kUnitRows == 2 * kMfmaDecodeWgs * 4 * kMfmaHeadTile, "partials of append and decode");
+static_assert(kTileRecWords * (kSplitPieces + kSplitMerges) <= 4 * kMfmaDecodeWgs * 4, "records of append and decode");
 
 extern "C" {
 
@@ -213,11 +219,12 @@ int rollattn_debug_read_append_plan(const rollattn_desc* desc, const void* works
   if (e != hipSuccess) return fail_hip(e);
   const char* base = (const char*)workspace;
   int32_t header[kPlanWords];
-  std::vector<int32_t> rec((size_t)w.list_cap * kTileRecWords);
   e = hipMemcpy(header, base + w.header, sizeof(header), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(rec.data(), base + w.wstart, sizeof(int32_t) * rec.size(), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail_hip(e);
-  const int32_t n = std::max(0, std::min(header[kPlanTiles], w.list_cap));
+  const int32_t n = std::max(0, std::min(header[kPlanTiles], header[kPlanMerges] > 0 ? w.max_pieces : w.workers));
+  std::vector<int32_t> rec((size_t)n * kTileRecWords);
+  if (n) e = hipMemcpy(rec.data(), base + w.wstart, sizeof(int32_t) * rec.size(), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) return fail_hip(e);
   int32_t tiles = 0;
   for (int32_t i = 0; i < n && tiles < w.workers; ++i) {
     const int32_t* r = rec.data() + (size_t)i * kTileRecWords;
@@ -410,7 +417,8 @@ int attn_decode_static(const rollattn_desc* desc, const void* q, const void* k_p
 
 // attn_append proper.  table_stride: int32 entries between the page-table rows of consecutive
 // trajectories; noncausal: every row sees all of [0, L_b) (then n_b <= L_b is not required);
-// lse as in decode_impl, [total_q][Hq].  table_stride and noncausal are for the bf16 kernels only.
+// lse as in decode_impl, [total_q][Hq].  table_stride and noncausal are for the bf16 kernels only.  lender: the decode half
+// of the same call, launched behind this one, whose room for partials this one may use first (null: a call of its own).
 struct AppendCall {
   AppendPlanArgs plan;
   AppendArgs args;
@@ -422,7 +430,7 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
                           int32_t total_q, int32_t max_q_len, const void* k_pages, const void* v_pages,
                           const int32_t* page_table, const int32_t* ctx_lens, void* out, void* workspace,
                           size_t workspace_bytes, int32_t table_stride, bool noncausal, float* lse, bool skip_unit_chunks,
-                          AppendCall* call) {
+                          const DecodeArgs* lender, AppendCall* call) {
   int rc = check_desc(desc);
   if (rc) return rc;
   if (total_q < 0 || max_q_len < 0) return ROLLATTN_EINVAL;
@@ -457,13 +465,17 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
   // ... and at least (every group of attn_decode_shared is one; in a mixed step up to B rows are not chunk rows): a list
   // that is too long to be cut, or as good as even already, needs neither the decision nor the merge launch
   const int64_t min_tiles = noncausal ? desc->batch : ((int64_t)total_q - (skip_unit_chunks ? desc->batch : 0)) / a.tile_tokens;
-  const bool may_cut = min_tiles <= w.max_pieces && !(noncausal && min_tiles * a.hkv >= kNumCUs);
+  // ... as does a table whose contexts are all shorter than two pieces.  Whether the workspace has room is told from its
+  // size alone: one as large as rollattn_workspace_bytes always has.
+  const bool may_cut = min_tiles <= w.max_pieces && !(noncausal && min_tiles * a.hkv >= kNumCUs) &&
+                       desc->max_pages_per_seq > (2 * kMinPieceBlocks - 1) * (kAppendBlockTokens / kPageSize) &&
+                       workspace_bytes >= (lender ? w.cut_list : w.cut_total);
   const int32_t max_pieces = may_cut ? w.max_pieces : 0;
   const int32_t tile_cap = std::max(max_tiles, max_pieces);
   a.tile_cap = tile_cap;
   a.merge_rec = (const int32_t*)(base + w.merge_rec);
-  a.partial_ml = (float*)(base + w.partial_ml);
-  a.partial_o = (float*)(base + w.partial_o);
+  a.partial_ml = lender ? lender->partial_ml : (float*)(base + w.partial_ml);
+  a.partial_o = lender ? lender->partial_o : (float*)(base + w.partial_o);
   a.total_q = total_q;
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
@@ -471,12 +483,12 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
 
   AppendPlanArgs& pa = call->plan;
   pa.q_lens = q_lens; pa.q_offsets = q_offsets; pa.ctx_lens = ctx_lens;
-  pa.batch = desc->batch; pa.hkv = a.hkv; pa.tile_tokens = a.tile_tokens;
-  pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_slots = w.max_slots;
+  pa.batch = desc->batch; pa.hkv = a.hkv; pa.group = a.group; pa.tile_tokens = a.tile_tokens;
+  pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_merges = w.max_merges; pa.max_units = w.max_units;
   pa.skip_unit_chunks = skip_unit_chunks; pa.noncausal = noncausal;
   pa.header = a.header; pa.tile_rec = (int32_t*)(base + w.wstart); pa.merge_rec = (int32_t*)(base + w.merge_rec);
   call->tile_cap = tile_cap;
-  call->max_merges = max_pieces ? std::min(max_tiles, w.max_slots / 2) : 0;
+  call->max_merges = max_pieces ? std::min(max_tiles, w.max_merges) : 0;
   return ROLLATTN_OK;
 }
 
@@ -523,7 +535,7 @@ static int append_impl(const rollattn_desc* desc, const void* q_chunk, const int
   if (!desc) return ROLLATTN_EINVAL;
   AppendCall call{};
   const int rc = append_prepare(desc, q_chunk, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                                workspace, workspace_bytes, desc->max_pages_per_seq, false, lse, false, &call);
+                                workspace, workspace_bytes, desc->max_pages_per_seq, false, lse, false, nullptr, &call);
   if (rc || call.args.batch == 0) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
   if (desc->q_dtype != ROLLATTN_F32) {
@@ -580,7 +592,7 @@ int attn_merge(const rollattn_desc* desc, int64_t rows, const void* o1, const fl
 
 size_t rollattn_step_workspace_bytes(const rollattn_desc* desc, int32_t total_q) {
   if (check_desc(desc) != ROLLATTN_OK || total_q < 0) return 0;
-  return align256(decode_layout(*desc).total) + append_layout(*desc, total_q).total;
+  return align256(decode_layout(*desc).total) + append_layout(*desc, total_q).cut_list;
 }
 
 size_t rollattn_step_append_offset(const rollattn_desc* desc) {
@@ -597,7 +609,7 @@ int attn_step(const rollattn_desc* desc, const void* q, const int32_t* q_lens, c
   if (desc->batch == 0 || total_q == 0) return ROLLATTN_OK;
   if (!workspace) return ROLLATTN_EINVAL;
   if (!aligned16(workspace)) return ROLLATTN_EALIGN;
-  if (workspace_bytes < rollattn_step_workspace_bytes(desc, total_q)) return ROLLATTN_EWORKSPACE;
+  if (workspace_bytes < align256(decode_layout(*desc).total) + append_layout(*desc, total_q).total) return ROLLATTN_EWORKSPACE;
   if (desc->q_dtype == ROLLATTN_F32) {
     // the float32 path has one kernel for chunks of any length, one token included
     return append_impl(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
@@ -613,13 +625,13 @@ int attn_step(const rollattn_desc* desc, const void* q, const int32_t* q_lens, c
   const size_t dec_bytes = align256(decode_layout(*desc).total);
   AppendCall app{};
   DecodeCall dec{};
-  rc = append_prepare(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
-                      (char*)workspace + dec_bytes, workspace_bytes - dec_bytes, desc->max_pages_per_seq, false, nullptr,
-                      /*skip_unit_chunks=*/true, &app);
-  if (!rc) rc = decode_prepare(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, dec_bytes, nullptr, q_lens, q_offsets, &dec);
+  rc = decode_prepare(desc, q, k_pages, v_pages, page_table, ctx_lens, out, workspace, dec_bytes, nullptr, q_lens, q_offsets, &dec);
+  if (!rc) rc = append_prepare(desc, q, q_lens, q_offsets, total_q, max_q_len, k_pages, v_pages, page_table, ctx_lens, out,
+                               (char*)workspace + dec_bytes, workspace_bytes - dec_bytes, desc->max_pages_per_seq, false, nullptr,
+                               /*skip_unit_chunks=*/true, &dec.args, &app);
   if (rc) return rc;
   // both plans in one launch, then the long tiles of the chunks first, then the decode rows and their merge; all on one
-  // stream, disjoint output rows
+  // stream, disjoint output rows (the partials of cut tiles are merged before the decode rows' partials take their place)
   hipStream_t s = (hipStream_t)hip_stream;
   const hipError_t e = launch_plan_step(app.plan, dec.plan, s);
   if (e != hipSuccess) return fail_hip(e);
@@ -642,7 +654,7 @@ SharedLayout shared_layout(const rollattn_desc& d, int32_t group_size) {
   L.grp.batch = d.batch / group_size;
   const size_t rows = (size_t)d.batch * d.num_q_heads;
   L.dec_bytes = decode_layout(d).total;
-  L.app_bytes = append_layout(L.grp, d.batch).total;
+  L.app_bytes = append_layout(L.grp, d.batch).cut_list;
   size_t off = 0;
   L.dec_ws = off;    off += align256(L.dec_bytes);
   L.app_ws = off;    off += align256(L.app_bytes);
@@ -695,11 +707,11 @@ int attn_decode_shared(const rollattn_desc* desc, const void* q, const void* k_p
   // member's table; private half: every trajectory from token S on
   AppendCall app{};
   DecodeCall dec{};
-  rc = append_prepare(&L.grp, q, nullptr, nullptr, desc->batch, group_size, k_pages, v_pages, page_table, nullptr,
-                      base + L.o1, base + L.app_ws, L.app_bytes, group_size * desc->max_pages_per_seq, true,
-                      (float*)(base + L.d1), false, &app);
-  if (!rc) rc = decode_prepare(desc, q, k_pages, v_pages, page_table, sh.own_ctx, base + L.o2, base + L.dec_ws, L.dec_bytes,
-                               (float*)(base + L.d2), nullptr, nullptr, &dec);
+  rc = decode_prepare(desc, q, k_pages, v_pages, page_table, sh.own_ctx, base + L.o2, base + L.dec_ws, L.dec_bytes,
+                      (float*)(base + L.d2), nullptr, nullptr, &dec);
+  if (!rc) rc = append_prepare(&L.grp, q, nullptr, nullptr, desc->batch, group_size, k_pages, v_pages, page_table, nullptr,
+                               base + L.o1, base + L.app_ws, L.app_bytes, group_size * desc->max_pages_per_seq, true,
+                               (float*)(base + L.d1), false, &dec.args, &app);
   if (rc) return rc;
   dec.args.first_page = sh.own_page;
   const hipError_t e = launch_plan_shared(sh, app.plan, dec.plan, s);

@@ -62,7 +62,7 @@ typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRowsPerWave = 32;
+constexpr int kRowsPerWave = kUnitRows;
 static_assert(kWaves * kRowsPerWave == kAppendTileRows, "tile rows");
 constexpr int kBlockTokens = kAppendBlockTokens;   // KV tokens staged per step
 constexpr float kSumLimit = 16384.f;               // a lane's 32 probabilities of a block may add up to this much before the row's reference moves
@@ -890,17 +890,17 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   int g_e;
   const int tile_e = tile_of(block_e, hkv_e, g_e);
   const const_rec_p rec_e = (const_rec_p)(args_e->tile_rec + (size_t)tile_e * kTileRecWords);
-  const int q0_e = rec_e[1], n_e = rec_e[2], qoff_e = rec_e[4], slot = rec_e[7];
+  const int q0_e = rec_e[1], n_e = rec_e[2], qoff_e = rec_e[4], unit = rec_e[7];
   const int lane_e = tid_e & 63, wave_e = __builtin_amdgcn_readfirstlane(tid_e >> 6), row_wave_e = HALF ? (wave_e & 3) : wave_e;
   const int rows_e = min(args_e->tile_tokens, n_e - q0_e) * group_e;
   const int row_e = row_wave_e * kRowsPerWave + (lane_e & 31);
   const bool upper = lane_e >= 32;
   const bool ok = row_e < rows_e;
   l_run = xor32_add(l_run);
-  if (slot >= 0) {
+  if (unit >= 0) {
     // a piece of a tile: accumulators as they lie, 16 bytes per lane and store, reference and sum of each row
     if (row_wave_e * kRowsPerWave < rows_e) {
-      const size_t part = ((size_t)slot * hkv_e + g_e) * kWaves + row_wave_e;
+      const size_t part = (size_t)(unit + row_wave_e) * hkv_e + g_e;
       float* po = args_e->partial_o + part * (kRowsPerWave * D) + lane_e * 4;
 #pragma unroll
       for (int dt = 0; dt < kDT; ++dt)
@@ -943,12 +943,12 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
   const int dt = unit % kDT, row_wave = (unit / kDT) % kWaves, m = unit / (kDT * kWaves);
   const int n_merges = a.header[kPlanMerges];
   const int32_t* rec = a.merge_rec + (size_t)m * kTileRecWords;     // (room for every m of the grid: leaves together with the count)
-  const int q0 = rec[0], n_b = rec[1], q_off = rec[2], slot0 = rec[3], pieces = rec[4];
+  const int q0 = rec[0], n_b = rec[1], q_off = rec[2], unit0 = rec[3], pieces = rec[4];
   if (m >= n_merges) return;
   const int rows_here = min(a.tile_tokens, n_b - q0) * a.group;
   if (row_wave * kRowsPerWave >= rows_here) return;
-  const size_t stride = (size_t)a.hkv * kWaves;            // parts from one piece to the next
-  const size_t part0 = (size_t)slot0 * stride + (size_t)g * kWaves + row_wave;
+  const size_t stride = (size_t)((rows_here + kRowsPerWave - 1) / kRowsPerWave) * a.hkv;   // parts from one piece to the next
+  const size_t part0 = (size_t)(unit0 + row_wave) * a.hkv + g;
   const floatx2* ml = (const floatx2*)a.partial_ml + part0 * kRowsPerWave + n32;
   const float* po = a.partial_o + part0 * (kRowsPerWave * D) + (dt * 4 * 64 + lane) * 4;
   floatx4 o[4];

@@ -48,14 +48,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodeP
 // shorter pieces fill the gaps.  kPieceCost is what a workgroup costs besides its blocks (start, first tiles from HBM,
 // epilogue, hand-over of the CU: 22,000 cycles against 2,500 per block when measured), kMergeCost the merge launch and
 // the float partials' way to memory and back.  Limits whose pieces or partials there is no room for are left out (13 chunks
-// of 64 tokens behind 16k, 32/8/128, bf16: the cheapest would need 91 slots per head).  The split is taken only where the
+// of 64 tokens behind 16k, 32/8/128, bf16: the cheapest would need 91 pieces of 256 rows per head).  The split is taken only where the
 // price drops by a tenth.
 // Measured: three observations of 16 .. 512 tokens behind 2k .. 16k (32/8/128, bf16, one of every four CUs idle before)
 // 275 -> 208 us with plan and merge; 33 of 3 .. 96 tokens behind up to 64k (64/4/128, FP8) 1410 -> 652 us.  The decision
 // adds 3 us to the plan of a short list, the merge takes 12 us where tiles were cut and 3 us where none was; lists too
 // long to be cut skip both (the host knows a lower bound of the number of tiles).
 constexpr int kRankBatch = 4096;
-constexpr int kSplitTiles = 1024;
+constexpr int kSplitTiles = kSplitPieces;
+static_assert(kSplitTiles <= kPlanThreads, "a thread per tile");
 constexpr float kPieceCost = 8.f;
 constexpr float kMergeCost = 8.f;
 
@@ -79,13 +80,14 @@ struct AppendPlanLds {
   int len_s[kRankBatch], order_s[kRankBatch];
   int2 chunk_s[kRankBatch];            // rows and offset of a chunk
   int first_s[kPlanThreads], count_s[kPlanThreads], b_s[kPlanThreads], qlen_s[kPlanThreads], ctx_s[kPlanThreads], qoff_s[kPlanThreads];
-  int tile_qoff_s[kSplitTiles], blocks_s[kSplitTiles];   // ... and number of blocks
-  int pieces_s[64], slots_s[64];
+  int tile_qoff_s[kSplitTiles], blocks_s[kSplitTiles], units_s[kSplitTiles];   // ... number of blocks, units of rows
+  int pieces_s[64], merges_s[64], piece_units_s[64];
 };
 
 template <class C>
 __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanLds& lds, const C& chunk) {
-  auto& [wave_tot, tile_s, len_s, order_s, chunk_s, first_s, count_s, b_s, qlen_s, ctx_s, qoff_s, tile_qoff_s, blocks_s, pieces_s, slots_s] = lds;
+  auto& [wave_tot, tile_s, len_s, order_s, chunk_s, first_s, count_s, b_s, qlen_s, ctx_s, qoff_s, tile_qoff_s, blocks_s, units_s, pieces_s, merges_s,
+         piece_units_s] = lds;
   const int tid = threadIdx.x;
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
@@ -133,7 +135,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
     qoff_s[tid] = q_off;
     __syncthreads();
     // One 32-byte record per tile with everything the tile's workgroup needs to start, so that it gets there with
-    // one dependent load instead of a chain of them: (b, first row, n_b, L_b, q_offsets[b], first block, blocks, slot).
+    // one dependent load instead of a chain of them: (b, first row, n_b, L_b, q_offsets[b], first block, blocks, unit).
     // The tiles of these trajectories are dealt to the threads one by one (a trajectory may have hundreds): a tile
     // finds its trajectory as the last one of the group that starts at or before it (those without tiles start where
     // the next one starts, and are never the last such).
@@ -155,6 +157,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
         tile_s[t] = make_int4(b_s[lo], q0, qlen_s[lo], ctx_s[lo]);
         tile_qoff_s[t] = qoff_s[lo];
         blocks_s[t] = blocks;
+        units_s[t] = (min(tile_tokens, qlen_s[lo] - q0) * a.group + kUnitRows - 1) / kUnitRows;
       }
     }
     __syncthreads();
@@ -182,7 +185,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const float mean = fmaxf((float)blocks_total / cus, 1.f);
   auto limit_of = [&](int i) { return fmaxf((float)kMinPieceBlocks, ceilf(mean * (0.3f + 0.04f * (float)i))); };
   float per_limit[4], below[4];
-  int pieces[4] = {0, 0, 0, 0}, slots[4] = {0, 0, 0, 0};
+  int pieces[4] = {0, 0, 0, 0}, merges[4] = {0, 0, 0, 0}, units[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const float p = limit_of(wave * 4 + c);
@@ -197,22 +200,25 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
       // is below 2^20 / p; a count of that size is past max_pieces whatever its last digit
       const int k = max(1, (int)((n + below[c]) * per_limit[c]));
       pieces[c] += k;
-      slots[c] += k > 1 ? k : 0;
+      merges[c] += k > 1 ? 1 : 0;
+      units[c] += k > 1 ? k * units_s[t] : 0;
     }
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int n = wave_sum(pieces[c]), m = wave_sum(slots[c]);
+    const int n = wave_sum(pieces[c]), m = wave_sum(merges[c]), u = wave_sum(units[c]);
     if (lane == 0) {
       pieces_s[wave * 4 + c] = n;
-      slots_s[wave * 4 + c] = m;
+      merges_s[wave * 4 + c] = m;
+      piece_units_s[wave * 4 + c] = u;
     }
   }
   __syncthreads();
   // prices as integers (a sixteenth of a block), complemented, so that the cheapest is the largest
   const int n_lane = pieces_s[lane];
   const float price_lane = split_price(limit_of(lane), (float)blocks_total, (float)n_lane, cus) + kMergeCost;
-  const bool fits = n_lane > tiles && n_lane <= a.max_pieces && slots_s[lane] <= a.max_slots;   // (the cheapest of those there is room for)
+  // (the cheapest of those there is room for)
+  const bool fits = n_lane > tiles && n_lane <= a.max_pieces && merges_s[lane] <= a.max_merges && piece_units_s[lane] <= a.max_units;
   const unsigned key = fits ? ~(unsigned)fminf(16.f * price_lane, 6e7f) : 0u;
   const unsigned cheapest = wave_max(key);
   const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == cheapest));
@@ -223,19 +229,20 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const int mine = tid < tiles ? blocks_s[tid] : 0;
   const int k = tid < tiles ? max(1, (mine + p_max - 1) / p_max) : 0;   // pieces of this thread's tile (one without blocks has zero rows to write)
   const bool cut = k > 1;
-  // pieces and cut tiles in one scan: at most kSplitPieces of the first, kSplitTiles of the second
-  int both;
-  const int before = block_exclusive_scan(k | (cut ? 1 << 16 : 0), wave_tot, &both);
-  const int piece0 = before & 0xffff, merge0 = before >> 16, n_pieces = both & 0xffff, n_merges = both >> 16;
-  const int slot0 = piece0 - (tid - merge0);   // every uncut tile is one piece without a slot
+  // pieces, cut tiles and units of partials in one scan: 10, 9 and 12 bits
+  static_assert(kSplitPieces < 1024 && kSplitMerges < 512 && kSplitUnits < 4096, "one scan");
+  const int my_units = cut ? units_s[tid] : 0;
+  int all;
+  const int before = block_exclusive_scan(k | (cut ? 1 << 10 : 0) | (k * my_units) << 19, wave_tot, &all);
+  const int piece0 = before & 1023, merge0 = (before >> 10) & 511, unit0 = before >> 19, n_pieces = all & 1023, n_merges = (all >> 10) & 511;
   if (cut) {
     int4* m = (int4*)(a.merge_rec + (size_t)merge0 * kTileRecWords);
-    m[0] = make_int4(tile_s[tid].y, tile_s[tid].z, tile_qoff_s[tid], slot0);   // (first row, n_b, q_offsets[b], first slot, pieces)
+    m[0] = make_int4(tile_s[tid].y, tile_s[tid].z, tile_qoff_s[tid], unit0);   // (first row, n_b, q_offsets[b], first unit, pieces)
     m[1] = make_int4(k, 0, 0, 0);
   }
   first_s[tid] = piece0;                                  // threads past the tiles hold n_pieces
   count_s[tid] = k;
-  b_s[tid] = cut ? slot0 : -1;
+  b_s[tid] = cut ? unit0 : -1;
   __syncthreads();
   for (int t = tid; t < n_pieces; t += kPlanThreads) {
     int lo = 0, hi = tiles;
@@ -249,7 +256,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
     const int blk0 = each * i + min(i, more), blk1 = blk0 + each + (i < more ? 1 : 0);
     int4* rec = (int4*)(a.tile_rec + (size_t)t * kTileRecWords);
     rec[0] = tile_s[lo];
-    rec[1] = make_int4(tile_qoff_s[lo], blk0, blk1 - blk0, b_s[lo] < 0 ? -1 : b_s[lo] + i);
+    rec[1] = make_int4(tile_qoff_s[lo], blk0, blk1 - blk0, b_s[lo] < 0 ? -1 : b_s[lo] + i * units_s[lo]);
   }
   if (tid == 0) {
     a.header[kPlanTiles] = n_pieces;

@@ -22,8 +22,10 @@ constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pair
 constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
 constexpr int kAppendBlockTokens = 64;  // KV tokens staged per step of the append kernel
 constexpr int kTileRecWords = 8;       // append: int32 per tile record (32 bytes: one scalar load)
-constexpr int kSplitPieces = 1024;      // append: a list whose tiles are cut into pieces has at most this many workgroups
-constexpr int kSplitSlots = 512;        // append: ... and this many of them leave partials (2 MB of workspace each 16 slots at D = 128)
+constexpr int kSplitPieces = 768;       // append: a list whose tiles are cut into pieces has at most this many workgroups
+constexpr int kSplitMerges = 256;       // append: ... from at most this many tiles
+constexpr int kSplitUnits = 2048;       // append: ... whose pieces leave at most this many partials of kUnitRows rows each
+constexpr int kUnitRows = 32;           // append: query rows per wave, and per unit of the partials of a tile's piece
 constexpr int kMinPieceBlocks = 8;      // append: shorter pieces cost more in their start and end than they save
 constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list that one XCD takes in a row (one per CU)
 
@@ -33,17 +35,19 @@ enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 
 // Byte offsets of the workspace regions (all multiples of 256).
 struct WorkspaceLayout {
   int32_t workers;        // decode: number of workers W; append: capacity in query tiles
-  int32_t list_cap;       // append: capacity of the work list, in tiles or pieces of tiles
-  int32_t max_pieces, max_slots;   // append: limits of a list whose tiles are cut (0: this call cuts none)
+  int32_t max_pieces, max_merges, max_units;   // append: limits per KV head of a list whose tiles are cut (0: none can be)
   int32_t head_tile;      // decode: query heads per row (16 or 4)
   int32_t rows_per_b;     // decode: rows per trajectory = Hkv * ceil(G / head_tile)
   size_t header;          // int32[kPlanWords]
   size_t prefix;          // decode: int32[B + 1] exclusive scan of per-trajectory block counts
-  size_t wstart;          // decode: int32[W][4] first (b, row, block) of every worker; append: int32[cap][8] tile records
-  size_t merge_rec;       // append: int32[max_slots / 2][8], one record per tile that was cut into pieces
-  size_t partial_ml;      // float[2 W][head_tile][2]   (max in log2 units, sum); append: float[slots][Hkv][8][32][2]
-  size_t partial_o;       // float[2 W][head_tile][D]   un-normalised; append: float[slots][Hkv][8][D / 8][64][4], as the accumulators lie
-  size_t total;
+  size_t wstart;          // decode: int32[W][4] first (b, row, block) of every worker; append: int32[workers][8] tile records
+  size_t merge_rec;       // append: int32[max_merges][8], one record per tile that was cut into pieces
+  size_t partial_ml;      // float[2 W][head_tile][2]   (max in log2 units, sum); append: float[max_units][Hkv][32][2]
+  size_t partial_o;       // float[2 W][head_tile][D]   un-normalised; append: float[max_units][Hkv][D / 8][64][4], as the accumulators lie
+  size_t total;           // what the call needs
+  // append: what it needs to cut tiles, without the partials and with them.  The list of a call that cuts is short, so
+  // merge_rec and the partials lie where a long list's tail would.
+  size_t cut_list, cut_total;
 };
 
 WorkspaceLayout decode_layout(const rollattn_desc& d);
@@ -109,10 +113,10 @@ struct AppendArgs {
   const float* v_scale;
   int32_t* header;
   // [tile_cap][kTileRecWords]: (b, first row of the tile in its chunk, n_b, L_b, q_offsets[b], first block, number of
-  // blocks, slot); slot: -1 for a whole tile, else where this piece of one leaves its partial result
+  // blocks, unit); unit: -1 for a whole tile, else where the partial results of this piece of one start
   const int32_t* tile_rec;
   int32_t tile_cap;
-  const int32_t* merge_rec;  // (first row of the tile, n_b, q_offsets[b], first slot, pieces, 0, 0, 0) of every tile that was cut
+  const int32_t* merge_rec;  // (first row of the tile, n_b, q_offsets[b], first unit, pieces, 0, 0, 0) of every tile that was cut
   float* partial_ml;
   float* partial_o;
   int32_t batch, hq, hkv, group, max_pages, tile_tokens, total_q;
@@ -138,9 +142,9 @@ struct AppendPlanArgs {
   const int32_t* q_lens;
   const int32_t* q_offsets;
   const int32_t* ctx_lens;
-  int32_t batch, hkv, tile_tokens;
+  int32_t batch, hkv, group, tile_tokens;
   int32_t cap;                     // room in the list
-  int32_t max_pieces, max_slots;   // cut tiles into pieces only within these (0: never)
+  int32_t max_pieces, max_merges, max_units;   // cut tiles into pieces only within these (0: never)
   bool skip_unit_chunks;           // mixed step: chunks of one token are decode rows
   bool noncausal;
   int32_t* header;

@@ -159,3 +159,19 @@ def test_plan_on_the_benchmark_length_draws():
         o_per, o_total, _, o_segs = O.split_plan(lens, w.num_kv_heads, 2048)
         assert (per, total) == (o_per, o_total) and np.array_equal(segs, o_segs)
         assert segs[:, 4].sum() == total == w.num_kv_heads * ((lens + 31) // 32).sum()
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,kv", [(64, 32, 8, 128, B.BF16), (1, 8, 8, 64, B.BF16), (512, 64, 4, 128, B.FP8_E4M3), (3000, 16, 1, 64, B.FP8_E4M3)])
+def test_workspace_sizes_do_not_depend_on_the_width_of_the_table(batch, hq, hkv, d, kv):
+    lib, one = B.lib(), ctypes.c_void_p(0x1000)
+    desc = lambda pages: _desc(batch=batch, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, q_dtype=B.BF16, kv_dtype=kv, max_pages_per_seq=pages,
+                               k_scale=one, v_scale=one)
+    for total_q in (batch, 40 * batch):
+        for f in (lib.rollattn_workspace_bytes, lib.rollattn_step_workspace_bytes, lib.rollattn_shared_workspace_bytes):
+            n = 1 if f is lib.rollattn_shared_workspace_bytes else total_q
+            assert f(ctypes.byref(desc(4096)), n) == f(ctypes.byref(desc(60)), n) > 0
+    # two partials of 16 rows per wave of 512 workgroups, and records: an append call's pieces ask for no more than a decode call,
+    # so what attn_decode_static takes is what the size says
+    partials = 512 * 4 * 2 * 16 * (d + 2) * 4
+    assert partials < lib.rollattn_workspace_bytes(ctypes.byref(desc(4096)), batch) <= partials + 33792 + 4 * batch
+    assert lib.rollattn_workspace_bytes(ctypes.byref(desc(4096)), batch) <= lib.rollattn_static_scratch_bytes()

@@ -1,4 +1,6 @@
 """Append calls with few tiles: their tiles are cut into pieces of the context whose partial results a merge folds."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -6,7 +8,7 @@ import torch
 from oracle import attention as O
 from paper_2512_22560_amd import binding as B
 from paper_2512_22560_amd import workloads as W
-from tests.gpu_common import check, oracle_append
+from tests.gpu_common import check, gpu_append, oracle_append
 from tests.helpers import oracle_args
 
 pytestmark = pytest.mark.gpu
@@ -62,3 +64,40 @@ def test_shared_prompts_of_few_groups_are_cut_too():
     out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8,
                                shared_lens=torch.from_numpy(shared.astype(np.int32)).to(DEV), sm_scale=b.workload.sm_scale)
     check(out, O.attn_decode(W.raw_numpy(b.q), **oracle_args(b)), "bf16", "shared")
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+def test_a_workspace_without_room_for_pieces_leaves_the_tiles_whole(kvd):
+    # sized for the records alone, all that a call needs; one for a decode step of the same descriptor is enough to cut
+    b = W.build(W.Workload("room", 2, 32, 8, 128, "bf16", kvd, ("uniform", 6000, 9000), qlen=("uniform", 20, 90), ctx_is_prefix=True,
+                           seed=W.BASE_SEED + 93), DEV)
+    w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    least = 256 + -(-32 * B.lib().rollattn_append_plan_capacity(ctypes.byref(desc), b.total_q) // 256) * 256
+    got = []
+    for n, cut in ((least, False), (B.workspace_bytes(desc, w.batch), True)):
+        ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+        got.append(gpu_append(b, workspace=ws))
+        assert (ws.view(torch.int32)[5].item() > 0) == cut
+        check(got[-1], oracle_append(b), "bf16", "room")
+    with pytest.raises(B.RollattnError):
+        gpu_append(b, workspace=torch.empty(least - 256, dtype=torch.uint8, device=DEV))
+    # a mixed step of the chunks alone cuts them where the decode rows' partials will lie: the same pieces, bit for bit
+    step = B.attn_step(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, k_scale=b.k_scale,
+                       v_scale=b.v_scale, max_q_len=int(b.q_lens_host.max()))
+    assert torch.equal(step, got[1])
+
+
+def test_a_mixed_step_with_cut_chunks_and_split_rows():
+    # two chunks behind long prefixes, cut; the decode rows, split over many workers, take the same room for their partials afterwards
+    b = W.build(W.Workload("both", 6, 32, 8, 128, "bf16", "bf16", ("uniform", 6000, 9000), qlen=("uniform", 20, 90), ctx_is_prefix=True,
+                           append_rows=2, seed=W.BASE_SEED + 94), DEV)
+    w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale)
+    ws = torch.empty(B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), b.total_q), dtype=torch.uint8, device=DEV)
+    args = (b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens)
+    kw = dict(sm_scale=w.sm_scale, max_q_len=int(b.q_lens_host.max()), workspace=ws)
+    out = B.attn_step(*args, **kw).clone()
+    assert ws[B.lib().rollattn_step_append_offset(ctypes.byref(desc)):].view(torch.int32)[5].item() > 0
+    check(out, oracle_append(b), "bf16", "both")
+    assert all(torch.equal(out, B.attn_step(*args, **kw)) for _ in range(3))
