@@ -419,6 +419,17 @@ int attn_decode_static(const rollattn_desc* desc, const void* q, const void* k_p
 // trajectories; noncausal: every row sees all of [0, L_b) (then n_b <= L_b is not required);
 // lse as in decode_impl, [total_q][Hq].  table_stride and noncausal are for the bf16 kernels only.  lender: the decode half
 // of the same call, launched behind this one, whose room for partials this one may use first (null: a call of its own).
+// Time in us of a block (64 tokens) of an append tile with few CUs busy and with all of them, from the slope over contexts
+// of 1k to 8k with 8 and 256 workgroups: what the plan prices pieces with.
+struct BlockTime {
+  float alone, full;
+};
+static BlockTime block_time(const rollattn_desc& d, bool half_tiles) {
+  const bool fp8 = d.kv_dtype == ROLLATTN_FP8_E4M3;
+  if (d.head_dim == 128) return half_tiles ? (fp8 ? BlockTime{0.85f, 1.10f} : BlockTime{0.76f, 1.42f}) : (fp8 ? BlockTime{1.28f, 1.82f} : BlockTime{1.05f, 1.75f});
+  return half_tiles ? (fp8 ? BlockTime{0.74f, 0.79f} : BlockTime{0.60f, 0.82f}) : (fp8 ? BlockTime{1.21f, 1.32f} : BlockTime{0.89f, 1.07f});
+}
+
 struct AppendCall {
   AppendPlanArgs plan;
   AppendArgs args;
@@ -465,13 +476,18 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
   // ... and at least (every group of attn_decode_shared is one; in a mixed step up to B rows are not chunk rows): a list
   // that is too long to be cut, or as good as even already, needs neither the decision nor the merge launch
   const int64_t min_tiles = noncausal ? desc->batch : ((int64_t)total_q - (skip_unit_chunks ? desc->batch : 0)) / a.tile_tokens;
-  // ... as does a table whose contexts are all shorter than two pieces.  Whether the workspace has room is told from its
-  // size alone: one as large as rollattn_workspace_bytes always has.
+  // ... as does a table whose contexts are all too short: the least that pays is a lone tile cut into shortest pieces.
+  // Whether the workspace has room is told from its size alone: one as large as rollattn_workspace_bytes always has.
+  const BlockTime t = block_time(*desc, half_tiles);
+  const float start = kPieceUs / t.full;
+  const int32_t min_longest = std::max(2 * kMinPieceBlocks, (int32_t)std::ceil(((t.alone * (kMinPieceBlocks + start) + kMergeUs + kCallUs + kSplitGainUs) / kSplitGain - kCallUs) / t.alone - start));
   const bool may_cut = min_tiles <= w.max_pieces && !(noncausal && min_tiles * a.hkv >= kNumCUs) &&
-                       desc->max_pages_per_seq > (2 * kMinPieceBlocks - 1) * (kAppendBlockTokens / kPageSize) &&
+                       desc->max_pages_per_seq > (min_longest - 1) * (kAppendBlockTokens / kPageSize) &&
                        workspace_bytes >= (lender ? w.cut_list : w.cut_total);
   const int32_t max_pieces = may_cut ? w.max_pieces : 0;
-  const int32_t tile_cap = std::max(max_tiles, max_pieces);
+  // (the launch has room for no more pieces than the plan may choose: two rounds above the tiles, none shorter than it may be)
+  const int64_t per_tile = (desc->max_pages_per_seq + (int64_t)kMinPieceBlocks * (kAppendBlockTokens / kPageSize) - 1) / (kMinPieceBlocks * (kAppendBlockTokens / kPageSize));
+  const int32_t tile_cap = (int32_t)std::max<int64_t>(max_tiles, std::min<int64_t>({max_pieces, (int64_t)max_tiles + split_extra_pieces(a.hkv), max_tiles * per_tile}));
   a.tile_cap = tile_cap;
   a.merge_rec = (const int32_t*)(base + w.merge_rec);
   a.partial_ml = lender ? lender->partial_ml : (float*)(base + w.partial_ml);
@@ -486,6 +502,9 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
   pa.batch = desc->batch; pa.hkv = a.hkv; pa.group = a.group; pa.tile_tokens = a.tile_tokens;
   pa.cap = tile_cap; pa.max_pieces = max_pieces; pa.max_merges = w.max_merges; pa.max_units = w.max_units;
   pa.skip_unit_chunks = skip_unit_chunks; pa.noncausal = noncausal;
+  pa.us_alone = t.alone; pa.us_full = t.full;
+  pa.min_longest = min_longest;
+  pa.us_per_unit = 0.004f * desc->head_dim / 128.f;
   pa.header = a.header; pa.tile_rec = (int32_t*)(base + w.wstart); pa.merge_rec = (int32_t*)(base + w.merge_rec);
   call->tile_cap = tile_cap;
   call->max_merges = max_pieces ? std::min(max_tiles, w.max_merges) : 0;

@@ -938,13 +938,15 @@ __global__ __launch_bounds__(256) void append_merge_kernel(const AppendArgs a) {
   const int lane = threadIdx.x & 63;
   const int n32 = lane & 31, h2 = lane >> 5;
   const int wave = threadIdx.x >> 6;
-  const int g = blockIdx.x % a.hkv, sub = blockIdx.x / a.hkv;    // head fastest, as in the append kernel: with 8 heads the XCD that wrote the partials reads them
-  const int unit = sub * (256 / 64) + wave;
-  const int dt = unit % kDT, row_wave = (unit / kDT) % kWaves, m = unit / (kDT * kWaves);
+  constexpr int kWgsPerTile = kWaves * kDT / 4;
+  // Where no tile was cut the launch costs its start, so nothing is worked out before the count is there.
   const int n_merges = a.header[kPlanMerges];
-  const int32_t* rec = a.merge_rec + (size_t)m * kTileRecWords;     // (room for every m of the grid: leaves together with the count)
-  const int q0 = rec[0], n_b = rec[1], q_off = rec[2], unit0 = rec[3], pieces = rec[4];
+  const int sub = blockIdx.x / a.hkv, g = blockIdx.x - sub * a.hkv;    // head fastest, as in the append kernel: with 8 heads the XCD that wrote the partials reads them
+  const int m = sub / kWgsPerTile, unit = (sub - m * kWgsPerTile) * 4 + wave;
+  const int dt = unit % kDT, row_wave = unit / kDT;
   if (m >= n_merges) return;
+  const int32_t* rec = a.merge_rec + (size_t)m * kTileRecWords;
+  const int q0 = rec[0], n_b = rec[1], q_off = rec[2], unit0 = rec[3], pieces = rec[4];
   const int rows_here = min(a.tile_tokens, n_b - q0) * a.group;
   if (row_wave * kRowsPerWave >= rows_here) return;
   const size_t stride = (size_t)((rows_here + kRowsPerWave - 1) / kRowsPerWave) * a.hkv;   // parts from one piece to the next

@@ -42,29 +42,40 @@ __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodeP
 // many CUs have nothing to do: a few observations behind long prefixes, or one 64k history among short ones, leave
 // most of the chip idle.  When the list is short enough to be looked at as a whole (kSplitTiles), the kernel asks
 // whether cutting the tiles into pieces of at most P blocks would end sooner: 64 values of P around the mean
-// load of a CU are tried side by side, each priced in blocks as
-//   max(P + kPieceCost, load + u (P + kPieceCost) (ceil(w) - w)),   w = pieces / CUs, load = (blocks + kPieceCost pieces) / CUs,
-// u = mean piece / P: with equal pieces that is the number of full rounds over the CUs, with unequal ones the later,
-// shorter pieces fill the gaps.  kPieceCost is what a workgroup costs besides its blocks (start, first tiles from HBM,
-// epilogue, hand-over of the CU: 22,000 cycles against 2,500 per block when measured), kMergeCost the merge launch and
-// the float partials' way to memory and back.  Limits whose pieces or partials there is no room for are left out (13 chunks
-// of 64 tokens behind 16k, 32/8/128, bf16: the cheapest would need 91 pieces of 256 rows per head).  The split is taken only where the
-// price drops by a tenth.
+// load of a CU are tried side by side, each priced in us as
+//   m (alone + (full - alone) (load / m)^3),   m = max(P + start, load + u (P + start) (ceil(w) - w)),
+//   w = pieces / CUs, load = (blocks + start pieces) / CUs, u = mean piece / P:
+// m is the length in blocks: with equal pieces the number of full rounds over the CUs, with unequal ones the later, shorter
+// pieces fill the gaps.  A block's time grows with the share of the CUs that are busy (memory, power), from `alone` to
+// `full`, which the host passes for the kernel that will run: 1.05 and 1.75 us for whole tiles of bf16 at D = 128, 0.76 and
+// 1.42 for half tiles, where it is memory that a full chip waits for and cutting gains nothing any more.  start: what a
+// workgroup costs besides its blocks (kPieceUs).  Cutting adds the partials' way to memory and back (us_per_unit) and the
+// folding.  It is done where that is a twentieth and 1.5 us shorter, fixed costs of the call (kCallUs) included.  Limits whose pieces or
+// partials there is no room for are left out (13 chunks of 64 tokens behind 16k, 32/8/128, bf16: the cheapest would need 91
+// pieces of 256 rows per head), and those of more than two rounds above the tiles, so that the launch need not have room
+// for them: an empty workgroup waits for a CU's LDS like any other.
+// Against the times of 193 calls, whole and cut, the price is off by 6 and 8 % (standard deviation).
 // Measured: three observations of 16 .. 512 tokens behind 2k .. 16k (32/8/128, bf16, one of every four CUs idle before)
-// 275 -> 208 us with plan and merge; 33 of 3 .. 96 tokens behind up to 64k (64/4/128, FP8) 1410 -> 652 us.  The decision
-// adds 3 us to the plan of a short list, the merge takes 12 us where tiles were cut and 3 us where none was; lists too
-// long to be cut skip both (the host knows a lower bound of the number of tiles).
+// 275 -> 207 us with plan and merge; 33 of 3 .. 96 tokens behind up to 64k (64/4/128, FP8) 1410 -> 650 us; 13 of 64 behind
+// 12k 281 -> 215 us.  40 chunks of 2 tokens behind 9000 (64/4/128, bf16) read at the memory's rate as they are, 135 us, and
+// stay whole; cut they took 152.  What the offer costs a call that stays whole: 1 us of plan where the list is priced, and
+// the start of a merge launch that finds nothing to do, 1.7 us.  The host makes none of it where the table is too narrow for
+// a context that could be cut, or the list too long.
 constexpr int kRankBatch = 4096;
 constexpr int kSplitTiles = kSplitPieces;
 static_assert(kSplitTiles <= kPlanThreads, "a thread per tile");
-constexpr float kPieceCost = 8.f;
-constexpr float kMergeCost = 8.f;
 
-__device__ __forceinline__ float split_price(float p, float blocks, float pieces, float cus) {
-  const float w = pieces / cus, load = (blocks + kPieceCost * pieces) / cus;
-  const float u = fminf(1.f, blocks / (pieces * p));
-  return fmaxf(p + kPieceCost, load + u * (p + kPieceCost) * (ceilf(w) - w));
-}
+struct SplitPrice {
+  float alone, full, per_cu, start;                      // per_cu: list entries (one workgroup per KV head) that a CU gets of each
+  __device__ SplitPrice(const AppendPlanArgs& a) : alone(a.us_alone), full(a.us_full), per_cu((float)a.hkv * (1.f / kNumCUs)), start(kPieceUs * __builtin_amdgcn_rcpf(a.us_full)) {}
+  __device__ __forceinline__ float operator()(float p, float blocks, float pieces) const {
+    const float w = pieces * per_cu, load = (blocks + start * pieces) * per_cu;
+    const float u = fminf(1.f, blocks * __builtin_amdgcn_rcpf(pieces * p));
+    const float m = fmaxf(p + start, load + u * (p + start) * (ceilf(w) - w));
+    const float busy = load * __builtin_amdgcn_rcpf(m);
+    return m * (alone + (full - alone) * busy * busy * busy);
+  }
+};
 
 // What the append plan asks about a chunk: its context, its rows, where they start in the packed query.
 struct ChunkLens {
@@ -91,6 +102,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const int tid = threadIdx.x;
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
+  if (tid < 64) pieces_s[tid] = merges_s[tid] = piece_units_s[tid] = 0;   // (barriers follow before they are added to)
   if (ranked) {
     // everything the plan reads, in one round trip to memory
     const int padded = (batch + 3) & ~3;
@@ -170,7 +182,8 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   }
   if (a.max_pieces == 0 || tiles == 0 || tiles > min(kSplitTiles, a.max_pieces)) return;
 
-  // ---- pieces: 64 limits P tried side by side, four per wave.  Two barriers to here: every wave totals the whole list.
+  // ---- pieces.  Two barriers to the decision: every wave totals the whole list; then a lane per limit P, the tiles dealt
+  // to the waves.  (Code that runs once costs its fetch: this is kept short.)
   const int lane = tid & 63, wave = tid >> 6;
   int blocks_total = 0;
   unsigned longest_seen = 0;
@@ -178,54 +191,40 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
     blocks_total += blocks_s[t];
     longest_seen = max(longest_seen, (unsigned)blocks_s[t]);
   }
-  blocks_total = wave_sum(blocks_total);
   const int longest = (int)wave_max(longest_seen);
-  if (longest < 2 * kMinPieceBlocks) return;
-  const float cus = (float)kNumCUs / (float)a.hkv;      // a list entry is one workgroup per KV head
-  const float mean = fmaxf((float)blocks_total / cus, 1.f);
-  auto limit_of = [&](int i) { return fmaxf((float)kMinPieceBlocks, ceilf(mean * (0.3f + 0.04f * (float)i))); };
-  float per_limit[4], below[4];
-  int pieces[4] = {0, 0, 0, 0}, merges[4] = {0, 0, 0, 0}, units[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const float p = limit_of(wave * 4 + c);
-    per_limit[c] = __builtin_amdgcn_rcpf(p);
-    below[c] = p - 0.5f;
+  if (longest < a.min_longest) return;
+  blocks_total = wave_sum(blocks_total);
+  const SplitPrice price(a);
+  const float limit = fmaxf((float)kMinPieceBlocks, ceilf((float)blocks_total * price.per_cu * (0.3f + 0.04f * (float)lane)));
+  const float per_limit = __builtin_amdgcn_rcpf(limit), below = limit - 0.5f;
+  int pieces = 0, merges = 0, units = 0;
+  for (int t = wave; t < tiles; t += kPlanThreads / 64) {
+    // n / p rounded up: (n + p - 1/2) / p lies half a block away from every whole number, more than its rounding while it
+    // is below 2^20 / p; a count of that size is past max_pieces whatever its last digit
+    const int k = max(1, (int)(((float)blocks_s[t] + below) * per_limit));
+    pieces += k;
+    merges += k > 1 ? 1 : 0;
+    units += k > 1 ? k * units_s[t] : 0;
   }
-  for (int t = lane; t < tiles; t += 64) {
-    const float n = (float)blocks_s[t];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      // n / p rounded up: (n + p - 1/2) / p lies half a block away from every whole number, more than its rounding while it
-      // is below 2^20 / p; a count of that size is past max_pieces whatever its last digit
-      const int k = max(1, (int)((n + below[c]) * per_limit[c]));
-      pieces[c] += k;
-      merges[c] += k > 1 ? 1 : 0;
-      units[c] += k > 1 ? k * units_s[t] : 0;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int n = wave_sum(pieces[c]), m = wave_sum(merges[c]), u = wave_sum(units[c]);
-    if (lane == 0) {
-      pieces_s[wave * 4 + c] = n;
-      merges_s[wave * 4 + c] = m;
-      piece_units_s[wave * 4 + c] = u;
-    }
-  }
+  atomicAdd(&pieces_s[lane], pieces);
+  atomicAdd(&merges_s[lane], merges);
+  atomicAdd(&piece_units_s[lane], units);
   __syncthreads();
-  // prices as integers (a sixteenth of a block), complemented, so that the cheapest is the largest
-  const int n_lane = pieces_s[lane];
-  const float price_lane = split_price(limit_of(lane), (float)blocks_total, (float)n_lane, cus) + kMergeCost;
-  // (the cheapest of those there is room for)
-  const bool fits = n_lane > tiles && n_lane <= a.max_pieces && merges_s[lane] <= a.max_merges && piece_units_s[lane] <= a.max_units;
-  const unsigned key = fits ? ~(unsigned)fminf(16.f * price_lane, 6e7f) : 0u;
+  pieces = pieces_s[lane];
+  merges = merges_s[lane];
+  units = piece_units_s[lane];
+  // prices as integers (a sixteenth of a us), complemented, so that the cheapest is the largest; the last lane prices the
+  // whole tiles
+  const float cost = price(lane == 63 ? (float)longest : limit, (float)blocks_total, (float)(lane == 63 ? tiles : pieces)) + kCallUs +
+                     (lane == 63 ? 0.f : kMergeUs + a.us_per_unit * (float)units * (float)a.hkv);
+  const unsigned ticks = (unsigned)fminf(16.f * cost, 6e7f);
+  const bool fits = lane != 63 && pieces > tiles && pieces <= min(a.max_pieces, tiles + split_extra_pieces(a.hkv)) && merges <= a.max_merges && units <= a.max_units;
+  const unsigned key = fits ? ~ticks : 0u;
   const unsigned cheapest = wave_max(key);
+  const unsigned whole = (unsigned)__builtin_amdgcn_readlane((int)ticks, 63);
+  if (cheapest == 0u || !((float)~cheapest < kSplitGain * (float)whole - 16.f * kSplitGainUs)) return;   // the same in every thread
   const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == cheapest));
-  const float best = cheapest ? (float)~cheapest * (1.f / 16.f) : INFINITY;
-  const float whole = split_price((float)longest, (float)blocks_total, (float)tiles, cus);
-  if (!(best < 0.9f * whole)) return;                    // the same in every thread
-  const int p_max = (int)limit_of(at);
+  const int p_max = __builtin_amdgcn_readlane((int)limit, at);
   const int mine = tid < tiles ? blocks_s[tid] : 0;
   const int k = tid < tiles ? max(1, (mine + p_max - 1) / p_max) : 0;   // pieces of this thread's tile (one without blocks has zero rows to write)
   const bool cut = k > 1;

@@ -27,6 +27,11 @@ constexpr int kSplitMerges = 256;       // append: ... from at most this many ti
 constexpr int kSplitUnits = 2048;       // append: ... whose pieces leave at most this many partials of kUnitRows rows each
 constexpr int kUnitRows = 32;           // append: query rows per wave, and per unit of the partials of a tile's piece
 constexpr int kMinPieceBlocks = 8;      // append: shorter pieces cost more in their start and end than they save
+constexpr float kPieceUs = 8.f;         // append, price of a cut in us: what a workgroup costs besides its blocks,
+constexpr float kMergeUs = 2.f;         // ... folding pieces, besides the way of the partials,
+constexpr float kCallUs = 7.f;          // ... the rest of the call;
+constexpr float kSplitGain = 0.95f, kSplitGainUs = 1.5f;   // ... a list is cut where that ends the call sooner by both shares
+constexpr int split_extra_pieces(int hkv) { return 2 * kNumCUs / hkv; }   // append: cutting makes a list at most this much longer (two rounds)
 constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list that one XCD takes in a row (one per CU)
 
 // Header words of the plan, at the start of the workspace.
@@ -145,6 +150,9 @@ struct AppendPlanArgs {
   int32_t batch, hkv, group, tile_tokens;
   int32_t cap;                     // room in the list
   int32_t max_pieces, max_merges, max_units;   // cut tiles into pieces only within these (0: never)
+  float us_alone, us_full;         // a block of the kernel that will run: on a chip with nothing else to do, on a full one
+  float us_per_unit;               // a unit of partials on its way to memory and back
+  int32_t min_longest;             // blocks: where the longest tile is shorter, no cut can pay
   bool skip_unit_chunks;           // mixed step: chunks of one token are decode rows
   bool noncausal;
   int32_t* header;

@@ -35,6 +35,8 @@ CASES = [
     ("sixteen", 2, 16, 16, 64, (2500, 2600), (257, 300), True), ("skewed", 30, 16, 4, 128, (10, 14000), (1, 200), True),
     # the cheapest cut would need more slots than there are, another one fits
     ("crowded", 13, 32, 8, 64, (12000, 12000), (64, 64), True),
+    # few tokens per chunk over bf16 pools: the chip already reads as fast as it can
+    ("at_memory_rate", 40, 64, 4, 128, (6000, 6000), (2, 2), None),
     ("steps", 40, 64, 4, 128, (0, 260), (1, 8), False), ("steps_d64", 40, 4, 2, 64, (0, 260), (1, 30), False),
 ]
 
@@ -45,6 +47,8 @@ def test_pieces_and_merge_against_the_oracle(name, batch, hq, hkv, d, prefix, ne
     b = W.build(W.Workload(name, batch, hq, hkv, d, "bf16", kvd, ("loguniform" if name == "skewed" else "uniform", *prefix),
                            qlen=("uniform", *new), ctx_is_prefix=True, seed=W.BASE_SEED + 91), DEV)
     out, lse, pieces, merges, tiles = _append(b)
+    if cut is None:                                   # whole over bf16 pools, cut over the half as wide FP8 ones
+        cut = kvd != "bf16"
     assert (merges > 0) == cut and (pieces > len(tiles)) == cut
     half = int(b.q_lens_host.max()) * (hq // hkv) <= 128
     assert np.array_equal(tiles, O.append_tile_plan(b.q_lens_host, b.ctx_lens_host, max(1, (128 if half else 256) // (hq // hkv)))[:, :2])
