@@ -40,7 +40,7 @@
 //
 // Half tiles.  A call whose chunks all fit into 128 rows gets tiles of 128 rows: waves w and w + 4 then own the
 // same 32 rows and split every step, and their two running states are merged when the tile ends.  Over FP8 pools a
-// step is two blocks there, 64 tokens to each wave (see the template parameter HALF below).
+// step of a long tile is two blocks, 64 tokens to each wave (see the template parameter HALF below).
 #include <type_traits>
 #include <utility>
 
@@ -65,6 +65,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kRowsPerWave = kUnitRows;
 static_assert(kWaves * kRowsPerWave == kAppendTileRows, "tile rows");
 constexpr int kBlockTokens = kAppendBlockTokens;   // KV tokens staged per step
+constexpr int kLongTileBlocks = 20;                // half tiles over FP8 pools: from this many blocks on a step is two of them
 constexpr float kSumLimit = 16384.f;               // a lane's 32 probabilities of a block may add up to this much before the row's reference moves
 
 // Row t of an S^T tile holds this token of its 16-token group: the middle two quads are
@@ -137,17 +138,86 @@ __device__ __forceinline__ void static_for(F&& f) {
 // step between them: the leading wave takes its first half, the trailing wave the other one, each with a
 // running reference, sum and accumulator of its own, merged through LDS when the tile ends.
 // What a phase costs besides its scores (tile loads, page ids and scales, their waits, the barrier) does not shrink with
-// them.  FP8 pools: two tiles of 128 tokens per pool fit the LDS, so a step is 128 tokens and each wave's share a whole
-// block (decode of 64 groups of 8 with prompts of 8192 tokens, 64/4/128: 253 -> 242 us in all, with steps of one block and
-// of two).  bf16 pools: a ring of four tiles is all the LDS there is, a step stays one block, 32 tokens to each wave.
+// them.  FP8 pools: two tiles of 128 tokens per pool fit the LDS, so a step may be two blocks and each wave's share a whole
+// one (decode of 64 groups of 8 with prompts of 8192 tokens, 64/4/128: 253 -> 242 us in all, with steps of one block and
+// of two).  A tile or piece of few blocks is mostly padding then, and takes steps of one: each workgroup picks by its own
+// blocks (kLongTileBlocks: 64 chunks of 4 tokens behind 200, 32/8/128, 23.9 us with steps of one and 25.0 of two, of 2 behind
+// 300 25.2 and 29.2, of 4 behind 900 47.7 and 48.4, of 4 behind 4000 142 and 126).  The choice costs 1 us at a tile's start,
+// so calls whose table is too narrow for a long tile run a kernel without it.  bf16 pools: a ring of four tiles is all
+// the LDS there is, a step stays one block, 32 tokens to each wave.
 // ONCE: the pools are read with the streaming hint.  For the shared half of attn_decode_shared, where a group is one tile and
 // no other reads its pages (64 groups of 8 behind 8192 tokens, 64/4/128, FP8: 242 -> 236 us in all).  Chunks of a few tokens
 // are one tile each as well, but their prompts may be shared: 256 of 4 tokens in groups behind a common prompt would take
 // 590 instead of 530 us over bf16 pools, against 516 instead of 557 us with prompts of their own.
-template <int D, bool FP8, bool HALF, bool ONCE>
-__global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs a) {
-  // KV tokens staged per step of the loop
-  constexpr int kStepTokens = HALF && FP8 ? 2 * kBlockTokens : kBlockTokens;
+// STEP: KV tokens staged per step of the loop.
+template <int D, bool FP8, bool HALF, int STEP>
+struct AppendGeo {
+  // bf16 pools go from HBM straight into LDS (no register stop): a ring of four tiles per pool gives
+  // every load a whole block period to land.  FP8 pools pass through registers to be widened: their
+  // LDS writes are immediate, two tiles are enough.
+  static constexpr int kRing = FP8 ? 2 : 4;
+  static constexpr int kTileBytes = STEP * D * 2;
+  // HALF: where the trailing waves leave their result for the leading ones: per wave pair the accumulators
+  // [D / 32][4][64 lanes] as 16-byte quads, and reference and sum.  The accumulators of the four pairs go into the K ring,
+  // which nobody reads, loads into or widens into any more by then (bf16: every wave has waited for its last loads; FP8: the
+  // last tile is widened in a wave's last matrix phase but one; the last read of a K tile lies before the trailing waves'
+  // last barrier); two FP8 tiles of one block are too small, there the accumulators get LDS of their own.
+  static constexpr int kMergeAcc = (D / 32) * 16 * 64;      // floats per wave pair
+  static constexpr bool kMergeInRing = (size_t)kRing * kTileBytes >= (size_t)(kWaves / 2) * kMergeAcc * sizeof(float);
+  static constexpr bool kMergeApart = HALF && !kMergeInRing;
+};
+// The LDS of a kernel with two instances, as one of them sees it.
+template <int D, bool FP8, bool HALF, int STEP>
+struct AppendLds {
+  typedef AppendGeo<D, FP8, HALF, STEP> Geo;
+  __attribute__((aligned(1024))) unsigned char k[Geo::kRing][Geo::kTileBytes], v[Geo::kRing][Geo::kTileBytes];
+  __attribute__((aligned(16))) float merge_acc[Geo::kMergeApart ? kWaves / 2 : 1][Geo::kMergeApart ? Geo::kMergeAcc : 4];
+  float merge_ml[HALF ? kWaves / 2 : 1][HALF ? 128 : 1];
+  long clock[2];
+};
+
+// Workgroup -> (tile, KV head).  Workgroups go to the 8 XCDs round-robin and every XCD has an L2 of its
+// own; tiles of one trajectory and KV head walk the same K/V stream and should share one L2.  With the
+// plain order (head fastest) that holds when the head count is a multiple of 8: XCD x then only ever sees
+// heads x, x + 8, ...  With 1, 2 or 4 KV heads a head's tiles would be dealt to 8, 4 or 2 XCDs and each of
+// them would fetch the whole stream; there the 8 / Hkv XCDs that serve a head take turns by runs of
+// kAppendXcdRun consecutive tiles of the list (the list keeps a trajectory's tiles together).
+__device__ __forceinline__ int tile_of(int block, int hkv, int& g) {
+  if (hkv < kXcds && kXcds % hkv == 0) {
+    const int x = block % kXcds, slot = block / kXcds;
+    const int parts = kXcds / hkv;
+    g = x % hkv;
+    return (slot / kAppendXcdRun) * (parts * kAppendXcdRun) + (x / hkv) * kAppendXcdRun + slot % kAppendXcdRun;
+  }
+  const int tile = block / hkv;
+  g = block - tile * hkv;
+  return tile;
+}
+
+// The kernel's arguments, from its argument segment; ANEW: not shared with what other code has read of them.
+typedef const __attribute__((address_space(4))) AppendArgs* const_args_p;
+template <bool ANEW>
+__device__ __forceinline__ decltype(auto) args_of(const AppendArgs& a) {
+  if constexpr (ANEW) {
+    const_args_p p = (const_args_p)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return (*p);
+  } else {
+    return (a);
+  }
+}
+
+template <bool FIRST, class A, class B>
+__device__ __forceinline__ decltype(auto) choose(A& a, B& b) {
+  if constexpr (FIRST) return (a); else return (b);
+}
+
+// kOneOfTwo: another instance in the same kernel, both in `shared`; what is worked out in one stays in it, behind the branch.
+template <int D, bool FP8, bool HALF, bool ONCE, int STEP, bool kOneOfTwo>
+__device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, AppendLds<D, FP8, HALF, STEP>* shared) {
+  auto& a = args_of<kOneOfTwo>(kernel_args);
+  typedef AppendGeo<D, FP8, HALF, STEP> Geo;
+  constexpr int kStepTokens = STEP;
   constexpr int kRowBytes = D * 2;                 // bf16 rows in LDS
   constexpr int kChunks = kRowBytes / 16;          // 16-byte chunks per LDS row
   constexpr int kTileBytes = kStepTokens * kRowBytes;
@@ -158,22 +228,22 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   constexpr int kDT = D / 32;                      // 32-wide output tiles along D
   static_assert((kStepTokens * kSrcChunks) % kThreads == 0 || kStepTokens * kSrcChunks < kThreads, "staging shape");
 
-  // bf16 pools go from HBM straight into LDS (no register stop): a ring of four tiles per pool gives
-  // every load a whole block period to land.  FP8 pools pass through registers to be widened: their
-  // LDS writes are immediate, two tiles are enough.
-  constexpr int kRing = FP8 ? 2 : 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char k_lds[kRing][kTileBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char v_lds[kRing][kTileBytes];
-  // HALF: where the trailing waves leave their result for the leading ones: per wave pair the accumulators
-  // [D / 32][4][64 lanes] as 16-byte quads, and reference and sum.  The accumulators of the four pairs go into the K ring,
-  // which nobody reads, loads into or widens into any more by then (bf16: every wave has waited for its last loads; FP8: the
-  // last tile is widened in a wave's last matrix phase but one; the last read of a K tile lies before the trailing waves'
-  // last barrier).
-  constexpr int kMergeAcc = (D / 32) * 16 * 64;      // floats per wave pair
-  static_assert(!HALF || (size_t)kRing * kTileBytes >= (size_t)(kWaves / 2) * kMergeAcc * sizeof(float), "K ring holds the accumulators");
-  __shared__ float merge_ml_s[HALF ? kWaves / 2 : 1][HALF ? 128 : 1];
+  constexpr int kRing = Geo::kRing;
+  constexpr int kMergeAcc = Geo::kMergeAcc;
+  constexpr bool kApart = Geo::kMergeApart && !kOneOfTwo;
+  __shared__ __attribute__((aligned(1024))) unsigned char k_own[kOneOfTwo ? 1 : kRing][kOneOfTwo ? 16 : kTileBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_own[kOneOfTwo ? 1 : kRing][kOneOfTwo ? 16 : kTileBytes];
+  __shared__ __attribute__((aligned(16))) float merge_acc_own[kApart ? kWaves / 2 : 1][kApart ? kMergeAcc : 4];
+  __shared__ float merge_ml_own[HALF && !kOneOfTwo ? kWaves / 2 : 1][HALF && !kOneOfTwo ? 128 : 1];
+  __shared__ long clock_own[2];
+  auto& k_lds = choose<kOneOfTwo>(shared->k, k_own);
+  auto& v_lds = choose<kOneOfTwo>(shared->v, v_own);
+  auto& merge_acc_s = choose<kOneOfTwo>(shared->merge_acc, merge_acc_own);
+  auto& merge_ml_s = choose<kOneOfTwo>(shared->merge_ml, merge_ml_own);
+  auto& clock_s = choose<kOneOfTwo>(shared->clock, clock_own);
 
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x, block = blockIdx.x;
+  if constexpr (kOneOfTwo) asm volatile("" : "+v"(tid), "+s"(block));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31;   // row (B column) / K token row (A row) carried by this lane
@@ -183,25 +253,8 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   const int hkv = a.hkv;
   const int tile_tokens = a.tile_tokens;
   const int n_tiles = a.header[kPlanTiles];
-  // Workgroup -> (tile, KV head).  Workgroups go to the 8 XCDs round-robin and every XCD has an L2 of its
-  // own; tiles of one trajectory and KV head walk the same K/V stream and should share one L2.  With the
-  // plain order (head fastest) that holds when the head count is a multiple of 8: XCD x then only ever sees
-  // heads x, x + 8, ...  With 1, 2 or 4 KV heads a head's tiles would be dealt to 8, 4 or 2 XCDs and each of
-  // them would fetch the whole stream; there the 8 / Hkv XCDs that serve a head take turns by runs of
-  // kAppendXcdRun consecutive tiles of the list (the list keeps a trajectory's tiles together).
-  auto tile_of = [](int block, int hkv, int& g) __attribute__((always_inline)) -> int {
-    if (hkv < kXcds && kXcds % hkv == 0) {
-      const int x = block % kXcds, slot = block / kXcds;
-      const int parts = kXcds / hkv;
-      g = x % hkv;
-      return (slot / kAppendXcdRun) * (parts * kAppendXcdRun) + (x / hkv) * kAppendXcdRun + slot % kAppendXcdRun;
-    }
-    const int tile = block / hkv;
-    g = block - tile * hkv;
-    return tile;
-  };
   int g;
-  const int tile = tile_of(blockIdx.x, hkv, g);
+  const int tile = tile_of(block, hkv, g);
   // The tile's record does not wait for the tile count (the index is clamped to the list's capacity): both loads
   // leave together, and everything else the workgroup needs to start hangs off the record alone.
   typedef const __attribute__((address_space(4))) int32_t* const_rec_p;
@@ -212,7 +265,6 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   const int b = rec[0], q0 = rec[1], n_b = rec[2], q_off = rec[4], blk0 = rec[5], n_blocks = kStepTokens == kBlockTokens ? rec[6] : (rec[6] + 1) / 2;   // (the latter in steps of the loop)
   const int ctx = rec[3] - blk0 * kBlockTokens;
   if (tile >= n_tiles) return;
-  __shared__ long clock_s[2];
   if (a.clock_sums && threadIdx.x == 0) {
     clock_s[0] = __builtin_amdgcn_s_memtime();
     clock_s[1] = __builtin_amdgcn_s_memrealtime();
@@ -570,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
           if ((i & 7) == 0) psum[pg] = p[sub][i];
           else psum[pg] += p[sub][i];
         }
-      if constexpr (kPg == 2) return psum[0] + psum[1];
+      if constexpr (kPg == 2) return FP8 ? psum[0] * ivs[0] + psum[1] * ivs[1] : psum[0] + psum[1];
       else if constexpr (FP8) return (psum[0] * ivs[0] + psum[1] * ivs[1]) + (psum[2] * ivs[2] + psum[3] * ivs[3]);
       else return (psum[0] + psum[1]) + (psum[2] + psum[3]);
     };
@@ -590,7 +642,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
         pm[q] = fmaxf(x, s[sub][o + 7]);
       }
       float mloc;
-      if constexpr (kPg == 2) mloc = fmaxf(pm[0], pm[1]) + m_old;
+      if constexpr (kPg == 2) mloc = FP8 ? fmaxf(pm[0] * sc[0], pm[1] * sc[1]) : fmaxf(pm[0], pm[1]) + m_old;
       else if constexpr (FP8) mloc = fmaxf(fmaxf(pm[0] * sc[0], pm[1] * sc[1]), fmaxf(pm[2] * sc[2], pm[3] * sc[3]));
       else mloc = fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) + m_old;
       const float m_new = fmaxf(m_run, xor32_max(mloc));           // the same in both lanes of a row
@@ -762,13 +814,18 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     if constexpr (FP8) {
       // scales of block i + 1: all loads in one statement, so that each keeps a register of its
       // own (the compiler would recycle one register and wait after every load)
-      static_assert(kPg == 4, "four pages of a step per wave");
-      asm volatile(
-          "s_load_dword %0, %8, %10\n\ts_load_dword %1, %8, %11\n\ts_load_dword %2, %8, %12\n\ts_load_dword %3, %8, %13\n\t"
-          "s_load_dword %4, %9, %10\n\ts_load_dword %5, %9, %11\n\ts_load_dword %6, %9, %12\n\ts_load_dword %7, %9, %13"
-          : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(kraw[2]), "=&s"(kraw[3]), "=&s"(vraw[0]), "=&s"(vraw[1]), "=&s"(vraw[2]), "=&s"(vraw[3])
-          : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u), "s"((unsigned)spid[2] * 4u),
-            "s"((unsigned)spid[3] * 4u));
+      if constexpr (kPg == 2)
+        asm volatile(
+            "s_load_dword %0, %4, %6\n\ts_load_dword %1, %4, %7\n\ts_load_dword %2, %5, %6\n\ts_load_dword %3, %5, %7"
+            : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(vraw[0]), "=&s"(vraw[1])
+            : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u));
+      else
+        asm volatile(
+            "s_load_dword %0, %8, %10\n\ts_load_dword %1, %8, %11\n\ts_load_dword %2, %8, %12\n\ts_load_dword %3, %8, %13\n\t"
+            "s_load_dword %4, %9, %10\n\ts_load_dword %5, %9, %11\n\ts_load_dword %6, %9, %12\n\ts_load_dword %7, %9, %13"
+            : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(kraw[2 % kPg]), "=&s"(kraw[3 % kPg]), "=&s"(vraw[0]), "=&s"(vraw[1]), "=&s"(vraw[2 % kPg]), "=&s"(vraw[3 % kPg])
+            : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u), "s"((unsigned)spid[2 % kPg] * 4u),
+              "s"((unsigned)spid[3 % kPg] * 4u));
       fetch_spids(i + 2);
     }
   };
@@ -776,8 +833,11 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) { pid_new[j] = __builtin_amdgcn_readfirstlane(pid_new[j]); asm volatile("" : "+s"(pid_new[j])); }   // arrived here, not wherever it is used next
     if constexpr (FP8) {
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(kraw[2]), "+s"(kraw[3]), "+s"(vraw[0]), "+s"(vraw[1]), "+s"(vraw[2]), "+s"(vraw[3]));
+      if constexpr (kPg == 2)
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(vraw[0]), "+s"(vraw[1]));
+      else
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(kraw[2 % kPg]), "+s"(kraw[3 % kPg]), "+s"(vraw[0]), "+s"(vraw[1]), "+s"(vraw[2 % kPg]), "+s"(vraw[3 % kPg]));
 #pragma unroll
       for (int p = 0; p < kPg; ++p) {
         spid[p] = __builtin_amdgcn_readfirstlane(spid[p]);
@@ -838,7 +898,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
     }
   };
   if (wave_active) run(std::true_type{}); else run(std::false_type{});
-  float* const mine = (float*)&k_lds[0][0] + (wave & 3) * kMergeAcc;   // HALF only
+  float* const mine = Geo::kMergeApart ? merge_acc_s[Geo::kMergeApart ? (wave & 3) : 0] : (float*)&k_lds[0][0] + (wave & 3) * kMergeAcc;   // HALF only
   float* const mine_ml = merge_ml_s[HALF ? (wave & 3) : 0];
   if constexpr (HALF) {
     // The trailing wave of a pair hands over its half of the tile: accumulators, reference and (per-lane) sum.
@@ -882,7 +942,6 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   // ---- normalise and store.  Where the rows go is worked out again here, from the thread and workgroup numbers, the
   // kernel's arguments and the tile's record, all read anew: what only the end of a tile needs occupies no register
   // during the loop (FP8, D = 128: 256 vector registers of 256 otherwise, and scalar ones that spill).
-  typedef const __attribute__((address_space(4))) AppendArgs* const_args_p;
   const_args_p args_e = (const_args_p)__builtin_amdgcn_kernarg_segment_ptr();
   int block_e = blockIdx.x, tid_e = threadIdx.x;
   asm volatile("" : "+s"(args_e), "+s"(block_e), "+v"(tid_e));
@@ -923,6 +982,23 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs 
   if (args_e->clock_sums && tid_e == 0) {
     atomicAdd(args_e->clock_sums, (unsigned long long)(__builtin_amdgcn_s_memtime() - clock_s[0]));
     atomicAdd(args_e->clock_sums + 1, (unsigned long long)(__builtin_amdgcn_s_memrealtime() - clock_s[1]));
+  }
+}
+
+template <int D, bool FP8, bool HALF, bool ONCE, int STEP>
+__global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs a) {
+  if constexpr (STEP == 0) {
+    __shared__ union {
+      AppendLds<D, FP8, HALF, kBlockTokens> one;
+      AppendLds<D, FP8, HALF, 2 * kBlockTokens> two;
+    } lds;
+    int g;
+    const int tile = tile_of(blockIdx.x, a.hkv, g);
+    const int blocks = ((const __attribute__((address_space(4))) int32_t*)(a.tile_rec + (size_t)min(tile, a.tile_cap - 1) * kTileRecWords))[6];
+    if (blocks < kLongTileBlocks) append_tile<D, FP8, HALF, ONCE, kBlockTokens, true>(a, &lds.one);
+    else append_tile<D, FP8, HALF, ONCE, 2 * kBlockTokens, true>(a, &lds.two);
+  } else {
+    append_tile<D, FP8, HALF, ONCE, STEP, false>(a, nullptr);
   }
 }
 
@@ -1022,15 +1098,18 @@ hipError_t launch_append_merge(const AppendArgs& a, int head_dim, int max_merges
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s) {
   if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
   const bool once = half_tiles && a.noncausal;
+  const bool short_tiles = a.max_pages < kLongTileBlocks * (kAppendBlockTokens / kPageSize);   // no context reaches a long tile
   auto launch = [&](auto d, auto f) {
     constexpr int D = decltype(d)::value;
     constexpr bool F = decltype(f)::value;
     if (once) {
-      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, true>), dim3(grid), dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, true, F ? 2 * kAppendBlockTokens : kAppendBlockTokens>), dim3(grid), dim3(kThreads), 0, s, a);
+    } else if (half_tiles && F && !short_tiles) {
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, false, F ? 0 : kAppendBlockTokens>), dim3(grid), dim3(kThreads), 0, s, a);
     } else if (half_tiles) {
-      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, true, false, kAppendBlockTokens>), dim3(grid), dim3(kThreads), 0, s, a);
     } else {
-      hipLaunchKernelGGL((append_mfma_kernel<D, F, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL((append_mfma_kernel<D, F, false, false, kAppendBlockTokens>), dim3(grid), dim3(kThreads), 0, s, a);
     }
   };
   std::integral_constant<int, 128> d128;

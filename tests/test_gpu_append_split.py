@@ -105,3 +105,17 @@ def test_a_mixed_step_with_cut_chunks_and_split_rows():
     assert ws[B.lib().rollattn_step_append_offset(ctypes.byref(desc)):].view(torch.int32)[5].item() > 0
     check(out, oracle_append(b), "bf16", "both")
     assert all(torch.equal(out, B.attn_step(*args, **kw)) for _ in range(3))
+
+
+# half tiles over FP8 pools: steps of one block and of two, chosen by each tile's blocks; below 20 blocks of 64 tokens and from there on
+@pytest.mark.parametrize("hq,hkv,d", [(64, 4, 128), (4, 2, 64)])
+@pytest.mark.parametrize("ctx", [(1, 70), (1000, 1208), (1209, 1290)])
+def test_steps_of_one_block_and_of_two(hq, hkv, d, ctx):
+    b = W.build(W.Workload("steps", 140, hq, hkv, d, "bf16", "fp8_e4m3", ("uniform", *ctx), qlen=("uniform", 1, 8), ctx_is_prefix=True,
+                           seed=W.BASE_SEED + 96), DEV)
+    out = gpu_append(b)
+    check(out, oracle_append(b), "bf16", "steps")
+    wide = torch.full((b.page_table.shape[0], 200), -1, dtype=torch.int32, device=DEV)
+    wide[:, :b.page_table.shape[1]] = b.page_table
+    b.page_table = wide
+    assert torch.equal(out, gpu_append(b))               # a wider table, the same tiles
