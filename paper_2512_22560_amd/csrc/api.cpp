@@ -299,7 +299,7 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   a.partial_o = (float*)(base + w.partial_o);
   a.batch = desc->batch; a.hq = desc->num_q_heads; a.hkv = desc->num_kv_heads;
   a.group = desc->num_q_heads / desc->num_kv_heads; a.max_pages = desc->max_pages_per_seq;
-  a.head_tile = w.head_tile; a.rows_per_b = w.rows_per_b; a.num_pages = desc->num_pages;
+  a.head_tile = w.head_tile; a.rows_per_b = w.rows_per_b;
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
   a.q_lens = q_lens;
@@ -308,6 +308,8 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   d.ctx_lens = ctx_lens; d.q_lens = q_lens; d.batch = desc->batch; d.rows_per_b = w.rows_per_b;
   // (the launch has w.workers workers whatever the partition is cut for: the others get a record without blocks)
   d.workers = plan_workers(w); d.slots = w.workers;
+  if (desc->q_dtype != ROLLATTN_F32) d.page_table = page_table;
+  d.max_pages = desc->max_pages_per_seq; d.num_pages = desc->num_pages; d.head_tiles = w.rows_per_b > desc->num_kv_heads;
   d.header = (int32_t*)(base + w.header); d.prefix = (int32_t*)(base + w.prefix); d.wstart = (int32_t*)(base + w.wstart);
   return ROLLATTN_OK;
 }

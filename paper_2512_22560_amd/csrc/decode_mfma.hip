@@ -86,9 +86,9 @@ struct Cursor {
   int n, len;      // blocks in the row, context length of the trajectory
 };
 
-// 16 bytes of a K or V row.  Every byte of the cache is read once per call, by one wave: with the streaming hint it does
-// not displace what is read again (page scales, 32 pages' to a cache line, page table, partials) and the last-level cache
-// does not spend its bandwidth on keeping it.  Worth 8 to 11 % of a launch: 64 contexts of 512 .. 8k (32/8/128, bf16)
+// 16 bytes of a K or V row.  Where every byte of a run is read once per call, by one wave (see all_read_again), the streaming
+// hint keeps it from displacing what is read again (page scales, 32 pages' to a cache line, page table, partials) and the
+// last-level cache from spending its bandwidth on it.  Worth 8 to 11 % of a launch: 64 contexts of 512 .. 8k (32/8/128, bf16)
 // 154.0 -> 138.1 us with the merge, 256 long-tailed ones (64/8/128) 1440 -> 1323 us, 384 over FP8 pools (64/4/128)
 // 798 -> 713 us (6.3 TB/s, what a streaming read reaches).
 template <bool STREAM>
@@ -387,28 +387,19 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * Geo<D, FP8>::kTileBytes];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int worker = blockIdx.x * kWaves + wave;
-  // (b, r << 20 | block, L_b, run length), and the blocks of all rows
-  int total = 0;
   int4 start;
+  bool read_again = false;
   if (a.plan.batch) {
-    start = plan_decode_in_wave(a.plan, worker, &total);
+    start = plan_decode_in_wave(a.plan, worker, &read_again);
   } else {
     start = *(const int4*)(a.wstart + 4 * worker);
-    total = a.header[kPlanTotal];
+    read_again = a.header[kPlanReadAgain] != 0;
   }
   if (start.x < 0) return;
-  // Grouped rollouts decoded without attn_decode_shared: the next reader of a page may find it in a cache, and the hint
-  // would cost 13 % (64 groups of 8 behind 8192 common tokens: 687 against 777 us).  Told by a neighbour that starts on the
-  // same page, or by contexts with more pages between them than the pool has (a block is two pages, the last of a row one
-  // or two).  The private half of attn_decode_shared has no page in common with others.
-  bool shared_pages = (long)(total / a.rows_per_b) * 2 - a.batch > a.num_pages;
-  if (!a.first_page) {
-    const int b = __builtin_amdgcn_readfirstlane(start.x);
-    const int32_t* row = a.page_table + (size_t)b * a.max_pages;
-    const int own = row[0], before = b > 0 ? row[-(long)a.max_pages] : -1, after = b + 1 < a.batch ? row[a.max_pages] : -1;
-    shared_pages = shared_pages || own == before || own == after;
-  }
-  if (shared_pages) decode_worker<D, FP8, false>(a, start, worker, lds[wave]);
+  // Where another worker reads some of the run's pages, too, it may find them in a cache, and the hint would cost that:
+  // 64 groups of 8 behind 8192 common tokens, decoded without attn_decode_shared (64/4/128, FP8), 687 against 777 us; 32
+  // query heads per KV head, two rows that read the same K and V (256 contexts, 32/1/128, bf16), 153 against 170 us.
+  if (read_again) decode_worker<D, FP8, false>(a, start, worker, lds[wave]);
   else decode_worker<D, FP8, true>(a, start, worker, lds[wave]);
 }
 

@@ -23,13 +23,71 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) {
 }
 
 // With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
+__device__ __forceinline__ int decode_len(const DecodePlanArgs& a, int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; }
 __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds) {
-  plan_decode(a, lds, [&](int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; });
+  plan_decode(a, lds, [&](int b) { return decode_len(a, b); });
 }
 
+// Whether the pages of this call are read by several workers.  Trajectories that share a prefix of their contexts have its
+// pages in common (grouped rollouts, a system prompt in front of all of them), wherever they stand in the batch.  Told by the
+// second page (a single shared page is not worth it): equal ids meet in a hash table in LDS.  The call's pages count as read
+// again where the trajectories that have met have an eighth of all blocks.  A workgroup of its own beside the plan's: both
+// wait for the lengths, and this one then for the tables (in one workgroup the plan of 200 trajectories took 2 us longer).
+struct ReadAgainLds {
+  int key[2 * kLdsPrefix], blocks[2 * kLdsPrefix];   // twice as many slots as trajectories, or more
+  unsigned int twice[2 * kLdsPrefix / 32];
+  int sum[2];
+};
+__device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAgainLds& lds) {
+  const int tid = threadIdx.x;
+  if (a.head_tiles || a.batch > kLdsPrefix) {
+    if (tid == 0) a.header[kPlanReadAgain] = 1;
+    return;
+  }
+  const int mask = (1 << (32 - __builtin_clz(2 * max(a.batch, 16) - 1))) - 1;
+  for (int i = tid; i <= mask; i += kPlanThreads) {
+    lds.key[i] = -1;
+    lds.blocks[i] = 0;
+  }
+  for (int i = tid; i <= mask / 32; i += kPlanThreads) lds.twice[i] = 0;
+  if (tid < 2) lds.sum[tid] = 0;
+  __syncthreads();
+  int all = 0, met = 0;
+  for (int b = tid; b < a.batch; b += kPlanThreads) {
+    const int len = decode_len(a, b), blocks = (len + kBlockTokens - 1) / kBlockTokens;
+    all += blocks;
+    const int page = len > kPageSize ? a.page_table[(size_t)b * a.max_pages + 1] : -1;
+    if (page < 0) continue;
+    int h = (int)(((unsigned int)page * 0x9e3779b1u) >> 15) & mask;
+    for (;; h = (h + 1) & mask) {                      // (a free slot is always found)
+      const int before = atomicCAS(&lds.key[h], -1, page);
+      if (before == page) atomicOr(&lds.twice[h / 32], 1u << (h % 32));
+      if (before == -1 || before == page) break;
+    }
+    atomicAdd(&lds.blocks[h], blocks);
+  }
+  __syncthreads();
+  for (int i = tid; i <= mask; i += kPlanThreads) met += (lds.twice[i / 32] >> (i % 32) & 1) ? lds.blocks[i] : 0;
+  all = wave_sum(all);
+  met = wave_sum(met);
+  if ((tid & 63) == 0) {
+    atomicAdd(&lds.sum[0], all);
+    atomicAdd(&lds.sum[1], met);
+  }
+  __syncthreads();
+  if (tid == 0) a.header[kPlanReadAgain] = all_read_again(a, lds.sum[0]) || (long)lds.sum[1] * 8 >= max(lds.sum[0], 1);
+}
+
+union DecodeLds {
+  DecodePlanLds plan;
+  ReadAgainLds pages;
+};
+
+// The second workgroup, where there is one, looks at the pages.
 __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodePlanArgs a) {
-  __shared__ DecodePlanLds lds;
-  plan_decode(a, lds);
+  __shared__ DecodeLds lds;
+  if (blockIdx.x == 0) plan_decode(a, lds.plan);
+  else plan_read_again(a, lds.pages);
 }
 
 // Append work list: each chunk cut into tiles of tile_tokens query tokens.  A tile's cost grows
@@ -268,18 +326,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_append_kernel(const AppendP
   plan_append(a, lds, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
 }
 
-// Two plans side by side, a workgroup each.
+// Plans side by side, a workgroup each.
 union PlanLds {
   AppendPlanLds append;
-  DecodePlanLds decode;
+  DecodeLds decode;
   __device__ PlanLds() {}
 };
 
-// Both plans of a mixed step.
+// Both plans of a mixed step, and its decode rows' pages.
 __global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPlanArgs a, const DecodePlanArgs d) {
   __shared__ PlanLds lds;
   if (blockIdx.x == 0) plan_append(a, lds.append, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
-  else plan_decode(d, lds.decode);
+  else if (blockIdx.x == 1) plan_decode(d, lds.decode.plan);
+  else plan_read_again(d, lds.decode.pages);
 }
 
 // Decode of groups that share a prompt: per group the shared length actually used, S = floor32(min(shared_lens[group],
@@ -322,19 +381,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
     };
     plan_append(a, lds.append, Groups{used, sh.group_size});
   } else {
+    // The private parts have no page in common with others, but for what a short member leaves of the prompt to the others'.
+    bool again = false;
     for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) {
       const int s = used(b / sh.group_size);
       sh.own_ctx[b] = sh.ctx_lens[b] - s;
       sh.own_page[b] = s / kPageSize;
+      again = again || sh.shared_lens[b / sh.group_size] - s >= 2 * kBlockTokens;
     }
-    plan_decode(d, lds.decode, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
+    again = __syncthreads_or(again);
+    plan_decode(d, lds.decode.plan, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
+    if (threadIdx.x == 0) d.header[kPlanReadAgain] = again || d.head_tiles;
   }
 }
 
 }  // namespace
 
 hipError_t launch_plan_decode(const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_decode_kernel, dim3(1), dim3(kPlanThreads), 0, s, d);
+  hipLaunchKernelGGL(plan_decode_kernel, dim3(d.page_table ? 2 : 1), dim3(kPlanThreads), 0, s, d);
   return hipGetLastError();
 }
 
@@ -344,7 +408,7 @@ hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_step_kernel, dim3(2), dim3(kPlanThreads), 0, s, a, d);
+  hipLaunchKernelGGL(plan_step_kernel, dim3(3), dim3(kPlanThreads), 0, s, a, d);
   return hipGetLastError();
 }
 

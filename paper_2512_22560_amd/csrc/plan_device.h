@@ -41,6 +41,13 @@ __device__ int block_exclusive_scan(int v, int4* wave_tot /*[kPlanThreads / 256]
   return base + incl - v;
 }
 
+// Which K and V rows are worth a place in the caches: those that another worker reads, too.  All of them where there are several
+// rows per KV head, or where the contexts have more pages between them than the pool (a block is two pages, the last of a
+// row one or two).
+__device__ __forceinline__ bool all_read_again(const DecodePlanArgs& a, int blocks) {
+  return a.head_tiles || (long)blocks * 2 - a.batch > a.num_pages;
+}
+
 // Decode partition.  Every trajectory is cut into blocks of kBlockTokens tokens; the rows
 // (trajectory b, row r in [0, rows_per_b)) are laid end to end, b outermost, each with
 // n_b = ceil(L_b / kBlockTokens) blocks; the resulting sequence of T blocks is dealt to the W
@@ -117,14 +124,16 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
 // The same rule for a batch of at most 64 trajectories, worked out by every wave of a decode launch for itself: a lane per
 // trajectory, the search for the worker's start one ballot.  Writes what the plan kernel would have written (the first
 // worker the header and the scan, each worker its record), because the merge and rollattn_debug_read_plan read it.
-// Returns the record (b, r << 20 | block, L_b, blocks in the run), the same in all lanes, and the blocks of all rows.
-__device__ __forceinline__ int4 plan_decode_in_wave(const DecodePlanArgs& a, int worker, int* blocks_of_all) {
+// Returns the record (b, r << 20 | block, L_b, blocks in the run), the same in all lanes, and whether the run's pages may be read
+// by another worker, too: told by a second page that another trajectory has as well (see plan_read_again).
+__device__ __forceinline__ int4 plan_decode_in_wave(const DecodePlanArgs& a, int worker, bool* read_again) {
   const int lane = threadIdx.x & 63;
   const int len = lane < a.batch ? a.ctx_lens[lane] : 0;
+  const int page = len > kPageSize ? a.page_table[(size_t)lane * a.max_pages + 1] : -1;
   const int count = (len + kBlockTokens - 1) / kBlockTokens;
   const int upto = wave_inclusive_scan(count), first = upto - count;
   const int blocks = __builtin_amdgcn_readlane(upto, 63);
-  const int total = *blocks_of_all = blocks * a.rows_per_b;
+  const int total = blocks * a.rows_per_b;
   const int per = max(1, (total + a.workers - 1) / a.workers);
   const unsigned int x = (unsigned int)worker * (unsigned int)per;
   if (worker == 0) {
@@ -144,7 +153,17 @@ __device__ __forceinline__ int4 plan_decode_in_wave(const DecodePlanArgs& a, int
     const int b = 63 - __builtin_clzll(before);
     const int n = __builtin_amdgcn_readlane(count, b);
     const int rem = (int)x - a.rows_per_b * __builtin_amdgcn_readlane(first, b);
-    st = make_int4(b, ((rem / n) << 20) | (rem % n), __builtin_amdgcn_readlane(len, b), min(per, total - (int)x));
+    const int mine = min(per, total - (int)x);
+    bool again = all_read_again(a, blocks);
+    // the trajectories of the run
+    const unsigned long long started = __builtin_amdgcn_ballot_w64(lane < a.batch && (unsigned int)(a.rows_per_b * first) < x + (unsigned int)mine);
+    for (int i = b; i < 64 - __builtin_clzll(started) && !again; ++i) {
+      const int p = __builtin_amdgcn_readlane(page, i);
+      again = p >= 0 && __builtin_popcountll(__builtin_amdgcn_ballot_w64(page == p)) > 1;
+    }
+    st = make_int4(b, ((rem / n) << 20) | (rem % n), __builtin_amdgcn_readlane(len, b), mine);
+    *read_again = again;
+    if (worker == 0 && lane == 0) a.header[kPlanReadAgain] = again;   // (of the first run, for who reads the plan)
   }
   if (lane == 0) *(int4*)(a.wstart + 4 * worker) = st;
   return st;

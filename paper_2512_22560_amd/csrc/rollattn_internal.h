@@ -35,7 +35,9 @@ constexpr int split_extra_pieces(int hkv) { return 2 * kNumCUs / hkv; }   // app
 constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list that one XCD takes in a row (one per CU)
 
 // Header words of the plan, at the start of the workspace.
-enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5, kPlanWords = 64 };
+enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5,
+                kPlanReadAgain = 32,   // (written by another workgroup than the rest, in a cache line of its own)
+                kPlanWords = 64 };
 
 // Byte offsets of the workspace regions (all multiples of 256).
 struct WorkspaceLayout {
@@ -64,6 +66,11 @@ struct DecodePlanArgs {
   const int32_t* q_lens;           // mixed step, else null
   int32_t batch, rows_per_b;
   int32_t workers, slots;          // how many the partition is cut for; records written (those past `workers` say "no blocks")
+  // What tells whether pages are read by several workers (kPlanReadAgain); page_table null: nobody asks.
+  const int32_t* page_table;
+  int64_t num_pages;
+  int32_t max_pages;
+  bool head_tiles;                 // several rows per KV head: each reads its K and V
   int32_t* header;
   int32_t* prefix;
   int32_t* wstart;
@@ -84,7 +91,6 @@ struct DecodeArgs {
   const int32_t* wstart;
   float* partial_ml;
   float* partial_o;
-  int64_t num_pages;
   int32_t batch, hq, hkv, group, max_pages, head_tile, rows_per_b;
   float scale_log2;     // sm_scale * log2(e)
   float* lse;           // optional [B][Hq]: log2 of each row's softmax denominator (reference included)

@@ -82,18 +82,60 @@ def test_small_batches_are_planned_by_the_decode_waves(batch, lens):
     assert (per, total) == (o_per, o_total) and np.array_equal(starts, o_starts)
 
 
+# Word 32 of the plan says whether pages are read by several workers (plain loads).  Up to 64 trajectories every wave decides for
+# its own run (the word is the first one's), for more the plan launch does (8200: more than it looks through).
+# Members of a group need not be neighbours; an empty trajectory's table is not looked at; one shared page is not worth plain loads.
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
-def test_pages_read_with_and_without_the_streaming_hint(kvd):
-    # four trajectories share pages: with the 100 pages they live on the pool has fewer than their contexts, with 100 more it has not
-    b = W.build(W.Workload("hint", 4, 8, 2, 128, "bf16", kvd, ("const", 768), seed=W.BASE_SEED + 101), DEV)
-    live = [t[:100].clone() for t in (b.k_pages, b.v_pages)]
-    scales = [None if t is None else t[:100].clone() for t in (b.k_scale, b.v_scale)]
-    table = (b.page_table % 100).contiguous()
-    run = lambda k, v, ks, vs: B.attn_decode(b.q, k, v, table, b.ctx_lens, sm_scale=b.workload.sm_scale, k_scale=ks, v_scale=vs)
-    more = lambda t: None if t is None else torch.cat([t, t])
-    out = run(*live, *scales)
-    table[1:, 0] = table[0, 0]                     # neighbours that start on the same page: not with the hint either
-    same = run(*live, *scales)
-    assert torch.isfinite(same).all() and torch.equal(same, run(*map(more, (*live, *scales))))
-    table[1:, 0] = b.page_table[1:, 0] % 100
-    assert torch.isfinite(out).all() and torch.equal(out, run(*map(more, (*live, *scales))))
+@pytest.mark.parametrize("groups,each", [(3, 8), (12, 8), (2050, 4)])
+def test_pages_read_with_and_without_the_streaming_hint(groups, each, kvd):
+    batch, pages = groups * each, 3 if groups > 100 else 20
+    lens = np.random.default_rng(groups).integers(17, 16 * pages + 1, batch)
+    lens[5::7] = 0
+    b = W.build(W.Workload("hint", batch, 8, 2, 128, "bf16", kvd, ("const", 1), seed=W.BASE_SEED + 101), DEV)
+    own = np.arange(batch * pages, dtype=np.int32).reshape(batch, pages)
+    own = np.random.default_rng(1).permutation(own.size).astype(np.int32)[own]
+    grouped = own.copy()
+    leader = np.arange(batch) % groups                    # member m of group g stands at m * groups + g
+    grouped[:, :2] = own[leader, :2]
+    first = own.copy()
+    first[:, 0] = own[0, 0]
+    stale = own.copy()
+    stale[lens == 0] = own[(np.flatnonzero(lens == 0) + 1) % batch]
+    gen = torch.Generator(device=DEV).manual_seed(102)
+    k, v = (torch.randn((own.size, 2, 16, 128), generator=gen, device=DEV) for _ in range(2))
+    ks = vs = None
+    if kvd != "bf16":
+        ks, vs = (x.abs().amax(dim=(1, 2, 3)) / 448.0 for x in (k, v))
+        k, v = ((x / s.view(-1, 1, 1, 1)).to(torch.float8_e4m3fn).view(torch.uint8) for x, s in ((k, ks), (v, vs)))
+    else:
+        k, v = k.bfloat16(), v.bfloat16()
+    cl = torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    members = np.bincount(leader[lens > 16], minlength=groups)
+    for table, expect in ((own, lens < 0), (grouped, (lens > 16) & (members[leader] > 1)), (first, lens < 0), (stale, lens < 0)):
+        pt = torch.from_numpy(table).to(DEV)
+        desc = B.make_desc(b.q, k, pt, sm_scale=b.workload.sm_scale, k_scale=ks, v_scale=vs)
+        ws = B.alloc_workspace(desc, batch, DEV)
+        out = B.attn_decode(b.q, k, v, pt, cl, sm_scale=b.workload.sm_scale, k_scale=ks, v_scale=vs, workspace=ws)
+        check(out, O.attn_decode(W.raw_numpy(b.q), k_pages=W.raw_numpy(k), v_pages=W.raw_numpy(v), page_table=table, ctx_lens=lens, sm_scale=b.workload.sm_scale,
+                                 q_dtype="bf16", kv_dtype=kvd, k_scale=W.raw_numpy(ks), v_scale=W.raw_numpy(vs)), "bf16", "hint")
+        per, total, starts = B.read_plan(desc, ws)
+        blocks = -(-lens // 32)
+        if batch > 64:                                   # an eighth of all blocks
+            again = batch > 8192 or 8 * blocks[expect].sum() >= blocks.sum()
+        else:
+            again = expect[:int(np.searchsorted(np.cumsum(2 * blocks), starts[0, 3])) + 1].any()
+        assert ws.view(torch.int32)[32].item() == again
+
+
+def test_rows_of_one_kv_head_read_its_pages_again():
+    # 20 query heads per KV head are two rows; a pool smaller than the contexts must be shared whatever the second pages say
+    for batch, hq, pool, again in ((4, 20, 200, True), (4, 10, 200, False), (4, 10, 100, True), (70, 20, 4000, True), (70, 10, 4000, False), (70, 10, 1700, True)):
+        b = W.build(W.Workload("tiles", batch, hq, 1, 128, "bf16", "bf16", ("const", 768), seed=W.BASE_SEED + 103), DEV)
+        table = torch.from_numpy((np.arange(batch * 48).reshape(batch, 48) % pool).astype(np.int32)).to(DEV)
+        k, v = (torch.randn((pool, 1, 16, 128), device=DEV, dtype=torch.bfloat16) for _ in range(2))
+        desc = B.make_desc(b.q, k, table, sm_scale=b.workload.sm_scale)
+        ws = B.alloc_workspace(desc, batch, DEV)
+        out = B.attn_decode(b.q, k, v, table, b.ctx_lens, sm_scale=b.workload.sm_scale, workspace=ws)
+        args = dict(oracle_args(b), k_pages=W.raw_numpy(k), v_pages=W.raw_numpy(v), page_table=W.raw_numpy(table))
+        check(out, O.attn_decode(W.raw_numpy(b.q), **args), "bf16", "tiles")
+        assert ws.view(torch.int32)[32].item() == again
