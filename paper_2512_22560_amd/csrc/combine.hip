@@ -10,10 +10,11 @@
 //
 // A row here is a decode row, (trajectory, KV head, tile of query heads): its heads lie side by side in every partial.
 // They are folded in chunks of 256 floats (four per lane, two heads at D = 128).  Bound by the latency of the partials'
-// loads, so up to eight pieces are under way at a time; a row of up to sixteen is one wave's work per chunk, and the four
-// waves of the workgroup take different chunks.  A row of more pieces (few trajectories, cut for all workers) has its pieces
-// dealt to the four waves, whose sums meet in LDS.  Which of the two a row takes depends on its pieces alone, so its
-// result does not depend on what else is in the batch.  Against one wave per (trajectory, head) and one piece at a time:
+// loads, so up to eight pieces are under way at a time; a row of up to sixteen is one wave's work per chunk.  A row of more
+// pieces (few trajectories, cut for all workers) has its pieces dealt to four sums that are folded in their order: four
+// waves make them where a workgroup has one chunk, which it has while those are few enough to be resident at once; with
+// more chunks each wave has one of its own and makes the four in turn.  So a row's result depends on its pieces alone, not on
+// what else is in the batch.  Against one wave per (trajectory, head) and one piece at a time:
 // 13.4 -> 5.2 us for 40 rows of about 50 pieces (5 trajectories, 8 KV heads), 15.5 -> 10.6 us for 1536 rows of two or
 // three (FP8, 384 trajectories, 64/4/128), 6.2 -> 5.5 us for 512 rows of about five.
 #include <algorithm>
@@ -37,23 +38,25 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ floatx4 widen(const bf16x4 x) { return floatx4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]}; }
 
-// One workgroup per (row, run of chunks_per_wg chunks of it).
+// TOGETHER: a workgroup per chunk, whose waves share the pieces of a row of many; else a chunk per wave.
 // SHARED (attn_decode_shared): another result over the first part of every context is folded in as one more piece, with
 // the weight 2^d of its denominator, and every row is written: one that a single worker finished is read back as a piece.
 // The merge of the two halves as a launch of its own cost 8 us of a 268 us step and rounded split rows to bf16 in between.
-template <int D, bool OUT_BF16, bool SHARED>
-__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, const SharedHalf other, int wgs_per_row, int chunks_per_wg) {
-  __shared__ __attribute__((aligned(16))) float sum_s[kWaves][64][4];
-  __shared__ float ml_s[kWaves][64][2];
+template <int D, bool OUT_BF16, bool SHARED, bool TOGETHER>
+__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, const SharedHalf other, int chunks_per_row) {
+  __shared__ __attribute__((aligned(16))) float sum_s[TOGETHER ? kWaves : 1][64][4];
+  __shared__ float ml_s[TOGETHER ? kWaves : 1][64][2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = blockIdx.x / wgs_per_row, part = blockIdx.x - row * wgs_per_row;
+  const int unit = TOGETHER ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + wave);
+  const int row = unit / chunks_per_row, c = unit - row * chunks_per_row;
   const int b = row / a.rows_per_b, r = row - b * a.rows_per_b;
+  if (b >= a.batch) return;
   if (a.q_lens && a.q_lens[b] != 1) return;                 // mixed step: not a decode row, nothing of ours to write
   const int ht = a.head_tile;
   const int n_ht = a.rows_per_b / a.hkv;
   const int g = r / n_ht, h0 = (r - g * n_ht) * ht;
   const int heads = min(ht, a.group - h0);
-  const int chunks = (heads * D + kChunkFloats - 1) / kChunkFloats;
+  if (c * kChunkFloats >= heads * D) return;                // (a row's last tile of heads may have fewer chunks)
   const int per = a.header[kPlanPer];
   const int first = a.prefix[b];
   const int n = a.prefix[b + 1] - first;
@@ -64,111 +67,127 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, c
   const int pieces = n ? wl - wf + 1 : 0;
   const int first_slot = ((long)wf * per < r0) ? 1 : 0;
   const size_t orow0 = (size_t)(a.q_offsets ? a.q_offsets[b] : b) * a.hq + (size_t)g * a.group + h0;   // where the row's first head goes
-  const bool shared_work = pieces > kAlone;                 // the four waves share each chunk's pieces
-  const int end = min(chunks, (part + 1) * chunks_per_wg);
-  for (int c = part * chunks_per_wg + (shared_work ? 0 : wave); c < end; c += shared_work ? 1 : kWaves) {
-    const int at = c * kChunkFloats + lane * 4;             // first of this lane's floats within a partial
-    const int head = at / D;
-    const bool ok = head < heads;                           // (the last chunk of an odd number of heads is not full)
-    const float* po = a.partial_o + (ok ? at : 0);
-    const float* pml = a.partial_ml + (ok ? head : 0) * 2;
-    floatx4 o = {0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;
-    const int step = shared_work ? kWaves : 1;
-    // folds pieces s0, s0 + step, ... of one batch; past the last piece the last one is loaded again, with weight zero
-    auto fold = [&](int s0, auto batch_c) __attribute__((always_inline)) {
-      constexpr int kN = decltype(batch_c)::value;
-      floatx4 y[kN];
-      floatx2 x[kN];
+  const bool dealt = pieces > kAlone;                       // to four sums
+  if (TOGETHER && !dealt && wave != 0) return;
+  const int at = c * kChunkFloats + lane * 4;               // first of this lane's floats within a partial
+  const int head = at / D;
+  const bool ok = head < heads;                             // (the last chunk of an odd number of heads is not full)
+  const float* po = a.partial_o + (ok ? at : 0);
+  const float* pml = a.partial_ml + (ok ? head : 0) * 2;
+  floatx4 o = {0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const int step = dealt ? kWaves : 1;
+  // folds pieces s0, s0 + step, ... of one batch; past the last piece the last one is loaded again, with weight zero
+  auto fold = [&](int s0, auto batch_c) __attribute__((always_inline)) {
+    constexpr int kN = decltype(batch_c)::value;
+    floatx4 y[kN];
+    floatx2 x[kN];
 #pragma unroll
-      for (int i = 0; i < kN; ++i) {
-        const int s = min(s0 + i * step, pieces - 1);
-        const size_t slot = ((size_t)(wf + s) * 2 + (s == 0 ? first_slot : 0)) * ht;
-        x[i] = *(const floatx2*)(pml + slot * 2);
-        y[i] = *(const floatx4*)(po + slot * D);
-      }
-      float top = m;
+    for (int i = 0; i < kN; ++i) {
+      const int s = min(s0 + i * step, pieces - 1);
+      const size_t slot = ((size_t)(wf + s) * 2 + (s == 0 ? first_slot : 0)) * ht;
+      x[i] = *(const floatx2*)(pml + slot * 2);
+      y[i] = *(const floatx4*)(po + slot * D);
+    }
+    float top = m;
 #pragma unroll
-      for (int i = 0; i < kN; ++i) {
-        if (s0 + i * step >= pieces) {                      // (zero times an infinity would not be zero)
-          x[i] = floatx2{-INFINITY, 0.f};
-          y[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-        top = fmaxf(top, x[i][0]);
+    for (int i = 0; i < kN; ++i) {
+      if (s0 + i * step >= pieces) {                      // (zero times an infinity would not be zero)
+        x[i] = floatx2{-INFINITY, 0.f};
+        y[i] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
-      const float keep = __builtin_amdgcn_exp2f(m - top);   // (a partial has seen at least one token: its maximum is finite)
-      m = top;
-      l *= keep;
-      o *= keep;
+      top = fmaxf(top, x[i][0]);
+    }
+    const float keep = __builtin_amdgcn_exp2f(m - top);   // (a partial has seen at least one token: its maximum is finite)
+    m = top;
+    l *= keep;
+    o *= keep;
 #pragma unroll
-      for (int i = 0; i < kN; ++i) {
-        const float f = __builtin_amdgcn_exp2f(x[i][0] - top);
-        l += f * x[i][1];
-        o += f * y[i];
-      }
-    };
-    const size_t dst = orow0 * D + at;
-    floatx4 o1 = {0.f, 0.f, 0.f, 0.f};
-    float d1 = -INFINITY;
-    if constexpr (SHARED) {
-      if (ok) {
-        o1 = widen(*(const bf16x4*)((const __bf16*)other.out + dst));
-        d1 = other.lse[orow0 + head];
-        if (pieces == 1) {
-          o = widen(*(const bf16x4*)((const __bf16*)a.out + dst));
-          m = a.lse[orow0 + head];
-          l = 1.f;
-        }
+    for (int i = 0; i < kN; ++i) {
+      const float f = __builtin_amdgcn_exp2f(x[i][0] - top);
+      l += f * x[i][1];
+      o += f * y[i];
+    }
+  };
+  const size_t dst = orow0 * D + at;
+  floatx4 o1 = {0.f, 0.f, 0.f, 0.f};
+  float d1 = -INFINITY;
+  if constexpr (SHARED) {
+    if (ok) {
+      o1 = widen(*(const bf16x4*)((const __bf16*)other.out + dst));
+      d1 = other.lse[orow0 + head];
+      if (pieces == 1) {
+        o = widen(*(const bf16x4*)((const __bf16*)a.out + dst));
+        m = a.lse[orow0 + head];
+        l = 1.f;
       }
     }
-    if (pieces < 2) {}                                      // nothing to fold (none: a zero row)
-    else if (pieces == 2) fold(0, std::integral_constant<int, 2>{});
-    else if (pieces == 3) fold(0, std::integral_constant<int, 3>{});
-    else if (pieces <= 5) fold(0, std::integral_constant<int, 5>{});
-    else for (int s0 = shared_work ? wave : 0; s0 < pieces; s0 += kBatch * step) fold(s0, std::integral_constant<int, kBatch>{});
-    if (shared_work) {
-      *(floatx4*)sum_s[wave][lane] = o;
-      ml_s[wave][lane][0] = m;
-      ml_s[wave][lane][1] = l;
-      __syncthreads();
-      if (wave == 0) {
+  }
+  // weights the four sums (x(w): maximum and sum of weights, y(w): weighted values) and adds them
+  auto join = [&](auto&& x, auto&& y) __attribute__((always_inline)) {
+    m = x(0)[0];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) m = fmaxf(m, ml_s[w][lane][0]);
-        float f = __builtin_amdgcn_exp2f(ml_s[0][lane][0] - m);
-        l *= f;
-        o *= f;
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, x(w)[0]);
+    float f = __builtin_amdgcn_exp2f(x(0)[0] - m);
+    l = x(0)[1] * f;
+    o = y(0) * f;
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) {
-          f = __builtin_amdgcn_exp2f(ml_s[w][lane][0] - m);
-          l += f * ml_s[w][lane][1];
-          o += f * *(const floatx4*)sum_s[w][lane];
-        }
-      }
-      __syncthreads();                                      // the next chunk reuses the LDS
-      if (wave != 0) continue;
+    for (int w = 1; w < kWaves; ++w) {
+      f = __builtin_amdgcn_exp2f(x(w)[0] - m);
+      l += f * x(w)[1];
+      o += f * y(w);
     }
-    if (!ok) continue;
-    if constexpr (SHARED) {
-      const float top = fmaxf(m, d1), base = (top == -INFINITY) ? 0.f : top;
-      const float w1 = __builtin_amdgcn_exp2f(d1 - base), w2 = __builtin_amdgcn_exp2f(m - base);   // 2^-inf = 0
-      const float tot = w1 + w2 * l, inv = tot > 0.f ? 1.f / tot : tot;
-      o = (w1 * o1 + w2 * o) * inv;
-      bf16x4 pk;
+  };
+  constexpr std::integral_constant<int, kBatch> batch_c{};
+  if (pieces < 2) {}                                        // nothing to fold (none: a zero row)
+  else if (pieces == 2) fold(0, std::integral_constant<int, 2>{});
+  else if (pieces == 3) fold(0, std::integral_constant<int, 3>{});
+  else if (pieces <= 5) fold(0, std::integral_constant<int, 5>{});
+  else if (!dealt) {
+    for (int s0 = 0; s0 < pieces; s0 += kBatch) fold(s0, batch_c);
+  } else if constexpr (TOGETHER) {
+    for (int s0 = wave; s0 < pieces; s0 += kBatch * kWaves) fold(s0, batch_c);
+    *(floatx4*)sum_s[wave][lane] = o;
+    ml_s[wave][lane][0] = m;
+    ml_s[wave][lane][1] = l;
+    __syncthreads();
+    if (wave != 0) return;
+    join([&](int w) { return floatx2{ml_s[w][lane][0], ml_s[w][lane][1]}; }, [&](int w) { return *(const floatx4*)sum_s[w][lane]; });
+  } else {
+    floatx2 x[kWaves];
+    floatx4 y[kWaves];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)o[e];
-      *(bf16x4*)((__bf16*)other.result + dst) = pk;
-      continue;
+    for (int w = 0; w < kWaves; ++w) {
+      o = floatx4{0.f, 0.f, 0.f, 0.f};
+      m = -INFINITY;
+      l = 0.f;
+      for (int s0 = w; s0 < pieces; s0 += kBatch * kWaves) fold(s0, batch_c);
+      x[w] = floatx2{m, l};
+      y[w] = o;
     }
-    const float inv = n ? 1.f / l : 0.f;
-    if (a.lse && at % D == 0) a.lse[orow0 + head] = n ? m + __builtin_amdgcn_logf(l) : -INFINITY;
-    if constexpr (OUT_BF16) {
-      bf16x4 pk;
+    join([&](int w) { return x[w]; }, [&](int w) { return y[w]; });
+  }
+  if (!ok) return;
+  if constexpr (SHARED) {
+    const float top = fmaxf(m, d1), base = (top == -INFINITY) ? 0.f : top;
+    const float w1 = __builtin_amdgcn_exp2f(d1 - base), w2 = __builtin_amdgcn_exp2f(m - base);   // 2^-inf = 0
+    const float tot = w1 + w2 * l, inv = tot > 0.f ? 1.f / tot : tot;
+    o = (w1 * o1 + w2 * o) * inv;
+    bf16x4 pk;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[e] * inv);
-      *(bf16x4*)((__bf16*)a.out + dst) = pk;
-    } else {
-      *(floatx4*)((float*)a.out + dst) = o * inv;
-    }
+    for (int e = 0; e < 4; ++e) pk[e] = (__bf16)o[e];
+    *(bf16x4*)((__bf16*)other.result + dst) = pk;
+    return;
+  }
+  const float inv = n ? 1.f / l : 0.f;
+  if (a.lse && at % D == 0) a.lse[orow0 + head] = n ? m + __builtin_amdgcn_logf(l) : -INFINITY;
+  if constexpr (OUT_BF16) {
+    bf16x4 pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[e] * inv);
+    *(bf16x4*)((__bf16*)a.out + dst) = pk;
+  } else {
+    *(floatx4*)((float*)a.out + dst) = o * inv;
   }
 }
 
@@ -231,48 +250,40 @@ hipError_t launch_check_inputs(const int32_t* page_table, const int32_t* ctx_len
 }
 
 namespace {
-struct CombineGrid {
-  dim3 grid;
-  int wgs_per_row, chunks_per_wg;
-};
-CombineGrid combine_grid(const DecodeArgs& a, int head_dim) {
+template <bool SHARED>
+hipError_t launch(const DecodeArgs& a, const SharedHalf& shared, int head_dim, bool out_bf16, hipStream_t s) {
   const int chunks = (std::min(a.head_tile, a.group) * head_dim + kChunkFloats - 1) / kChunkFloats;
-  const long rows = (long)a.batch * a.rows_per_b;
+  const long units = (long)a.batch * a.rows_per_b * chunks;
   // A workgroup per chunk while those are few enough to be resident at once, so that the waves of a row of many pieces
-  // have one chunk to share; with more rows (of few pieces each) a chunk per wave.
-  const int chunks_per_wg = rows * chunks <= kCombineResident ? 1 : std::min(chunks, kWaves);
-  const int wgs_per_row = (chunks + chunks_per_wg - 1) / chunks_per_wg;
-  return {dim3((unsigned)(rows * wgs_per_row)), wgs_per_row, chunks_per_wg};
+  // have one chunk to share; with more rows (of few pieces each) a chunk per wave: 1024 contexts of 16 .. 64 tokens with 8 or
+  // 64 KV heads of one query head take 35.2 and 210 us with workgroups of one working wave, 29.6 and 167 with four.
+  const bool together = units <= kCombineResident;
+  const dim3 grid((unsigned)(together ? units : (units + kWaves - 1) / kWaves));
+  auto go = [&](auto d, auto bf16, auto tog) {
+    hipLaunchKernelGGL((combine_kernel<decltype(d)::value, decltype(bf16)::value, SHARED, decltype(tog)::value>), grid, dim3(kThreads), 0, s, a, shared, chunks);
+  };
+  auto with_dim = [&](auto bf16, auto tog) {
+    if (head_dim == 128) go(std::integral_constant<int, 128>{}, bf16, tog);
+    else go(std::integral_constant<int, 64>{}, bf16, tog);
+  };
+  auto with_type = [&](auto tog) {
+    if constexpr (SHARED) with_dim(std::true_type{}, tog);
+    else if (out_bf16) with_dim(std::true_type{}, tog);
+    else with_dim(std::false_type{}, tog);
+  };
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+  if (together) with_type(std::true_type{});
+  else with_type(std::false_type{});
+  return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s) {
-  const CombineGrid c = combine_grid(a, head_dim);
-  const SharedHalf none{};
-  if (head_dim == 128 && out_bf16) {
-    hipLaunchKernelGGL((combine_kernel<128, true, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
-  } else if (head_dim == 128) {
-    hipLaunchKernelGGL((combine_kernel<128, false, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
-  } else if (head_dim == 64 && out_bf16) {
-    hipLaunchKernelGGL((combine_kernel<64, true, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
-  } else if (head_dim == 64) {
-    hipLaunchKernelGGL((combine_kernel<64, false, false>), c.grid, dim3(kThreads), 0, s, a, none, c.wgs_per_row, c.chunks_per_wg);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return launch<false>(a, SharedHalf{}, head_dim, out_bf16, s);
 }
 
 hipError_t launch_combine_shared(const DecodeArgs& a, const SharedHalf& shared, int head_dim, hipStream_t s) {
-  const CombineGrid c = combine_grid(a, head_dim);
-  if (head_dim == 128) {
-    hipLaunchKernelGGL((combine_kernel<128, true, true>), c.grid, dim3(kThreads), 0, s, a, shared, c.wgs_per_row, c.chunks_per_wg);
-  } else if (head_dim == 64) {
-    hipLaunchKernelGGL((combine_kernel<64, true, true>), c.grid, dim3(kThreads), 0, s, a, shared, c.wgs_per_row, c.chunks_per_wg);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return launch<true>(a, shared, head_dim, /*out_bf16=*/true, s);
 }
 
 hipError_t launch_gather(const void* pages, const int32_t* page_table, const int32_t* ctx_lens, int32_t b,

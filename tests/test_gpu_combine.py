@@ -139,3 +139,39 @@ def test_rows_of_one_kv_head_read_its_pages_again():
         args = dict(oracle_args(b), k_pages=W.raw_numpy(k), v_pages=W.raw_numpy(v), page_table=W.raw_numpy(table))
         check(out, O.attn_decode(W.raw_numpy(b.q), **args), "bf16", "tiles")
         assert ws.view(torch.int32)[32].item() == again
+
+
+def test_a_row_of_many_pieces_folds_alike_alone_and_among_many_rows():
+    # three long contexts in a step of 150 trajectories (a chunk of the merge per wave) and by themselves (a workgroup per chunk)
+    batch, long_ = 150, 3
+    lens = np.full(batch, 40)
+    lens[::50] = 20000
+    b = W.build(W.Workload("fold", batch, 32, 8, 128, "bf16", "bf16", ("const", 1), seed=W.BASE_SEED + 104), DEV)
+    rows, sel = np.where(lens > 40, 1, 2), np.flatnonzero(lens > 40)
+    pages = (lens + 15) // 16
+    table = np.full((batch, int(pages.max())), -1, dtype=np.int32)
+    for i, end in enumerate(np.cumsum(pages)):
+        table[i, :pages[i]] = np.arange(end - pages[i], end)
+    gen = torch.Generator(device=DEV).manual_seed(105)
+    k, v = (torch.randn((int(pages.sum()), 8, 16, 128), generator=gen, device=DEV).bfloat16() for _ in range(2))
+    q = torch.randn((int(rows.sum()), 32, 128), generator=gen, device=DEV).bfloat16()
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x).astype(np.int32)).to(DEV)
+    off = np.concatenate([[0], np.cumsum(rows)])
+    kw = dict(sm_scale=b.workload.sm_scale)
+    step = B.attn_step(q, to(rows), to(off), k, v, to(table), to(lens), max_q_len=2, **kw)
+    alone = B.attn_decode(q[off[sel]].contiguous(), k, v, to(table[sel]), to(lens[sel]), **kw)
+    assert len(sel) == long_ and torch.equal(step[off[sel]], alone)
+
+
+def test_more_rows_than_a_launch_has_workgroups():
+    # 64 rows of one head per trajectory, 2^24 of them and some: a workgroup per row would be more threads than a launch may have
+    batch = (1 << 18) + 60
+    q = torch.ones((batch, 64, 64), dtype=torch.bfloat16, device=DEV)
+    k, v = (torch.randn((1, 64, 16, 64), device=DEV).bfloat16() for _ in range(2))
+    table = torch.zeros((batch, 1), dtype=torch.int32, device=DEV)
+    lens = torch.ones(batch, dtype=torch.int32, device=DEV)
+    lens[::1000] = 0
+    out = B.attn_decode(q, k, v, table, lens, sm_scale=0.125)
+    assert torch.equal(out[1], v[0, :, 0]) and not out[::1000].any()
+    out[::1000] = v[0, :, 0]
+    assert bool((out == v[0, :, 0]).all())
