@@ -61,12 +61,23 @@ def test_pieces_and_merge_against_the_oracle(name, batch, hq, hkv, d, prefix, ne
     assert torch.equal(out, again[0]) and torch.equal(lse, again[1])
 
 
-def test_shared_prompts_of_few_groups_are_cut_too():
-    shared = np.array([4000, 0])                      # one long prompt, one group that shares nothing
-    b = W.build(W.Workload("sp", 16, 32, 8, 128, "bf16", "bf16", ("uniform", 4100, 4400), seed=W.BASE_SEED + 92), DEV)
+# over FP8 pools the pieces of the 63-block prompt have odd numbers of blocks too, and end inside a step of two
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("prompt", [4000, 6976])
+def test_shared_prompts_of_few_groups_are_cut_too(prompt, kvd):
+    shared = np.array([prompt, 0])                    # one long prompt, one group that shares nothing
+    b = W.build(W.Workload("sp", 16, 32, 8, 128, "bf16", kvd, ("uniform", prompt + 100, prompt + 400), seed=W.BASE_SEED + 92), DEV)
     b = W.alias_shared_prefix(b, 8, shared)
-    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8,
-                               shared_lens=torch.from_numpy(shared.astype(np.int32)).to(DEV), sm_scale=b.workload.sm_scale)
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=b.workload.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    ws = torch.empty(B.lib().rollattn_shared_workspace_bytes(ctypes.byref(desc), 8), dtype=torch.uint8, device=DEV)
+    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8, shared_lens=torch.from_numpy(shared.astype(np.int32)).to(DEV),
+                               sm_scale=b.workload.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale, workspace=ws)
+    # (the shared half's plan lies behind the private half's workspace, as in a mixed step)
+    app = ws[B.lib().rollattn_step_append_offset(ctypes.byref(desc)):]
+    tiles, merges = app.view(torch.int32)[4:6].tolist()
+    blocks = app[256:].view(torch.int32)[:8 * tiles].view(-1, 8)[:, 6].tolist()
+    assert merges == 1 and tiles > 3 and sum(blocks) == -(-prompt // 64)
+    assert any(n % 2 for n in blocks if n)
     check(out, O.attn_decode(W.raw_numpy(b.q), **oracle_args(b)), "bf16", "shared")
 
 
