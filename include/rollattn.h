@@ -130,8 +130,11 @@ int rollattn_static_init(void);
  * max n_b are host scalars.  max_q_len only picks the tile shape: when no chunk has
  * more than 128 / (Hq / Hkv) tokens the call uses half-size tiles that two waves share
  * (same result within rounding, faster); a value that understates the longest chunk
- * costs speed, not correctness.  Requires n_b <= L_b.  With every n_b == 1 the result equals attn_decode.
- * total_q == 0 succeeds without a launch. */
+ * costs speed, not correctness.  Where few or uneven tiles would leave the chip idle, tiles are cut into pieces of
+ * their context whose partial results are kept in float and folded in a fixed order; whether and where follows from
+ * the lengths of the whole call, so a row's result depends on the rest of the batch within rounding, and is
+ * reproducible bit for bit for one batch.  Requires n_b <= L_b.  With every n_b == 1 the result equals attn_decode
+ * within rounding.  total_q == 0 succeeds without a launch. */
 int attn_append(const rollattn_desc *desc, const void *q_chunk, const int32_t *q_lens,
                 const int32_t *q_offsets, int32_t total_q, int32_t max_q_len, const void *k_pages,
                 const void *v_pages, const int32_t *page_table, const int32_t *ctx_lens, void *out,
@@ -177,7 +180,8 @@ size_t rollattn_step_workspace_bytes(const rollattn_desc *desc, int32_t total_q)
 /* Decode step for groups of trajectories that share a prompt: rollouts are sampled in groups of
  * group_size per prompt with prefix caching on (Section 7.1), so the members of a group alias the
  * same physical pages for their first tokens.  The result is that of attn_decode on the same
- * arguments (to rounding: the two halves below are each rounded to BF16 before they are merged);
+ * arguments (to rounding: the shared half's rows, and those of the private half that were not split, are rounded to
+ * BF16 before they are merged);
  * the shared range is read once per group for all of the group's query heads instead of once per
  * trajectory.  Trajectories b = j * group_size .. (j + 1) * group_size - 1 form group j; B must be a
  * multiple of group_size.  shared_lens [B / group_size] int32 (device): the caller promises that
@@ -220,8 +224,11 @@ int kv_write(const rollattn_desc *desc, const void *k_new, const void *v_new, co
              void *hip_stream);
 
 /* Bytes of workspace either call needs for this descriptor; total_q is the number of
- * query rows (B for decode).  Depends on the descriptor only, never on device data.
- * Returns 0 for an invalid descriptor. */
+ * query rows (B for decode).  Depends on the descriptor only, never on device data, and
+ * not on max_pages_per_seq.  Nearly all of it (34 MB for BF16 at D = 128) holds partial
+ * results; attn_append and attn_step also take a workspace without room for those of
+ * cut tiles and then leave every tile whole (attn_append: records alone, about 32 bytes
+ * per tile and trajectory).  Returns 0 for an invalid descriptor. */
 size_t rollattn_workspace_bytes(const rollattn_desc *desc, int32_t total_q);
 
 /* Paging logic alone (Section 7.1's prefix cache as a data structure): copies logical
