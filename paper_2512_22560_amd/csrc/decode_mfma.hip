@@ -86,11 +86,11 @@ struct Cursor {
   int n, len;      // blocks in the row, context length of the trajectory
 };
 
-// 16 bytes of a K or V row.  Where every byte of a run is read once per call, by one wave (see all_read_again), the streaming
-// hint keeps it from displacing what is read again (page scales, 32 pages' to a cache line, page table, partials) and the
-// last-level cache from spending its bandwidth on it.  Worth 8 to 11 % of a launch: 64 contexts of 512 .. 8k (32/8/128, bf16)
-// 154.0 -> 138.1 us with the merge, 256 long-tailed ones (64/8/128) 1440 -> 1323 us, 384 over FP8 pools (64/4/128)
-// 798 -> 713 us (6.3 TB/s, what a streaming read reaches).
+// 16 bytes of a K or V row.  Where every byte of a run is read once per call, by one wave (see all_read_again), it is read
+// with the streaming hint.  Over FP8 pools that keeps page scales, 32 pages' to a cache line, from being displaced (384
+// contexts: 4.73 -> 4.54 GB read); over bf16 pools as many bytes come faster.  Worth 8 to 11 % of a launch: 64 contexts of
+// 512 .. 8k (32/8/128, bf16) 154.0 -> 138.1 us with the merge, 256 long-tailed ones (64/8/128) 1440 -> 1323 us, 384 over
+// FP8 pools (64/4/128) 798 -> 713 us (6.3 TB/s, what a streaming read reaches).
 template <bool STREAM>
 __device__ __forceinline__ uint4 load16(const unsigned char* p) {
   typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));

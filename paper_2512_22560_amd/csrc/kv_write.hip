@@ -81,8 +81,9 @@ struct KvWriteArgs {
 // Bound by the latency of each workgroup's chain (lengths -> page id and rows -> maximum -> codes), so nothing on it waits
 // that need not: the lengths and the offset leave together, the rows' addresses hang off these alone and the page id is on
 // its way meanwhile, all of a thread's rows leave before the first is looked at, heads and slots are stepped, not divided.
-// As the compiler ordered the plain statements that was five dependent scalar loads and a row at a time: 24.0 us against
-// 22.4 for the chunks of 128 trajectories (32 .. 512 tokens, 4 heads of 128, FP8: 110 MB), 20.1 if the divisions were free.
+// As the compiler ordered the plain statements that was five dependent scalar loads and a row at a time: 24.0 us under the
+// profiler against 22.4 for the chunks of 128 trajectories (32 .. 512 tokens, 4 heads of 128, FP8: 110 MB), 20.1 if the
+// divisions were free; the call, start of the launch included, 24.9 against 24.3.
 // SRC_BYTES: 4 (float32) or 2 (bf16); FP8: pool holds E4M3 codes, else the source type
 template <int D, int SRC_BYTES, bool FP8>
 __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a) {

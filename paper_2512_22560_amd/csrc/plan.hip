@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodeP
 // Pieces.  A tile walks its visible context block by block, so a call ends no earlier than its longest tile, however
 // many CUs have nothing to do: a few observations behind long prefixes, or one 64k history among short ones, leave
 // most of the chip idle.  When the list is short enough to be looked at as a whole (kSplitTiles), the kernel asks
-// whether cutting the tiles into pieces of at most P blocks would end sooner: 64 values of P around the mean
+// whether cutting the tiles into pieces of at most P blocks would end sooner: 63 values of P around the mean
 // load of a CU are tried side by side, each priced in us as
 //   m (alone + (full - alone) (load / m)^3),   m = max(P + start, load + u (P + start) (ceil(w) - w)),
 //   w = pieces / CUs, load = (blocks + start pieces) / CUs, u = mean piece / P:
