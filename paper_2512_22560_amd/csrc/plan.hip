@@ -38,7 +38,9 @@ struct ReadAgainLds {
   unsigned int twice[2 * kLdsPrefix / 32];
   int sum[2];
 };
-__device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAgainLds& lds) {
+// len_of(b): tokens of trajectory b that take part; second_page(b): entry of the second page of those.
+template <class L, class P>
+__device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAgainLds& lds, L&& len_of, P&& second_page) {
   const int tid = threadIdx.x;
   if (a.head_tiles || a.batch > kLdsPrefix) {
     if (tid == 0) a.header[kPlanReadAgain] = 1;
@@ -54,9 +56,9 @@ __device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAga
   __syncthreads();
   int all = 0, met = 0;
   for (int b = tid; b < a.batch; b += kPlanThreads) {
-    const int len = decode_len(a, b), blocks = (len + kBlockTokens - 1) / kBlockTokens;
+    const int len = len_of(b), blocks = (len + kBlockTokens - 1) / kBlockTokens;
     all += blocks;
-    const int page = len > kPageSize ? a.page_table[(size_t)b * a.max_pages + 1] : -1;
+    const int page = len > kPageSize ? a.page_table[(size_t)b * a.max_pages + second_page(b)] : -1;
     if (page < 0) continue;
     int h = (int)(((unsigned int)page * 0x9e3779b1u) >> 15) & mask;
     for (;; h = (h + 1) & mask) {                      // (a free slot is always found)
@@ -76,6 +78,10 @@ __device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAga
   }
   __syncthreads();
   if (tid == 0) a.header[kPlanReadAgain] = all_read_again(a, lds.sum[0]) || (long)lds.sum[1] * 8 >= max(lds.sum[0], 1);
+}
+
+__device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAgainLds& lds) {
+  plan_read_again(a, lds, [&](int b) { return decode_len(a, b); }, [](int) { return 1; });
 }
 
 union DecodeLds {
@@ -344,8 +350,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPla
 // Decode of groups that share a prompt: per group the shared length actually used, S = floor32(min(shared_lens[group],
 // min over the group of L_b - 1)), so that every trajectory keeps at least its current token for itself and the private
 // part starts on a block boundary.  One workgroup plans the shared half (a chunk per group, its members' query rows, over
-// the group's first S tokens), the other one the private half (every trajectory from token S on), whose lengths and
-// first table entries it writes out for the decode kernel.  Each works S out for itself: a launch that did, and
+// the group's first S tokens), another one the private half (every trajectory from token S on), whose lengths and
+// first table entries it writes out for the decode kernel, a third looks at the private half's pages.  Each works S out for itself: a launch that did, and
 // copied the table shifted by S, took 5 us, and the plans one after the other 12 where this launch takes 8 (64 groups of 8).
 constexpr int kSharedGroups = 4096;   // up to this many groups their lengths are settled in LDS
 
@@ -371,6 +377,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
     }
     return s & ~(kBlockTokens - 1);
   };
+  auto own_len = [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); };
   if (blockIdx.x == 0) {
     struct Groups {
       decltype(used)& len;
@@ -380,18 +387,17 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
       __device__ __forceinline__ int offset(int g) const { return g * size; }
     };
     plan_append(a, lds.append, Groups{used, sh.group_size});
+  } else if (blockIdx.x == 2) {
+    // (the private parts have pages in common where a short member leaves some of the prompt to the others, or where the
+    // caller says less than there is)
+    plan_read_again(d, lds.decode.pages, own_len, [&](int b) { return used(b / sh.group_size) / kPageSize + 1; });
   } else {
-    // The private parts have no page in common with others, but for what a short member leaves of the prompt to the others'.
-    bool again = false;
     for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) {
       const int s = used(b / sh.group_size);
       sh.own_ctx[b] = sh.ctx_lens[b] - s;
       sh.own_page[b] = s / kPageSize;
-      again = again || sh.shared_lens[b / sh.group_size] - s >= 2 * kBlockTokens;
     }
-    again = __syncthreads_or(again);
-    plan_decode(d, lds.decode.plan, [&](int b) { return sh.ctx_lens[b] - used(b / sh.group_size); });
-    if (threadIdx.x == 0) d.header[kPlanReadAgain] = again || d.head_tiles;
+    plan_decode(d, lds.decode.plan, own_len);
   }
 }
 
@@ -413,7 +419,7 @@ hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hi
 }
 
 hipError_t launch_plan_shared(const SharedPlanArgs& sh, const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_shared_kernel, dim3(2), dim3(kPlanThreads), 0, s, sh, a, d);
+  hipLaunchKernelGGL(plan_shared_kernel, dim3(3), dim3(kPlanThreads), 0, s, sh, a, d);
   return hipGetLastError();
 }
 

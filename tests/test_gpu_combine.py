@@ -1,4 +1,6 @@
 """The merge of split rows at every count of pieces where it changes its way of folding them."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -175,3 +177,21 @@ def test_more_rows_than_a_launch_has_workgroups():
     assert torch.equal(out[1], v[0, :, 0]) and not out[::1000].any()
     out[::1000] = v[0, :, 0]
     assert bool((out == v[0, :, 0]).all())
+
+
+# pages left in common by the private parts: none; a short member leaves the prompt to the others; the caller says nothing
+@pytest.mark.parametrize("groups", [4, 40])
+@pytest.mark.parametrize("said,short,again", [(640, False, False), (656, False, False), (640, True, True), (0, False, True)])
+def test_private_parts_that_share_pages_read_them_plainly(groups, said, short, again):
+    b = W.build(W.Workload("own", 8 * groups, 16, 4, 128, "bf16", "bf16", ("uniform", 700, 900), seed=W.BASE_SEED + 106), DEV)
+    b = W.alias_shared_prefix(b, 8, np.full(groups, max(said, 640)))
+    lens = b.ctx_lens_host.copy()
+    if short:
+        lens[3::8] = 40
+    cl = torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=b.workload.sm_scale)
+    ws = torch.empty(B.lib().rollattn_shared_workspace_bytes(ctypes.byref(desc), 8), dtype=torch.uint8, device=DEV)
+    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, cl, group_size=8, shared_lens=torch.full((groups,), said, dtype=torch.int32, device=DEV),
+                               sm_scale=b.workload.sm_scale, workspace=ws)
+    assert ws.view(torch.int32)[32].item() == again
+    check(out, O.attn_decode(W.raw_numpy(b.q), **dict(oracle_args(b), ctx_lens=lens)), "bf16", "own")
