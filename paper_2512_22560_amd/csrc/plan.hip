@@ -129,6 +129,8 @@ constexpr int kRankBatch = 4096;
 constexpr int kSplitTiles = kSplitPieces;
 static_assert(kSplitTiles <= kPlanThreads, "a thread per tile");
 
+constexpr int kMaxCutBlocks = 1 << 19;   // 33 million tokens
+
 struct SplitPrice {
   float alone, full, per_cu, start;                      // per_cu: list entries (one workgroup per KV head) that a CU gets of each
   __device__ SplitPrice(const AppendPlanArgs& a) : alone(a.us_alone), full(a.us_full), per_cu((float)a.hkv * (1.f / kNumCUs)), start(kPieceUs * __builtin_amdgcn_rcpf(a.us_full)) {}
@@ -256,15 +258,15 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
     longest_seen = max(longest_seen, (unsigned)blocks_s[t]);
   }
   const int longest = (int)wave_max(longest_seen);
-  if (longest < a.min_longest) return;
+  if (longest < a.min_longest || longest >= kMaxCutBlocks) return;
   blocks_total = wave_sum(blocks_total);
   const SplitPrice price(a);
   const float limit = fmaxf((float)kMinPieceBlocks, ceilf((float)blocks_total * price.per_cu * (0.3f + 0.04f * (float)lane)));
   const float per_limit = __builtin_amdgcn_rcpf(limit), below = limit - 0.5f;
   int pieces = 0, merges = 0, units = 0;
   for (int t = wave; t < tiles; t += kPlanThreads / 64) {
-    // n / p rounded up: (n + p - 1/2) / p lies half a block away from every whole number, more than its rounding while it
-    // is below 2^20 / p; a count of that size is past max_pieces whatever its last digit
+    // n / p rounded up, exactly: (n + p - 1/2) / p lies half a block away from every whole number, more than its rounding
+    // below kMaxCutBlocks
     const int k = max(1, (int)(((float)blocks_s[t] + below) * per_limit));
     pieces += k;
     merges += k > 1 ? 1 : 0;
