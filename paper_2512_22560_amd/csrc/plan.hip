@@ -1,6 +1,6 @@
 // Device-side planning: turns ctx_lens / q_lens into compact work lists without a host
 // round trip, so a call never synchronises.  The partition depends on the lengths only,
-// never on physical page ids.
+// never on physical page ids (which only say how the decode kernel's loads treat the caches).
 #include "plan_device.h"
 
 namespace rollattn {
@@ -31,8 +31,11 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
 // Whether the pages of this call are read by several workers.  Trajectories that share a prefix of their contexts have its
 // pages in common (grouped rollouts, a system prompt in front of all of them), wherever they stand in the batch.  Told by the
 // second page (a single shared page is not worth it): equal ids meet in a hash table in LDS.  The call's pages count as read
-// again where the trajectories that have met have an eighth of all blocks.  A workgroup of its own beside the plan's: both
-// wait for the lengths, and this one then for the tables (in one workgroup the plan of 200 trajectories took 2 us longer).
+// again where the trajectories that have met have a quarter of all blocks: with so many in groups of 8 that share nine tenths
+// the hint still takes 0.91 to 0.99 of the plain loads' time (256 contexts of 8k over FP8 pools 290 against 317 us, 72 over
+// bf16 384 against 389), with half of them 0.97 to 1.04, with all 1.09 to 1.64 (bf16, 256 of 4k: 459 against 282 us).
+// A workgroup of its own beside the plan's: both wait for the lengths, and this one then for the tables (in one workgroup
+// the plan of 200 trajectories took 2 us longer).
 struct ReadAgainLds {
   int key[2 * kLdsPrefix], blocks[2 * kLdsPrefix];   // twice as many slots as trajectories, or more
   unsigned int twice[2 * kLdsPrefix / 32];
@@ -77,7 +80,7 @@ __device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAga
     atomicAdd(&lds.sum[1], met);
   }
   __syncthreads();
-  if (tid == 0) a.header[kPlanReadAgain] = all_read_again(a, lds.sum[0]) || (long)lds.sum[1] * 8 >= max(lds.sum[0], 1);
+  if (tid == 0) a.header[kPlanReadAgain] = all_read_again(a, lds.sum[0]) || (long)lds.sum[1] * 4 >= max(lds.sum[0], 1);
 }
 
 __device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAgainLds& lds) {

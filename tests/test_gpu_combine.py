@@ -122,8 +122,8 @@ def test_pages_read_with_and_without_the_streaming_hint(groups, each, kvd):
                                  q_dtype="bf16", kv_dtype=kvd, k_scale=W.raw_numpy(ks), v_scale=W.raw_numpy(vs)), "bf16", "hint")
         per, total, starts = B.read_plan(desc, ws)
         blocks = -(-lens // 32)
-        if batch > 64:                                   # an eighth of all blocks
-            again = batch > 8192 or 8 * blocks[expect].sum() >= blocks.sum()
+        if batch > 64:                                   # a quarter of all blocks
+            again = batch > 8192 or 4 * blocks[expect].sum() >= blocks.sum()
         else:
             again = expect[:int(np.searchsorted(np.cumsum(2 * blocks), starts[0, 3])) + 1].any()
         assert ws.view(torch.int32)[32].item() == again
