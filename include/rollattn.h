@@ -225,10 +225,12 @@ int kv_write(const rollattn_desc *desc, const void *k_new, const void *v_new, co
 
 /* Bytes of workspace either call needs for this descriptor; total_q is the number of
  * query rows (B for decode).  Depends on the descriptor only, never on device data, and
- * not on max_pages_per_seq.  Nearly all of it (34 MB for BF16 at D = 128) holds partial
- * results; attn_append and attn_step also take a workspace without room for those of
- * cut tiles and then leave every tile whole (attn_append: records alone, about 32 bytes
- * per tile and trajectory).  Returns 0 for an invalid descriptor. */
+ * not on max_pages_per_seq.  Nearly all of it holds partial results: for BF16 at D = 128
+ * 34 MB, and 68 MB for an append call (total_q > B) of few enough rows that its tiles may
+ * be cut (768 / Hkv tiles of 256 rows).  attn_append and attn_step also take less: with
+ * room as for decode they cut tiles into fewer pieces, with room for records alone
+ * (attn_append: about 32 bytes per tile and trajectory) into none, which gives the same
+ * result within rounding.  Returns 0 for an invalid descriptor. */
 size_t rollattn_workspace_bytes(const rollattn_desc *desc, int32_t total_q);
 
 /* Paging logic alone (Section 7.1's prefix cache as a data structure): copies logical

@@ -116,7 +116,7 @@ static int32_t plan_workers(const WorkspaceLayout& w) {
   return (g_debug_workers > 0 && g_debug_workers < w.workers) ? g_debug_workers : w.workers;
 }
 
-WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
+WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q, int32_t units) {
   WorkspaceLayout w{};
   const int group = d.num_q_heads / d.num_kv_heads;
   // room for the list of half-size tiles too (a call whose chunks are all short chooses them)
@@ -126,7 +126,7 @@ WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
   if (d.q_dtype != ROLLATTN_F32 && d.num_kv_heads <= kSplitMerges) {
     w.max_pieces = kSplitPieces / d.num_kv_heads;
     w.max_merges = kSplitMerges / d.num_kv_heads;
-    w.max_units = kSplitUnits / d.num_kv_heads;
+    w.max_units = units / d.num_kv_heads;
   }
   const size_t rec = sizeof(int32_t) * kTileRecWords, parts = (size_t)w.max_units * d.num_kv_heads;
   size_t off = 0;
@@ -148,17 +148,24 @@ WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q) {
 using namespace rollattn;
 
 static_assert(kPlanBlockTokens == kBlockTokens, "the host twin and the kernels cut rows into the same blocks");
-// The partials of an append call's pieces take the room that the decode partials of the same descriptor take, and its list
-// no more than the start records: a workspace that is large enough for the decode call lets an append call cut its tiles,
-// and attn_step and attn_decode_shared lend the one region to both halves in turn.
-static_assert(kSplitUnits * kUnitRows == 2 * kMfmaDecodeWgs * 4 * kMfmaHeadTile, "partials of append and decode");
+// kLentUnits partials of an append call's pieces take the room that the decode partials of the same descriptor take, and its
+// list no more than the start records: a workspace that is large enough for the decode call lets an append call cut its
+// tiles, and attn_decode_shared, and attn_step where the workspace has no more, lend the one region to both halves in turn.
+static_assert(kLentUnits * kUnitRows == 2 * kMfmaDecodeWgs * 4 * kMfmaHeadTile, "partials of append and decode");
 static_assert(kTileRecWords * (kSplitPieces + kSplitMerges) <= 4 * kMfmaDecodeWgs * 4, "records of append and decode");
+
+// What an append call is told to bring: room for all the pieces its tiles may be cut into, unless it has more tiles than
+// are ever cut (it has rows / 256 at least, counted with a group's heads).
+static size_t append_bytes(const rollattn_desc& d, int32_t total_q, int64_t rows) {
+  const WorkspaceLayout w = append_layout(d, total_q);
+  return rows / std::max(1, kAppendTileRows / (d.num_q_heads / d.num_kv_heads)) <= w.max_pieces ? w.cut_total : w.total;
+}
 
 extern "C" {
 
 size_t rollattn_workspace_bytes(const rollattn_desc* desc, int32_t total_q) {
   if (check_desc(desc) != ROLLATTN_OK || total_q < 0) return 0;
-  return std::max(decode_layout(*desc).total, append_layout(*desc, total_q).total);
+  return std::max(decode_layout(*desc).total, append_bytes(*desc, total_q, total_q > desc->batch ? total_q : INT32_MAX));
 }
 
 int32_t rollattn_plan_capacity(const rollattn_desc* desc) {
@@ -457,8 +464,10 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
       !aligned16(v_pages) || !aligned16(page_table) || !aligned16(ctx_lens) || !aligned16(out) ||
       !aligned16(workspace))
     return ROLLATTN_EALIGN;
-  const WorkspaceLayout w = append_layout(*desc, total_q);
+  WorkspaceLayout w = append_layout(*desc, total_q);
   if (workspace_bytes < w.total) return ROLLATTN_EWORKSPACE;
+  const bool lent = lender && workspace_bytes < w.cut_total;
+  if (lent || workspace_bytes < w.cut_total) w = append_layout(*desc, total_q, kLentUnits);
 
   char* base = (char*)workspace;
   AppendArgs& a = call->args;
@@ -479,21 +488,22 @@ static int append_prepare(const rollattn_desc* desc, const void* q_chunk, const 
   // that is too long to be cut, or as good as even already, needs neither the decision nor the merge launch
   const int64_t min_tiles = noncausal ? desc->batch : ((int64_t)total_q - (skip_unit_chunks ? desc->batch : 0)) / a.tile_tokens;
   // ... as does a table whose contexts are all too short: the least that pays is a lone tile cut into shortest pieces.
-  // Whether the workspace has room is told from its size alone: one as large as rollattn_workspace_bytes always has.
+  // Whether the workspace has room is told from its size alone: one as large as the call is told to bring has, one that is
+  // large enough for a decode call has for kLentUnits.
   const BlockTime t = block_time(*desc, half_tiles);
   const float start = kPieceUs / t.full;
   const int32_t min_longest = std::max(2 * kMinPieceBlocks, (int32_t)std::ceil(((t.alone * (kMinPieceBlocks + start) + kMergeUs + kCallUs + kSplitGainUs) / kSplitGain - kCallUs) / t.alone - start));
   const bool may_cut = min_tiles <= w.max_pieces && !(noncausal && min_tiles * a.hkv >= kNumCUs) &&
                        desc->max_pages_per_seq > (min_longest - 1) * (kAppendBlockTokens / kPageSize) &&
-                       workspace_bytes >= (lender ? w.cut_list : w.cut_total);
+                       workspace_bytes >= (lent ? w.cut_list : w.cut_total);
   const int32_t max_pieces = may_cut ? w.max_pieces : 0;
   // (the launch has room for no more pieces than the plan may choose: two rounds above the tiles, none shorter than it may be)
   const int64_t per_tile = (desc->max_pages_per_seq + (int64_t)kMinPieceBlocks * (kAppendBlockTokens / kPageSize) - 1) / (kMinPieceBlocks * (kAppendBlockTokens / kPageSize));
   const int32_t tile_cap = (int32_t)std::max<int64_t>(max_tiles, std::min<int64_t>({max_pieces, (int64_t)max_tiles + split_extra_pieces(a.hkv), max_tiles * per_tile}));
   a.tile_cap = tile_cap;
   a.merge_rec = (const int32_t*)(base + w.merge_rec);
-  a.partial_ml = lender ? lender->partial_ml : (float*)(base + w.partial_ml);
-  a.partial_o = lender ? lender->partial_o : (float*)(base + w.partial_o);
+  a.partial_ml = lent ? lender->partial_ml : (float*)(base + w.partial_ml);
+  a.partial_o = lent ? lender->partial_o : (float*)(base + w.partial_o);
   a.total_q = total_q;
   a.scale_log2 = desc->sm_scale * 1.4426950408889634f;
   a.lse = lse;
@@ -613,7 +623,7 @@ int attn_merge(const rollattn_desc* desc, int64_t rows, const void* o1, const fl
 
 size_t rollattn_step_workspace_bytes(const rollattn_desc* desc, int32_t total_q) {
   if (check_desc(desc) != ROLLATTN_OK || total_q < 0) return 0;
-  return align256(decode_layout(*desc).total) + append_layout(*desc, total_q).cut_list;
+  return align256(decode_layout(*desc).total) + std::max(append_layout(*desc, total_q).cut_list, append_bytes(*desc, total_q, std::max(0, total_q - desc->batch)));
 }
 
 size_t rollattn_step_append_offset(const rollattn_desc* desc) {

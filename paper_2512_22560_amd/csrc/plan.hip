@@ -298,11 +298,11 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const int k = tid < tiles ? max(1, (mine + p_max - 1) / p_max) : 0;   // pieces of this thread's tile (one without blocks has zero rows to write)
   const bool cut = k > 1;
   // pieces, cut tiles and units of partials in one scan: 10, 9 and 12 bits
-  static_assert(kSplitPieces < 1024 && kSplitMerges < 512 && kSplitUnits < 4096, "one scan");
+  static_assert(kSplitPieces < 1024 && kSplitMerges < 512 && kSplitUnits <= 4096, "one scan");
   const int my_units = cut ? units_s[tid] : 0;
   int all;
   const int before = block_exclusive_scan(k | (cut ? 1 << 10 : 0) | (k * my_units) << 19, wave_tot, &all);
-  const int piece0 = before & 1023, merge0 = (before >> 10) & 511, unit0 = before >> 19, n_pieces = all & 1023, n_merges = (all >> 10) & 511;
+  const int piece0 = before & 1023, merge0 = (before >> 10) & 511, unit0 = (int)((unsigned)before >> 19), n_pieces = all & 1023, n_merges = (all >> 10) & 511;
   if (cut) {
     int4* m = (int4*)(a.merge_rec + (size_t)merge0 * kTileRecWords);
     m[0] = make_int4(tile_s[tid].y, tile_s[tid].z, tile_qoff_s[tid], unit0);   // (first row, n_b, q_offsets[b], first unit, pieces)

@@ -24,7 +24,8 @@ constexpr int kAppendBlockTokens = 64;  // KV tokens staged per step of the appe
 constexpr int kTileRecWords = 8;       // append: int32 per tile record (32 bytes: one scalar load)
 constexpr int kSplitPieces = 768;       // append: a list whose tiles are cut into pieces has at most this many workgroups
 constexpr int kSplitMerges = 256;       // append: ... from at most this many tiles
-constexpr int kSplitUnits = 2048;       // append: ... whose pieces leave at most this many partials of kUnitRows rows each
+constexpr int kSplitUnits = 4096;       // append: ... whose pieces leave at most this many partials of kUnitRows rows each,
+constexpr int kLentUnits = 2048;        // ... or as many as there is room for decode partials, where the workspace has no more
 constexpr int kUnitRows = 32;           // append: query rows per wave, and per unit of the partials of a tile's piece
 constexpr int kMinPieceBlocks = 8;      // append: shorter pieces cost more in their start and end than they save
 constexpr float kPieceUs = 8.f;         // append, price of a cut in us: what a workgroup costs besides its blocks,
@@ -58,7 +59,7 @@ struct WorkspaceLayout {
 };
 
 WorkspaceLayout decode_layout(const rollattn_desc& d);
-WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q);
+WorkspaceLayout append_layout(const rollattn_desc& d, int32_t total_q, int32_t units = kSplitUnits);
 
 // Inputs and outputs of the decode partition.
 struct DecodePlanArgs {

@@ -170,8 +170,18 @@ def test_workspace_sizes_do_not_depend_on_the_width_of_the_table(batch, hq, hkv,
         for f in (lib.rollattn_workspace_bytes, lib.rollattn_step_workspace_bytes, lib.rollattn_shared_workspace_bytes):
             n = 1 if f is lib.rollattn_shared_workspace_bytes else total_q
             assert f(ctypes.byref(desc(4096)), n) == f(ctypes.byref(desc(60)), n) > 0
-    # two partials of 16 rows per wave of 512 workgroups, and records: an append call's pieces ask for no more than a decode call,
-    # so what attn_decode_static takes is what the size says
+    # two partials of 16 rows per wave of 512 workgroups, and records: what attn_decode_static takes is what the size says
     partials = 512 * 4 * 2 * 16 * (d + 2) * 4
     assert partials < lib.rollattn_workspace_bytes(ctypes.byref(desc(4096)), batch) <= partials + 33792 + 4 * batch
     assert lib.rollattn_workspace_bytes(ctypes.byref(desc(4096)), batch) <= lib.rollattn_static_scratch_bytes()
+
+
+def test_only_calls_with_few_tiles_are_told_to_bring_room_for_pieces():
+    lib = B.lib()
+    d = _desc(batch=64, num_q_heads=32, num_kv_heads=8, head_dim=128, q_dtype=B.BF16, kv_dtype=B.BF16, max_pages_per_seq=4096)
+    ref = ctypes.byref(d)
+    decode, pieces = lib.rollattn_workspace_bytes(ref, 64), 4096 * 32 * (128 + 2) * 4
+    assert decode < 35 << 20 and lib.rollattn_workspace_bytes(ref, 32686) == decode           # 511 tiles, never cut
+    assert pieces < lib.rollattn_workspace_bytes(ref, 640) < pieces + (1 << 16)
+    assert lib.rollattn_step_workspace_bytes(ref, 32686) < decode + (1 << 20)
+    assert decode + pieces < lib.rollattn_step_workspace_bytes(ref, 640) < decode + pieces + (1 << 16)

@@ -83,33 +83,40 @@ def test_shared_prompts_of_few_groups_are_cut_too(prompt, kvd):
 
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
 def test_a_workspace_without_room_for_pieces_leaves_the_tiles_whole(kvd):
-    # sized for the records alone, all that a call needs; one for a decode step of the same descriptor is enough to cut
-    b = W.build(W.Workload("room", 2, 32, 8, 128, "bf16", kvd, ("uniform", 6000, 9000), qlen=("uniform", 20, 90), ctx_is_prefix=True,
+    # sized for the records alone, all that a call needs; one for a decode step of the same descriptor is enough to cut, if
+    # into fewer pieces than the size the call is told to bring
+    b = W.build(W.Workload("room", 18, 32, 8, 64, "bf16", kvd, ("loguniform", 3000, 12000), qlen=("uniform", 40, 70), ctx_is_prefix=True,
                            seed=W.BASE_SEED + 93), DEV)
     w = b.workload
     desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
     least = 256 + -(-32 * B.lib().rollattn_append_plan_capacity(ctypes.byref(desc), b.total_q) // 256) * 256
-    got = []
-    for n, cut in ((least, False), (B.workspace_bytes(desc, w.batch), True)):
+    got, pieces, ref = [], [], oracle_append(b)
+    for n in (least, B.workspace_bytes(desc, w.batch), B.workspace_bytes(desc, b.total_q)):
         ws = torch.empty(n, dtype=torch.uint8, device=DEV)
         got.append(gpu_append(b, workspace=ws))
-        assert (ws.view(torch.int32)[5].item() > 0) == cut
-        check(got[-1], oracle_append(b), "bf16", "room")
+        pieces.append(ws.view(torch.int32)[4].item() if ws.view(torch.int32)[5].item() else 0)
+        check(got[-1], ref, "bf16", "room")
+    assert 0 == pieces[0] < pieces[1] <= pieces[2] and (pieces[1] < pieces[2] or kvd == "bf16")
     with pytest.raises(B.RollattnError):
         gpu_append(b, workspace=torch.empty(least - 256, dtype=torch.uint8, device=DEV))
-    # a mixed step of the chunks alone cuts them where the decode rows' partials will lie: the same pieces, bit for bit
-    step = B.attn_step(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, k_scale=b.k_scale,
-                       v_scale=b.v_scale, max_q_len=int(b.q_lens_host.max()))
-    assert torch.equal(step, got[1])
+    # a mixed step of the chunks alone cuts them alike, where it has to in the room of the decode rows' partials
+    more = B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), b.total_q)
+    less = B.lib().rollattn_step_append_offset(ctypes.byref(desc)) + 256 + 32 * 8 * (96 + 32)
+    for n, same in ((more, got[2]), (less, got[1])):
+        step = B.attn_step(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, k_scale=b.k_scale,
+                           v_scale=b.v_scale, max_q_len=int(b.q_lens_host.max()), workspace=torch.empty(n, dtype=torch.uint8, device=DEV))
+        assert torch.equal(step, same)
 
 
-def test_a_mixed_step_with_cut_chunks_and_split_rows():
+@pytest.mark.parametrize("lend", [False, True])
+def test_a_mixed_step_with_cut_chunks_and_split_rows(lend):
     # two chunks behind long prefixes, cut; the decode rows, split over many workers, take the same room for their partials afterwards
     b = W.build(W.Workload("both", 6, 32, 8, 128, "bf16", "bf16", ("uniform", 6000, 9000), qlen=("uniform", 20, 90), ctx_is_prefix=True,
                            append_rows=2, seed=W.BASE_SEED + 94), DEV)
     w = b.workload
     desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale)
-    ws = torch.empty(B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), b.total_q), dtype=torch.uint8, device=DEV)
+    n = B.lib().rollattn_step_append_offset(ctypes.byref(desc)) + 256 + 32 * 8 * (96 + 32) if lend else B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), b.total_q)
+    ws = torch.empty(n, dtype=torch.uint8, device=DEV)
     args = (b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens)
     kw = dict(sm_scale=w.sm_scale, max_q_len=int(b.q_lens_host.max()), workspace=ws)
     out = B.attn_step(*args, **kw).clone()
