@@ -171,7 +171,6 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   const int tid = threadIdx.x;
   const int batch = a.batch, tile_tokens = a.tile_tokens;
   const bool ranked = batch <= kRankBatch;
-  if (tid < 64) pieces_s[tid] = merges_s[tid] = piece_units_s[tid] = 0;   // (barriers follow before they are added to)
   if (ranked) {
     // everything the plan reads, in one round trip to memory
     const int padded = (batch + 3) & ~3;
@@ -234,7 +233,7 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
       int4* rec = (int4*)(a.tile_rec + (size_t)t * kTileRecWords);
       rec[0] = make_int4(b_s[lo], q0, qlen_s[lo], ctx_s[lo]);
       rec[1] = make_int4(qoff_s[lo], 0, blocks, -1);
-      if (t < kSplitTiles) {
+      if (a.max_pieces && t < kSplitTiles) {
         tile_s[t] = make_int4(b_s[lo], q0, qlen_s[lo], ctx_s[lo]);
         tile_qoff_s[t] = qoff_s[lo];
         blocks_s[t] = blocks;
@@ -262,6 +261,8 @@ __device__ __forceinline__ void plan_append(const AppendPlanArgs& a, AppendPlanL
   }
   const int longest = (int)wave_max(longest_seen);
   if (longest < a.min_longest || longest >= kMaxCutBlocks) return;
+  if (wave == 0) pieces_s[lane] = merges_s[lane] = piece_units_s[lane] = 0;
+  __syncthreads();
   blocks_total = wave_sum(blocks_total);
   const SplitPrice price(a);
   const float limit = fmaxf((float)kMinPieceBlocks, ceilf((float)blocks_total * price.per_cu * (0.3f + 0.04f * (float)lane)));
