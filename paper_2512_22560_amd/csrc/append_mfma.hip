@@ -25,10 +25,17 @@
 // cycle counters, a vector-memory instruction issued between the MFMAs costs the phase 70-90
 // cycles (four of them stretched 32 MFMAs from 1270 to 1400 cycles), while the same instruction
 // costs the vector phase little more than its issue slot.  All tile loads and the scalar loads of
-// page ids and page scales therefore belong to the vector phase; only the widening of FP8 tiles
+// page ids therefore belong to the vector phase; only the widening of FP8 tiles
 // (conversions and LDS writes of registers loaded two blocks earlier) stays between the MFMAs,
-// where it was measured to cost less than in a vector phase that is bound by its own instruction
-// stream.  The vector phase keeps its VALU work short in turn:
+// where it was measured to cost less than in the vector phase (all of it there, the two halves a unit apart:
+// the mixed step 12.91 -> 13.9 ms; behind the softmax, or V alone: no difference).
+// A wave issues one instruction per 4 cycles whatever its kind (vector instructions 6 beside a partner's MFMAs, exponentials
+// 4 more), so the scalar instructions of a vector phase count like the others: page ids by running offsets, page scales once
+// for 64 pages (fill_scales), LDS offsets as immediates and no maximum of the row to look at took it from about 150 vector
+// and 95 scalar instructions to 121 and 20 over FP8 pools, and with waits for the tile loads by their true count the
+// calls from 4.217 to 4.117 ms (64 chunks of 64 .. 1024 tokens behind 2k .. 16k, 32/8/128, bf16), 5.824 to 5.753 (without
+// a prefix, 512 .. 8k tokens), 13.08 to 12.91 (mixed step of 512 trajectories, 64/4/128, FP8), all on one box: the clock gives most of the cycles
+// back (the part is at its power limit).  The vector phase keeps its VALU work short in turn:
 //   bf16 pools: the query is multiplied by sm_scale * log2(e) once, when it is loaded (one extra
 //     bf16 rounding of q, far below the rounding of P), and the score accumulators start from
 //     minus the row's reference instead of zero, so the MFMA result already is the exponent and
@@ -66,6 +73,7 @@ constexpr int kRowsPerWave = kUnitRows;
 static_assert(kWaves * kRowsPerWave == kAppendTileRows, "tile rows");
 constexpr int kBlockTokens = kAppendBlockTokens;   // KV tokens staged per step
 constexpr int kLongTileBlocks = 20;                // half tiles over FP8 pools: from this many blocks on a step is two of them
+constexpr int kScaleWindow = 64;                   // FP8: pages whose scales are fetched at a time, a lane each
 constexpr float kSumLimit = 16384.f;               // a lane's 32 probabilities of a block may add up to this much before the row's reference moves
 
 // Row t of an S^T tile holds this token of its 16-token group: the middle two quads are
@@ -124,6 +132,14 @@ __device__ __forceinline__ void store_row_dims(__bf16* dst, bool row_ok, float i
   }
 }
 
+// The operand reads and tile writes of the block loop: a lane's part of the LDS address is a pointer of its own that stays in a
+// register over the whole loop, and everything else is the instruction's immediate offset.
+typedef __attribute__((address_space(3))) unsigned char* lds_p;
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds_at(lds_p base, int offset) {
+  return (__attribute__((address_space(3))) T*)(base + offset);
+}
+
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -165,6 +181,8 @@ struct AppendGeo {
   static constexpr int kMergeAcc = (D / 32) * 16 * 64;      // floats per wave pair
   static constexpr bool kMergeInRing = (size_t)kRing * kTileBytes >= (size_t)(kWaves / 2) * kMergeAcc * sizeof(float);
   static constexpr bool kMergeApart = HALF && !kMergeInRing;
+  // FP8: what the softmax needs of a page's scales, for two windows of kScaleWindow pages (see fill_scales below)
+  static constexpr int kScales = FP8 ? 2 * kScaleWindow : 4;
 };
 // The LDS of a kernel with two instances, as one of them sees it.
 template <int D, bool FP8, bool HALF, int STEP>
@@ -173,6 +191,7 @@ struct AppendLds {
   __attribute__((aligned(1024))) unsigned char k[Geo::kRing][Geo::kTileBytes], v[Geo::kRing][Geo::kTileBytes];
   __attribute__((aligned(16))) float merge_acc[Geo::kMergeApart ? kWaves / 2 : 1][Geo::kMergeApart ? Geo::kMergeAcc : 4];
   float merge_ml[HALF ? kWaves / 2 : 1][HALF ? 128 : 1];
+  __attribute__((aligned(16))) float scales[3][Geo::kScales];
   long clock[2];
 };
 
@@ -235,11 +254,13 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   __shared__ __attribute__((aligned(1024))) unsigned char v_own[kOneOfTwo ? 1 : kRing][kOneOfTwo ? 16 : kTileBytes];
   __shared__ __attribute__((aligned(16))) float merge_acc_own[kApart ? kWaves / 2 : 1][kApart ? kMergeAcc : 4];
   __shared__ float merge_ml_own[HALF && !kOneOfTwo ? kWaves / 2 : 1][HALF && !kOneOfTwo ? 128 : 1];
+  __shared__ __attribute__((aligned(16))) float scales_own[3][kOneOfTwo ? 4 : Geo::kScales];
   __shared__ long clock_own[2];
   auto& k_lds = choose<kOneOfTwo>(shared->k, k_own);
   auto& v_lds = choose<kOneOfTwo>(shared->v, v_own);
   auto& merge_acc_s = choose<kOneOfTwo>(shared->merge_acc, merge_acc_own);
   auto& merge_ml_s = choose<kOneOfTwo>(shared->merge_ml, merge_ml_own);
+  auto& scales_s = choose<kOneOfTwo>(shared->scales, scales_own);
   auto& clock_s = choose<kOneOfTwo>(shared->clock, clock_own);
 
   int tid = threadIdx.x, block = blockIdx.x;
@@ -329,11 +350,13 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_ref = 0.f, l_run = 0.f;               // the row's reference, zero as long as it has seen nothing, and its sum
+  float sum_limit = row_ok ? -1.f : INFINITY;   // a lane's probabilities of a block may add up to this much; below zero: no reference yet
+  auto seen_max = [&]() __attribute__((always_inline)) { return sum_limit < 0.f ? -INFINITY : m_ref; };
   floatx16 negm;            // bf16 pools: minus the row's reference in every element, the value the score accumulators start from
 #pragma unroll
   for (int i = 0; i < 16; ++i) negm[i] = 0.f;
-  const bool positive_scale = a.scale_log2 > 0.f;   // the usual case; FP8 page scales are positive too
+  const bool positive_scale = __float_as_int(a.scale_log2) > 0;   // the usual case (compared as an integer, in a scalar register); FP8 page scales are positive too
 
   // ---- staging.  Unit u = (K block u + 1, V block u): the two tiles that the matrix phase of
   // block u + 1 reads; block j lives in ring slot j % kRing of its pool.  Per thread and load, the
@@ -352,7 +375,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // for V.  The register path (FP8) applies the swizzle when it writes LDS; the direct path has to
   // apply it on the global side, because there the LDS position of a lane's chunk is fixed.
   unsigned int goff[kLoads][2], goff_last[kLoads][2];   // [][0]: K, [][1]: V
-  int woff[kLoads][2];
+  lds_p wptr[kLoads][3];                                // FP8: where a widened chunk goes, K's two halves and V
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
     const int idx = j * kThreads + tid;
@@ -365,54 +388,50 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     goff[j][1] = tslot * kSrcRowBytes + cv * 16;
     goff_last[j][0] = min(tslot, last_slot) * kSrcRowBytes + ck * 16;
     goff_last[j][1] = min(tslot, last_slot) * kSrcRowBytes + cv * 16;
-    woff[j][0] = trow * kRowBytes + (((2 * c) ^ kkey) & (kChunks - 1)) * 16;   // FP8 only
-    woff[j][1] = trow * kRowBytes + (((2 * c) ^ vkey) & (kChunks - 1)) * 16;
+    if constexpr (FP8) {
+      // the two 16-byte halves of the widened chunk sit in chunks 2c and 2c + 1: 16 bytes apart after the swizzle (V: the upper
+      // one behind the lower, its key is even)
+      const int kat = trow * kRowBytes + (((2 * c) ^ kkey) & (kChunks - 1)) * 16;
+      wptr[j][0] = (lds_p)(k_lds[0] + kat);
+      wptr[j][1] = (lds_p)(k_lds[0] + (kat ^ 16));
+      wptr[j][2] = (lds_p)(v_lds[0] + trow * kRowBytes + (((2 * c) ^ vkey) & (kChunks - 1)) * 16);
+    }
   }
-  // The 64 chunks a wave fetches with one instruction lie in one page, so its id is a scalar.
-  // fetch_pids: the page ids behind this wave's kLoads loads of one block (block index clamped to
-  // the last block, page index to the last live page).
-  int pj[kLoads], lim[kLoads];
-  const_i32_p table_j[kLoads];
+  // The 64 chunks a wave fetches with one instruction lie in one page, so its id is a scalar.  Block after block the entries
+  // behind a load lie kPagesPerBlock apart: their byte offset in the table runs along, no further than to the page of the last
+  // block (page_end) or the last live page (page_live), whose rows are clamped too.
+  int page_run[kLoads], page_end[kLoads];
+  const int page_live = (live_pages - 1) * 4;
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
-    pj[j] = ((j * kThreads + wave * 64) / kSrcChunks) / kPageSize;
-    lim[j] = live_pages - 1 - pj[j];                  // first page of a block >= lim: the load touches the last live page
-    table_j[j] = table + pj[j];
+    page_run[j] = ((j * kThreads + wave * 64) / kSrcChunks) / kPageSize * 4;
+    page_end[j] = min(last_blk * kPagesPerBlock * 4 + page_run[j], page_live);
   }
-  auto fetch_pids = [&](int blk, int* dst) __attribute__((always_inline)) {
-    const int b4 = min(blk, last_blk) * kPagesPerBlock;
+  // the page ids behind this wave's kLoads loads of one block, and whether that is the last live page; the blocks in order
+  auto fetch_pids = [&](int* dst, int* at) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) dst[j] = table_j[j][min(b4, lim[j])];
+    for (int j = 0; j < kLoads; ++j) {
+      at[j] = min(page_run[j], page_end[j]);
+      dst[j] = *(const_i32_p)((const __attribute__((address_space(4))) char*)table + (unsigned int)at[j]);
+      page_run[j] += kPagesPerBlock * 4;
+    }
   };
   // byte offset of the (page, KV head) tile in either pool
   auto tile_off_of = [&](int pid) __attribute__((always_inline)) -> size_t {
     return (size_t)(unsigned int)(pid * hkv + g) * tile_stride;
   };
-  // one wave-wide 16-byte load of block blk: scalar tile base, per-lane offset
+  // one wave-wide 16-byte load: scalar tile base, per-lane offset
   struct TileAddr { const unsigned char* base; unsigned int off; };
-  auto tile_addr = [&](const void* pool, int pool_i, int blk, size_t toff, int j) __attribute__((always_inline)) -> TileAddr {
-    const int b4 = min(blk, last_blk) * kPagesPerBlock;
-    return TileAddr{(const unsigned char*)pool + toff, (b4 >= lim[j]) ? goff_last[j][pool_i] : goff[j][pool_i]};
+  auto tile_addr = [&](const void* pool, int pool_i, size_t toff, bool last, int j) __attribute__((always_inline)) -> TileAddr {
+    return TileAddr{(const unsigned char*)pool + toff, last ? goff_last[j][pool_i] : goff[j][pool_i]};
   };
   // -- register path (FP8)
   uintx4 kreg[2][kLoads], vreg[2][kLoads];   // two units in flight
-  auto issue = [&](int u, const int* pk, const int* pv, auto slot_c) __attribute__((always_inline)) {
-    constexpr int slot = decltype(slot_c)::value;
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
-        const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, tile_off_of(pk[j]), j), va = tile_addr(a.v_pages, 1, u, tile_off_of(pv[j]), j);
-        kreg[slot][j] = load16<ONCE>(ka.base + ka.off);
-        vreg[slot][j] = load16<ONCE>(va.base + va.off);
-      }
-    }
-  };
-  auto put = [&](unsigned char* tile, int off, const uintx4 raw) __attribute__((always_inline)) {
-    // the two 16-byte halves of the widened chunk sit in chunks 2c and 2c + 1: 16 bytes apart after the swizzle
+  auto put = [&](lds_p lo_at, lds_p hi_at, int offset, const uintx4 raw) __attribute__((always_inline)) {
     uintx4 lo, hi;
     fp8x16_to_bf16(raw, lo, hi);
-    *(uintx4*)(tile + off) = lo;
-    *(uintx4*)(tile + (off ^ 16)) = hi;
+    *lds_at<uintx4>(lo_at, offset) = lo;
+    *lds_at<uintx4>(hi_at, offset) = hi;
   };
   // -- direct path (bf16): HBM -> LDS without a register stop.  Lane l's 16 bytes land at
   // M0 + 16 l.  The compiler does not see these loads as loads: completion is awaited by count
@@ -427,52 +446,54 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   };
 #define DMA_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n))
 
-  // FP8: scales of the pages of a block that this wave's tokens lie in (four, or two of them), by scalar loads,
-  // folded with the softmax scale; the page ids behind them are fetched one vector phase before the scales,
-  // the scales one vector phase before use
-  constexpr int kPg = HALF ? kPagesPerBlock / 2 : kPagesPerBlock;
-  float ksc_cur[kPg], lvs_cur[kPg], ivs_cur[kPg];   // per page: K scale times softmax scale, log2 of the V scale, its reciprocal
-  int spid[kPg];
-  auto fetch_spids = [&](int blk) __attribute__((always_inline)) {
-#pragma unroll
-    for (int p = 0; p < kPg; ++p)
-      spid[p] = FP8 ? table[min(min(blk, last_blk) * kPagesPerBlock + (HALF ? grp * kPg : 0) + p, live_pages - 1)] : 0;
+  // FP8: per page, K scale times softmax scale, log2 of the V scale, and its reciprocal.  Worked out by wave 0 for kScaleWindow
+  // pages at a time, a lane each, and left in LDS: scalar loads in every wave and block (page ids, then scales, then two
+  // transcendentals per page that all lanes compute alike) took a quarter of the instructions of a vector phase, which is bound
+  // by how fast one wave issues.
+  constexpr int kPg = HALF ? kPagesPerBlock / 2 : kPagesPerBlock;   // pages of a block that this wave's tokens lie in
+  constexpr int kWindowBlocks = kScaleWindow / kPagesPerBlock;
+  float ksc_cur[kPg], lvs_cur[kPg], ivs_cur[kPg];
+  unsigned int window_k = 0;      // the page's id, then its K scale
+  float window_v = 1.f;
+  auto window_ids = [&](int blk) __attribute__((always_inline)) {      // of the window that starts at block blk
+    window_k = *(const unsigned int*)((const char*)(const int32_t*)table + (unsigned int)min((blk * kPagesPerBlock + lane) * 4, page_live));
   };
-  auto load_scales = [&]() __attribute__((always_inline)) {
+  auto window_scales = [&]() __attribute__((always_inline)) {
+    window_v = a.v_scale[window_k];
+    window_k = __float_as_uint(a.k_scale[window_k]);
+  };
+  auto window_write = [&](int blk) __attribute__((always_inline)) {
+    const int at = (blk * kPagesPerBlock + lane) % (2 * kScaleWindow);
+    scales_s[0][at] = __uint_as_float(window_k) * a.scale_log2;
+    scales_s[1][at] = __builtin_amdgcn_logf(window_v);
+    scales_s[2][at] = __builtin_amdgcn_rcpf(window_v);
+  };
+  // this wave's pages of block blk
+  auto read_scales = [&](int blk) __attribute__((always_inline)) {
+    const int at = (blk * kPagesPerBlock) % (2 * kScaleWindow) + (HALF ? grp * kPg : 0);
 #pragma unroll
-    for (int p = 0; p < kPg; ++p) {
-      if (FP8) {
-        const float vs = v_scale_c[spid[p]];
-        ksc_cur[p] = k_scale_c[spid[p]] * a.scale_log2;
-        lvs_cur[p] = __builtin_amdgcn_logf(vs);
-        ivs_cur[p] = __builtin_amdgcn_rcpf(vs);
-      } else {
-        ksc_cur[p] = 1.f;
-        lvs_cur[p] = 0.f;
-        ivs_cur[p] = 1.f;
-      }
-    }
+    for (int p = 0; p < kPg; ++p) { ksc_cur[p] = scales_s[0][at + p]; lvs_cur[p] = scales_s[1][at + p]; ivs_cur[p] = scales_s[2][at + p]; }
   };
 
-  // Per-lane LDS byte offsets that do not change over the loop: the K row this lane feeds as an A
+  // Per-lane LDS pointers that do not change over the loop: the K row this lane feeds as an A
   // operand for each 16-dim step, and the V row / column pair it addresses in each transposed
   // read.  Everything else (buffer, sub-block, token group) is a compile-time immediate.
-  int koff[kKK], voff[kDT];
+  lds_p kptr[kKK], vptr[kDT];
+  const int sub_bytes = tok_wave * kRowBytes;           // HALF: where this wave's tokens start in a K or V tile
   {
     const int t = (n32 & 16) + tau(n32 & 15);
 #pragma unroll
-    for (int kk = 0; kk < kKK; ++kk) koff[kk] = t * kRowBytes + (((kk * 2 + h2) ^ (t & 15)) & (kChunks - 1)) * 16;
+    for (int kk = 0; kk < kKK; ++kk) kptr[kk] = (lds_p)(k_lds[0] + sub_bytes + t * kRowBytes + (((kk * 2 + h2) ^ (t & 15)) & (kChunks - 1)) * 16);
     const int j = lane & 15;
     const int tv = h2 * 8 + (j >> 2);
 #pragma unroll
     for (int dt = 0; dt < kDT; ++dt)
-      voff[dt] = tv * kRowBytes +
-                 (((dt * 4 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ ((tv & 3) << 2)) & (kChunks - 1)) * 16 + (j & 1) * 8;
+      vptr[dt] = (lds_p)(v_lds[0] + sub_bytes + tv * kRowBytes +
+                 (((dt * 4 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ ((tv & 3) << 2)) & (kChunks - 1)) * 16 + (j & 1) * 8);
   }
 
   constexpr int kSubs = kStepTokens / (HALF ? 64 : 32);   // 32-token sub-blocks of a step that this wave works on
   constexpr int kPvSteps = 8 * kSubs, kSteps = 16 * kSubs;
-  const int sub_bytes = tok_wave * kRowBytes;           // HALF: where this wave's tokens start in a K or V tile
   floatx16 s[kSubs];        // scores of the block between its two phases
   bf16x8 pop[kSubs][2];     // its probabilities, as B operands of the second product
 
@@ -491,35 +512,32 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // complete one phase earlier), so that the phase does not open with an LDS round trip.
   constexpr bool kEarly = !FP8;
   bf16x8 early[kAhead];
-  typedef __attribute__((address_space(3))) shortx4 lds_s4;
-  auto read_v_operand = [&](const unsigned char* vbuf, auto t_c, bf16x8& dst) __attribute__((always_inline)) {
+  auto read_v_operand = [&](int vbo, auto t_c, bf16x8& dst) __attribute__((always_inline)) {
     constexpr int t = decltype(t_c)::value;
     constexpr int sub = t >> 3, ks = (t >> 2) & 1, dt = t & 3;
     if constexpr (dt < kDT) {
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         const shortx4 raw = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_s4*)(vbuf + (sub * 32 + ks * 16 + hf * 4) * kRowBytes + voff[dt]));
+            lds_at<shortx4>(vptr[dt], vbo + (sub * 32 + ks * 16 + hf * 4) * kRowBytes));
         const bf16x4 h4 = __builtin_bit_cast(bf16x4, raw);
         dst[hf * 4 + 0] = h4[0]; dst[hf * 4 + 1] = h4[1]; dst[hf * 4 + 2] = h4[2]; dst[hf * 4 + 3] = h4[3];
       }
     }
   };
   auto read_early = [&](int vbo) __attribute__((always_inline)) {
-    static_for<kAhead>([&](auto t_c) __attribute__((always_inline)) { read_v_operand(v_lds[0] + vbo + sub_bytes, t_c, early[decltype(t_c)::value]); });
+    static_for<kAhead>([&](auto t_c) __attribute__((always_inline)) { read_v_operand(vbo, t_c, early[decltype(t_c)::value]); });
   };
   auto matrix_phase = [&](auto first_c, auto last_c, int kbo, int vbo, auto&& piece) __attribute__((always_inline)) {
     constexpr int T0 = decltype(first_c)::value, T1 = decltype(last_c)::value;
-    const unsigned char* kbuf = k_lds[0] + kbo + sub_bytes;    // byte offsets of the ring slots
-    const unsigned char* vbuf = v_lds[0] + vbo + sub_bytes;
     bf16x8 ops[kSteps];
     auto fetch = [&](auto t_c) __attribute__((always_inline)) {
       constexpr int t = decltype(t_c)::value;
       if constexpr (t < kPvSteps) {
-        read_v_operand(vbuf, t_c, ops[t]);
+        read_v_operand(vbo, t_c, ops[t]);
       } else {
         constexpr int u = t - kPvSteps, kk = u / kSubs, sub = u % kSubs;
-        if constexpr (kk < kKK) ops[t] = *(const bf16x8*)(kbuf + sub * 32 * kRowBytes + koff[kk]);
+        if constexpr (kk < kKK) ops[t] = *lds_at<const bf16x8>(kptr[kk], kbo + sub * 32 * kRowBytes);
       }
     };
     auto fire = [&](auto t_c) __attribute__((always_inline)) {
@@ -568,7 +586,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   //   FP8 pools:  s is the raw product with the codes; per page sc = K scale times the softmax scale and
   //               ad = log2(V scale) - reference, so p' = 2^(s * sc + ad) = p * vs is the weight the second
   //               product needs, and the row sum takes each page's share divided by vs again.
-  // The reference m_run of a row only moves when it has to.  The exponentials are taken against the
+  // The reference of a row only moves when it has to.  The exponentials are taken against the
   // reference as it stands, without looking for the block's maximum first, and may exceed one: float
   // sums and bf16 P hold large values with the same relative precision as small ones.  Only when the p
   // of one lane add up to more than kSumLimit (so that no single p ever exceeds it), or when a row has no
@@ -600,14 +618,14 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
           if (tok > my_pos) s[sub][i] = -INFINITY;
         }
     }
-    const float m_old = (m_run == -INFINITY) ? 0.f : m_run;   // what the exponents in s (bf16 pools) are relative to
+    const float m_old = m_ref;                         // what the exponents in s (bf16 pools) are relative to
     float p[kSubs][16];
     // exponentials of the block against reference m_old + shift, and this lane's share of the row sums
     auto exponentials = [&](auto first_c, float shift) __attribute__((always_inline)) -> float {
       float ad[kPg], psum[kPg];
       if constexpr (FP8) {
 #pragma unroll
-        for (int pg = 0; pg < kPg; ++pg) ad[pg] = lvs[pg] - (m_old + shift);
+        for (int pg = 0; pg < kPg; ++pg) ad[pg] = lvs[pg] - (decltype(first_c)::value ? m_old : m_old + shift);
       }
 #pragma unroll
       for (int sub = 0; sub < kSubs; ++sub)
@@ -628,8 +646,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     };
     float lane_sum = exponentials(std::true_type{}, 0.f);
     // (an infinite or undefined sum also fails the comparison and takes the slow path)
-    const bool bump = row_ok && (m_run == -INFINITY || !(lane_sum <= kSumLimit));
-    if (__builtin_amdgcn_ballot_w64(bump)) {
+    if (__builtin_amdgcn_ballot_w64(!(lane_sum <= sum_limit))) {
       // largest exponent of the block: FP8 page scales and the softmax scale are positive here, so the maximum
       // can be taken on the raw products of each page
       float pm[kPg];
@@ -645,6 +662,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       if constexpr (kPg == 2) mloc = FP8 ? fmaxf(pm[0] * sc[0], pm[1] * sc[1]) : fmaxf(pm[0], pm[1]) + m_old;
       else if constexpr (FP8) mloc = fmaxf(fmaxf(pm[0] * sc[0], pm[1] * sc[1]), fmaxf(pm[2] * sc[2], pm[3] * sc[3]));
       else mloc = fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])) + m_old;
+      const float m_run = seen_max();
       const float m_new = fmaxf(m_run, xor32_max(mloc));           // the same in both lanes of a row
       const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;     // rows that see nothing yet
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
@@ -653,7 +671,8 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[dt][i] *= alpha;
-      m_run = m_new;
+      m_ref = m_safe;
+      if (row_ok && m_new != -INFINITY) sum_limit = kSumLimit;
       if constexpr (!FP8) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) negm[i] = -m_safe;
@@ -697,8 +716,6 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // direct loads are awaited by count where they are issued.
 #define BARRIER_RAW() do { if (FP8) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); else asm volatile("s_barrier" ::: "memory"); } while (0)
 #define PHASE_END() do { __builtin_amdgcn_sched_barrier(0); BARRIER_RAW(); __builtin_amdgcn_sched_barrier(0); } while (0)
-  constexpr std::integral_constant<int, 0> even{};
-  constexpr std::integral_constant<int, 1> odd{};
   constexpr std::integral_constant<int, kPvSteps> c_pv{};   // first step of the first product
   constexpr std::integral_constant<int, kSteps> c_end{};     // end of the phase
   // Page ids run ahead of the tile loads, so that no load ever waits for an address: U = i + kLead being
@@ -706,44 +723,56 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // phase) the tile offsets of block U and pid_new the page ids of block U + 1.
   constexpr int kLead = 2;
   size_t toff[2][kLoads];      // rotated at the start of the staging step: then [0] is K block U + 1, [1] V block U
-  int pid_new[kLoads];         // not yet turned into an offset
-  // ko[d]: byte offset of the ring slot of block i + d (i = the block whose matrix phase came
-  // last); block i - 1 shares the slot of block i + kRing - 1.
-  int ko[kRing];
-#pragma unroll
-  for (int d = 0; d < kRing; ++d) ko[d] = d * kTileBytes;
-  unsigned int kraw[kPg], vraw[kPg];
+  bool is_last[2][kLoads];     // ... whose page is the last live one
+  int pid_new[kLoads], at_new[kLoads];   // not yet turned into an offset
   {
-    int h0[kLoads], h1[kLoads], h2[kLoads], h3[kLoads];
-    fetch_pids(0, h0); fetch_pids(1, h1); fetch_pids(2, h2); fetch_pids(3, h3);
-    fetch_spids(0);
-    load_scales();
-    fetch_spids(1);
+    int h[4][kLoads], at[4][kLoads];
+    size_t off[4][kLoads];
+    bool end[4][kLoads];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) fetch_pids(h[d], at[d]);
+    if constexpr (FP8) {
+      if (wave == 0) window_ids(0);
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) { off[d][j] = tile_off_of(h[d][j]); end[d][j] = at[d][j] == page_live; }
     if constexpr (FP8) {
       // K block 0 goes to LDS here; units 0 and 1 wait in registers
       uintx4 k0[kLoads];
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
         if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
-          const TileAddr ka = tile_addr(a.k_pages, 0, 0, tile_off_of(h0[j]), j);
+          const TileAddr ka = tile_addr(a.k_pages, 0, off[0][j], end[0][j], j);
           k0[j] = load16<ONCE>(ka.base + ka.off);
         }
-      issue(0, h1, h0, even);
-      issue(1, h2, h1, odd);
+#pragma unroll
+      for (int u = 0; u < kLead; ++u)
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j)
+          if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
+            const TileAddr ka = tile_addr(a.k_pages, 0, off[u + 1][j], end[u + 1][j], j), va = tile_addr(a.v_pages, 1, off[u][j], end[u][j], j);
+            kreg[u][j] = load16<ONCE>(ka.base + ka.off);
+            vreg[u][j] = load16<ONCE>(va.base + va.off);
+          }
+      if (wave == 0) {
+        window_scales();
+        window_write(0);
+      }
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
-        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) put(k_lds[0], woff[j][0], k0[j]);
+        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) put(wptr[j][0], wptr[j][1], 0, k0[j]);
     } else {
-      const int* hh[4] = {h0, h1, h2, h3};
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
-        dma(tile_addr(a.k_pages, 0, 0, tile_off_of(h0[j]), j), k_lds[0] + wave * 1024 + j * kThreads * 16);
+        dma(tile_addr(a.k_pages, 0, off[0][j], end[0][j], j), k_lds[0] + wave * 1024 + j * kThreads * 16);
 #pragma unroll
-      for (int u0 = 0; u0 < kLead; ++u0)             // units 0 .. kLead - 1
+      for (int u = 0; u < kLead; ++u)                // units 0 .. kLead - 1
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) {
-          dma(tile_addr(a.k_pages, 0, u0 + 1, tile_off_of(hh[u0 + 1][j]), j), k_lds[0] + (u0 + 1) * kTileBytes + wave * 1024 + j * kThreads * 16);
-          dma(tile_addr(a.v_pages, 1, u0, tile_off_of(hh[u0][j]), j), v_lds[0] + u0 * kTileBytes + wave * 1024 + j * kThreads * 16);
+          dma(tile_addr(a.k_pages, 0, off[u + 1][j], end[u + 1][j], j), k_lds[0] + (u + 1) * kTileBytes + wave * 1024 + j * kThreads * 16);
+          dma(tile_addr(a.v_pages, 1, off[u][j], end[u][j], j), v_lds[0] + u * kTileBytes + wave * 1024 + j * kThreads * 16);
         }
       // the query rows have been under way since the top of the kernel; their scaling (bf16 pools: the
       // scores then leave the matrix core as exponents) waits for them here, behind the tile loads
@@ -759,35 +788,55 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     }
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      pid_new[j] = h3[j];
-      toff[0][j] = tile_off_of(h2[j]);
+      pid_new[j] = h[3][j];
+      at_new[j] = at[3][j];
+      toff[0][j] = off[2][j];
+      is_last[0][j] = end[2][j];
     }
   }
   // Staging.  The tile addresses of the unit whose loads start in this vector phase:
   auto stage_addresses = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) { toff[1][j] = toff[0][j]; toff[0][j] = tile_off_of(pid_new[j]); }
+    for (int j = 0; j < kLoads; ++j) {
+      toff[1][j] = toff[0][j];
+      is_last[1][j] = is_last[0][j];
+      toff[0][j] = tile_off_of(pid_new[j]);
+      is_last[0][j] = at_new[j] == page_live;
+    }
   };
-  // ... those loads, in the vector phase of block i (slot: the register slot that the matrix phase of block
-  // i has just drained, FP8 only) ...
-  auto stage_loads = [&](int i, auto slot_c) __attribute__((always_inline)) {
-    const int u = i + kLead;
-    if constexpr (FP8) {
-      constexpr int slot = decltype(slot_c)::value;
+  // Byte offset of the ring slot of block i + d, block i - 1 sharing that of block i + kRing - 1.  The loop is unrolled twice
+  // (slot_c: i % 2 from here on): a ring of two needs no variable, the offset goes into the LDS instructions as it is.
+  int ko[kRing];
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        // (units past the tile's last block are not loaded: what the registers then hold is widened into tiles nobody reads)
-        if (u <= last_blk && (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens)) {
-          const TileAddr ka = tile_addr(a.k_pages, 0, u + 1, toff[0][j], j), va = tile_addr(a.v_pages, 1, u, toff[1][j], j);
+  for (int d = 0; d < kRing; ++d) ko[d] = d * kTileBytes;
+  auto ring = [&](auto slot_c, auto d_c) __attribute__((always_inline)) -> int {
+    constexpr int slot = decltype(slot_c)::value, d = (decltype(d_c)::value + kRing) % kRing;
+    if constexpr (kRing == 2) return (slot + d) % 2 * kTileBytes;
+    else return ko[d];
+  };
+  constexpr std::integral_constant<int, 1> c1{};
+  constexpr std::integral_constant<int, 2> c2{};
+  constexpr std::integral_constant<int, -1> cm1{};
+  // ... those loads, in the vector phase of block i (FP8: into the register slot that the matrix phase of block
+  // i has just drained) ...
+  auto stage_loads = [&](int i, auto slot_c) __attribute__((always_inline)) {
+    constexpr int slot = decltype(slot_c)::value;
+    if constexpr (FP8) {
+      // (units past the tile's last block are loaded as well, the last block once more, and widened into tiles nobody reads:
+      // a branch around them would have every wait for an earlier unit wait for this one too, since on the other way round
+      // the branch nothing follows the earlier unit)
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j)
+        if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
+          const TileAddr ka = tile_addr(a.k_pages, 0, toff[0][j], is_last[0][j], j), va = tile_addr(a.v_pages, 1, toff[1][j], is_last[1][j], j);
           kreg[slot][j] = load16<ONCE>(ka.base + ka.off);
           vreg[slot][j] = load16<ONCE>(va.base + va.off);
         }
-      }
-    } else if (u <= last_blk) {
+    } else if (i + kLead <= last_blk) {
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
-        dma(tile_addr(a.k_pages, 0, u + 1, toff[0][j], j), k_lds[0] + ko[kRing - 1] + wave * 1024 + j * kThreads * 16);
-        dma(tile_addr(a.v_pages, 1, u, toff[1][j], j), v_lds[0] + ko[kRing - 2] + wave * 1024 + j * kThreads * 16);
+        dma(tile_addr(a.k_pages, 0, toff[0][j], is_last[0][j], j), k_lds[0] + ring(slot_c, cm1) + wave * 1024 + j * kThreads * 16);
+        dma(tile_addr(a.v_pages, 1, toff[1][j], is_last[1][j], j), v_lds[0] + ring(slot_c, c2) + wave * 1024 + j * kThreads * 16);
       }
       DMA_WAIT(2 * kLoads);                          // everything but the unit just started has landed
     } else {
@@ -802,95 +851,87 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
         const bool mine = kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens;
-        if (pos == 2 + 12 * j / kLoads && mine) put(k_lds[0] + ko[1], woff[j][0], kreg[slot][j]);
-        if (pos == 6 + 12 * j / kLoads && mine) put(v_lds[0] + ko[0], woff[j][1], vreg[slot][j]);
+        if (pos == 2 + 12 * j / kLoads && mine) put(wptr[j][0], wptr[j][1], ring(slot_c, c1), kreg[slot][j]);
+        if (pos == 6 + 12 * j / kLoads && mine) put(wptr[j][2], wptr[j][2] + 16, ring(slot_c, c0), vreg[slot][j]);
       }
     }
   };
-  // Scalar loads (page ids of the unit started two vector phases from now, FP8 page scales of the next
-  // block) go out before the softmax and are awaited after it.
-  auto scalar_issue = [&](int i) __attribute__((always_inline)) {
-    fetch_pids(i + kLead + 2, pid_new);
-    if constexpr (FP8) {
-      // scales of block i + 1: all loads in one statement, so that each keeps a register of its
-      // own (the compiler would recycle one register and wait after every load)
-      if constexpr (kPg == 2)
-        asm volatile(
-            "s_load_dword %0, %4, %6\n\ts_load_dword %1, %4, %7\n\ts_load_dword %2, %5, %6\n\ts_load_dword %3, %5, %7"
-            : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(vraw[0]), "=&s"(vraw[1])
-            : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u));
-      else
-        asm volatile(
-            "s_load_dword %0, %8, %10\n\ts_load_dword %1, %8, %11\n\ts_load_dword %2, %8, %12\n\ts_load_dword %3, %8, %13\n\t"
-            "s_load_dword %4, %9, %10\n\ts_load_dword %5, %9, %11\n\ts_load_dword %6, %9, %12\n\ts_load_dword %7, %9, %13"
-            : "=&s"(kraw[0]), "=&s"(kraw[1]), "=&s"(kraw[2 % kPg]), "=&s"(kraw[3 % kPg]), "=&s"(vraw[0]), "=&s"(vraw[1]), "=&s"(vraw[2 % kPg]), "=&s"(vraw[3 % kPg])
-            : "s"(a.k_scale), "s"(a.v_scale), "s"((unsigned)spid[0] * 4u), "s"((unsigned)spid[1] * 4u), "s"((unsigned)spid[2 % kPg] * 4u),
-              "s"((unsigned)spid[3 % kPg] * 4u));
-      fetch_spids(i + 2);
-    }
-  };
-  auto scalar_await = [&]() __attribute__((always_inline)) {
+  // The page ids of the unit started two vector phases from now go out before the softmax and are awaited after it.
+  auto ids_await = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) { pid_new[j] = __builtin_amdgcn_readfirstlane(pid_new[j]); asm volatile("" : "+s"(pid_new[j])); }   // arrived here, not wherever it is used next
-    if constexpr (FP8) {
-      if constexpr (kPg == 2)
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(vraw[0]), "+s"(vraw[1]));
-      else
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+s"(kraw[0]), "+s"(kraw[1]), "+s"(kraw[2 % kPg]), "+s"(kraw[3 % kPg]), "+s"(vraw[0]), "+s"(vraw[1]), "+s"(vraw[2 % kPg]), "+s"(vraw[3 % kPg]));
-#pragma unroll
-      for (int p = 0; p < kPg; ++p) {
-        spid[p] = __builtin_amdgcn_readfirstlane(spid[p]);
-        asm volatile("" : "+s"(spid[p]));
-        ksc_cur[p] = __uint_as_float(kraw[p]) * a.scale_log2;   // the softmax of this block is done with the old ones
-        lvs_cur[p] = __builtin_amdgcn_logf(__uint_as_float(vraw[p]));
-        ivs_cur[p] = __builtin_amdgcn_rcpf(__uint_as_float(vraw[p]));
-      }
-    }
   };
-  auto next_block = [&]() __attribute__((always_inline)) {
-    const int t = ko[0];
-#pragma unroll
-    for (int d = 0; d + 1 < kRing; ++d) ko[d] = ko[d + 1];
-    ko[kRing - 1] = t;
+  // FP8: the next window's page scales, in three steps a few blocks apart, in wave 0 (whose rows are never all past the end).
+  // A window is written two blocks before its first use at the latest, and a whole window after the last read of what was
+  // in its place.
+  auto fill_scales = [&](int i) __attribute__((always_inline)) {
+    if (wave == 0) {
+      const int step = i % kWindowBlocks, next = i - step + kWindowBlocks;
+      if (step == 2) window_ids(next);
+      else if (step == 2 + kWindowBlocks / 4) window_scales();
+      else if (step == 2 + kWindowBlocks / 2) window_write(next);
+    }
   };
   // A wave whose 32 rows all lie past the tile's last row (ragged last tile of a chunk, or a group
   // call with few rows) keeps its share of the staging and every barrier but skips the products and
   // the softmax: it would only compete with the wave it shares a SIMD with.
   auto run = [&](auto active_c) __attribute__((always_inline)) {
     constexpr bool kActive = decltype(active_c)::value;
-    // slot: parity of the block, the register slot of the unit that is widened and reloaded (FP8)
-    auto matrix = [&](auto first_c, auto last_c, auto slot_c) __attribute__((always_inline)) {
-      auto piece = [&](auto pos_c) __attribute__((always_inline)) { stage_widen(slot_c, pos_c); };
+    auto block = [&](int i, auto first_c, auto slot_c) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_c)::value;
+      // the pointers could be others in every block, as far as the compiler can tell: it would keep each sum of one and an
+      // offset in a register of its own, two hundred of them, instead of using the offset as it is
+#pragma unroll
+      for (int kk = 0; kk < kKK; ++kk) asm volatile("" : "+v"(kptr[kk]));
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt) asm volatile("" : "+v"(vptr[dt]));
+      if constexpr (FP8) {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) asm volatile("" : "+v"(wptr[j][0]), "+v"(wptr[j][1]), "+v"(wptr[j][2]));
+      }
+      auto piece = [&](auto pos_c) __attribute__((always_inline)) {
+        stage_widen(slot_c, pos_c);
+        if constexpr (FP8 && kActive && decltype(pos_c)::value == 24) read_scales(i);
+      };
       if constexpr (kActive) {
         __builtin_amdgcn_s_setprio(1);
-        matrix_phase(first_c, last_c, ko[0], ko[kRing - 1], piece);
+        matrix_phase(first_c, c_end, ring(slot_c, c0), ring(slot_c, cm1), piece);
         __builtin_amdgcn_s_setprio(0);
       } else {
         static_for<32>(piece);
       }
       PHASE_END();
-    };
-    auto vector = [&](int i, auto slot_c) __attribute__((always_inline)) {
       stage_addresses();
+      if constexpr (FP8 && kActive && slot == 0) fill_scales(i);
       stage_loads(i, slot_c);
-      scalar_issue(i);
+      fetch_pids(pid_new, at_new);
       if constexpr (kActive) softmax(i);
-      scalar_await();
-      if constexpr (kEarly && kActive) read_early(ko[0]);   // V block i, for the matrix phase that follows
+      ids_await();
+      if constexpr (kEarly && kActive) read_early(ring(slot_c, c0));   // V block i, for the matrix phase that follows
       PHASE_END();
-      next_block();
+      const int t = ko[0];
+#pragma unroll
+      for (int d = 0; d + 1 < kRing; ++d) ko[d] = ko[d + 1];
+      ko[kRing - 1] = t;
     };
-    matrix(c_pv, c_end, even);                          // block 0 has no predecessor: scores only
-    vector(0, even);
-    for (int i = 1; i < n_blocks; i += 2) {
-      matrix(c0, c_end, odd);
-      vector(i, odd);
-      if (i + 1 < n_blocks) {
-        matrix(c0, c_end, even);
-        vector(i + 1, even);
+    if constexpr (FP8 && !kActive) {
+      // nothing of this side is worked out in front of the branch and kept in registers over the other side's loop
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        asm volatile("" : "+v"(kreg[0][j]), "+v"(vreg[0][j]), "+v"(kreg[1][j]), "+v"(vreg[1][j]));
+#pragma unroll
+        for (int pool = 0; pool < 2; ++pool) asm volatile("" : "+v"(goff[j][pool]), "+v"(goff_last[j][pool]));
       }
     }
+    block(0, c_pv, c0);                                 // block 0 has no predecessor: scores only
+    // (two blocks at a time and the odd one behind the loop: on a way through the loop from an odd block to the next odd one,
+    // the loads of the even block between them would be missing, and the waits by count would have to do with fewer)
+    int i = 1;
+    for (; i + 1 < n_blocks; i += 2) {
+      block(i, c0, c1);
+      block(i + 1, c0, c0);
+    }
+    if (i < n_blocks) block(i, c0, c1);
     if constexpr (kActive) {
       __builtin_amdgcn_s_setprio(1);
       matrix_phase(c0, c_pv, 0, ko[kRing - 1], [](auto) {});
@@ -898,6 +939,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     }
   };
   if (wave_active) run(std::true_type{}); else run(std::false_type{});
+  float m_run = seen_max();
   float* const mine = Geo::kMergeApart ? merge_acc_s[Geo::kMergeApart ? (wave & 3) : 0] : (float*)&k_lds[0][0] + (wave & 3) * kMergeAcc;   // HALF only
   float* const mine_ml = merge_ml_s[HALF ? (wave & 3) : 0];
   if constexpr (HALF) {
