@@ -315,14 +315,18 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   d.ctx_lens = ctx_lens; d.q_lens = q_lens; d.batch = desc->batch; d.rows_per_b = w.rows_per_b;
   // (the launch has w.workers workers whatever the partition is cut for: the others get a record without blocks)
   d.workers = plan_workers(w); d.slots = w.workers;
+  // (whole rows instead, where the plan says so: not where the number of workers is forced, and not for so many rows that
+  // a grid could not have a worker for each)
+  d.whole_late = desc->kv_dtype == ROLLATTN_FP8_E4M3 ? kWholeLateFp8 : kWholeLate;
+  a.whole_rows = desc->q_dtype != ROLLATTN_F32 && d.workers == w.workers && (int64_t)desc->batch * w.rows_per_b <= 16 * (int64_t)kWholeRows;
   if (desc->q_dtype != ROLLATTN_F32) d.page_table = page_table;
   d.max_pages = desc->max_pages_per_seq; d.num_pages = desc->num_pages; d.head_tiles = w.rows_per_b > desc->num_kv_heads;
   d.header = (int32_t*)(base + w.header); d.prefix = (int32_t*)(base + w.prefix); d.wstart = (int32_t*)(base + w.wstart);
   return ROLLATTN_OK;
 }
 
-// The launches behind the plan.  shared: the other half of attn_decode_shared, folded in by the merge.
-static int decode_launch(const rollattn_desc* desc, const DecodeArgs& a, hipStream_t s, const SharedHalf* shared = nullptr) {
+// The launches behind the plan.
+static int decode_launch(const rollattn_desc* desc, const DecodeArgs& a, hipStream_t s) {
   const bool f32 = desc->q_dtype == ROLLATTN_F32;
   hipError_t e;
   {
@@ -330,12 +334,13 @@ static int decode_launch(const rollattn_desc* desc, const DecodeArgs& a, hipStre
     if (f32) {
       e = launch_decode_f32(a, desc->head_dim, kF32DecodeWgs, s);
     } else {
-      e = launch_decode_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3, kMfmaDecodeWgs, s);
+      e = launch_decode_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3,
+                             a.whole_rows ? std::max(kMfmaDecodeWgs, (a.batch * a.rows_per_b + 3) / 4) : kMfmaDecodeWgs, s);
     }
     prof.stop();
   }
   if (e != hipSuccess) return fail_hip(e);
-  e = shared ? launch_combine_shared(a, *shared, desc->head_dim, s) : launch_combine(a, desc->head_dim, !f32, s);
+  e = a.shared.result ? launch_combine_shared(a, desc->head_dim, s) : launch_combine(a, desc->head_dim, !f32, s);
   if (e != hipSuccess) return fail_hip(e);
   return ROLLATTN_OK;
 }
@@ -358,6 +363,7 @@ static int decode_impl(const rollattn_desc* desc, const void* q, const void* k_p
                          : desc->batch <= kWavePlanBatch;
   if (alone) {
     call.args.plan = call.plan;
+    call.args.whole_rows = 0;
   } else {
     const hipError_t e = launch_plan_decode(call.plan, s);
     if (e != hipSuccess) return fail_hip(e);
@@ -749,8 +755,8 @@ int attn_decode_shared(const rollattn_desc* desc, const void* q, const void* k_p
   if (e != hipSuccess) return fail_hip(e);
   rc = append_launch(&L.grp, app, s);
   if (rc) return rc;
-  const SharedHalf shared{base + L.o1, (const float*)(base + L.d1), out};
-  return decode_launch(desc, dec.args, s, &shared);
+  dec.args.shared = SharedHalf{base + L.o1, (const float*)(base + L.d1), out};
+  return decode_launch(desc, dec.args, s);
 }
 
 int kv_write(const rollattn_desc* desc, const void* k_new, const void* v_new, const int32_t* q_lens,

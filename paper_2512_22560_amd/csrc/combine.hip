@@ -43,37 +43,49 @@ __device__ __forceinline__ floatx4 widen(const bf16x4 x) { return floatx4{(float
 // the weight 2^d of its denominator, and every row is written: one that a single worker finished is read back as a piece.
 // The merge of the two halves as a launch of its own cost 8 us of a 268 us step and rounded split rows to bf16 in between.
 template <int D, bool OUT_BF16, bool SHARED, bool TOGETHER>
-__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, const SharedHalf other, int chunks_per_row) {
+__global__ __launch_bounds__(kThreads) void combine_kernel(const DecodeArgs a, int chunks_per_row) {
   __shared__ __attribute__((aligned(16))) float sum_s[TOGETHER ? kWaves : 1][64][4];
   __shared__ float ml_s[TOGETHER ? kWaves : 1][64][2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int unit = TOGETHER ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + wave);
+  // What decides whether there is anything to do comes in two trips to memory, the arguments and then what they point to, and not
+  // in one trip per question.
+  const int32_t* q_lens = a.q_lens;
+  const int32_t* q_offsets = a.q_offsets;
+  const int32_t *header = a.header, *prefix = a.prefix;
+  const float *partial_ml = a.partial_ml, *partial_o = a.partial_o;
+  const int batch = a.batch, rows_per_b = a.rows_per_b, hkv = a.hkv, hq = a.hq, ht = a.head_tile, group = a.group, may_be_whole = a.whole_rows;
+  asm volatile("" ::"s"(q_lens), "s"(q_offsets), "s"(header), "s"(prefix), "s"(partial_ml), "s"(partial_o), "s"(batch), "s"(rows_per_b), "s"(hkv), "s"(hq), "s"(ht),
+               "s"(group), "s"(may_be_whole), "s"(chunks_per_row));
   const int row = unit / chunks_per_row, c = unit - row * chunks_per_row;
-  const int b = row / a.rows_per_b, r = row - b * a.rows_per_b;
-  if (b >= a.batch) return;
-  if (a.q_lens && a.q_lens[b] != 1) return;                 // mixed step: not a decode row, nothing of ours to write
-  const int ht = a.head_tile;
-  const int n_ht = a.rows_per_b / a.hkv;
+  const int b = row / rows_per_b, r = row - b * rows_per_b;
+  if (b >= batch) return;
+  const int per = header[kPlanPer], whole = may_be_whole & header[kPlanWhole];
+  const int first = prefix[b], end = prefix[b + 1];
+  const int new_rows = q_lens ? q_lens[b] : 1, row0 = q_offsets ? q_offsets[b] : b;
+  asm volatile("" ::"s"(per), "s"(whole), "s"(first), "s"(end), "s"(new_rows), "s"(row0));
+  if (new_rows != 1) return;                                // mixed step: not a decode row, nothing of ours to write
+  const int n_ht = rows_per_b / hkv;
   const int g = r / n_ht, h0 = (r - g * n_ht) * ht;
-  const int heads = min(ht, a.group - h0);
+  const int heads = min(ht, group - h0);
   if (c * kChunkFloats >= heads * D) return;                // (a row's last tile of heads may have fewer chunks)
-  const int per = a.header[kPlanPer];
-  const int first = a.prefix[b];
-  const int n = a.prefix[b + 1] - first;
-  const long r0 = (long)a.rows_per_b * first + (long)r * n;
+  const SharedHalf& other = a.shared;
+  const int n = end - first;
+  if (whole && n) return;                                   // its worker has written it
+  const long r0 = (long)rows_per_b * first + (long)r * n;
   const int wf = n ? (int)(r0 / per) : 0;
   const int wl = n ? (int)((r0 + n - 1) / per) : 0;
   if (!SHARED && n && wf == wl) return;                     // one worker had the whole row
   const int pieces = n ? wl - wf + 1 : 0;
   const int first_slot = ((long)wf * per < r0) ? 1 : 0;
-  const size_t orow0 = (size_t)(a.q_offsets ? a.q_offsets[b] : b) * a.hq + (size_t)g * a.group + h0;   // where the row's first head goes
+  const size_t orow0 = (size_t)row0 * hq + (size_t)g * group + h0;   // where the row's first head goes
   const bool dealt = pieces > kAlone;                       // to four sums
   if (TOGETHER && !dealt && wave != 0) return;
   const int at = c * kChunkFloats + lane * 4;               // first of this lane's floats within a partial
   const int head = at / D;
   const bool ok = head < heads;                             // (the last chunk of an odd number of heads is not full)
-  const float* po = a.partial_o + (ok ? at : 0);
-  const float* pml = a.partial_ml + (ok ? head : 0) * 2;
+  const float* po = partial_o + (ok ? at : 0);
+  const float* pml = partial_ml + (ok ? head : 0) * 2;
   floatx4 o = {0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
   const int step = dealt ? kWaves : 1;
@@ -251,7 +263,7 @@ hipError_t launch_check_inputs(const int32_t* page_table, const int32_t* ctx_len
 
 namespace {
 template <bool SHARED>
-hipError_t launch(const DecodeArgs& a, const SharedHalf& shared, int head_dim, bool out_bf16, hipStream_t s) {
+hipError_t launch(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s) {
   const int chunks = (std::min(a.head_tile, a.group) * head_dim + kChunkFloats - 1) / kChunkFloats;
   const long units = (long)a.batch * a.rows_per_b * chunks;
   // A workgroup per chunk while those are few enough to be resident at once, so that the waves of a row of many pieces
@@ -260,7 +272,7 @@ hipError_t launch(const DecodeArgs& a, const SharedHalf& shared, int head_dim, b
   const bool together = units <= kCombineResident;
   const dim3 grid((unsigned)(together ? units : (units + kWaves - 1) / kWaves));
   auto go = [&](auto d, auto bf16, auto tog) {
-    hipLaunchKernelGGL((combine_kernel<decltype(d)::value, decltype(bf16)::value, SHARED, decltype(tog)::value>), grid, dim3(kThreads), 0, s, a, shared, chunks);
+    hipLaunchKernelGGL((combine_kernel<decltype(d)::value, decltype(bf16)::value, SHARED, decltype(tog)::value>), grid, dim3(kThreads), 0, s, a, chunks);
   };
   auto with_dim = [&](auto bf16, auto tog) {
     if (head_dim == 128) go(std::integral_constant<int, 128>{}, bf16, tog);
@@ -279,11 +291,11 @@ hipError_t launch(const DecodeArgs& a, const SharedHalf& shared, int head_dim, b
 }  // namespace
 
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s) {
-  return launch<false>(a, SharedHalf{}, head_dim, out_bf16, s);
+  return launch<false>(a, head_dim, out_bf16, s);
 }
 
-hipError_t launch_combine_shared(const DecodeArgs& a, const SharedHalf& shared, int head_dim, hipStream_t s) {
-  return launch<true>(a, shared, head_dim, /*out_bf16=*/true, s);
+hipError_t launch_combine_shared(const DecodeArgs& a, int head_dim, hipStream_t s) {
+  return launch<true>(a, head_dim, /*out_bf16=*/true, s);
 }
 
 hipError_t launch_gather(const void* pages, const int32_t* page_table, const int32_t* ctx_lens, int32_t b,

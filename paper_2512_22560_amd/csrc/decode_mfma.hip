@@ -11,9 +11,13 @@
 //   O^T += V^T P^T       (dims x heads, V read back transposed with ds_read_b64_tr_*)
 // A run that covers a whole row writes the row's output itself; a run that starts or ends
 // inside a row leaves an un-normalised partial (max, sum, O) for the merge kernel.
+// Where rows are many and none much longer than a run, the plan says so and a worker takes a row instead (rows_stay_whole in
+// plan_device.h): no partials, and in attn_decode_shared the shared half is folded in here as well.
 // The transposed products keep "head" on the lane axis in both results, so the online
 // softmax state (running max, running sum, rescale factor) is one scalar per lane and P
 // feeds the second product straight from the first one's accumulator registers.
+#include <type_traits>
+
 #include "plan_device.h"
 
 namespace rollattn {
@@ -98,8 +102,9 @@ __device__ __forceinline__ uint4 load16(const unsigned char* p) {
   return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
-template <int D, bool FP8, bool STREAM>
-__device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, unsigned char* const k_lds) {
+// WHOLE: rows may be whole ones whose shared part is folded in here (fold_shared).
+template <int D, bool FP8, bool STREAM, bool WHOLE>
+__device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, bool fold_shared, unsigned char* const k_lds) {
   using G_ = Geo<D, FP8>;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));   // (what is worked out from it stays in this instance: shared by both in front of the branch, it would not fit the registers)
@@ -248,9 +253,11 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
     const bool head_ok = h0 + r16 < group;
     if (seg_first_blk == 0 && cc.blk == cc.n - 1) {
       // the whole row was ours: normalise and store
-      const float inv = 1.f / l_tot;
       const size_t orow = row_of(cc.b) * a.hq + (size_t)g * group + h0 + r16;
-      __bf16* dst = (__bf16*)a.out + orow * D + q4 * 4;
+      const float inv = 1.f / l_tot;
+      int at = q4 * 4;
+      asm volatile("" : "+v"(at));             // (added to the row's address here, as below)
+      __bf16* dst = (__bf16*)a.out + orow * D + at;
       if (a.lse && head_ok && q4 == 0) a.lse[orow] = m_run + __builtin_amdgcn_logf(l_tot);
       if (head_ok) {
 #pragma unroll
@@ -264,7 +271,9 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
     } else {
       const size_t slot = (size_t)worker * 2 + (first_segment ? 0 : 1);
       if (head_ok) {
-        float* dst = a.partial_o + (slot * kMfmaHeadTile + r16) * D + q4 * 4;
+        int at = r16 * D + q4 * 4;
+        asm volatile("" : "+v"(at));           // (added to the slot's address here; a sum made in front of the loop would take registers in it)
+        float* dst = a.partial_o + slot * (kMfmaHeadTile * D) + at;
 #pragma unroll
         for (int dt = 0; dt < G_::kDT; ++dt) *(floatx4*)(dst + dt * 16) = acc[dt];
         if (q4 == 0) {
@@ -374,49 +383,90 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
         if (i + G_::kStages < n_mine) issue(st);   // the registers just drained take the next block
         if (i == 0 || cc.blk == 0) begin_segment();
         compute(kscale, vscale);
-        if (cc.blk == cc.n - 1 || i == n_mine - 1) end_segment();
+        if ((cc.blk == cc.n - 1 || i == n_mine - 1) && !(WHOLE && fold_shared)) end_segment();   // (its one row is finished behind the loop)
         if (i + 1 < n_mine) advance(cc);
+      }
+    }
+  }
+  if (WHOLE && fold_shared) {
+    // the private part of a row whose other part is there: both weighted by their denominators, as the merge would
+    int b = __builtin_amdgcn_readfirstlane(start.x), r = __builtin_amdgcn_readfirstlane(start.y) >> 20, tid = threadIdx.x;
+    asm volatile("" : "+s"(b), "+s"(r), "+v"(tid));   // (worked out again, so that nothing of it takes a register during the loop)
+    const int r16 = tid & 15, q4 = (tid >> 4) & 3;
+    const int g = r / n_ht;
+    const int h0 = (r - g * n_ht) * kMfmaHeadTile;
+    const float l_tot = xor32_add(xor16_add(l_run));
+    if (h0 + r16 < group) {
+      const size_t orow = (size_t)b * a.hq + (size_t)g * group + h0 + r16;
+      const __bf16* src = (const __bf16*)a.shared.out + orow * D + q4 * 4;
+      __bf16* dst = (__bf16*)a.shared.result + orow * D + q4 * 4;
+      bf16x4 o1[G_::kDT];
+#pragma unroll
+      for (int dt = 0; dt < G_::kDT; ++dt) o1[dt] = *(const bf16x4*)(src + dt * 16);
+      const float d1 = a.shared.lse[orow];
+      const float top = fmaxf(m_run, d1);
+      const float w1 = __builtin_amdgcn_exp2f(d1 - top), w2 = __builtin_amdgcn_exp2f(m_run - top);   // 2^-inf = 0
+      const float inv = 1.f / (w1 + w2 * l_tot);
+#pragma unroll
+      for (int dt = 0; dt < G_::kDT; ++dt) {
+        bf16x4 pk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((w1 * (float)o1[dt][e] + w2 * acc[dt][e]) * inv);
+        *(bf16x4*)(dst + dt * 16) = pk;
       }
     }
   }
 }
 
-template <int D, bool FP8>
+// IN_WAVE: no plan was launched, and rows are never whole.  (One kernel for both had 254 registers instead of 246 over bf16 pools
+// and took 0.3 us longer on a call of 30, 1 % on long ones.)
+template <int D, bool FP8, bool IN_WAVE>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeArgs a) {
   // Per wave: one K tile and one V tile.
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * Geo<D, FP8>::kTileBytes];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int worker = blockIdx.x * kWaves + wave;
   int4 start;
-  bool read_again = false;
-  if (a.plan.batch) {
+  bool read_again = false, whole = false;
+  if constexpr (IN_WAVE) {
     start = plan_decode_in_wave(a.plan, worker, &read_again);
   } else {
-    start = *(const int4*)(a.wstart + 4 * worker);
+    start = *(const int4*)(a.wstart + 4 * min(worker, kMfmaDecodeWgs * kWaves - 1));
+    whole = (a.header[kPlanWhole] & a.whole_rows) != 0;
     read_again = a.header[kPlanReadAgain] != 0;
+    if (whole) {
+      const int b = worker / a.rows_per_b, r = worker - b * a.rows_per_b, at = min(b, a.batch - 1);
+      const int len = a.ctx_lens[at], one = a.q_lens ? a.q_lens[at] : 1;
+      start = make_int4(b < a.batch && one == 1 && len > 0 ? b : -1, r << 20, len, (len + kBlockTokens - 1) / kBlockTokens);
+    } else if (worker >= kMfmaDecodeWgs * kWaves) {
+      return;
+    }
   }
   if (start.x < 0) return;
   // Where another worker reads some of the run's pages, too, it may find them in a cache, and the hint would cost that:
   // 64 groups of 8 behind 8192 common tokens, decoded without attn_decode_shared (64/4/128, FP8), 687 against 777 us; 32
   // query heads per KV head, two rows that read the same K and V (256 contexts, 32/1/128, bf16), 153 against 170 us.
-  if (read_again) decode_worker<D, FP8, false>(a, start, worker, lds[wave]);
-  else decode_worker<D, FP8, true>(a, start, worker, lds[wave]);
+  const bool fold_shared = whole && a.shared.result;
+  if (read_again) decode_worker<D, FP8, false, !IN_WAVE>(a, start, worker, fold_shared, lds[wave]);
+  else decode_worker<D, FP8, true, !IN_WAVE>(a, start, worker, fold_shared, lds[wave]);
 }
 
 }  // namespace
 
 hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int grid, hipStream_t s) {
-  if (head_dim == 128 && !fp8) {
-    hipLaunchKernelGGL((decode_mfma_kernel<128, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 128 && fp8) {
-    hipLaunchKernelGGL((decode_mfma_kernel<128, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && !fp8) {
-    hipLaunchKernelGGL((decode_mfma_kernel<64, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else if (head_dim == 64 && fp8) {
-    hipLaunchKernelGGL((decode_mfma_kernel<64, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  auto launch = [&](auto d, auto f) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool F = decltype(f)::value;
+    if (a.plan.batch) hipLaunchKernelGGL((decode_mfma_kernel<D, F, true>), dim3(grid), dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((decode_mfma_kernel<D, F, false>), dim3(grid), dim3(kThreads), 0, s, a);
+  };
+  std::integral_constant<int, 128> d128;
+  std::integral_constant<int, 64> d64;
+  if (head_dim == 128 && fp8) launch(d128, std::true_type{});
+  else if (head_dim == 128) launch(d128, std::false_type{});
+  else if (head_dim == 64 && fp8) launch(d64, std::true_type{});
+  else if (head_dim == 64) launch(d64, std::false_type{});
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

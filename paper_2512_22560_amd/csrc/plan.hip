@@ -7,21 +7,6 @@ namespace rollattn {
 
 namespace {
 
-__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), 63); }
-
-// Largest of one unsigned per lane, by the same steps (a step that has no source lane contributes zero).
-__device__ __forceinline__ unsigned wave_max(unsigned v) {
-  int x = (int)v;
-  auto step = [&](int other) { x = (int)max((unsigned)x, (unsigned)other); };
-  step(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
-  return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
-
 // With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
 __device__ __forceinline__ int decode_len(const DecodePlanArgs& a, int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; }
 __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds) {

@@ -17,6 +17,8 @@ constexpr int kMfmaHeadTile = 16;       // query heads per MFMA decode row
 constexpr int kF32DecodeWgs = 4 * kNumCUs;    // one workgroup-worker each
 constexpr int kF32HeadTile = 4;         // query heads per float32 decode row
 constexpr int kWavePlanBatch = 64;      // batches up to this size are planned by every decode wave for itself
+constexpr int kWholeLateFp8 = 16, kWholeLate = 10;   // MFMA decode: rows stay whole where the longest ends at most this many blocks late
+constexpr int kWholeRows = 1 << 20;     // ... and where there are no more than this
 constexpr int kDirectPages = 32;        // float32 contexts of at most this many pages are not cut
 constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pairs) per append workgroup
 constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
@@ -36,7 +38,7 @@ constexpr int split_extra_pieces(int hkv) { return 2 * kNumCUs / hkv; }   // app
 constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list that one XCD takes in a row (one per CU)
 
 // Header words of the plan, at the start of the workspace.
-enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5,
+enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5, kPlanWhole = 6,
                 kPlanReadAgain = 32,   // (written by another workgroup than the rest, in a cache line of its own)
                 kPlanWords = 64 };
 
@@ -72,9 +74,17 @@ struct DecodePlanArgs {
   int64_t num_pages;
   int32_t max_pages;
   bool head_tiles;                 // several rows per KV head: each reads its K and V
+  int32_t whole_late;              // blocks that the longest row may end behind the others for rows to stay whole
   int32_t* header;
   int32_t* prefix;
   int32_t* wstart;
+};
+
+// The shared half's result, which the private half's rows are folded into (attn_decode_shared; all null otherwise).
+struct SharedHalf {
+  const void* out;      // bf16 [B][Hq][D], normalised
+  const float* lse;     // [B][Hq]
+  void* result;         // where the whole rows go
 };
 
 // Kernel arguments (passed by value).
@@ -103,13 +113,8 @@ struct DecodeArgs {
   const int32_t* first_page;
   // Set (batch > 0) where no plan was launched: the decode kernel plans for itself.
   DecodePlanArgs plan;
-};
-
-// The shared half's result, which the merge of the private half's rows folds in (attn_decode_shared; all null otherwise).
-struct SharedHalf {
-  const void* out;      // bf16 [B][Hq][D], normalised
-  const float* lse;     // [B][Hq]
-  void* result;         // where the whole rows go
+  int32_t whole_rows;   // 1: the plan may say that every row is one worker's (kPlanWhole); the launch has a worker for each then
+  SharedHalf shared;
 };
 
 struct AppendArgs {
@@ -178,8 +183,8 @@ hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, int grid, hipStr
 hipError_t launch_decode_f32_direct(const DecodeArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int grid, hipStream_t s);
 hipError_t launch_combine(const DecodeArgs& a, int head_dim, bool out_bf16, hipStream_t s);
-// the same for bf16 rows of which `shared` holds another part of the context: every row is written, to shared.result
-hipError_t launch_combine_shared(const DecodeArgs& a, const SharedHalf& shared, int head_dim, hipStream_t s);
+// the same for bf16 rows of which a.shared holds another part of the context: every row is written, to a.shared.result
+hipError_t launch_combine_shared(const DecodeArgs& a, int head_dim, hipStream_t s);
 // half_tiles: every tile has at most kAppendTileRows / 2 rows (a.tile_tokens is set accordingly) and the
 // two waves of a SIMD split each block of a tile between them instead of owning different rows
 hipError_t launch_append_mfma(const AppendArgs& a, int head_dim, bool fp8, bool half_tiles, int grid, hipStream_t s);

@@ -1,0 +1,119 @@
+"""Decode rows taken whole by a worker each: on both sides of the rule that chooses it (word 6 of the plan), against the oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as O
+from paper_2512_22560_amd import binding as B
+from paper_2512_22560_amd import workloads as W
+from tests.gpu_common import check
+from tests.helpers import oracle_args
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+WORKERS = 2048
+
+
+def _whole(lens, rows_per_b, kvd, taking_part):
+    blocks = -(-lens // 32)
+    per = max(1, -(-int(blocks.sum()) * rows_per_b // WORKERS))
+    longest = int(blocks.max(initial=0))
+    late = longest - per
+    if taking_part * rows_per_b > WORKERS:
+        late = max(late, longest // 2)
+    return taking_part > 64 and late <= (16 if kvd == "fp8_e4m3" else 10)
+
+
+def _batch(name, batch, heads, kvd, lens, seed):
+    b = W.build(W.Workload(name, batch, *heads, "bf16", kvd, ("const", int(max(1, lens.max()))), seed=W.BASE_SEED + seed), DEV)
+    b.ctx_lens_host[:] = lens
+    b.ctx_lens.copy_(torch.from_numpy(lens.astype(np.int32)))
+    return b
+
+
+# rows per KV head: one, and two of 20 query heads; one row per worker, several, none for some; contexts of one token, of whole
+# blocks and none; the longest one at the rule's edge and a block past it
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("batch,heads,base,longest", [
+    (65, (8, 2, 128), 30, 352), (65, (8, 2, 128), 30, 353), (65, (8, 2, 128), 30, 544), (65, (8, 2, 128), 30, 545), (64, (8, 2, 128), 64, 64),
+    (130, (40, 2, 64), 100, 320), (1100, (8, 2, 64), 40, 384), (1100, (8, 2, 64), 40, 416), (1100, (32, 2, 128), 33, 576), (257, (64, 8, 128), 17, 200),
+])
+def test_rows_whole_and_dealt(batch, heads, base, longest, kvd):
+    lens = np.random.default_rng(batch).integers(1, base + 1, batch)
+    lens[3::11] = 0
+    lens[1::13] = 32
+    lens[batch // 2] = longest
+    b = _batch("whole", batch, heads, kvd, lens, 210)
+    w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    ws = B.alloc_workspace(desc, batch, DEV)
+    out, lse = B.attn_decode_lse(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale, workspace=ws)
+    ref = O.attn_decode(W.raw_numpy(b.q), **dict(oracle_args(b), ctx_lens=lens))
+    check(out, ref, "bf16", "whole rows")
+    if batch > 64:
+        rows_per_b = heads[1] * -(-(heads[0] // heads[1]) // 16)
+        assert ws.view(torch.int32)[6].item() == _whole(lens, rows_per_b, kvd, batch)
+    # the same rows dealt to one worker less: the same attention and denominators, but for the order of the sums
+    before = B.set_decode_workers(WORKERS - 1)
+    try:
+        dealt, lse_dealt = B.attn_decode_lse(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    finally:
+        B.set_decode_workers(before)
+    check(dealt, ref, "bf16", "dealt rows")
+    live = torch.from_numpy(lens > 0).to(DEV)
+    assert torch.equal(torch.isinf(lse), torch.isinf(lse_dealt)) and bool(torch.isinf(lse[~live]).all())
+    # float sums of up to 2^11 weights in two orders: 2^11 roundings of 2^-24 at most, in log2 units, and as much for the references
+    assert (lse[live] - lse_dealt[live]).abs().max().item() <= 1e-3
+
+
+@pytest.mark.parametrize("heads,kvd", [((64, 4, 128), "fp8_e4m3"), ((40, 2, 64), "bf16"), ((32, 8, 128), "bf16")])
+@pytest.mark.parametrize("groups,prompt,own", [(9, 320, (1, 90)), (9, 0, (1, 300)), (40, 96, (1, 64)), (40, 96, (300, 700))])
+def test_whole_private_parts_take_the_shared_half(groups, prompt, own, heads, kvd):
+    b = W.build(W.Workload("own", 8 * groups, *heads, "bf16", kvd, ("uniform", prompt + own[0], prompt + own[1]), seed=W.BASE_SEED + 211), DEV)
+    if prompt:
+        b = W.alias_shared_prefix(b, 8, np.full(groups, prompt))
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=b.workload.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    ws = torch.full((B.lib().rollattn_shared_workspace_bytes(ctypes.byref(desc), 8),), 255, dtype=torch.uint8, device=DEV)
+    out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8, sm_scale=b.workload.sm_scale, workspace=ws,
+                               shared_lens=torch.full((groups,), prompt, dtype=torch.int32, device=DEV), k_scale=b.k_scale, v_scale=b.v_scale)
+    rows_per_b = heads[1] * -(-(heads[0] // heads[1]) // 16)
+    shared = np.minimum(prompt, b.ctx_lens_host.reshape(groups, 8).min(1) - 1) // 32 * 32
+    assert ws.view(torch.int32)[6].item() == _whole(b.ctx_lens_host - np.repeat(shared, 8), rows_per_b, kvd, 8 * groups)
+    check(out, O.attn_decode(W.raw_numpy(b.q), **oracle_args(b)), "bf16", "shared")
+
+
+@pytest.mark.parametrize("decode_rows", [64, 65, 200])
+def test_a_step_takes_its_rows_as_a_call_of_their_own_would(decode_rows):
+    # (with 64 the call of their own plans in its waves, and the step must not take them whole either)
+    b = W.build(W.Workload("step", decode_rows + 30, 16, 4, 128, "bf16", "bf16", ("uniform", 1, 150), qlen=("uniform", 2, 40), append_rows=30,
+                           ctx_is_prefix=True, seed=W.BASE_SEED + 212), DEV)
+    sel = np.flatnonzero(b.q_lens_host == 1)
+    assert len(sel) == decode_rows
+    w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale)
+    ws = torch.empty(B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), int(b.q_lens_host.sum())), dtype=torch.uint8, device=DEV)
+    out = B.attn_step(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, max_q_len=40, workspace=ws)
+    at = torch.from_numpy(np.concatenate([[0], np.cumsum(b.q_lens_host)])[sel]).to(DEV)
+    rows = torch.from_numpy(sel).to(DEV)
+    own = B.attn_decode(b.q[at].contiguous(), b.k_pages, b.v_pages, b.page_table[rows].contiguous(), b.ctx_lens[rows].contiguous(), sm_scale=w.sm_scale)
+    assert torch.equal(out[at], own)
+
+
+# Page scales are worked out for 64 pages at a time: contexts that end at, before and behind a window of them (1024 tokens), in steps
+# of 64 tokens and of 128 (short chunks), with scales that differ from page to page.
+@pytest.mark.parametrize("new", [3, 40])
+@pytest.mark.parametrize("hkv,d", [(1, 128), (2, 64)])
+def test_append_over_fp8_pages_of_several_scale_windows(new, hkv, d):
+    lens = np.array([1008, 1023, 1024, 1025, 1040, 1088, 2047, 2049, 2112, 3071, 3073, 4100])
+    b = W.build(W.Workload("windows", len(lens), 8 * hkv, hkv, d, "bf16", "fp8_e4m3", ("const", 4100), qlen=("const", new), seed=W.BASE_SEED + 213), DEV)
+    factor = torch.exp2(torch.from_numpy(np.random.default_rng(3).integers(-2, 2, b.k_scale.numel()).astype(np.float32)).to(DEV))
+    b.k_scale.mul_(factor)
+    b.v_scale.mul_(torch.flip(factor, [0]) * 0.5)          # (values of unit scale or less, where the bar is stated)
+    b.ctx_lens_host[:] = lens
+    b.ctx_lens.copy_(torch.from_numpy(lens.astype(np.int32)))
+    w = b.workload
+    out = B.attn_append(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, max_q_len=new,
+                        k_scale=b.k_scale, v_scale=b.v_scale)
+    check(out, O.attn_append(W.raw_numpy(b.q), b.q_lens_host, **dict(oracle_args(b), ctx_lens=lens)), "bf16", "windows")
