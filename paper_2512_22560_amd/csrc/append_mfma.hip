@@ -270,21 +270,31 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   const int n32 = lane & 31;   // row (B column) / K token row (A row) carried by this lane
   const int h2 = lane >> 5;    // half of the contraction this lane feeds
 
+  // Everything a tile's start hangs off comes in three trips to memory: the arguments, then the tile's record, then page ids
+  // (and behind them the tiles and the query rows): 637.4 -> 634.5 us for 33 chunks of 3 .. 96 tokens behind up to 64k (64/4/128,
+  // FP8), 12.31 -> 12.28 ms for the mixed step of 512; no difference over bf16 pools.
   const int group = a.group;
   const int hkv = a.hkv;
   const int tile_tokens = a.tile_tokens;
-  const int n_tiles = a.header[kPlanTiles];
+  const int tile_cap = a.tile_cap, max_pages = a.max_pages, hq = a.hq, noncausal = a.noncausal;
+  const int32_t *tile_recs = a.tile_rec, *header = a.header, *page_table = a.page_table;
+  const void *q = a.q, *k_pages = a.k_pages, *v_pages = a.v_pages;
+  asm volatile("" ::"s"(group), "s"(hkv), "s"(tile_tokens), "s"(tile_cap), "s"(max_pages), "s"(hq), "s"(noncausal), "s"(tile_recs), "s"(header), "s"(page_table), "s"(q),
+               "s"(k_pages), "s"(v_pages));
   int g;
   const int tile = tile_of(block, hkv, g);
   // The tile's record does not wait for the tile count (the index is clamped to the list's capacity): both loads
   // leave together, and everything else the workgroup needs to start hangs off the record alone.
   typedef const __attribute__((address_space(4))) int32_t* const_rec_p;
-  const const_rec_p rec = (const_rec_p)(a.tile_rec + (size_t)min(tile, a.tile_cap - 1) * kTileRecWords);
+  const const_rec_p rec = (const_rec_p)(tile_recs + (size_t)min(tile, tile_cap - 1) * kTileRecWords);
   // A record is a whole tile, or a piece of one: blocks [blk0, blk0 + n_blocks) of the context.  The piece sees the
   // context as if it started there (table, length and positions shifted), so nothing below differs; rows whose last
   // token lies before it have negative positions and see nothing.
-  const int b = rec[0], q0 = rec[1], n_b = rec[2], q_off = rec[4], blk0 = rec[5], n_blocks = kStepTokens == kBlockTokens ? rec[6] : (rec[6] + 1) / 2;   // (the latter in steps of the loop)
-  const int ctx = rec[3] - blk0 * kBlockTokens;
+  const int b = rec[0], q0 = rec[1], n_b = rec[2], ctx_all = rec[3], q_off = rec[4], blk0 = rec[5], blocks = rec[6];
+  const int n_tiles = *(const __attribute__((address_space(4))) int32_t*)(header + kPlanTiles);
+  asm volatile("" ::"s"(b), "s"(q0), "s"(n_b), "s"(ctx_all), "s"(q_off), "s"(blk0), "s"(blocks), "s"(n_tiles));
+  const int n_blocks = kStepTokens == kBlockTokens ? blocks : (blocks + 1) / 2;   // (the latter in steps of the loop)
+  const int ctx = ctx_all - blk0 * kBlockTokens;
   if (tile >= n_tiles) return;
   if (a.clock_sums && threadIdx.x == 0) {
     clock_s[0] = __builtin_amdgcn_s_memtime();
@@ -295,13 +305,13 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // Causal mode: row i of the chunk sits at position L_b - n_b + i and sees tokens up to itself.
   // Non-causal mode (the shared part of a decode step for a group of trajectories): every row sees
   // all of [0, L_b), the rows' own tokens lie outside this range.
-  const bool causal = a.noncausal == 0;
+  const bool causal = noncausal == 0;
   const int pos0 = causal ? ctx - n_b + q0 : ctx - 1;    // position of the tile's first token
   // Page ids and page scales are inputs nobody writes during the call: reading them through the
   // constant address space lets every such load (all uniform) take the scalar path.
   typedef const __attribute__((address_space(4))) int32_t* const_i32_p;
   typedef const __attribute__((address_space(4))) float* const_f32_p;
-  const const_i32_p table = (const_i32_p)(a.page_table + (size_t)b * a.max_pages + blk0 * (kBlockTokens / kPageSize));
+  const const_i32_p table = (const_i32_p)(page_table + (size_t)b * max_pages + blk0 * (kBlockTokens / kPageSize));
   const const_f32_p k_scale_c = (const_f32_p)a.k_scale;
   const const_f32_p v_scale_c = (const_f32_p)a.v_scale;
   const size_t tile_stride = (size_t)kPageSize * kSrcRowBytes;
@@ -320,29 +330,60 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   int wave_min_pos = wave_active ? (causal ? pos0 + (row_wave * kRowsPerWave) / group : pos0) : -1;
   if constexpr (kStepTokens != kBlockTokens) {
     // a piece of an odd number of blocks ends inside its last step: what follows is another piece's
-    my_pos = min(my_pos, rec[6] * kBlockTokens - 1);
-    wave_min_pos = min(wave_min_pos, rec[6] * kBlockTokens - 1);
+    my_pos = min(my_pos, blocks * kBlockTokens - 1);
+    wave_min_pos = min(wave_min_pos, blocks * kBlockTokens - 1);
   }
 
   if (n_blocks <= 0) {                                   // nothing to attend to (non-causal mode with L_b = 0): zero rows
-    if (row_ok) {
-      __bf16* orow = (__bf16*)a.out + ((size_t)(q_off + q0 + tok_in_tile) * a.hq + head) * D;
+    int tid_z = threadIdx.x;
+    asm volatile("" : "+v"(tid_z));                      // (worked out again: kept for here, it would take registers in the loop)
+    const int row_z = row_wave * kRowsPerWave + (tid_z & 31), half_z = (tid_z >> 5) & 1;
+    const int tok_z = row_z / group;
+    if (row_z < rows_here) {
+      const size_t at_z = (size_t)(q_off + q0 + tok_z) * hq + g * group + (row_z - tok_z * group);
+      __bf16* orow = (__bf16*)a.out + at_z * D;
 #pragma unroll
-      for (int d0 = h2 * (D / 2); d0 < (h2 + 1) * (D / 2); d0 += 4) *(bf16x4*)(orow + d0) = bf16x4{0, 0, 0, 0};
-      if (a.lse && h2 == 0) a.lse[(size_t)(q_off + q0 + tok_in_tile) * a.hq + head] = -INFINITY;
+      for (int d0 = half_z * (D / 2); d0 < (half_z + 1) * (D / 2); d0 += 4) *(bf16x4*)(orow + d0) = bf16x4{0, 0, 0, 0};
+      if (a.lse && half_z == 0) a.lse[at_z] = -INFINITY;
     }
     return;
   }
 
+  const int live_pages = (ctx + kPageSize - 1) / kPageSize;
+  const int last_blk = n_blocks - 1;
+  constexpr int kPagesPerBlock = kStepTokens / kPageSize;
+  // The 64 chunks a wave fetches with one instruction lie in one page, so its id is a scalar.  Block after block the entries
+  // behind a load lie kPagesPerBlock apart: their byte offset in the table runs along, no further than to the page of the last
+  // block (page_end) or the last live page (page_live), whose rows are clamped too.
+  int page_run[kLoads], page_end[kLoads];
+  const int page_live = (live_pages - 1) * 4;
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    page_run[j] = ((j * kThreads + wave * 64) / kSrcChunks) / kPageSize * 4;
+    page_end[j] = min(last_blk * kPagesPerBlock * 4 + page_run[j], page_live);
+  }
+  // the page ids behind this wave's kLoads loads of one block, and whether that is the last live page; the blocks in order
+  auto fetch_pids = [&](int* dst, int* at) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      at[j] = min(page_run[j], page_end[j]);
+      dst[j] = *(const_i32_p)((const __attribute__((address_space(4))) char*)table + (unsigned int)at[j]);
+      page_run[j] += kPagesPerBlock * 4;
+    }
+  };
+  // those of the first four blocks, on their way while the query rows' addresses are worked out
+  int first_ids[4][kLoads], first_at[4][kLoads];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) fetch_pids(first_ids[d], first_at[d]);
+
+  // Rows past the tile's last read that one again: what becomes of them is neither stored nor looked at.  (A branch around each
+  // load had one of them waited for before the next was sent.)
   bf16x8 qop[kKK];
   {
-    const __bf16* qrow = (const __bf16*)a.q + ((size_t)(q_off + q0 + tok_in_tile) * a.hq + head) * D;
+    const int qtok = row_ok ? tok_in_tile : tokens_here - 1, qhead = row_ok ? head : g * group;
+    const __bf16* qrow = (const __bf16*)q + ((size_t)(q_off + q0 + qtok) * hq + qhead) * D;
 #pragma unroll
-    for (int kk = 0; kk < kKK; ++kk) {
-      bf16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (row_ok) v = *(const bf16x8*)(qrow + kk * 16 + h2 * 8);
-      qop[kk] = v;                                 // bf16 pools: scaled further down, once the first tiles are on their way
-    }
+    for (int kk = 0; kk < kKK; ++kk) qop[kk] = *(const bf16x8*)(qrow + kk * 16 + h2 * 8);   // bf16 pools: scaled further down, once the first tiles are on their way
   }
 
   floatx16 acc[kDT];
@@ -365,10 +406,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // then be waited on by count).  Rows at or past L_b (ragged
   // last block, or a block index clamped at the end of the loop) re-read the trajectory's last
   // token instead: finite data that the causal / length mask never lets through.
-  const int live_pages = (ctx + kPageSize - 1) / kPageSize;
-  const int last_blk = n_blocks - 1;
   const int last_slot = (ctx - 1) % kPageSize;
-  constexpr int kPagesPerBlock = kStepTokens / kPageSize;
   constexpr bool kAllThreadsLoad = kStepTokens * kSrcChunks >= kThreads;
   // Chunk idx = j * kThreads + tid of a block sits in LDS row idx / kChunks at chunk position
   // (idx % kChunks), holding the row's chunk (position ^ key): key = row & 15 for K, (row & 3) << 2
@@ -397,25 +435,6 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       wptr[j][2] = (lds_p)(v_lds[0] + trow * kRowBytes + (((2 * c) ^ vkey) & (kChunks - 1)) * 16);
     }
   }
-  // The 64 chunks a wave fetches with one instruction lie in one page, so its id is a scalar.  Block after block the entries
-  // behind a load lie kPagesPerBlock apart: their byte offset in the table runs along, no further than to the page of the last
-  // block (page_end) or the last live page (page_live), whose rows are clamped too.
-  int page_run[kLoads], page_end[kLoads];
-  const int page_live = (live_pages - 1) * 4;
-#pragma unroll
-  for (int j = 0; j < kLoads; ++j) {
-    page_run[j] = ((j * kThreads + wave * 64) / kSrcChunks) / kPageSize * 4;
-    page_end[j] = min(last_blk * kPagesPerBlock * 4 + page_run[j], page_live);
-  }
-  // the page ids behind this wave's kLoads loads of one block, and whether that is the last live page; the blocks in order
-  auto fetch_pids = [&](int* dst, int* at) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      at[j] = min(page_run[j], page_end[j]);
-      dst[j] = *(const_i32_p)((const __attribute__((address_space(4))) char*)table + (unsigned int)at[j]);
-      page_run[j] += kPagesPerBlock * 4;
-    }
-  };
   // byte offset of the (page, KV head) tile in either pool
   auto tile_off_of = [&](int pid) __attribute__((always_inline)) -> size_t {
     return (size_t)(unsigned int)(pid * hkv + g) * tile_stride;
@@ -423,7 +442,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // one wave-wide 16-byte load: scalar tile base, per-lane offset
   struct TileAddr { const unsigned char* base; unsigned int off; };
   auto tile_addr = [&](const void* pool, int pool_i, size_t toff, bool last, int j) __attribute__((always_inline)) -> TileAddr {
-    return TileAddr{(const unsigned char*)pool + toff, last ? goff_last[j][pool_i] : goff[j][pool_i]};
+    return TileAddr{(const unsigned char*)pool + toff, last ? goff_last[j][FP8 ? 0 : pool_i] : goff[j][FP8 ? 0 : pool_i]};   // (FP8: the same for both pools)
   };
   // -- register path (FP8)
   uintx4 kreg[2][kLoads], vreg[2][kLoads];   // two units in flight
@@ -726,11 +745,10 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   bool is_last[2][kLoads];     // ... whose page is the last live one
   int pid_new[kLoads], at_new[kLoads];   // not yet turned into an offset
   {
-    int h[4][kLoads], at[4][kLoads];
+    auto& h = first_ids;
+    auto& at = first_at;
     size_t off[4][kLoads];
     bool end[4][kLoads];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) fetch_pids(h[d], at[d]);
     if constexpr (FP8) {
       if (wave == 0) window_ids(0);
     }
@@ -887,7 +905,10 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       for (int dt = 0; dt < kDT; ++dt) asm volatile("" : "+v"(vptr[dt]));
       if constexpr (FP8) {
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) asm volatile("" : "+v"(wptr[j][0]), "+v"(wptr[j][1]), "+v"(wptr[j][2]));
+        for (int j = 0; j < kLoads; ++j) {
+          asm volatile("" : "+v"(wptr[j][0]), "+v"(wptr[j][1]), "+v"(wptr[j][2]));
+          asm volatile("" : "+v"(goff[j][0]), "+v"(goff_last[j][0]));   // (nor widened to 64 bits)
+        }
       }
       auto piece = [&](auto pos_c) __attribute__((always_inline)) {
         stage_widen(slot_c, pos_c);
@@ -919,8 +940,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
         asm volatile("" : "+v"(kreg[0][j]), "+v"(vreg[0][j]), "+v"(kreg[1][j]), "+v"(vreg[1][j]));
-#pragma unroll
-        for (int pool = 0; pool < 2; ++pool) asm volatile("" : "+v"(goff[j][pool]), "+v"(goff_last[j][pool]));
+        asm volatile("" : "+v"(goff[j][0]), "+v"(goff_last[j][0]));
       }
     }
     block(0, c_pv, c0);                                 // block 0 has no predecessor: scores only
