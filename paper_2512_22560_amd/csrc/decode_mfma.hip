@@ -102,8 +102,8 @@ __device__ __forceinline__ uint4 load16(const unsigned char* p) {
   return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
-// WHOLE: rows may be whole ones whose shared part is folded in here (fold_shared).
-template <int D, bool FP8, bool STREAM, bool WHOLE>
+// FOLD: rows may be whole ones whose shared part is folded in here (fold_shared).
+template <int D, bool FP8, bool STREAM, bool FOLD>
 __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, bool fold_shared, unsigned char* const k_lds) {
   using G_ = Geo<D, FP8>;
   int tid = threadIdx.x;
@@ -383,12 +383,12 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
         if (i + G_::kStages < n_mine) issue(st);   // the registers just drained take the next block
         if (i == 0 || cc.blk == 0) begin_segment();
         compute(kscale, vscale);
-        if ((cc.blk == cc.n - 1 || i == n_mine - 1) && !(WHOLE && fold_shared)) end_segment();   // (its one row is finished behind the loop)
+        if ((cc.blk == cc.n - 1 || i == n_mine - 1) && !(FOLD && fold_shared)) end_segment();   // (its one row is finished behind the loop)
         if (i + 1 < n_mine) advance(cc);
       }
     }
   }
-  if (WHOLE && fold_shared) {
+  if (FOLD && fold_shared) {
     // the private part of a row whose other part is there: both weighted by their denominators, as the merge would
     int b = __builtin_amdgcn_readfirstlane(start.x), r = __builtin_amdgcn_readfirstlane(start.y) >> 20, tid = threadIdx.x;
     asm volatile("" : "+s"(b), "+s"(r), "+v"(tid));   // (worked out again, so that nothing of it takes a register during the loop)
@@ -418,9 +418,9 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
   }
 }
 
-// IN_WAVE: no plan was launched, and rows are never whole.  (One kernel for both had 254 registers instead of 246 over bf16 pools
-// and took 0.3 us longer on a call of 30, 1 % on long ones.)
-template <int D, bool FP8, bool IN_WAVE>
+// IN_WAVE: no plan was launched, and rows are never whole.  FOLD: for attn_decode_shared.  (One kernel for all had 254 registers
+// instead of 246 over bf16 pools and took 0.3 us longer on a call of 30, 1 % on long ones.)
+template <int D, bool FP8, bool IN_WAVE, bool FOLD>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeArgs a) {
   // Per wave: one K tile and one V tile.
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * Geo<D, FP8>::kTileBytes];
@@ -447,8 +447,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
   // 64 groups of 8 behind 8192 common tokens, decoded without attn_decode_shared (64/4/128, FP8), 687 against 777 us; 32
   // query heads per KV head, two rows that read the same K and V (256 contexts, 32/1/128, bf16), 153 against 170 us.
   const bool fold_shared = whole && a.shared.result;
-  if (read_again) decode_worker<D, FP8, false, !IN_WAVE>(a, start, worker, fold_shared, lds[wave]);
-  else decode_worker<D, FP8, true, !IN_WAVE>(a, start, worker, fold_shared, lds[wave]);
+  if (read_again) decode_worker<D, FP8, false, FOLD>(a, start, worker, fold_shared, lds[wave]);
+  else decode_worker<D, FP8, true, FOLD>(a, start, worker, fold_shared, lds[wave]);
 }
 
 }  // namespace
@@ -457,8 +457,9 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, int head_dim, bool fp8, int g
   auto launch = [&](auto d, auto f) {
     constexpr int D = decltype(d)::value;
     constexpr bool F = decltype(f)::value;
-    if (a.plan.batch) hipLaunchKernelGGL((decode_mfma_kernel<D, F, true>), dim3(grid), dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((decode_mfma_kernel<D, F, false>), dim3(grid), dim3(kThreads), 0, s, a);
+    if (a.plan.batch) hipLaunchKernelGGL((decode_mfma_kernel<D, F, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
+    else if (a.shared.result) hipLaunchKernelGGL((decode_mfma_kernel<D, F, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((decode_mfma_kernel<D, F, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
   };
   std::integral_constant<int, 128> d128;
   std::integral_constant<int, 64> d64;
