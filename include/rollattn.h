@@ -96,7 +96,7 @@ typedef struct {
 /* Decode step: one query token per trajectory at position L_b - 1 (Section 3.1, the
  * bandwidth-bound phase; Section 6.1, the engine's decode step).  The KV range of each
  * trajectory is partitioned over wavefronts by a plan computed on the device from
- * ctx_lens alone (never from page ids) and partial results are merged with the
+ * ctx_lens alone (never from page ids; where rows are many and alike each stays whole) and partial results are merged with the
  * log-sum-exp rule in a fixed order, so results are reproducible bit for bit and do not
  * depend on where pages sit physically.
  *   q [B][Hq][D], out [B][Hq][D], ctx_lens [B] int32 (device).
@@ -279,7 +279,9 @@ int32_t rollattn_debug_set_decode_workers(int32_t workers);
 
 /* Copies the plan the last attn_decode call left in `workspace` back to the host
  * (synchronises the stream): per, T, and 4 int32 per worker, (b, r << 20 | block, L_b, blocks
- * in its run) for the first block of its run, or (-1, 0, 0, 0) for a worker without blocks.
+ * in its run) for the first block of its run, or (-1, 0, 0, 0) for a worker without blocks.  For BF16 queries and
+ * many short contexts the call may have given every row whole to a worker of its own instead; the records
+ * then tell what the equal runs would have been.
  * starts_out must hold 4 * rollattn_plan_workers(desc) int32. */
 int rollattn_debug_read_plan(const rollattn_desc *desc, const void *workspace, int32_t *per_out,
                              int32_t *total_out, int32_t *starts_out, void *hip_stream);
