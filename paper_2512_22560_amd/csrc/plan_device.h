@@ -107,14 +107,16 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
   int32_t* const prefix = a.prefix;
   int32_t* const wstart = a.wstart;
   const bool in_lds = batch <= kLdsPrefix;
+  const bool counted = a.q_lens && batch > kWavePlanBatch;   // (no batch of fewer stays whole)
   int running = 0, longest = 0;
   if (tid == 0) {
     lds.longest = 0;
-    lds.taking_part = a.q_lens ? 0 : batch;
+    lds.taking_part = counted ? 0 : batch;
   }
   for (int b0 = 0; b0 < batch; b0 += kPlanThreads) {
     const int b = b0 + tid;
     const int len = b < batch ? len_of(b) : 0;
+    const bool one = counted && b < batch && a.q_lens[b] == 1;   // (the load that len_of has sent anyway)
     const int count = (len + kBlockTokens - 1) / kBlockTokens;
     int tile_total;
     const int first = running + block_exclusive_scan(count, wave_tot, &tile_total);
@@ -127,8 +129,8 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
     }
     running += tile_total;
     longest = max(longest, count);
-    if (a.q_lens) {
-      const unsigned long long ones = __builtin_amdgcn_ballot_w64(b < batch && a.q_lens[b] == 1);
+    if (counted) {
+      const unsigned long long ones = __builtin_amdgcn_ballot_w64(one);
       if ((tid & 63) == 0) atomicAdd(&lds.taking_part, __builtin_popcountll(ones));   // (behind the scan's barriers)
     }
   }
