@@ -315,10 +315,9 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   d.ctx_lens = ctx_lens; d.q_lens = q_lens; d.batch = desc->batch; d.rows_per_b = w.rows_per_b;
   // (the launch has w.workers workers whatever the partition is cut for: the others get a record without blocks)
   d.workers = plan_workers(w); d.slots = w.workers;
-  // (whole rows instead, where the plan says so: not where the number of workers is forced, and not for so many rows that
-  // a grid could not have a worker for each)
+  // (whole rows instead, where the plan says so: not where the number of workers is forced)
   d.whole_late = desc->kv_dtype == ROLLATTN_FP8_E4M3 ? kWholeLateFp8 : kWholeLate;
-  a.whole_rows = desc->q_dtype != ROLLATTN_F32 && d.workers == w.workers && (int64_t)desc->batch * w.rows_per_b <= 16 * (int64_t)kWholeRows;
+  a.whole_rows = desc->q_dtype != ROLLATTN_F32 && d.workers == w.workers;
   if (desc->q_dtype != ROLLATTN_F32) d.page_table = page_table;
   d.max_pages = desc->max_pages_per_seq; d.num_pages = desc->num_pages; d.head_tiles = w.rows_per_b > desc->num_kv_heads;
   d.header = (int32_t*)(base + w.header); d.prefix = (int32_t*)(base + w.prefix); d.wstart = (int32_t*)(base + w.wstart);
@@ -334,8 +333,7 @@ static int decode_launch(const rollattn_desc* desc, const DecodeArgs& a, hipStre
     if (f32) {
       e = launch_decode_f32(a, desc->head_dim, kF32DecodeWgs, s);
     } else {
-      e = launch_decode_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3,
-                             a.whole_rows ? std::max(kMfmaDecodeWgs, (a.batch * a.rows_per_b + 3) / 4) : kMfmaDecodeWgs, s);
+      e = launch_decode_mfma(a, desc->head_dim, desc->kv_dtype == ROLLATTN_FP8_E4M3, a.whole_rows && desc->head_dim == 64 ? kMfmaDecodeWgsD64 : kMfmaDecodeWgs, s);
     }
     prof.stop();
   }

@@ -11,8 +11,8 @@
 //   O^T += V^T P^T       (dims x heads, V read back transposed with ds_read_b64_tr_*)
 // A run that covers a whole row writes the row's output itself; a run that starts or ends
 // inside a row leaves an un-normalised partial (max, sum, O) for the merge kernel.
-// Where rows are many and none much longer than a run, the plan says so and a worker takes a row instead (rows_stay_whole in
-// plan_device.h): no partials, and in attn_decode_shared the shared half is folded in here as well.
+// Where it pays, the plan says that every row is taken whole, by one wave: no partials, and in attn_decode_shared the shared half is
+// folded in here as well.
 // The transposed products keep "head" on the lane axis in both results, so the online
 // softmax state (running max, running sum, rescale factor) is one scalar per lane and P
 // feeds the second product straight from the first one's accumulator registers.
@@ -85,6 +85,9 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint32_t lo, uint32_t hi) {
   return r;
 }
 
+// (worked out where it is used: the thread's index would take a register over the whole of a worker's rows)
+__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)); }
+
 struct Cursor {
   int b, r, blk;   // trajectory, row within it, block within the row
   int n, len;      // blocks in the row, context length of the trajectory
@@ -102,11 +105,13 @@ __device__ __forceinline__ uint4 load16(const unsigned char* p) {
   return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
-// FOLD: rows may be whole ones whose shared part is folded in here (fold_shared).
-template <int D, bool FP8, bool STREAM, bool FOLD>
-__device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, bool fold_shared, unsigned char* const k_lds) {
+// One run of blocks.  WHOLE: it is one row from its first block to its last; FOLD: whose other part, in attn_decode_shared, is there
+// and folded in.
+template <int D, bool FP8, bool STREAM, bool WHOLE, bool FOLD>
+__device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 start, int worker, unsigned char* const k_lds) {
+  static_assert(WHOLE || !FOLD, "cut rows are folded by the merge");
   using G_ = Geo<D, FP8>;
-  int tid = threadIdx.x;
+  int tid = lane_id();
   asm volatile("" : "+v"(tid));   // (what is worked out from it stays in this instance: shared by both in front of the branch, it would not fit the registers)
   const int lane = tid & 63;
   const int r16 = lane & 15;   // MFMA row / column index carried by this lane
@@ -126,7 +131,7 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
   pc.n = (pc.len + kBlockTokens - 1) / kBlockTokens;
   Cursor cc = pc;   // consumer: block being computed
   auto advance = [&](Cursor& c) {
-    if (++c.blk < c.n) return;
+    if (++c.blk < c.n || WHOLE) return;
     c.blk = 0;
     if (++c.r < rows_per_b) return;
     c.r = 0;
@@ -197,7 +202,8 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
     }
     // step to the next block of the run (never past its end: the rows after the last block need
     // not exist); a new row starts with a fresh page-id window
-    if (++issued < n_mine) {
+    if (++issued < n_mine && WHOLE) advance(pc);
+    else if (issued < n_mine) {
       const int row_before = pc.b * rows_per_b + pc.r;
       advance(pc);
       if (pc.b * rows_per_b + pc.r != row_before) pwin = -1;
@@ -251,7 +257,7 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
     const int h0 = (cc.r - g * n_ht) * kMfmaHeadTile;
     const float l_tot = xor32_add(xor16_add(l_run));
     const bool head_ok = h0 + r16 < group;
-    if (seg_first_blk == 0 && cc.blk == cc.n - 1) {
+    if (WHOLE || (seg_first_blk == 0 && cc.blk == cc.n - 1)) {
       // the whole row was ours: normalise and store
       const size_t orow = row_of(cc.b) * a.hq + (size_t)g * group + h0 + r16;
       const float inv = 1.f / l_tot;
@@ -368,6 +374,7 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
     }
   };
 
+  if constexpr (WHOLE) begin_segment();              // (its query rows in front of its tiles: nothing waits for them then)
   // ---- software pipeline over this worker's run of n_mine blocks
 #pragma unroll
   for (int st = 0; st < G_::kStages; ++st) {
@@ -381,16 +388,17 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int4 st
         commit(st);
         const float kscale = FP8 ? ksc[st] : 1.f, vscale = FP8 ? vsc[st] : 1.f;
         if (i + G_::kStages < n_mine) issue(st);   // the registers just drained take the next block
-        if (i == 0 || cc.blk == 0) begin_segment();
+        if (!WHOLE && (i == 0 || cc.blk == 0)) begin_segment();
         compute(kscale, vscale);
-        if ((cc.blk == cc.n - 1 || i == n_mine - 1) && !(FOLD && fold_shared)) end_segment();   // (its one row is finished behind the loop)
+        if (!WHOLE && (cc.blk == cc.n - 1 || i == n_mine - 1)) end_segment();   // (a whole row is finished behind the loop)
         if (i + 1 < n_mine) advance(cc);
       }
     }
   }
-  if (FOLD && fold_shared) {
+  if constexpr (WHOLE && !FOLD) end_segment();
+  if constexpr (FOLD) {
     // the private part of a row whose other part is there: both weighted by their denominators, as the merge would
-    int b = __builtin_amdgcn_readfirstlane(start.x), r = __builtin_amdgcn_readfirstlane(start.y) >> 20, tid = threadIdx.x;
+    int b = __builtin_amdgcn_readfirstlane(start.x), r = __builtin_amdgcn_readfirstlane(start.y) >> 20, tid = lane_id();
     asm volatile("" : "+s"(b), "+s"(r), "+v"(tid));   // (worked out again, so that nothing of it takes a register during the loop)
     const int r16 = tid & 15, q4 = (tid >> 4) & 3;
     const int g = r / n_ht;
@@ -426,29 +434,51 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const DecodeAr
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * Geo<D, FP8>::kTileBytes];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int worker = blockIdx.x * kWaves + wave;
+  // Where another worker reads some of the run's pages, too, it may find them in a cache, and the hint would cost that:
+  // 64 groups of 8 behind 8192 common tokens, decoded without attn_decode_shared (64/4/128, FP8), 687 against 777 us; 32
+  // query heads per KV head, two rows that read the same K and V (256 contexts, 32/1/128, bf16), 153 against 170 us.
+  bool read_again = false;
   int4 start;
-  bool read_again = false, whole = false;
   if constexpr (IN_WAVE) {
     start = plan_decode_in_wave(a.plan, worker, &read_again);
   } else {
     start = *(const int4*)(a.wstart + 4 * min(worker, kMfmaDecodeWgs * kWaves - 1));
-    whole = (a.header[kPlanWhole] & a.whole_rows) != 0;
     read_again = a.header[kPlanReadAgain] != 0;
-    if (whole) {
-      const int b = worker / a.rows_per_b, r = worker - b * a.rows_per_b, at = min(b, a.batch - 1);
-      const int len = a.ctx_lens[at], one = a.q_lens ? a.q_lens[at] : 1;
-      start = make_int4(b < a.batch && one == 1 && len > 0 ? b : -1, r << 20, len, (len + kBlockTokens - 1) / kBlockTokens);
-    } else if (worker >= kMfmaDecodeWgs * kWaves) {
+    if (a.header[kPlanWhole] & a.whole_rows) {
+      // However many rows there are, the launch is one of workgroups that are resident at once: a workgroup per four rows cost the
+      // calls that stay cut their empty ones' starts (1024 x 8 rows, FP8, 32 .. 64 tokens and one of 8192: 47.4 -> 48.9 us,
+      // now 47.8).  Tickets 0, 1, 2, ... of a workgroup are rows blockIdx.x, blockIdx.x + gridDim.x, ..., and a wave that is done
+      // draws the next: the four have rows of different trajectories then, and what one wave's are shorter another takes.  32768
+      // rows of 32 .. 512 tokens (FP8): 462 us for a workgroup per four rows, 467 with the rows of a wave fixed and neighbours
+      // in one workgroup, 448 with them fixed and apart, 439 as they are; drawn for all workgroups from one counter in memory,
+      // 12 ns each, 505.  131072 rows of 16 .. 100 (bf16), where a start costs as much as the draw evens out: 880 -> 905 us.
+      // Rows that read the same K and V stay side by side, kWaves at a time (256 contexts of 1024 .. 1200, 20 query heads per
+      // KV head, bf16: 177 us apart, 126 together).
+      const unsigned int rows = (unsigned int)a.batch * a.rows_per_b, side = a.rows_per_b > a.hkv ? kWaves : 1;
+      auto row_of_ticket = [&](unsigned int t) { return (t / side * gridDim.x + blockIdx.x) * side + t % side; };
+      __shared__ unsigned int drawn;
+      if (threadIdx.x == 0) drawn = kWaves;
+      __syncthreads();
+      for (unsigned int row = row_of_ticket(wave); row < rows;) {
+        const int b = row / a.rows_per_b, r = row - b * a.rows_per_b;
+        const int len = a.ctx_lens[b], new_rows = a.q_lens ? a.q_lens[b] : 1;
+        if (new_rows == 1 && len > 0) {
+          const int4 all = make_int4(b, r << 20, len, (len + kBlockTokens - 1) / kBlockTokens);
+          if (read_again) decode_worker<D, FP8, false, true, FOLD>(a, all, worker, lds[wave]);
+          else decode_worker<D, FP8, true, true, FOLD>(a, all, worker, lds[wave]);
+        }
+        unsigned int ticket = 0;
+        if (lane_id() == 0) ticket = atomicAdd(&drawn, 1u);
+        row = row_of_ticket((unsigned int)__builtin_amdgcn_readfirstlane((int)ticket));
+      }
       return;
     }
+    if (worker >= kMfmaDecodeWgs * kWaves) return;
   }
+  start = make_int4(__builtin_amdgcn_readfirstlane(start.x), __builtin_amdgcn_readfirstlane(start.y), __builtin_amdgcn_readfirstlane(start.z), __builtin_amdgcn_readfirstlane(start.w));
   if (start.x < 0) return;
-  // Where another worker reads some of the run's pages, too, it may find them in a cache, and the hint would cost that:
-  // 64 groups of 8 behind 8192 common tokens, decoded without attn_decode_shared (64/4/128, FP8), 687 against 777 us; 32
-  // query heads per KV head, two rows that read the same K and V (256 contexts, 32/1/128, bf16), 153 against 170 us.
-  const bool fold_shared = whole && a.shared.result;
-  if (read_again) decode_worker<D, FP8, false, FOLD>(a, start, worker, fold_shared, lds[wave]);
-  else decode_worker<D, FP8, true, FOLD>(a, start, worker, fold_shared, lds[wave]);
+  if (read_again) decode_worker<D, FP8, false, false, false>(a, start, worker, lds[wave]);
+  else decode_worker<D, FP8, true, false, false>(a, start, worker, lds[wave]);
 }
 
 }  // namespace

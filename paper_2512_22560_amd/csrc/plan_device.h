@@ -93,7 +93,7 @@ struct DecodePlanLds {
 __device__ __forceinline__ bool rows_stay_whole(const DecodePlanArgs& a, int longest, int per, int taking_part) {
   const long rows = (long)taking_part * a.rows_per_b;
   const int late = rows > a.workers ? max(longest - per, longest / 2) : longest - per;
-  return taking_part > kWavePlanBatch && rows <= kWholeRows && late <= a.whole_late;
+  return taking_part > kWavePlanBatch && late <= a.whole_late;
 }
 
 template <class L>

@@ -18,7 +18,7 @@ constexpr int kF32DecodeWgs = 4 * kNumCUs;    // one workgroup-worker each
 constexpr int kF32HeadTile = 4;         // query heads per float32 decode row
 constexpr int kWavePlanBatch = 64;      // batches up to this size are planned by every decode wave for itself
 constexpr int kWholeLateFp8 = 16, kWholeLate = 10;   // MFMA decode: rows stay whole where the longest ends at most this many blocks late
-constexpr int kWholeRows = 1 << 20;     // ... and where there are no more than this
+constexpr int kMfmaDecodeWgsD64 = 3 * kNumCUs;   // MFMA decode, D = 64: workgroups that run at once, all of them where rows stay whole
 constexpr int kDirectPages = 32;        // float32 contexts of at most this many pages are not cut
 constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pairs) per append workgroup
 constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
@@ -104,6 +104,7 @@ struct DecodeArgs {
   float* partial_o;
   int32_t batch, hq, hkv, group, max_pages, head_tile, rows_per_b;
   float scale_log2;     // sm_scale * log2(e)
+  int32_t whole_rows;   // 1: the plan may say that every row is one worker's (kPlanWhole); with the first of the arguments, whose cache lines are read first
   float* lse;           // optional [B][Hq]: log2 of each row's softmax denominator (reference included)
   // Mixed step (both null otherwise): only trajectories with q_lens[b] == 1 are decode rows, the others count
   // as empty here; the query and output row of trajectory b is q_offsets[b] instead of b.
@@ -111,10 +112,9 @@ struct DecodeArgs {
   const int32_t* q_offsets;
   // Private half of attn_decode_shared (null otherwise): the context of trajectory b starts at this entry of its table row.
   const int32_t* first_page;
+  SharedHalf shared;
   // Set (batch > 0) where no plan was launched: the decode kernel plans for itself.
   DecodePlanArgs plan;
-  int32_t whole_rows;   // 1: the plan may say that every row is one worker's (kPlanWhole); the launch has a worker for each then
-  SharedHalf shared;
 };
 
 struct AppendArgs {

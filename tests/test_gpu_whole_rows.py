@@ -68,6 +68,31 @@ def test_rows_whole_and_dealt(batch, heads, base, longest, kvd):
     assert (lse[live] - lse_dealt[live]).abs().max().item() <= 1e-3
 
 
+def test_more_rows_than_a_launch_has_waves():
+    # a million rows over few pages: each wave takes hundreds, some trajectories have none
+    n, heads = 131080, (8, 8, 64)
+    gen, rng = torch.Generator(device=DEV).manual_seed(5), np.random.default_rng(5)
+    lens = rng.integers(0, 17, n).astype(np.int32)
+    table = rng.integers(0, 64, (n, 1)).astype(np.int32)
+    q = torch.randn((n, heads[0], heads[2]), generator=gen, device=DEV, dtype=torch.bfloat16)
+    k, v = (torch.randn((64, heads[1], 16, heads[2]), generator=gen, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    args = (q, k, v, torch.from_numpy(table).to(DEV), torch.from_numpy(lens).to(DEV))
+    ws = B.alloc_workspace(B.make_desc(q, k, args[3], sm_scale=0.125), n, DEV)
+    out = torch.full_like(q, float("nan"))
+    B.attn_decode(*args, sm_scale=0.125, out=out, workspace=ws)
+    assert ws.view(torch.int32)[6].item() == 1
+    before = B.set_decode_workers(WORKERS - 1)
+    try:
+        dealt = B.attn_decode(*args, sm_scale=0.125)       # rows of one block are never cut
+    finally:
+        B.set_decode_workers(before)
+    assert torch.equal(out, dealt)
+    some = np.concatenate([np.arange(40), rng.integers(0, n, 60), [n - 1]])
+    at = torch.from_numpy(some).to(DEV)
+    check(out[at], O.attn_decode(W.raw_numpy(q[at]), W.raw_numpy(k), W.raw_numpy(v), table[some], lens[some], sm_scale=0.125, q_dtype="bf16", kv_dtype="bf16"),
+          "bf16", "many rows")
+
+
 @pytest.mark.parametrize("heads,kvd", [((64, 4, 128), "fp8_e4m3"), ((40, 2, 64), "bf16"), ((32, 8, 128), "bf16")])
 @pytest.mark.parametrize("groups,prompt,own", [(9, 320, (1, 90)), (9, 0, (1, 300)), (40, 96, (1, 64)), (40, 96, (300, 700))])
 def test_whole_private_parts_take_the_shared_half(groups, prompt, own, heads, kvd):
