@@ -316,7 +316,9 @@ static int decode_prepare(const rollattn_desc* desc, const void* q, const void* 
   // (the launch has w.workers workers whatever the partition is cut for: the others get a record without blocks)
   d.workers = plan_workers(w); d.slots = w.workers;
   // (whole rows instead, where the plan says so: not where the number of workers is forced)
-  d.whole_late = desc->kv_dtype == ROLLATTN_FP8_E4M3 ? kWholeLateFp8 : kWholeLate;
+  const int n_ht = w.rows_per_b / desc->num_kv_heads;
+  d.whole_busy = (desc->kv_dtype == ROLLATTN_FP8_E4M3 ? kWholeBusyFp8 : kWholeBusy) * n_ht;   // (several rows read the same K and V)
+  d.whole_gain = kWholeGain * (a.group * desc->head_dim) / (float)(n_ht * kMfmaHeadTile * 128);   // (as large as its partials)
   a.whole_rows = desc->q_dtype != ROLLATTN_F32 && d.workers == w.workers;
   if (desc->q_dtype != ROLLATTN_F32) d.page_table = page_table;
   d.max_pages = desc->max_pages_per_seq; d.num_pages = desc->num_pages; d.head_tiles = w.rows_per_b > desc->num_kv_heads;

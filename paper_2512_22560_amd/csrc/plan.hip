@@ -7,6 +7,21 @@ namespace rollattn {
 
 namespace {
 
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), 63); }
+
+// Largest of one unsigned per lane, by the same steps (a step that has no source lane contributes zero).
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+  int x = (int)v;
+  auto step = [&](int other) { x = (int)max((unsigned)x, (unsigned)other); };
+  step(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return (unsigned)__builtin_amdgcn_readlane(x, 63);
+}
+
 // With q_lens given (mixed step) only the trajectories with q_lens[b] == 1 take part; the others count as empty.
 __device__ __forceinline__ int decode_len(const DecodePlanArgs& a, int b) { return (!a.q_lens || a.q_lens[b] == 1) ? a.ctx_lens[b] : 0; }
 __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds) {
@@ -72,16 +87,104 @@ __device__ __forceinline__ void plan_read_again(const DecodePlanArgs& a, ReadAga
   plan_read_again(a, lds, [&](int b) { return decode_len(a, b); }, [](int) { return 1; });
 }
 
+// Whole rows (kPlanWhole).  A run that starts or ends inside a row leaves a float partial to be written, read and folded: of 16
+// query heads per KV head, twice that is four blocks of FP8 codes or two of bf16 values.  Instead every row may be taken whole,
+// by one wave (the records then only tell what the runs would have been).  What that costs is that long rows go on by themselves
+// when the others have ended: memory is busy with about `whole_busy` waves, and every block that fewer are left for costs a
+// wave's own time, 0.6 us or so at D = 128.  So rows stay whole where
+//   sum over i = 1 .. longest of max(0, 1 - n_i / busy)  -  the same of the runs  <=  1.2 + cuts * whole_gain (+ 4),
+// n_i: rows of i blocks or more, as a share of the waves where there are more rows than those (the longest could come
+// last; 4 because their sums even out and neighbours read neighbouring pages); 1.2: a merge that finds nothing to do; cuts:
+// boundaries of runs that fall inside rows.  n_i is counted at 32 lengths.  busy, 900 waves over FP8 pools and 450 over bf16 pools, whose blocks are twice the
+// bytes, and whole_gain, a block's time for 130 cuts of 16 heads of 128, are fitted to 250 calls of 65 to 200000 contexts of 1
+// to 8 KV heads, uniform, lognormal, of two lengths, and short ones with one or four long ones among them.  Over these the
+// choice takes 0.7 % more than the better of the two on average, and never more than 1 % where it is whole rows.  (The longest
+// row's lateness alone, up to 16 blocks or 10, let one row of 17 blocks decide for 520 of one: 12.9 -> 29.8 us.)
+// us per call, runs against whole rows, the choice first; 16 query heads per KV head over FP8 pools, 4 over bf16 pools, D = 128,
+// contexts uniform in the range:
+//   FP8, 512 x 4 KV heads: 256-512 whole 50.3, 63.4; 64-1024 whole 67.3, 80.7; 1024-2048 whole 145, 169; 512-4096 runs 239, 233
+//   FP8, 512 x 4, 256 and one of 800: runs 50.2, 47.5; 210 x 4: 33-64 whole 15.6, 23.3; 64-1024 runs 42.4, 46.8; 512-4096 runs 106, 142
+//   FP8, 65 x 1, 256-512: runs 15.9, 22.2; 65 x 8 (4 heads each), 32 and one of 544: runs 13.3, 23.5
+//   bf16, 256 x 8: 256-512 whole 72.7, 79.2; 1024-2048 whole 265, 270; 512-4096 runs 396, 424; 512 x 8: 256-512 whole 138, 151
+//   bf16, 128 x 8: 64-1024 runs 58.6, 59.1; 65 x 1 (16 heads), 256-320: runs 15.6, 17.6
+// Not for batches that the decode waves plan for themselves, nor for a mixed step with as few decode rows, so that a
+// step's rows are bit for bit those of a call of their own.  A workgroup of its own, like the look at the pages.
+constexpr int kWholeLevels = 32;
+struct WholeLds {
+  int4 of_wave[kPlanThreads / 64];
+  int at_least[kWholeLevels];
+};
+template <class L>
+__device__ __forceinline__ void plan_whole(const DecodePlanArgs& a, WholeLds& lds, L&& len_of) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < kWholeLevels) lds.at_least[tid] = 0;
+  auto blocks_of = [&](int b) { return b < a.batch ? (len_of(b) + kBlockTokens - 1) / kBlockTokens : 0; };
+  const int mine = blocks_of(tid);
+  int blocks = 0, longest = 0, part = 0, live = 0;
+  for (int b = tid; b < a.batch; b += kPlanThreads) {
+    const int n = b == tid ? mine : blocks_of(b);
+    blocks += n;
+    longest = max(longest, n);
+    part += !a.q_lens || a.q_lens[b] == 1;
+    live += n > 0;
+  }
+  blocks = wave_sum(blocks);
+  longest = (int)wave_max((unsigned)longest);
+  part = wave_sum(part);
+  live = wave_sum(live);
+  if (lane == 0) lds.of_wave[wave] = make_int4(blocks, longest, part, live);
+  __syncthreads();
+  blocks = longest = part = live = 0;
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    const int4 x = lds.of_wave[w];
+    blocks += x.x;
+    longest = max(longest, x.y);
+    part += x.z;
+    live += x.w;
+  }
+  if (part <= kWavePlanBatch || longest == 0) {
+    if (tid == 0) a.header[kPlanWhole] = 0;
+    return;
+  }
+  // level j stands for the lengths (j * step, (j + 1) * step]
+  const int step = (longest + kWholeLevels - 1) / kWholeLevels;
+  int at_least = 0;                                    // of level `lane`
+  for (int b0 = wave * 64; b0 < a.batch; b0 += kPlanThreads) {
+    const int n = b0 == wave * 64 ? mine : blocks_of(b0 + lane);
+    int level = (step - 1) / 2;
+#pragma unroll 4
+    for (int j = 0; j < kWholeLevels; ++j, level += step) {
+      const int hits = __builtin_popcountll(__builtin_amdgcn_ballot_w64(n > level));
+      at_least += lane == j ? hits : 0;
+    }
+  }
+  if (lane < kWholeLevels && at_least) atomicAdd(&lds.at_least[lane], at_least);
+  __syncthreads();
+  if (wave != 0) return;
+  const float rows = (float)live * (float)a.rows_per_b, workers = (float)a.workers;
+  const float share = rows > workers ? workers / rows : 1.f;
+  auto idle = [&](float n) { return fmaxf(0.f, 1.f - n / a.whole_busy); };
+  float late = 0.f;
+  if (lane < kWholeLevels) late = (float)max(0, min(step, longest - lane * step)) * idle((float)lds.at_least[lane] * (float)a.rows_per_b * share);
+#pragma unroll
+  for (int i = 1; i < kWholeLevels; i *= 2) late += __shfl_xor(late, i);
+  const int total = blocks * a.rows_per_b, per = max(1, (total + a.workers - 1) / a.workers), used = (total + per - 1) / per;
+  const float cuts = (float)(used - 1) * (1.f - rows / (float)total);
+  if (lane == 0) a.header[kPlanWhole] = late - (float)per * idle((float)used) <= 1.2f + cuts * a.whole_gain + (rows > workers ? 4.f : 0.f);
+}
+
 union DecodeLds {
   DecodePlanLds plan;
   ReadAgainLds pages;
+  WholeLds whole;
 };
 
-// The second workgroup, where there is one, looks at the pages.
+// The second workgroup looks at the pages and the third decides on whole rows, where there are such.
 __global__ __launch_bounds__(kPlanThreads) void plan_decode_kernel(const DecodePlanArgs a) {
   __shared__ DecodeLds lds;
   if (blockIdx.x == 0) plan_decode(a, lds.plan);
-  else plan_read_again(a, lds.pages);
+  else if (blockIdx.x == 1) plan_read_again(a, lds.pages);
+  else plan_whole(a, lds.whole, [&](int b) { return decode_len(a, b); });
 }
 
 // Append work list: each chunk cut into tiles of tile_tokens query tokens.  A tile's cost grows
@@ -330,19 +433,21 @@ union PlanLds {
   __device__ PlanLds() {}
 };
 
-// Both plans of a mixed step, and its decode rows' pages.
+// Both plans of a mixed step, its decode rows' pages, and whether they stay whole.
 __global__ __launch_bounds__(kPlanThreads) void plan_step_kernel(const AppendPlanArgs a, const DecodePlanArgs d) {
   __shared__ PlanLds lds;
   if (blockIdx.x == 0) plan_append(a, lds.append, ChunkLens{a.ctx_lens, a.q_lens, a.q_offsets});
   else if (blockIdx.x == 1) plan_decode(d, lds.decode.plan);
-  else plan_read_again(d, lds.decode.pages);
+  else if (blockIdx.x == 2) plan_read_again(d, lds.decode.pages);
+  else plan_whole(d, lds.decode.whole, [&](int b) { return decode_len(d, b); });
 }
 
 // Decode of groups that share a prompt: per group the shared length actually used, S = floor32(min(shared_lens[group],
 // min over the group of L_b - 1)), so that every trajectory keeps at least its current token for itself and the private
 // part starts on a block boundary.  One workgroup plans the shared half (a chunk per group, its members' query rows, over
 // the group's first S tokens), another one the private half (every trajectory from token S on), whose lengths and
-// first table entries it writes out for the decode kernel, a third looks at the private half's pages.  Each works S out for itself: a launch that did, and
+// first table entries it writes out for the decode kernel, a third looks at the private half's pages, a
+// fourth decides on whole rows.  Each works S out for itself: a launch that did, and
 // copied the table shifted by S, took 5 us, and the plans one after the other 12 where this launch takes 8 (64 groups of 8).
 constexpr int kSharedGroups = 4096;   // up to this many groups their lengths are settled in LDS
 
@@ -382,6 +487,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
     // (the private parts have pages in common where a short member leaves some of the prompt to the others, or where the
     // caller says less than there is)
     plan_read_again(d, lds.decode.pages, own_len, [&](int b) { return used(b / sh.group_size) / kPageSize + 1; });
+  } else if (blockIdx.x == 3) {
+    plan_whole(d, lds.decode.whole, own_len);
   } else {
     for (int b = threadIdx.x; b < sh.batch; b += kPlanThreads) {
       const int s = used(b / sh.group_size);
@@ -395,7 +502,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_shared_kernel(const SharedP
 }  // namespace
 
 hipError_t launch_plan_decode(const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_decode_kernel, dim3(d.page_table ? 2 : 1), dim3(kPlanThreads), 0, s, d);
+  hipLaunchKernelGGL(plan_decode_kernel, dim3(d.page_table ? 3 : 1), dim3(kPlanThreads), 0, s, d);
   return hipGetLastError();
 }
 
@@ -405,12 +512,12 @@ hipError_t launch_plan_append(const AppendPlanArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_plan_step(const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_step_kernel, dim3(3), dim3(kPlanThreads), 0, s, a, d);
+  hipLaunchKernelGGL(plan_step_kernel, dim3(4), dim3(kPlanThreads), 0, s, a, d);
   return hipGetLastError();
 }
 
 hipError_t launch_plan_shared(const SharedPlanArgs& sh, const AppendPlanArgs& a, const DecodePlanArgs& d, hipStream_t s) {
-  hipLaunchKernelGGL(plan_shared_kernel, dim3(3), dim3(kPlanThreads), 0, s, sh, a, d);
+  hipLaunchKernelGGL(plan_shared_kernel, dim3(4), dim3(kPlanThreads), 0, s, sh, a, d);
   return hipGetLastError();
 }
 

@@ -21,21 +21,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
   return x;
 }
 
-__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), 63); }
-
-// Largest of one unsigned per lane, by the same steps (a step that has no source lane contributes zero).
-__device__ __forceinline__ unsigned wave_max(unsigned v) {
-  int x = (int)v;
-  auto step = [&](int other) { x = (int)max((unsigned)x, (unsigned)other); };
-  step(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
-  step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
-  return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
-
 // Exclusive scan of one int per thread across the workgroup; returns this thread's prefix
 // and leaves the workgroup total in *total.  A plan kernel is one workgroup that every CU waits for, so its barriers
 // and LDS round trips count: two barriers, four reads.
@@ -73,29 +58,7 @@ __device__ __forceinline__ bool all_read_again(const DecodePlanArgs& a, int bloc
 struct DecodePlanLds {
   int4 wave_tot[kPlanThreads / 256];
   int prefix_s[kLdsPrefix + 1], len_s[kLdsPrefix];
-  int longest, taking_part;
 };
-
-// Whole rows (kPlanWhole).  Equal runs end together, but a row that is cut leaves two or more float partials to be written, read
-// and folded: a quarter of what it reads, with 16 query heads per KV head and 17 blocks of FP8 codes.  Where no row is much
-// longer than a run, every row is therefore taken whole by a worker of its own (the records then only tell what the runs would
-// have been).  What that costs is that the longest rows end late: by the blocks they have beyond a run while all rows are
-// under way at once, with more rows by about half of the longest (their workgroups start as others end).  Up to 16 such
-// blocks it pays over FP8 pools, up to 10 over bf16 pools, whose blocks are twice the bytes.  us per call, runs against
-// whole rows (64/4/128 FP8 and 32/8/128 bf16; contexts uniform in the range):
-//   FP8, 512 of 256-512: 64.0, 52.1; 64-1024 (late by 15): 82.0, 74.1; 1024-2048 (16): 169.2, 151.9; 512-4096 (56): 238, 249
-//   FP8, 210 of 256-512 (11): 37.6, 35.2; 1024-2048 (44): 79, 102; private parts 1024-1200 of 512 in groups of 8: 176.6, 158.4
-//   bf16, 256 of 256-512 (4): 81.0, 76.1; 1024-2048 (16): 271.8, 274; 512-4096 (56): 392, 431
-//   bf16, 512 (two rows per worker) of 256-512 (8): 151.3, 141.2; 64-1024 (16): 213, 205; 512-4096 (64): 761, 811
-//   bf16, 128 of 256-512 (10): 47.5, 44.7; private parts 32-512 (11): 72.3, 74.9; 64-1024 (23): 60, 66
-// Not for batches that the decode waves plan for themselves, nor for a mixed step with as few decode rows, so that a
-// step's rows are bit for bit those of a call of their own.
-__device__ __forceinline__ bool rows_stay_whole(const DecodePlanArgs& a, int longest, int per, int taking_part) {
-  const long rows = (long)taking_part * a.rows_per_b;
-  const int late = rows > a.workers ? max(longest - per, longest / 2) : longest - per;
-  return taking_part > kWavePlanBatch && late <= a.whole_late;
-}
-
 template <class L>
 __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanLds& lds, L&& len_of) {
   int4* const wave_tot = lds.wave_tot;
@@ -107,16 +70,10 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
   int32_t* const prefix = a.prefix;
   int32_t* const wstart = a.wstart;
   const bool in_lds = batch <= kLdsPrefix;
-  const bool counted = a.q_lens && batch > kWavePlanBatch;   // (no batch of fewer stays whole)
-  int running = 0, longest = 0;
-  if (tid == 0) {
-    lds.longest = 0;
-    lds.taking_part = counted ? 0 : batch;
-  }
+  int running = 0;
   for (int b0 = 0; b0 < batch; b0 += kPlanThreads) {
     const int b = b0 + tid;
     const int len = b < batch ? len_of(b) : 0;
-    const bool one = counted && b < batch && a.q_lens[b] == 1;   // (the load that len_of has sent anyway)
     const int count = (len + kBlockTokens - 1) / kBlockTokens;
     int tile_total;
     const int first = running + block_exclusive_scan(count, wave_tot, &tile_total);
@@ -128,14 +85,7 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
       }
     }
     running += tile_total;
-    longest = max(longest, count);
-    if (counted) {
-      const unsigned long long ones = __builtin_amdgcn_ballot_w64(one);
-      if ((tid & 63) == 0) atomicAdd(&lds.taking_part, __builtin_popcountll(ones));   // (behind the scan's barriers)
-    }
   }
-  const int longest_of_wave = (int)wave_max((unsigned)longest);
-  if ((tid & 63) == 0) atomicMax(&lds.longest, longest_of_wave);   // (behind the scan's barriers)
   if (tid == 0) {
     prefix[batch] = running;
     if (in_lds) prefix_s[batch] = running;
@@ -150,7 +100,6 @@ __device__ __forceinline__ void plan_decode(const DecodePlanArgs& a, DecodePlanL
   }
   __threadfence_block();
   __syncthreads();   // prefix[] written above is read below by other threads of this workgroup
-  if (tid == kPlanThreads - 1) header[kPlanWhole] = rows_stay_whole(a, lds.longest, per, lds.taking_part);
   for (int w = tid; w < slots; w += kPlanThreads) {
     const long x = (long)w * per;
     int4 st = make_int4(-1, 0, 0, 0);

@@ -17,7 +17,7 @@ constexpr int kMfmaHeadTile = 16;       // query heads per MFMA decode row
 constexpr int kF32DecodeWgs = 4 * kNumCUs;    // one workgroup-worker each
 constexpr int kF32HeadTile = 4;         // query heads per float32 decode row
 constexpr int kWavePlanBatch = 64;      // batches up to this size are planned by every decode wave for itself
-constexpr int kWholeLateFp8 = 16, kWholeLate = 10;   // MFMA decode: rows stay whole where the longest ends at most this many blocks late
+constexpr float kWholeBusyFp8 = 900.f, kWholeBusy = 450.f, kWholeGain = 1.f / 130;   // MFMA decode: what rows that stay whole are priced with (plan_whole)
 constexpr int kMfmaDecodeWgsD64 = 3 * kNumCUs;   // MFMA decode, D = 64: workgroups that run at once, all of them where rows stay whole
 constexpr int kDirectPages = 32;        // float32 contexts of at most this many pages are not cut
 constexpr int kAppendTileRows = 256;    // query rows (token, head-in-group pairs) per append workgroup
@@ -74,7 +74,7 @@ struct DecodePlanArgs {
   int64_t num_pages;
   int32_t max_pages;
   bool head_tiles;                 // several rows per KV head: each reads its K and V
-  int32_t whole_late;              // blocks that the longest row may end behind the others for rows to stay whole
+  float whole_busy, whole_gain;    // whether rows stay whole: waves that keep memory busy; blocks' time that a cut is worth
   int32_t* header;
   int32_t* prefix;
   int32_t* wstart;

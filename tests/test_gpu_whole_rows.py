@@ -1,4 +1,4 @@
-"""Decode rows taken whole by a worker each: on both sides of the rule that chooses it (word 6 of the plan), against the oracle."""
+"""Decode rows taken whole by a wave each: on both sides of the rule that chooses it (word 6 of the plan), against the oracle."""
 import ctypes
 
 import numpy as np
@@ -8,7 +8,7 @@ import torch
 from oracle import attention as O
 from paper_2512_22560_amd import binding as B
 from paper_2512_22560_amd import workloads as W
-from tests.gpu_common import check
+from tests.gpu_common import check, oracle_append
 from tests.helpers import oracle_args
 
 pytestmark = pytest.mark.gpu
@@ -16,14 +16,25 @@ DEV = "cuda:0"
 WORKERS = 2048
 
 
-def _whole(lens, rows_per_b, kvd, taking_part):
-    blocks = -(-lens // 32)
-    per = max(1, -(-int(blocks.sum()) * rows_per_b // WORKERS))
-    longest = int(blocks.max(initial=0))
-    late = longest - per
-    if taking_part * rows_per_b > WORKERS:
-        late = max(late, longest // 2)
-    return taking_part > 64 and late <= (16 if kvd == "fp8_e4m3" else 10)
+def _whole(lens, heads, kvd):
+    """The rule, as plan_whole states it, for the trajectories that take part.  No case here is a near tie."""
+    group, tiles = heads[0] // heads[1], -(-(heads[0] // heads[1]) // 16)
+    rows_per_b = heads[1] * tiles
+    blocks = -(-np.asarray(lens) // 32)
+    if len(blocks) <= 64 or not blocks.any():
+        return False
+    busy = (900 if kvd == "fp8_e4m3" else 450) * tiles
+    longest, rows, total = int(blocks.max()), int((blocks > 0).sum()) * rows_per_b, int(blocks.sum()) * rows_per_b
+    step = -(-longest // 32)
+    levels = np.arange(0, longest, step)
+    n = (blocks[None, :] > (levels + (step - 1) // 2)[:, None]).sum(1) * rows_per_b * min(1.0, WORKERS / rows)
+    late = (np.minimum(step, longest - levels) * np.maximum(0.0, 1 - n / busy)).sum()
+    per = max(1, -(-total // WORKERS))
+    used = -(-total // per)
+    late -= per * max(0.0, 1 - used / busy)
+    gain = 1.2 + (used - 1) * (1 - rows / total) * group * heads[2] / (tiles * 16 * 128) / 130 + (4 if rows > WORKERS else 0)
+    assert abs(late - gain) > 0.01
+    return late <= gain
 
 
 def _batch(name, batch, heads, kvd, lens, seed):
@@ -33,18 +44,24 @@ def _batch(name, batch, heads, kvd, lens, seed):
     return b
 
 
-# rows per KV head: one, and two of 20 query heads; one row per worker, several, none for some; contexts of one token, of whole
-# blocks and none; the longest one at the rule's edge and a block past it
+# rows per KV head: one, and two of 20 query heads; rows fewer than waves and more of them, none for some; contexts of one token, of whole
+# blocks and none; short ones alone, and the same with one long one among them, which would go on by itself for most of the call
+WHOLE, DEALT = True, False
+
+
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
-@pytest.mark.parametrize("batch,heads,base,longest", [
-    (65, (8, 2, 128), 30, 352), (65, (8, 2, 128), 30, 353), (65, (8, 2, 128), 30, 544), (65, (8, 2, 128), 30, 545), (64, (8, 2, 128), 64, 64),
-    (130, (40, 2, 64), 100, 320), (1100, (8, 2, 64), 40, 384), (1100, (8, 2, 64), 40, 416), (1100, (32, 2, 128), 33, 576), (257, (64, 8, 128), 17, 200),
+@pytest.mark.parametrize("batch,heads,lens,longest,expect", [
+    (64, (64, 4, 128), (33, 64), 64, DEALT), (65, (64, 4, 128), (33, 64), 64, WHOLE), (65, (64, 4, 128), (33, 64), 544, DEALT),
+    (65, (32, 8, 128), (32, 32), 544, DEALT), (400, (40, 2, 64), (200, 260), 260, WHOLE), (400, (40, 2, 64), (200, 260), 800, DEALT),
+    (1300, (32, 2, 128), (1, 70), 96, WHOLE), (1300, (32, 2, 128), (1, 70), 900, DEALT), (1300, (8, 2, 64), (1, 33), 64, WHOLE),
+    (300, (16, 8, 128), (1, 100), 128, WHOLE), (300, (16, 8, 128), (1, 100), 700, DEALT),
 ])
-def test_rows_whole_and_dealt(batch, heads, base, longest, kvd):
-    lens = np.random.default_rng(batch).integers(1, base + 1, batch)
-    lens[3::11] = 0
+def test_rows_whole_and_dealt(batch, heads, lens, longest, expect, kvd):
+    lens = np.random.default_rng(batch).integers(lens[0], lens[1] + 1, batch)
+    lens[3::41] = 0
     lens[1::13] = 32
     lens[batch // 2] = longest
+    assert _whole(lens, heads, kvd) == expect
     b = _batch("whole", batch, heads, kvd, lens, 210)
     w = b.workload
     desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
@@ -53,8 +70,7 @@ def test_rows_whole_and_dealt(batch, heads, base, longest, kvd):
     ref = O.attn_decode(W.raw_numpy(b.q), **dict(oracle_args(b), ctx_lens=lens))
     check(out, ref, "bf16", "whole rows")
     if batch > 64:
-        rows_per_b = heads[1] * -(-(heads[0] // heads[1]) // 16)
-        assert ws.view(torch.int32)[6].item() == _whole(lens, rows_per_b, kvd, batch)
+        assert ws.view(torch.int32)[6].item() == expect
     # the same rows dealt to one worker less: the same attention and denominators, but for the order of the sums
     before = B.set_decode_workers(WORKERS - 1)
     try:
@@ -103,26 +119,31 @@ def test_whole_private_parts_take_the_shared_half(groups, prompt, own, heads, kv
     ws = torch.full((B.lib().rollattn_shared_workspace_bytes(ctypes.byref(desc), 8),), 255, dtype=torch.uint8, device=DEV)
     out = B.attn_decode_shared(b.q, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, group_size=8, sm_scale=b.workload.sm_scale, workspace=ws,
                                shared_lens=torch.full((groups,), prompt, dtype=torch.int32, device=DEV), k_scale=b.k_scale, v_scale=b.v_scale)
-    rows_per_b = heads[1] * -(-(heads[0] // heads[1]) // 16)
     shared = np.minimum(prompt, b.ctx_lens_host.reshape(groups, 8).min(1) - 1) // 32 * 32
-    assert ws.view(torch.int32)[6].item() == _whole(b.ctx_lens_host - np.repeat(shared, 8), rows_per_b, kvd, 8 * groups)
+    assert ws.view(torch.int32)[6].item() == _whole(b.ctx_lens_host - np.repeat(shared, 8), heads, kvd)
     check(out, O.attn_decode(W.raw_numpy(b.q), **oracle_args(b)), "bf16", "shared")
 
 
-@pytest.mark.parametrize("decode_rows", [64, 65, 200])
-def test_a_step_takes_its_rows_as_a_call_of_their_own_would(decode_rows):
+@pytest.mark.parametrize("decode_rows,ctx,whole", [(64, (33, 64), DEALT), (65, (33, 64), WHOLE), (200, (33, 150), WHOLE), (200, (33, 3000), DEALT)])
+def test_a_step_takes_its_rows_as_a_call_of_their_own_would(decode_rows, ctx, whole):
     # (with 64 the call of their own plans in its waves, and the step must not take them whole either)
-    b = W.build(W.Workload("step", decode_rows + 30, 16, 4, 128, "bf16", "bf16", ("uniform", 1, 150), qlen=("uniform", 2, 40), append_rows=30,
+    heads = (64, 4, 128)
+    b = W.build(W.Workload("step", decode_rows + 30, *heads, "bf16", "bf16", ("uniform", *ctx), qlen=("uniform", 2, 40), append_rows=30,
                            ctx_is_prefix=True, seed=W.BASE_SEED + 212), DEV)
     sel = np.flatnonzero(b.q_lens_host == 1)
-    assert len(sel) == decode_rows
+    assert len(sel) == decode_rows and _whole(b.ctx_lens_host[sel], heads, "bf16") == whole
     w = b.workload
     desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale)
     ws = torch.empty(B.lib().rollattn_step_workspace_bytes(ctypes.byref(desc), int(b.q_lens_host.sum())), dtype=torch.uint8, device=DEV)
     out = B.attn_step(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, max_q_len=40, workspace=ws)
+    assert ws.view(torch.int32)[6].item() == whole
+    check(out, oracle_append(b), "bf16", "step")
     at = torch.from_numpy(np.concatenate([[0], np.cumsum(b.q_lens_host)])[sel]).to(DEV)
     rows = torch.from_numpy(sel).to(DEV)
-    own = B.attn_decode(b.q[at].contiguous(), b.k_pages, b.v_pages, b.page_table[rows].contiguous(), b.ctx_lens[rows].contiguous(), sm_scale=w.sm_scale)
+    q, table, ctx_lens = b.q[at].contiguous(), b.page_table[rows].contiguous(), b.ctx_lens[rows].contiguous()
+    own_ws = B.alloc_workspace(B.make_desc(q, b.k_pages, table, sm_scale=w.sm_scale), decode_rows, DEV)
+    own = B.attn_decode(q, b.k_pages, b.v_pages, table, ctx_lens, sm_scale=w.sm_scale, workspace=own_ws)
+    assert decode_rows == 64 or own_ws.view(torch.int32)[6].item() == whole
     assert torch.equal(out[at], own)
 
 
