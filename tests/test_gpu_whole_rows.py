@@ -147,11 +147,13 @@ def test_a_step_takes_its_rows_as_a_call_of_their_own_would(decode_rows, ctx, wh
     assert torch.equal(out[at], own)
 
 
-# Page scales are worked out for 64 pages at a time: contexts that end at, before and behind a window of them (1024 tokens), in steps
-# of 64 tokens and of 128 (short chunks), with scales that differ from page to page.
+# Page scales are worked out for 64 pages at a time: contexts that end at, before and behind such windows (1024 tokens), in steps
+# of 64 tokens and of 128 (short chunks), with scales that differ from page to page; tiles that walk five windows, and the same cut
+# into pieces, which start again at the first.
+@pytest.mark.parametrize("cut", [False, True])
 @pytest.mark.parametrize("new", [3, 40])
 @pytest.mark.parametrize("hkv,d", [(1, 128), (2, 64)])
-def test_append_over_fp8_pages_of_several_scale_windows(new, hkv, d):
+def test_append_over_fp8_pages_of_several_scale_windows(new, hkv, d, cut):
     lens = np.array([1008, 1023, 1024, 1025, 1040, 1088, 2047, 2049, 2112, 3071, 3073, 4100])
     b = W.build(W.Workload("windows", len(lens), 8 * hkv, hkv, d, "bf16", "fp8_e4m3", ("const", 4100), qlen=("const", new), seed=W.BASE_SEED + 213), DEV)
     factor = torch.exp2(torch.from_numpy(np.random.default_rng(3).integers(-2, 2, b.k_scale.numel()).astype(np.float32)).to(DEV))
@@ -160,6 +162,23 @@ def test_append_over_fp8_pages_of_several_scale_windows(new, hkv, d):
     b.ctx_lens_host[:] = lens
     b.ctx_lens.copy_(torch.from_numpy(lens.astype(np.int32)))
     w = b.workload
+    desc = B.make_desc(b.q, b.k_pages, b.page_table, sm_scale=w.sm_scale, k_scale=b.k_scale, v_scale=b.v_scale)
+    least = 256 + -(-32 * B.lib().rollattn_append_plan_capacity(ctypes.byref(desc), b.total_q) // 256) * 256   # room for the list, none for partials
+    ws = torch.empty(B.workspace_bytes(desc, b.total_q) if cut else least, dtype=torch.uint8, device=DEV)
     out = B.attn_append(b.q, b.q_lens, b.q_offsets, b.k_pages, b.v_pages, b.page_table, b.ctx_lens, sm_scale=w.sm_scale, max_q_len=new,
-                        k_scale=b.k_scale, v_scale=b.v_scale)
-    check(out, O.attn_append(W.raw_numpy(b.q), b.q_lens_host, **dict(oracle_args(b), ctx_lens=lens)), "bf16", "windows")
+                        k_scale=b.k_scale, v_scale=b.v_scale, workspace=ws)
+    tiles, merges = ws.view(torch.int32)[4:6].tolist()
+    longest = max(ws[256:].view(torch.int32)[:8 * tiles].view(-1, 8)[:, 6].tolist())
+    assert (merges > 0) == cut and (longest < 32 if cut else longest == -(-4100 // 64))
+    args = dict(oracle_args(b), ctx_lens=lens)
+    ref = O.attn_append(W.raw_numpy(b.q), b.q_lens_host, **args)
+    check(out, ref, "bf16", "windows")
+    # (the bar tells scales of two windows before from the right ones)
+    table, stale = args["page_table"], {}
+    for name in ("k_scale", "v_scale"):
+        stale[name] = args[name].copy()
+        for i, n in enumerate(-(-lens // 16)):
+            stale[name][table[i, 128:n]] = args[name][table[i, :max(0, n - 128)]]
+    wrong = O.attn_append(W.raw_numpy(b.q), b.q_lens_host, **dict(args, **stale))
+    with pytest.raises(AssertionError):
+        check(torch.from_numpy(wrong), ref, "bf16", "stale windows")
