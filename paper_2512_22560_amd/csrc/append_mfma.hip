@@ -1048,7 +1048,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
 }
 
 template <int D, bool FP8, bool HALF, bool ONCE, int STEP>
-__global__ __launch_bounds__(kThreads) void append_mfma_kernel(const AppendArgs a) {
+__global__ __launch_bounds__(kThreads, HALF && D == 64 && STEP == kBlockTokens ? 4 : 2) void append_mfma_kernel(const AppendArgs a) {
   if constexpr (STEP == 0) {
     __shared__ union {
       AppendLds<D, FP8, HALF, kBlockTokens> one;
