@@ -383,7 +383,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     const int qtok = row_ok ? tok_in_tile : tokens_here - 1, qhead = row_ok ? head : g * group;
     const __bf16* qrow = (const __bf16*)q + ((size_t)(q_off + q0 + qtok) * hq + qhead) * D;
 #pragma unroll
-    for (int kk = 0; kk < kKK; ++kk) qop[kk] = *(const bf16x8*)(qrow + kk * 16 + h2 * 8);   // bf16 pools: scaled further down, once the first tiles are on their way
+    for (int kk = 0; kk < kKK; ++kk) qop[kk] = *(const bf16x8*)(qrow + kk * 16 + h2 * 8);   // bf16 pools: scaled further down
   }
 
   floatx16 acc[kDT];
@@ -782,6 +782,16 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       for (int j = 0; j < kLoads; ++j)
         if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) put(wptr[j][0], wptr[j][1], 0, k0[j]);
     } else {
+      // The query rows have been under way as long as the page ids; their scaling (bf16 pools: the scores then leave the
+      // matrix core as exponents) waits for them in front of the tile loads.  Those are no loads to the compiler: behind them,
+      // its wait for the rows would be one for all of them, unit 1 included (4096 tiles of 1, 2 and 6 blocks, 32/8/128: 216.9,
+      // 244.2 and 359.5 us that way, 207.6, 235.5 and 352.1 this way).
+#pragma unroll
+      for (int kk = 0; kk < kKK; ++kk) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qop[kk][e] = (__bf16)((float)qop[kk][e] * a.scale_log2);
+        asm volatile("" : "+v"(qop[kk]));
+      }
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
         dma(tile_addr(a.k_pages, 0, off[0][j], end[0][j], j), k_lds[0] + wave * 1024 + j * kThreads * 16);
@@ -792,12 +802,6 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
           dma(tile_addr(a.k_pages, 0, off[u + 1][j], end[u + 1][j], j), k_lds[0] + (u + 1) * kTileBytes + wave * 1024 + j * kThreads * 16);
           dma(tile_addr(a.v_pages, 1, off[u][j], end[u][j], j), v_lds[0] + u * kTileBytes + wave * 1024 + j * kThreads * 16);
         }
-      // the query rows have been under way since the top of the kernel; their scaling (bf16 pools: the
-      // scores then leave the matrix core as exponents) waits for them here, behind the tile loads
-#pragma unroll
-      for (int kk = 0; kk < kKK; ++kk)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qop[kk][e] = (__bf16)((float)qop[kk][e] * a.scale_log2);
       DMA_WAIT((kLead - 1) * 2 * kLoads);            // K block 0 and unit 0 have landed (unit 0 is read early, one barrier from now)
     }
     PHASE_END();
