@@ -307,13 +307,10 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // all of [0, L_b), the rows' own tokens lie outside this range.
   const bool causal = noncausal == 0;
   const int pos0 = causal ? ctx - n_b + q0 : ctx - 1;    // position of the tile's first token
-  // Page ids and page scales are inputs nobody writes during the call: reading them through the
-  // constant address space lets every such load (all uniform) take the scalar path.
+  // Page ids are an input nobody writes during the call: reading them through the constant address space lets the loads of
+  // those behind the tile loads (all uniform) take the scalar path.
   typedef const __attribute__((address_space(4))) int32_t* const_i32_p;
-  typedef const __attribute__((address_space(4))) float* const_f32_p;
   const const_i32_p table = (const_i32_p)(page_table + (size_t)b * max_pages + blk0 * (kBlockTokens / kPageSize));
-  const const_f32_p k_scale_c = (const_f32_p)a.k_scale;
-  const const_f32_p v_scale_c = (const_f32_p)a.v_scale;
   const size_t tile_stride = (size_t)kPageSize * kSrcRowBytes;
 
   // ---- this lane's query row

@@ -39,7 +39,7 @@ constexpr int kAppendXcdRun = 16;       // append: consecutive tiles of the list
 
 // Header words of the plan, at the start of the workspace.
 enum PlanWord { kPlanPer = 0, kPlanTotal = 1, kPlanWorkers = 2, kPlanRowsPerB = 3, kPlanTiles = 4, kPlanMerges = 5, kPlanWhole = 6,
-                kPlanReadAgain = 32,   // (written by another workgroup than the rest, in a cache line of its own)
+                kPlanReadAgain = 32,   // (this word and kPlanWhole are each written by another workgroup than the rest)
                 kPlanWords = 64 };
 
 // Byte offsets of the workspace regions (all multiples of 256).
