@@ -56,7 +56,7 @@ HEADLINE = 2
 # those sources are unchanged.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 CSRC = os.path.join(ROOT, "paper_2512_22560_amd", "csrc")
-MAIN_KERNEL_SOURCES = {"decode": ["decode_mfma.hip", "plan_device.h", "rollattn_internal.h"], "append": ["append_mfma.hip", "rollattn_internal.h"]}
+MAIN_KERNEL_SOURCES = {"decode": ["decode_mfma.hip", "plan.hip", "plan_device.h", "rollattn_internal.h"], "append": ["append_mfma.hip", "rollattn_internal.h"]}
 
 
 def source_hash(files):
