@@ -280,7 +280,7 @@ int32_t rollattn_debug_set_decode_workers(int32_t workers);
 /* Copies the plan the last attn_decode call left in `workspace` back to the host
  * (synchronises the stream): per, T, and 4 int32 per worker, (b, r << 20 | block, L_b, blocks
  * in its run) for the first block of its run, or (-1, 0, 0, 0) for a worker without blocks.  For BF16 queries and
- * many short contexts the call may have given every row whole to a worker of its own instead; the records
+ * more than 64 contexts the call may have given every row whole to one worker instead, where that ends sooner; the records
  * then tell what the equal runs would have been.
  * starts_out must hold 4 * rollattn_plan_workers(desc) int32. */
 int rollattn_debug_read_plan(const rollattn_desc *desc, const void *workspace, int32_t *per_out,
