@@ -26,9 +26,9 @@
 // cycles (four of them stretched 32 MFMAs from 1270 to 1400 cycles), while the same instruction
 // costs the vector phase little more than its issue slot.  All tile loads and the scalar loads of
 // page ids therefore belong to the vector phase; only the widening of FP8 tiles
-// (conversions and LDS writes of registers loaded two blocks earlier) stays between the MFMAs,
-// where it was measured to cost less than in the vector phase (all of it there, the two halves a unit apart:
-// the mixed step 12.91 -> 13.9 ms; behind the softmax, or V alone: no difference).
+// (conversions and LDS writes of registers loaded two blocks earlier) stays between the MFMAs, one instruction behind
+// each (stage_widen), where it was measured to cost less than in the vector phase (all of it there, the two halves a unit
+// apart: the mixed step 12.91 -> 13.9 ms; behind the softmax, or V alone: no difference).
 // A wave issues one instruction per 4 cycles whatever its kind (vector instructions 6 beside a partner's MFMAs, exponentials
 // 4 more), so the scalar instructions of a vector phase count like the others: page ids by running offsets, page scales once
 // for 64 pages (fill_scales), LDS offsets as immediates and no maximum of the row to look at took it from about 150 vector
@@ -89,17 +89,11 @@ __device__ __forceinline__ float xor32_add(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Sixteen E4M3 codes to bf16, exactly (every E4M3 value is a bf16 value): the hardware's scaled
+// Pair `pair` of sixteen E4M3 codes to bf16, exactly (every E4M3 value is a bf16 value): the hardware's scaled
 // conversion with a scale of one turns two codes into a packed pair per instruction.
-__device__ __forceinline__ void fp8x16_to_bf16(const uintx4 raw, uintx4& lo, uintx4& hi) {
-  uint32_t o[8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    o[2 * i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[i], 1.0f, false));
-    o[2 * i + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[i], 1.0f, true));
-  }
-  lo = uintx4{o[0], o[1], o[2], o[3]};
-  hi = uintx4{o[4], o[5], o[6], o[7]};
+template <int PAIR>
+__device__ __forceinline__ uint32_t fp8_pair(const uintx4 codes) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes[PAIR / 2], 1.0f, PAIR % 2 != 0));
 }
 
 // 16 bytes of a pool; once: nobody reads them again, so they go past the caches' care (see load16 in decode_mfma.hip).
@@ -443,11 +437,9 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   };
   // -- register path (FP8)
   uintx4 kreg[2][kLoads], vreg[2][kLoads];   // two units in flight
-  auto put = [&](lds_p lo_at, lds_p hi_at, int offset, const uintx4 raw) __attribute__((always_inline)) {
-    uintx4 lo, hi;
-    fp8x16_to_bf16(raw, lo, hi);
-    *lds_at<uintx4>(lo_at, offset) = lo;
-    *lds_at<uintx4>(hi_at, offset) = hi;
+  auto put = [&](lds_p lo_at, lds_p hi_at, int offset, const uintx4 codes) __attribute__((always_inline)) {
+    *lds_at<uintx4>(lo_at, offset) = uintx4{fp8_pair<0>(codes), fp8_pair<1>(codes), fp8_pair<2>(codes), fp8_pair<3>(codes)};
+    *lds_at<uintx4>(hi_at, offset) = uintx4{fp8_pair<4>(codes), fp8_pair<5>(codes), fp8_pair<6>(codes), fp8_pair<7>(codes)};
   };
   // -- direct path (bf16): HBM -> LDS without a register stop.  Lane l's 16 bytes land at
   // M0 + 16 l.  The compiler does not see these loads as loads: completion is awaited by count
@@ -521,8 +513,8 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // it: the FP8 path threads its LDS writes between the MFMAs there.
   // (how far ahead, measured with everything else alike.  bf16: 1, 2, 3, 4, 5 steps: 5.33, 4.13, 4.02, 4.05, 4.11 ms on 64 chunks
   // of 64 .. 1024 tokens behind 2k .. 16k, 32/8/128; 7.20, 5.74, 5.64, 5.66, 5.75 ms without a prefix, 512 .. 8k tokens.
-  // FP8: 3, 4, 5, 6: 12.98, 12.87, 13.07, 13.03 ms on the mixed step of 512 trajectories, 64/4/128)
-  constexpr int kAhead = FP8 ? 4 : 3;
+  // FP8: 3, 4: 1701, 1701 us on 32 chunks of 256 tokens behind 8k, 64/4/128)
+  constexpr int kAhead = 3;
   // bf16 pools: the operands of the first kAhead steps of a phase that starts with the second product are
   // read at the end of the vector phase before it, in front of the barrier (the V tile they come from was
   // complete one phase earlier), so that the phase does not open with an LDS round trip.
@@ -862,17 +854,29 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
       DMA_WAIT(0);                                   // past the tile's last block nothing is started: the units still on their way are real ones
     }
   };
-  // ... and, FP8 only, the widening of unit i (K block i + 1, V block i) from registers into LDS during the
-  // matrix phase of block i, at two fixed places between its MFMAs.
+  // ... and, FP8 only, the widening of unit i (K block i + 1, V block i) from registers into LDS during the matrix phase of
+  // block i: 16 conversions and 4 writes per load, one behind each MFMA.  A wave issues in order, an MFMA takes the matrix core 33
+  // cycles and its own issue 10, the operand read in front of it 12: one or two instructions more per MFMA cost nothing, ten in
+  // one place keep the core waiting for 40 cycles.  With a chunk's ten instructions behind one MFMA a block took 2976 cycles,
+  // so 2709; 32 chunks of 256 tokens behind 8k (64/4/128) 1770 -> 1701 us, the rest went into the clock (1.69 -> 1.61 GHz).
+  // All of it in front of the 20th or 26th of 32 MFMAs instead of the 31st: 1 to 2 % slower.
+  uintx4 wide[kLoads];
   auto stage_widen = [&](auto slot_c, auto pos_c) __attribute__((always_inline)) {
     if constexpr (FP8) {
       constexpr int slot = decltype(slot_c)::value, pos = decltype(pos_c)::value;
-#pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        const bool mine = kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens;
-        if (pos == 2 + 12 * j / kLoads && mine) put(wptr[j][0], wptr[j][1], ring(slot_c, c1), kreg[slot][j]);
-        if (pos == 6 + 12 * j / kLoads && mine) put(wptr[j][2], wptr[j][2] + 16, ring(slot_c, c0), vreg[slot][j]);
-      }
+      constexpr int kItems = 20 * kLoads;
+      static_for<kItems>([&](auto item_c) __attribute__((always_inline)) {
+        constexpr int item = decltype(item_c)::value;
+        if constexpr (item * 31 / kItems == pos) {
+          constexpr int j = item % kLoads, part = item / kLoads / 5, m = item / kLoads % 5;   // the halves of K's chunk, then V's
+          if constexpr (m < 4) {
+            wide[j][m] = fp8_pair<(part & 1) * 4 + m>((part < 2 ? kreg : vreg)[slot][j]);
+          } else if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
+            if constexpr (part < 2) *lds_at<uintx4>(wptr[j][part], ring(slot_c, c1)) = wide[j];
+            else *lds_at<uintx4>(wptr[j][2], ring(slot_c, c0) + (part - 2) * 16) = wide[j];
+          }
+        }
+      });
     }
   };
   // The page ids of the unit started two vector phases from now go out before the softmax and are awaited after it.
