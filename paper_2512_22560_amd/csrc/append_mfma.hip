@@ -134,6 +134,9 @@ __device__ __forceinline__ __attribute__((address_space(3))) T* lds_at(lds_p bas
   return (__attribute__((address_space(3))) T*)(base + offset);
 }
 
+// The pointer with one bit of its address the other way round.
+__device__ __forceinline__ lds_p flip(lds_p p, unsigned int bit) { return (lds_p)((unsigned int)(uintptr_t)p ^ bit); }
+
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -400,26 +403,34 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   const int last_slot = (ctx - 1) % kPageSize;
   constexpr bool kAllThreadsLoad = kStepTokens * kSrcChunks >= kThreads;
   // Chunk idx = j * kThreads + tid of a block sits in LDS row idx / kChunks at chunk position
-  // (idx % kChunks), holding the row's chunk (position ^ key): key = row & 15 for K, (row & 3) << 2
-  // for V.  The register path (FP8) applies the swizzle when it writes LDS; the direct path has to
-  // apply it on the global side, because there the LDS position of a lane's chunk is fixed.
+  // (idx % kChunks), holding the row's chunk (position ^ key): key = row & 15 for K, v_key for V.  The
+  // register path (FP8) applies the swizzle when it writes LDS; the direct path has to apply it on the
+  // global side, because there the LDS position of a lane's chunk is fixed.
+  // V: the four rows of a transposing read lie a quarter of a row apart.
+  // FP8: a chunk becomes two, so that one write has every other position of a row.  Eight lanes write 128 bytes at once: with
+  // four chunks of each of two rows, one in even positions and the other (both keys have the row's last bit) in odd ones, they
+  // meet all banks; with a row's eight they meet half of them twice: 8.5 M conflicts in 35.5 M busy cycles of the LDS over the
+  // shared half of 64 groups of 8 behind 8192 tokens (64/4/128), none in 27.0 M this way; 64 chunks of 8 tokens behind 8k 195 -> 186 us.
+  auto v_key = [](int row) __attribute__((always_inline)) { return (row & 3) << 2 | (FP8 ? row & 1 : 0); };
   unsigned int goff[kLoads][2], goff_last[kLoads][2];   // [][0]: K, [][1]: V
   lds_p wptr[kLoads][3];                                // FP8: where a widened chunk goes, K's two halves and V
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
     const int idx = j * kThreads + tid;
-    const int trow = idx / kSrcChunks;
+    // (FP8, D = 128: lanes 0-3 and 8-11 the first of two rows, the others the second)
+    constexpr bool kPairs = FP8 && kSrcChunks == 8;
+    const int trow = kPairs ? idx / 16 * 2 + (idx >> 2 & 1) : idx / kSrcChunks;
     const int tslot = trow % kPageSize;               // token slot within its page
-    const int c = idx % kSrcChunks;
-    const int kkey = trow & 15, vkey = (trow & 3) << 2;
+    const int c = kPairs ? (idx >> 3 & 1) * 4 + (idx & 3) : idx % kSrcChunks;
+    const int kkey = trow & 15, vkey = v_key(trow);
     const int ck = FP8 ? c : ((c ^ kkey) & (kChunks - 1)), cv = FP8 ? c : ((c ^ vkey) & (kChunks - 1));
     goff[j][0] = tslot * kSrcRowBytes + ck * 16;
     goff[j][1] = tslot * kSrcRowBytes + cv * 16;
     goff_last[j][0] = min(tslot, last_slot) * kSrcRowBytes + ck * 16;
     goff_last[j][1] = min(tslot, last_slot) * kSrcRowBytes + cv * 16;
     if constexpr (FP8) {
-      // the two 16-byte halves of the widened chunk sit in chunks 2c and 2c + 1: 16 bytes apart after the swizzle (V: the upper
-      // one behind the lower, its key is even)
+      // the two 16-byte halves of the widened chunk sit in chunks 2c and 2c + 1: 16 bytes apart after the swizzle, one behind the
+      // other or in front of it
       const int kat = trow * kRowBytes + (((2 * c) ^ kkey) & (kChunks - 1)) * 16;
       wptr[j][0] = (lds_p)(k_lds[0] + kat);
       wptr[j][1] = (lds_p)(k_lds[0] + (kat ^ 16));
@@ -497,7 +508,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
 #pragma unroll
     for (int dt = 0; dt < kDT; ++dt)
       vptr[dt] = (lds_p)(v_lds[0] + sub_bytes + tv * kRowBytes +
-                 (((dt * 4 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ ((tv & 3) << 2)) & (kChunks - 1)) * 16 + (j & 1) * 8);
+                 (((dt * 4 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ v_key(tv)) & (kChunks - 1)) * 16 + (j & 1) * 8);
   }
 
   constexpr int kSubs = kStepTokens / (HALF ? 64 : 32);   // 32-token sub-blocks of a step that this wave works on
@@ -873,7 +884,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
             wide[j][m] = fp8_pair<(part & 1) * 4 + m>((part < 2 ? kreg : vreg)[slot][j]);
           } else if (kAllThreadsLoad || (j * kThreads + tid) / kSrcChunks < kStepTokens) {
             if constexpr (part < 2) *lds_at<uintx4>(wptr[j][part], ring(slot_c, c1)) = wide[j];
-            else *lds_at<uintx4>(wptr[j][2], ring(slot_c, c0) + (part - 2) * 16) = wide[j];
+            else *lds_at<uintx4>(part == 2 ? wptr[j][2] : flip(wptr[j][2], 16), ring(slot_c, c0)) = wide[j];
           }
         }
       });
