@@ -157,3 +157,28 @@ def test_mixed_step_chunks_full_size():
     k_new, v_new = _new_rows(sub, 13, (0.2, 1.0, 5.0))
     gpu, ref = _run_both(sub, k_new, v_new, sub.k_pages, sub.v_pages, sub.k_scale, sub.v_scale)
     _assert_same(gpu, ref, "mixed step chunks")
+
+
+@pytest.mark.parametrize("prefix,n,d", [(0, 16, 128), (5, 40, 128), (15, 1, 64), (0, 3, 64)])
+def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(prefix, n, d):
+    # the rows with zeros in their place, which count for no scale either, are the oracle's; only the codes of the undefined
+    # values differ from those of the zeros: -448, whatever the sign
+    w = _wl(f"kvnan_{prefix}_{n}", 3, 4, d, "bf16", "fp8_e4m3", ("const", prefix), ("const", n), 77)
+    b = W.build(w, DEV)
+    k_new, v_new = _new_rows(b, 78)
+    spots = [(0, 0, 0), (b.total_q - 1, 3, d - 1), (b.total_q // 2, 1, d // 2 + 1)]
+    for rows in (k_new, v_new):
+        for i, at in enumerate(spots):
+            rows[at] = -float("nan") if i else float("nan")
+    zeroed = [torch.where(torch.isnan(x), torch.zeros_like(x), x) for x in (k_new, v_new)]
+    scales = (b.k_scale, b.v_scale)
+    got = tuple(x.clone() for x in (b.k_pages, b.v_pages, *scales))
+    B.kv_write(k_new, v_new, b.q_lens, b.q_offsets, got[0], got[1], b.page_table, b.ctx_lens, max_q_len=n, k_scale=got[2], v_scale=got[3])
+    same, ref = _run_both(b, *zeroed, b.k_pages, b.v_pages, *scales)
+    _assert_same(same, ref, "zeros in their place")
+    for name, g, z in zip(("k_scale", "v_scale"), got[2:], same[2:]):
+        assert torch.equal(g.view(torch.int32), z.view(torch.int32)), name
+    for name, g, z in zip(("k_pages", "v_pages"), got[:2], same[:2]):
+        differ = g.view(torch.uint8) != z.view(torch.uint8)
+        assert int(differ.sum()) == len(spots), name
+        assert bool((g.view(torch.uint8)[differ] == 0xFE).all()), name
