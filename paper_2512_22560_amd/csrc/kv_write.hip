@@ -22,12 +22,7 @@ typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
 constexpr float kE4m3Max = 448.f;
 
-// (one instruction, the median, where a minimum of a maximum is two; both make -448 of an undefined value)
-__device__ __forceinline__ float clamp448(float x) { return __builtin_amdgcn_fmed3f(x, -kE4m3Max, kE4m3Max); }
-
-// The new rows are read once, by one workgroup: with the streaming hint they stay out of the caches' way.  (Rows that are copied
-// as they are do not gain by it: 268 MB into bf16 pools 63.3 us, 63.8 with the hint.)
-__device__ __forceinline__ uintx4 load16(const unsigned char* p) { return __builtin_nontemporal_load((const uintx4*)p); }
+__device__ __forceinline__ float clamp448(float x) { return fminf(fmaxf(x, -kE4m3Max), kE4m3Max); }
 
 // eight floats -> eight E4M3 codes
 __device__ __forceinline__ uintx2 encode8(const float* x) {
@@ -88,9 +83,7 @@ struct KvWriteArgs {
 // its way meanwhile, all of a thread's rows leave before the first is looked at, heads and slots are stepped, not divided.
 // As the compiler ordered the plain statements that was five dependent scalar loads and a row at a time: 24.0 us under the
 // profiler against 22.4 for the chunks of 128 trajectories (32 .. 512 tokens, 4 heads of 128, FP8: 110 MB), 20.1 if the
-// divisions were free; the call, start of the launch included, 24.9 against 24.3.  The streaming hint on the rows and the clamp in
-// one instruction take that call, with buffers that change from one to the next, from 27.0 to 24.8 us (the hint alone to 25.8); the
-// maximum two values at a time, as whole numbers, gains nothing more.
+// divisions were free; the call, start of the launch included, 24.9 against 24.3.
 // SRC_BYTES: 4 (float32) or 2 (bf16); FP8: pool holds E4M3 codes, else the source type
 template <int D, int SRC_BYTES, bool FP8>
 __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a) {
@@ -159,7 +152,7 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
         // (past the last chunk the last one again: the maximum does not mind)
 #pragma unroll
         for (int i = 0; i < kKeep; ++i)
-          if (i * kThreads < chunks) held[i] = load16(src + (size_t)min((int)threadIdx.x + i * kThreads, chunks - 1) * 16);
+          if (i * kThreads < chunks) held[i] = *(const uintx4*)(src + (size_t)min((int)threadIdx.x + i * kThreads, chunks - 1) * 16);
       }
       float* scale = (pool ? a.v_scale : a.k_scale) + page_id;
       unsigned char* tile = pages + (size_t)(int64_t)page_id * hkv * kPageSize * D;
