@@ -144,12 +144,20 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
       constexpr int kKeep = 8;
       const bool keep = chunks <= kKeep * kThreads;
       uintx4 held[kKeep];
-      float amax = 0.f;
+      // The largest magnitude, as an integer: a bf16's bits at the top of a word and shifted once more have lost their sign and
+      // order like the values (behind the upper element of a pair the lower one's bits, below its last place), and kPastInf on top
+      // carries the undefined ones alone, whatever their payload, out of the word and below zero's place.  (A maximum of floats
+      // passes over quiet ones only: of a signalling one and what came before it, it forgets the latter.)  As many instructions:
+      // the chunks of 128 trajectories (above) 23.9 us with either, 24.3 with a mask, an addition and a packed maximum.
+      constexpr unsigned int kPastInf = 0u - (0x7f81u << 17);
+      unsigned int top = kPastInf;
       auto see = [&](const uintx4 raw) {
-        float x[8];
-        bf16x8_to_float(raw, x);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
+        for (int i = 0; i < 4; ++i) {
+          unsigned int upper;                                // (as an expression the compiler makes a 64-bit product of the two)
+          asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(upper) : "v"(raw[i]), "s"(kPastInf));
+          top = max(max(top, (raw[i] << 17) + kPastInf), upper);
+        }
       };
       if (keep) {
         // (past the last chunk the last one again: the maximum does not mind)
@@ -172,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a)
       } else {
         for (int c = threadIdx.x; c < chunks; c += kThreads) see(*(const uintx4*)(src + (size_t)c * 16));
       }
-      amax = block_max(amax, red);
+      const float amax = block_max(__uint_as_float((top - kPastInf) >> 17 << 16), red);
       const float need = amax / kE4m3Max;
       float s_new;
       if (s0 == 0) {

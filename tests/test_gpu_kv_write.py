@@ -159,18 +159,25 @@ def test_mixed_step_chunks_full_size():
     _assert_same(gpu, ref, "mixed step chunks")
 
 
-@pytest.mark.parametrize("prefix,n,d", [(0, 16, 128), (5, 40, 128), (15, 1, 64), (0, 3, 64)])
-def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(prefix, n, d):
+@pytest.mark.parametrize("prefix,n,d,mag", [(0, 16, 128, 1.0), (5, 40, 128, 1.0), (15, 1, 64, 1.0), (0, 3, 64, 1.0), (0, 20, 128, 2.0 ** -112)])
+def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(prefix, n, d, mag):
     # the rows with zeros in their place, which count for no scale either, are the oracle's; only the codes of the undefined
-    # values differ from those of the zeros: -448, whatever the sign
+    # values differ from those of the zeros: -448, whatever the sign and the payload, quiet or signalling, and on both sides of
+    # the range of scales where the quotients share a reciprocal (2^-112: a page's scale is below 2^-100).  As bit patterns:
+    # an assignment of -nan would store the positive quiet one.
     w = _wl(f"kvnan_{prefix}_{n}", 3, 4, d, "bf16", "fp8_e4m3", ("const", prefix), ("const", n), 77)
     b = W.build(w, DEV)
-    k_new, v_new = _new_rows(b, 78)
-    spots = [(0, 0, 0), (b.total_q - 1, 3, d - 1), (b.total_q // 2, 1, d // 2 + 1)]
+    k_new, v_new = (x * mag for x in _new_rows(b, 78))
+    spots = {(0, 0, 0): 0x7FC0, (b.total_q // 2, 1, d // 2 + 1): 0xFFC0, (0, 2, 1): 0x7F81, (b.total_q - 1, 3, d - 1): 0xFF81}
+    zeroed = []
     for rows in (k_new, v_new):
-        for i, at in enumerate(spots):
-            rows[at] = -float("nan") if i else float("nan")
-    zeroed = [torch.where(torch.isnan(x), torch.zeros_like(x), x) for x in (k_new, v_new)]
+        rows[0, 2, 0] = 50.0 * mag                     # the page's largest value, in front of an undefined one
+        zeros = rows.clone()
+        for at, pattern in spots.items():
+            rows.view(torch.int16)[at] = pattern - ((pattern & 0x8000) << 1)
+            zeros[at] = 0.0
+        assert [int(rows.view(torch.int16)[at]) & 0xFFFF for at in spots] == list(spots.values())
+        zeroed.append(zeros)
     scales = (b.k_scale, b.v_scale)
     got = tuple(x.clone() for x in (b.k_pages, b.v_pages, *scales))
     B.kv_write(k_new, v_new, b.q_lens, b.q_offsets, got[0], got[1], b.page_table, b.ctx_lens, max_q_len=n, k_scale=got[2], v_scale=got[3])
@@ -178,6 +185,9 @@ def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(
     _assert_same(same, ref, "zeros in their place")
     for name, g, z in zip(("k_scale", "v_scale"), got[2:], same[2:]):
         assert torch.equal(g.view(torch.int32), z.view(torch.int32)), name
+    if prefix == 0:
+        written = W.raw_numpy(same[2])[W.raw_numpy(b.page_table)[:, 0]]
+        assert ((written < 2.0 ** -100) == (mag < 1.0)).all()
     for name, g, z in zip(("k_pages", "v_pages"), got[:2], same[:2]):
         differ = g.view(torch.uint8) != z.view(torch.uint8)
         assert int(differ.sum()) == len(spots), name
