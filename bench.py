@@ -23,8 +23,8 @@ against the nominal peaks (HBM 8 TB/s, dense bf16 MFMA 2.5 PFLOP/s) and against 
 microbenchmarks of libbench_peaks.so reach on this GPU in this run (a streaming read of 4 GiB
 and a register-resident MFMA loop).  Legs that run the MFMA append kernel also report the shader clock that kernel
 got ("append_kernel_clock_mhz": cycles over ticks of the constant 100 MHz counter, summed inside its tiles by the
-library while profiling is on) and their fraction of the peak at that clock: the part runs these kernels at its
-power limit, well below the 2.4 GHz that the nominal peak assumes.
+library while profiling is on) and their fraction of the peak at that clock: the part runs these kernels well
+below the 2.4 GHz that the nominal peak assumes (over bf16 pools at its power limit).
 
 The "roofline" object is for the main kernel of the headline workload.  "cpu_baseline" is the
 float64 oracle, untuned, on the host cores of the same box, on the same bytes;

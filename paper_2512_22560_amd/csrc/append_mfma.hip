@@ -26,8 +26,8 @@
 // cycles (four of them stretched 32 MFMAs from 1270 to 1400 cycles), while the same instruction
 // costs the vector phase little more than its issue slot.  All tile loads and the scalar loads of
 // page ids therefore belong to the vector phase; only the widening of FP8 tiles
-// (conversions and LDS writes of registers loaded two blocks earlier) stays between the MFMAs, one instruction behind
-// each (stage_widen), where it was measured to cost less than in the vector phase (all of it there, the two halves a unit
+// (conversions and LDS writes of registers loaded two blocks earlier) stays between the MFMAs, spread over the
+// phase (stage_widen), where it was measured to cost less than in the vector phase (all of it there, the two halves a unit
 // apart: the mixed step 12.91 -> 13.9 ms; behind the softmax, or V alone: no difference).
 // A wave issues one instruction per 4 cycles whatever its kind (vector instructions 6 beside a partner's MFMAs, exponentials
 // 4 more), so the scalar instructions of a vector phase count like the others: page ids by running offsets, page scales once
@@ -35,7 +35,7 @@
 // and 95 scalar instructions to 121 and 20 over FP8 pools, and with waits for the tile loads by their true count the
 // calls from 4.217 to 4.117 ms (64 chunks of 64 .. 1024 tokens behind 2k .. 16k, 32/8/128, bf16), 5.824 to 5.753 (without
 // a prefix, 512 .. 8k tokens), 13.08 to 12.91 (mixed step of 512 trajectories, 64/4/128, FP8), all on one box: the clock gives most of the cycles
-// back (the part is at its power limit).  The vector phase keeps its VALU work short in turn:
+// back over bf16 pools, where the part is at its power limit, and some over FP8 pools.  The vector phase keeps its VALU work short in turn:
 //   bf16 pools: the query is multiplied by sm_scale * log2(e) once, when it is loaded (one extra
 //     bf16 rounding of q, far below the rounding of P), and the score accumulators start from
 //     minus the row's reference instead of zero, so the MFMA result already is the exponent and
@@ -89,7 +89,7 @@ __device__ __forceinline__ float xor32_add(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Pair `pair` of sixteen E4M3 codes to bf16, exactly (every E4M3 value is a bf16 value): the hardware's scaled
+// Pair PAIR of sixteen E4M3 codes to bf16, exactly (every E4M3 value is a bf16 value): the hardware's scaled
 // conversion with a scale of one turns two codes into a packed pair per instruction.
 template <int PAIR>
 __device__ __forceinline__ uint32_t fp8_pair(const uintx4 codes) {
@@ -866,10 +866,13 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
     }
   };
   // ... and, FP8 only, the widening of unit i (K block i + 1, V block i) from registers into LDS during the matrix phase of
-  // block i: 16 conversions and 4 writes per load, one behind each MFMA.  A wave issues in order, an MFMA takes the matrix core 33
-  // cycles and its own issue 10, the operand read in front of it 12: one or two instructions more per MFMA cost nothing, ten in
-  // one place keep the core waiting for 40 cycles.  With a chunk's ten instructions behind one MFMA a block took 2976 cycles,
-  // so 2709; 32 chunks of 256 tokens behind 8k (64/4/128) 1770 -> 1701 us, the rest went into the clock (1.69 -> 1.61 GHz).
+  // block i: 16 conversions and 4 writes per load, spread over the first 31 of the phase's 32 positions.  Whole tiles at D = 128
+  // have 20 of them for 32 MFMAs, at most one behind each; a tile's first block, without the second product, 20 for 16.  Half
+  // tiles have 40 for 32 in steps of two blocks and 20 for 16 in steps of one, up to two behind an MFMA; at D = 64 half of the
+  // steps have no MFMA.  A wave issues in order, an MFMA takes the matrix core 33 cycles and its own issue 10, the operand read
+  // in front of it 12: one or two instructions more per MFMA cost nothing, ten in one place keep the core waiting for 40
+  // cycles.  With a chunk's ten instructions behind one MFMA a block of a whole tile took
+  // 2976 cycles, so 2709; 32 chunks of 256 tokens behind 8k (64/4/128) 1770 -> 1701 us, the rest went into the clock (1.69 -> 1.61 GHz).
   // All of it in front of the 20th or 26th of 32 MFMAs instead of the 31st: 1 to 2 % slower.
   uintx4 wide[kLoads];
   auto stage_widen = [&](auto slot_c, auto pos_c) __attribute__((always_inline)) {

@@ -1,6 +1,7 @@
 // Two microbenchmarks that say what this GPU delivers at best, for the fractions the benchmark reports
 // next to the nominal peaks: a streaming read of a large buffer (HBM bandwidth) and a register-resident loop
-// of the matrix instruction the append kernel uses (bf16 MFMA rate).  Built into a library of its own,
+// of the matrix instruction the append kernel uses (bf16 MFMA rate, of operands that are the same in every
+// instruction: the clock that it gets need not be the one of operands that change).  Built into a library of its own,
 // libbench_peaks.so; nothing of it is part of librollattn.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
