@@ -872,7 +872,8 @@ __device__ __forceinline__ void append_tile(const AppendArgs& kernel_args, Appen
   // steps have no MFMA.  A wave issues in order, an MFMA takes the matrix core 33 cycles and its own issue 10, the operand read
   // in front of it 12: one or two instructions more per MFMA cost nothing, ten in one place keep the core waiting for 40
   // cycles.  With a chunk's ten instructions behind one MFMA a block of a whole tile took
-  // 2976 cycles, so 2709; 32 chunks of 256 tokens behind 8k (64/4/128) 1770 -> 1701 us, the rest went into the clock (1.69 -> 1.61 GHz).
+  // 3300 cycles, so 3003; 32 chunks of 256 tokens behind 8k (64/4/128), back to back, 1840 -> 1797 us, the rest went into the clock
+  // (1.81 -> 1.68 GHz); with pauses between the launches 1770 -> 1701 us.
   // All of it in front of the 20th or 26th of 32 MFMAs instead of the 31st: 1 to 2 % slower.
   uintx4 wide[kLoads];
   auto stage_widen = [&](auto slot_c, auto pos_c) __attribute__((always_inline)) {
