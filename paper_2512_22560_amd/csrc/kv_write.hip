@@ -84,10 +84,10 @@ struct KvWriteArgs {
 // its way meanwhile, all of a thread's rows leave before the first is looked at, heads and slots are stepped, not divided.
 // As the compiler ordered the plain statements that was five dependent scalar loads and a row at a time: 24.0 us under the
 // profiler against 22.4 for the chunks of 128 trajectories (32 .. 512 tokens, 4 heads of 128, FP8: 110 MB), 20.1 if the
-// divisions were free; the call, start of the launch included, 24.9 against 24.3.  The clamp in one instruction: the call 24.34 -> 23.86
-// us with buffers that change from call to call; with the same ones, between events around the launch and on another box, 25.2 -> 24.6.
-// The streaming hint on the rows gains
-// 4 % where they come from memory and loses 10 % where they are still in the caches, as behind a projection: plain loads.
+// divisions were free; the call, start of the launch included, 24.9 against 24.3.  The clamp in one instruction: the call
+// 24.34 -> 23.86 us with buffers that change from call to call; with the same ones, between events around the launch and on
+// another GPU, 25.2 -> 24.6.  The streaming hint on the rows gains 4 % where they come from memory and loses 10 % where they are
+// still in the caches, as behind a projection: plain loads.
 // SRC_BYTES: 4 (float32) or 2 (bf16); FP8: pool holds E4M3 codes, else the source type
 template <int D, int SRC_BYTES, bool FP8>
 __global__ __launch_bounds__(kThreads) void kv_write_kernel(const KvWriteArgs a) {

@@ -159,13 +159,14 @@ def test_mixed_step_chunks_full_size():
     _assert_same(gpu, ref, "mixed step chunks")
 
 
-@pytest.mark.parametrize("prefix,n,d,mag", [(0, 16, 128, 1.0), (5, 40, 128, 1.0), (15, 1, 64, 1.0), (0, 3, 64, 1.0), (0, 20, 128, 2.0 ** -112)])
-def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(prefix, n, d, mag):
+@pytest.mark.parametrize("prefix,n,hkv,d,mag", [(0, 16, 4, 128, 1.0), (5, 40, 4, 128, 1.0), (15, 1, 4, 64, 1.0), (0, 3, 4, 64, 1.0),
+                                                (0, 20, 4, 128, 2.0 ** -112), (0, 16, 12, 128, 1.0)])
+def test_undefined_values_become_the_lowest_code_and_do_not_count_for_the_scale(prefix, n, hkv, d, mag):
     # the rows with zeros in their place, which count for no scale either, are the oracle's; only the codes of the undefined
     # values differ from those of the zeros: -448, whatever the sign and the payload, quiet or signalling, and on both sides of
     # the range of scales where the quotients share a reciprocal (2^-112: a page's scale is below 2^-100).  As bit patterns:
-    # an assignment of -nan would store the positive quiet one.
-    w = _wl(f"kvnan_{prefix}_{n}", 3, 4, d, "bf16", "fp8_e4m3", ("const", prefix), ("const", n), 77)
+    # an assignment of -nan would store the positive quiet one.  Twelve heads: a page's rows are not kept in registers.
+    w = _wl(f"kvnan_{prefix}_{n}_{hkv}", 3, hkv, d, "bf16", "fp8_e4m3", ("const", prefix), ("const", n), 77)
     b = W.build(w, DEV)
     k_new, v_new = (x * mag for x in _new_rows(b, 78))
     spots = {(0, 0, 0): 0x7FC0, (b.total_q // 2, 1, d // 2 + 1): 0xFFC0, (0, 2, 1): 0x7F81, (b.total_q - 1, 3, d - 1): 0xFF81}
